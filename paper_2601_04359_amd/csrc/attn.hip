@@ -14,9 +14,10 @@
 //     (and the accumulators rescaled) only when one of its row sums runs away.
 //   * With scale = ln 2 (the caller multiplied Q by scale * log2(e), e.g. while rotating it)
 //     the affine step c*s - m is taken out of the loop: see kUnitC below.
-// fp32 tier (D = 64 or 128): one query row per thread, plain FMA; the correctness tier.
+// fp32 tier (D = 64 or 128): fp32 MFMA, sixteen query rows per work-group (see attn_f32_kernel).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lds_dma.h"
@@ -398,14 +399,17 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   }
 }
 
-// Merge of the key shares: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s with M = max_s m_s.
-// A thread owns four dims of one row.
+// Merge of the key shares: O = sum_s e^(m_s - M) O_s / sum_s e^(m_s - M) l_s with M = max_s m_s
+// (bf16 tier: base 2, as its kernel keeps its references).  A thread owns four dims of one row.
+template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float2* __restrict__ part_ml,
-                                                         uint16_t* __restrict__ O, float* __restrict__ lse,
+                                                         T* __restrict__ O, float* __restrict__ lse,
                                                          int Hq, int Nq, int64_t o_stride_h, int n_splits) {
-  const int64_t r = static_cast<int64_t>(blockIdx.x) * 8 + (threadIdx.x >> 5);
-  const int c = threadIdx.x & 31;
+  constexpr bool kF32 = sizeof(T) == 4;
+  constexpr int kLanes = D / 4;  // threads per row
+  const int64_t r = static_cast<int64_t>(blockIdx.x) * (256 / kLanes) + threadIdx.x / kLanes;
+  const int c = threadIdx.x % kLanes;
   const int64_t n_rows = static_cast<int64_t>(Hq) * Nq;
   if (r >= n_rows) return;
   float M = -INFINITY;
@@ -414,19 +418,25 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < n_splits; ++s) {
     const float2 ml = part_ml[s * n_rows + r];
-    const float w = __builtin_amdgcn_exp2f(ml.x - M);
+    const float w = kF32 ? expf(ml.x - M) : __builtin_amdgcn_exp2f(ml.x - M);
     l += w * ml.y;
-    const f32x4 v = *reinterpret_cast<const f32x4*>(part_o + (s * n_rows + r) * kD + c * 4);
+    const f32x4 v = *reinterpret_cast<const f32x4*>(part_o + (s * n_rows + r) * D + c * 4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] += w * v[e];
   }
   const float inv = 1.f / l;
   const int h = static_cast<int>(r / Nq), row = static_cast<int>(r % Nq);
-  u32x2 out;
-  out[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-  out[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-  *reinterpret_cast<u32x2*>(O + h * o_stride_h + static_cast<int64_t>(row) * kD + c * 4) = out;
-  if (lse != nullptr && c == 0) lse[r] = (M + log2f(l)) * 0.6931471805599453f;
+  T* out = O + h * o_stride_h + static_cast<int64_t>(row) * D + c * 4;
+  if constexpr (kF32) {
+    store_f32x4(out, acc * inv);
+    if (lse != nullptr && c == 0) lse[r] = M + logf(l);
+  } else {
+    u32x2 packed;
+    packed[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+    packed[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+    *reinterpret_cast<u32x2*>(out) = packed;
+    if (lse != nullptr && c == 0) lse[r] = (M + log2f(l)) * 0.6931471805599453f;
+  }
 }
 
 // How many shares to cut the keys into: none unless it fills the 256 compute units in whole
@@ -448,82 +458,230 @@ int choose_key_splits(int base_blocks, int n_tiles) {
   return best;
 }
 
-size_t attn_partial_bytes(int Hq, int Nq, int n_splits) {
+// Workspace of n_splits key shares: the partial O rows, then the (m, l) pairs.
+size_t attn_partial_o_bytes(int Hq, int Nq, int D, int n_splits) {
+  return align_up(static_cast<size_t>(n_splits) * Hq * Nq * D * sizeof(float), 256);
+}
+size_t attn_partial_bytes(int Hq, int Nq, int D, int n_splits) {
   return n_splits <= 1 ? 0
-                       : align_up(static_cast<size_t>(n_splits) * Hq * Nq * kD * sizeof(float), 256) +
+                       : attn_partial_o_bytes(Hq, Nq, D, n_splits) +
                              align_up(static_cast<size_t>(n_splits) * Hq * Nq * sizeof(float2), 256);
+}
+// The largest number of shares not above `want` whose partial results fit the caller's workspace
+// (1, no shares, without one: always valid).
+int splits_that_fit(int want, int Hq, int Nq, int D, const void* ws, size_t ws_bytes) {
+  if (ws == nullptr || reinterpret_cast<uintptr_t>(ws) % 16 != 0) return 1;
+  while (want > 1 && attn_partial_bytes(Hq, Nq, D, want) > ws_bytes) --want;
+  return want;
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 correctness tier: one query row per thread, K/V tiles broadcast from LDS.
+// fp32 tier: the 16x16x4 fp32 MFMA (fp32 operands and accumulation throughout; 2,048 FLOP in 32
+// cycles, twice the rate of scalar FMAs).  Bound: matrix rate when the chip is full, latency at
+// the few-hundred-token sizes this tier is used at, so the work is cut fine: a work-group owns 16
+// query rows, its 8 waves take the keys in groups of 32 by turns (no LDS, no barrier in the loop)
+// and merge their (O, m, l) through LDS once; when that leaves compute units idle the host cuts
+// the keys into shares as well (f32_key_splits).
+//   * S^T = K Q^T: lane (r = l % 16, kg = l / 16) holds key row r, dims 16 s + 4 kg .. + 3 as one
+//     16-byte load; the four MFMAs of step s contract over (kg, element e), the same permutation
+//     of the head dimension on both operands.
+//   * The result leaves lane (q = l % 16, kg) with keys 4 kg .. 4 kg + 3 of its query column:
+//     max and sum need two cross-lane steps, and P^T is already the B operand of O^T += V^T P^T
+//     (product e contracts over keys 4 kg + e).
+//   * V is the A operand through 16-byte loads too: row r of output block (db, e) stands for dim
+//     64 db + 4 r + e, so a lane's accumulators are whole 16-byte pieces of its output row.
+// Measured (8/2 heads, 252 rows, 1,804 keys, D = 128; 1.86 GFLOP, 12 us at the rate a large fp32
+// product reaches): one thread per row with K / V broadcast from LDS and plain FMA 3,945 us a call,
+// this kernel 38 us with two key shares and 56 us without; 24/8 heads, 1,000 rows, 8,000 keys:
+// 1,179 us, 83 TFLOP/s (K and V come through L2 once per 16 rows).
 // ------------------------------------------------------------------------------------------
-constexpr int kF32Threads = 64;
-constexpr int kF32Tile = 16;
+constexpr int kMaxKeySplits = 16;
+constexpr int kF32Waves = 8;
+constexpr int kF32Threads = 64 * kF32Waves;
+constexpr int kF32Rows = 16;        // query rows per work-group
+constexpr int kF32Keys = 32;        // keys per wave and step (two 16-key MFMA tiles)
+
+template <int D>
+constexpr size_t f32_smem_bytes() {
+  return sizeof(float) * kF32Waves * kF32Rows * (D + 2);
+}
 
 template <int D>
 __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
-    int64_t kv_stride_h, int64_t o_stride_h, float scale) {
-  __shared__ float ks[kF32Tile][D];
-  __shared__ float vs[kF32Tile][D];
-  const int h = blockIdx.y, kvh = h / rep;
-  const int row = blockIdx.x * kF32Threads + threadIdx.x;
-  const int rowc = min(row, Nq - 1);
-  const float* qrow = Q + h * q_stride_h + static_cast<int64_t>(rowc) * D;
-  float q[D], acc[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    q[d] = qrow[d];
-    acc[d] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
+    int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split,
+    float* __restrict__ part_o, float2* __restrict__ part_ml) {
+  constexpr int kS = D / 16, kB = D / 64;
+  extern __shared__ __align__(16) uint8_t smem_raw[];
+  float* s_o = reinterpret_cast<float*>(smem_raw);        // [wave][row][D]
+  float* s_m = s_o + kF32Waves * kF32Rows * D;            // [wave][row]
+  float* s_l = s_m + kF32Waves * kF32Rows;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kg = lane >> 4;
+  const int h = blockIdx.y, kvh = h / rep, split = blockIdx.z;
+  const int row0 = blockIdx.x * kF32Rows;
   const float* Kh = K + kvh * kv_stride_h;
   const float* Vh = V + kvh * kv_stride_h;
-  for (int k0 = 0; k0 < Nk; k0 += kF32Tile) {
-    const int nt = min(kF32Tile, Nk - k0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < nt * D; e += kF32Threads) {
-      ks[e / D][e % D] = Kh[static_cast<int64_t>(k0) * D + e];
-      vs[e / D][e % D] = Vh[static_cast<int64_t>(k0) * D + e];
-    }
-    __syncthreads();
-    float s[kF32Tile];
-    float mt = m;
+  const int k_begin = split * keys_per_split, k_end = min(k_begin + keys_per_split, Nk);
+
+  f32x4 q[kS];
+  {
+    const float* qrow = Q + h * q_stride_h + static_cast<int64_t>(min(row0 + r, Nq - 1)) * D + kg * 4;
 #pragma unroll
-    for (int j = 0; j < kF32Tile; ++j) {
-      float dot = 0.f;
-      if (j < nt) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) dot = fmaf(q[d], ks[j][d], dot);
-        s[j] = dot * scale;
-        mt = fmaxf(mt, s[j]);
-      } else {
-        s[j] = -INFINITY;
-      }
-    }
-    const float alpha = expf(m - mt);  // exp(-inf) = 0 on the first tile
-    l *= alpha;
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] *= alpha;
-#pragma unroll
-    for (int j = 0; j < kF32Tile; ++j) {
-      if (j < nt) {
-        const float p = expf(s[j] - mt);
-        l += p;
-#pragma unroll
-        for (int d = 0; d < D; ++d) acc[d] = fmaf(p, vs[j][d], acc[d]);
-      }
-    }
-    m = mt;
+    for (int s = 0; s < kS; ++s) q[s] = load_f32x4(qrow + s * 16);
   }
-  if (row < Nq) {
-    float* orow = O + h * o_stride_h + static_cast<int64_t>(row) * D;
-    const float inv = 1.f / l;
+  f32x4 o[kB][4];
 #pragma unroll
-    for (int d = 0; d < D; ++d) orow[d] = acc[d] * inv;
-    if (lse) lse[static_cast<int64_t>(h) * Nq + row] = m + logf(l);
+  for (int b = 0; b < kB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+
+  // Software pipeline: the V loads of a step fly during its score products, the K loads of the
+  // next step (into the registers those products just freed) during its softmax and value products.
+  f32x4 kf[2][kS], v[2][4][kB];
+  auto load_k = [&](int k0) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const float* krow = Kh + static_cast<int64_t>(min(k0 + t * 16 + r, Nk - 1)) * D + kg * 4;
+#pragma unroll
+      for (int s = 0; s < kS; ++s) kf[t][s] = load_f32x4(krow + s * 16);
+    }
+  };
+  load_k(k_begin + wave * kF32Keys);
+  for (int k0 = k_begin + wave * kF32Keys; k0 < k_end; k0 += kF32Waves * kF32Keys) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float* vrow = Vh + static_cast<int64_t>(min(k0 + t * 16 + kg * 4 + e, Nk - 1)) * D + r * 4;
+#pragma unroll
+        for (int b = 0; b < kB; ++b) v[t][e][b] = load_f32x4(vrow + b * 64);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < kS; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][s][e], q[s][e], sc[t], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(k0 + kF32Waves * kF32Keys);  // past the end: clamped rows, never used
+    __builtin_amdgcn_sched_barrier(0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sc[t][e] = k0 + t * 16 + kg * 4 + e < k_end ? sc[t][e] * scale : -INFINITY;
+        mx = fmaxf(mx, sc[t][e]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = wave_half_max(mx);
+    const float m_new = fmaxf(m, mx);      // finite: key k0 itself is inside the share
+    const float alpha = expf(m - m_new);   // exp(-inf) = 0 on the first step
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sc[t][e] = expf(sc[t][e] - m_new);
+        sum += sc[t][e];
+      }
+    l = l * alpha + sum;
+    m = m_new;
+#pragma unroll
+    for (int b = 0; b < kB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[b][e] *= alpha;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < kB; ++b)
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            o[b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[t][e][b][x], sc[t][e], o[b][x], 0, 0, 0);
   }
+  l += __shfl_xor(l, 16);
+  l = wave_half_sum(l);
+
+  // accumulator element (b, x, i) of lane (q = r, kg) is dim 64 b + 16 kg + 4 i + x of query row r
+  float* mine = s_o + (wave * kF32Rows + r) * D + kg * 16;
+#pragma unroll
+  for (int b = 0; b < kB; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4*>(mine + b * 64 + i * 4) = f32x4{o[b][0][i], o[b][1][i], o[b][2][i], o[b][3][i]};
+  if (kg == 0) {
+    s_m[wave * kF32Rows + r] = m;
+    s_l[wave * kF32Rows + r] = l;
+  }
+  __syncthreads();
+  // merge in wave order: a thread owns four dims of one row
+  const int row = threadIdx.x / (D / 4), c = threadIdx.x % (D / 4);
+  if (row >= kF32Rows || row0 + row >= Nq) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, s_m[w * kF32Rows + row]);
+  float lt = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) {
+    const float wt = expf(s_m[w * kF32Rows + row] - M);   // 0 for a wave that had no keys
+    lt += wt * s_l[w * kF32Rows + row];
+    acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + c * 4);
+  }
+  if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
+    const int64_t at = (static_cast<int64_t>(split) * gridDim.y + h) * Nq + row0 + row;
+    *reinterpret_cast<f32x4*>(part_o + at * D + c * 4) = acc;
+    if (c == 0) part_ml[at] = make_float2(M, lt);
+    return;
+  }
+  store_f32x4(O + h * o_stride_h + static_cast<int64_t>(row0 + row) * D + c * 4, acc * (1.f / lt));
+  if (lse != nullptr && c == 0) lse[static_cast<int64_t>(h) * Nq + row0 + row] = M + logf(lt);
+}
+
+// Key shares of the fp32 tier.  A work-group takes its share in steps of 8 x 32 keys; two
+// work-groups fit a compute unit (their LDS).  Shares pay while they fill idle compute units, at
+// the price of a merge launch (3-4 us) and of the partial rows.
+int f32_key_splits(int Hq, int Nq, int Nk) {
+  const int blocks = ceil_div(Nq, kF32Rows) * Hq, steps = ceil_div(Nk, kF32Waves * kF32Keys);
+  return std::max(1, std::min(std::min(256 / blocks, steps / 2), kMaxKeySplits));
+}
+
+template <int D>
+int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, int Nq, int Nk, int64_t q_stride_h,
+             int64_t kv_stride_h, int64_t o_stride_h, float scale, float* O, float* lse, void* ws, size_t ws_bytes,
+             hipStream_t s) {
+  static std::atomic<uint64_t> lds_ok{0};
+  if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<D>), f32_smem_bytes<D>(), lds_ok,
+                                 "pc_frame_attn"))
+    return rc;
+  int n_splits = splits_that_fit(f32_key_splits(Hq, Nq, Nk), Hq, Nq, D, ws, ws_bytes);
+  // whole steps per share, and as many shares as that leaves (none is empty)
+  const int per = ceil_div(ceil_div(Nk, kF32Keys), n_splits) * kF32Keys;
+  n_splits = ceil_div(Nk, per);
+  float* part_o = nullptr;
+  float2* part_ml = nullptr;
+  if (n_splits > 1) {
+    part_o = static_cast<float*>(ws);
+    part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, n_splits));
+  }
+  attn_f32_kernel<D><<<dim3(ceil_div(Nq, kF32Rows), Hq, n_splits), kF32Threads, f32_smem_bytes<D>(), s>>>(
+      Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, per, part_o, part_ml);
+  PC_CHECK_LAUNCH("pc_frame_attn");
+  if (n_splits > 1) {
+    constexpr int kRowsPerBlock = 256 / (D / 4);
+    const int64_t rows = static_cast<int64_t>(Hq) * Nq;
+    attn_merge_kernel<float, D><<<static_cast<unsigned>((rows + kRowsPerBlock - 1) / kRowsPerBlock), 256, 0, s>>>(
+        part_o, part_ml, O, lse, Hq, Nq, o_stride_h, n_splits);
+    PC_CHECK_LAUNCH("pc_frame_attn merge");
+  }
+  return PC_OK;
 }
 
 }  // namespace
@@ -532,8 +690,10 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
 using namespace pc;
 
 extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
-  if (D != kD || Hq <= 0 || Nq <= 0 || Nk <= 0) return 0;   // only the bf16 kernel splits the keys
-  return attn_partial_bytes(Hq, Nq, choose_key_splits(Hq * ceil_div(Nq, kBM), ceil_div(Nk, kBN)));
+  if ((D != 64 && D != 128) || Hq <= 0 || Nq <= 0 || Nk <= 0) return 0;
+  int splits = f32_key_splits(Hq, Nq, Nk);   // the call does not say which tier it will be
+  if (D == kD) splits = std::max(splits, choose_key_splits(Hq * ceil_div(Nq, kBM), ceil_div(Nk, kBN)));
+  return attn_partial_bytes(Hq, Nq, D, splits);
 }
 
 extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq,
@@ -567,14 +727,12 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     // Key shares need the caller's workspace for the partial results; without it (or with one
     // that is too small or misaligned) the keys are not split, which is always valid.
     int n_splits = choose_key_splits(Hq * n_tiles_q, ceil_div(Nk, kBN));
-    if (ws == nullptr || ws_bytes < attn_partial_bytes(Hq, Nq, n_splits) || reinterpret_cast<uintptr_t>(ws) % 16 != 0)
-      n_splits = 1;
+    if (splits_that_fit(n_splits, Hq, Nq, D, ws, ws_bytes) != n_splits) n_splits = 1;
     float* part_o = nullptr;
     float2* part_ml = nullptr;
     if (n_splits > 1) {
       part_o = static_cast<float*>(ws);
-      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) +
-                                          align_up(static_cast<size_t>(n_splits) * Hq * Nq * kD * sizeof(float), 256));
+      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, n_splits));
     }
     (unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>)<<<dim3(n_tiles_q * Hq * n_splits), kPPThreads, kSmemBytes, s>>>(
         static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
@@ -582,20 +740,18 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
         kv_stride_h, o_stride_h, c, n_tiles_q, n_splits, part_o, part_ml);
     if (n_splits > 1) {
       PC_CHECK_LAUNCH("pc_frame_attn");
-      attn_merge_kernel<<<static_cast<unsigned>((static_cast<int64_t>(Hq) * Nq + 7) / 8), 256, 0, s>>>(
+      attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((static_cast<int64_t>(Hq) * Nq + 7) / 8), 256, 0, s>>>(
           part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, n_splits);
     }
   } else {
     PC_REQUIRE(D == 64 || D == 128, PC_ERR_UNSUPPORTED, "pc_frame_attn: fp32 tier needs D=64 or 128, got %d", D);
-    const dim3 grid(ceil_div(Nq, kF32Threads), Hq);
     if (D == 64)
-      attn_f32_kernel<64><<<grid, kF32Threads, 0, s>>>(
-          static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(V),
-          static_cast<float*>(O), lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale);
-    else
-      attn_f32_kernel<128><<<grid, kF32Threads, 0, s>>>(
-          static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(V),
-          static_cast<float*>(O), lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale);
+      return attn_f32<64>(static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(V), Hq,
+                          rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, static_cast<float*>(O), lse, ws,
+                          ws_bytes, s);
+    return attn_f32<128>(static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(V), Hq,
+                         rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, static_cast<float*>(O), lse, ws,
+                         ws_bytes, s);
   }
   PC_CHECK_LAUNCH("pc_frame_attn");
   return PC_OK;

@@ -57,6 +57,11 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
+// fp32 tensors only promise element alignment; the hardware takes 16-byte accesses at any dword.
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+__device__ __forceinline__ f32x4 load_f32x4(const float* p) { return *reinterpret_cast<const f32x4_any*>(p); }
+__device__ __forceinline__ void store_f32x4(float* p, f32x4 v) { *reinterpret_cast<f32x4_any*>(p) = v; }
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }

@@ -270,6 +270,29 @@ def test_frame_attn_f32_shapes(d, nq, nk):
     _attn_check("f32", Q, K, V, d ** -0.5)
 
 
+# edges of the fp32 kernel's 16-row tiles, 32-key steps and key shares (17 rows x 5,000 keys: shares)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nq,nk", [(15, 31), (16, 32), (17, 33), (31, 255), (32, 256), (33, 257), (17, 5000)])
+def test_frame_attn_f32_tile_edges_and_key_shares(d, nq, nk):
+    Q, K, V = _attn_case("f32", 3, 1, nq, nk, d, d + nq + nk)
+    _attn_check("f32", Q, K, V, d ** -0.5)
+    # without a workspace the keys are not cut: the same sums in another order
+    a = pk.pc_frame_attn(dev(Q, None), dev(K, None), dev(V, None), nk, d ** -0.5)
+    b = pk.pc_frame_attn(dev(Q, None), dev(K, None), dev(V, None), nk, d ** -0.5,
+                         ws=torch.empty(16, dtype=torch.uint8, device=DEV))
+    assert (a - b).abs().max().item() <= 2e-6   # two fp32 results of |O| < 4, each within a few 2^-24 |O| of exact
+
+
+def test_frame_attn_f32_takes_buffers_that_are_not_16_byte_aligned():
+    Q, K, V = _attn_case("f32", 2, 1, 20, 70, 64, 12)
+    def odd(x):
+        t = torch.empty(x.size + 1, dtype=torch.float32, device=DEV)[1:].view(x.shape)
+        return t.copy_(dev(x, None))
+    O = pk.pc_frame_attn(odd(Q), odd(K), odd(V), 70, 0.125, O=odd(np.zeros_like(Q)))
+    Ow, _ = orc.frame_attn(Q, K, V, 0.125)
+    assert np.abs(host(O) - Ow).max() <= 1e-5
+
+
 def test_frame_attn_capacity_larger_than_rows():
     # K/V live in buffers with spare capacity (head stride > Nk*D), as a cache does
     Q, K, V = _attn_case("bf16", 4, 2, 100, 300, 128, 11)
