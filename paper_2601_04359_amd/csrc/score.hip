@@ -286,15 +286,14 @@ __global__ void score_merge_rows(const float2* __restrict__ part, float* __restr
 }
 
 // A caller's natural-log LSE, indexed like the rows of Qs, -> the dense [head][n_pad] layout
-// of pass 2 (times `mul`: -log2(e) for the base-2 kernels, which add the negated normaliser);
-// padding rows get `pad`.
+// of pass 2 in base 2, negated (pass 2 adds it); padding rows hold -inf.
 __global__ void score_import_lse(const float* __restrict__ lse, int64_t lse_stride_h,
                                  const int32_t* __restrict__ q_rows, float* __restrict__ out, int Hq, int n_qs,
-                                 int n_pad, float mul, float pad) {
+                                 int n_pad) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= Hq * n_pad) return;
   const int h = r / n_pad, row = r % n_pad;
-  out[r] = row < n_qs ? lse[h * lse_stride_h + (q_rows ? q_rows[row] : row)] * mul : pad;
+  out[r] = row < n_qs ? lse[h * lse_stride_h + (q_rows ? q_rows[row] : row)] * -1.4426950408889634f : -INFINITY;
 }
 
 // ---- pass 2: column mass --------------------------------------------------------------------
@@ -475,92 +474,174 @@ __global__ void score_reduce(const float* __restrict__ part, float* __restrict__
   }
 }
 
-// ---- fp32 correctness tier ------------------------------------------------------------------
-constexpr int kF32Tile = 16;
+// ---- fp32 tier ------------------------------------------------------------------------------
+// Both passes on the 16x16x4 fp32 MFMA (fp32 operands and accumulation), S^T = K Q^T: lane
+// (r = l % 16, kg = l / 16) holds dims 16 s + 4 kg .. + 3 of key row r and of query row r as
+// 16-byte loads, the four MFMAs of step s contract over (kg, element e), and the result leaves the
+// lane with keys 4 kg .. 4 kg + 3 of query column r.  Operands come from global memory (a few
+// hundred rows: they live in the caches), nothing is staged.  A work-group is 8 waves that share
+// the stationary 16 rows, take the streamed axis by turns and merge through LDS once, in wave
+// order: bit-reproducible.  Latency-bound at the sizes this tier runs at, hence the fine cut:
+// 2 heads x 64 rows x 336 keys, D = 64: 106 + 79 us with one thread per row / key and plain FMA,
+// 6.6 + 4.8 us like this.
+constexpr int kF32Waves = 8;
+constexpr int kF32Threads = 64 * kF32Waves;
 
 template <int D>
-__global__ __launch_bounds__(64) void score_rowpass_f32(const float* __restrict__ Qs,
-                                                        const int32_t* __restrict__ q_rows,
-                                                        const float* __restrict__ K,
-                                                        float* __restrict__ lse, int rep, int n_qs,
-                                                        int Nk, int64_t q_stride_h,
-                                                        int64_t k_stride_h, float scale) {
-  __shared__ float ks[kF32Tile][D];
-  const int h = blockIdx.y, kvh = h / rep;
-  const int row = blockIdx.x * 64 + threadIdx.x;
-  int qr = min(row, n_qs - 1);
-  if (q_rows) qr = q_rows[qr];
-  const float* qrow = Qs + h * q_stride_h + static_cast<int64_t>(qr) * D;
-  float q[D];
+struct F32Frag {  // one row of a 16-row operand, this lane's quarter of it
+  f32x4 v[D / 16];
+  __device__ __forceinline__ void load(const float* row, int kg) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) q[d] = qrow[d];
-  const float* Kh = K + kvh * k_stride_h;
-  float m = -INFINITY, l = 0.f;
-  for (int k0 = 0; k0 < Nk; k0 += kF32Tile) {
-    const int nt = min(kF32Tile, Nk - k0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < nt * D; e += 64) ks[e / D][e % D] = Kh[static_cast<int64_t>(k0) * D + e];
-    __syncthreads();
-    float s[kF32Tile], mt = m;
-#pragma unroll
-    for (int j = 0; j < kF32Tile; ++j) {
-      s[j] = -INFINITY;
-      if (j < nt) {
-        float dot = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) dot = fmaf(q[d], ks[j][d], dot);
-        s[j] = dot * scale;
-        mt = fmaxf(mt, s[j]);
-      }
-    }
-    l *= expf(m - mt);
-#pragma unroll
-    for (int j = 0; j < kF32Tile; ++j)
-      if (j < nt) l += expf(s[j] - mt);
-    m = mt;
+    for (int s = 0; s < D / 16; ++s) v[s] = load_f32x4(row + s * 16 + kg * 4);
   }
-  if (row < n_qs) lse[static_cast<int64_t>(h) * n_qs + row] = m + logf(l);
+};
+// two independent 16x16 products, interleaved: neither waits for its own last MFMA
+template <int D>
+__device__ __forceinline__ void f32_products(const F32Frag<D>& k0, const F32Frag<D>& q0, const F32Frag<D>& k1,
+                                             const F32Frag<D>& q1, f32x4 (&sc)[2]) {
+  sc[0] = sc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_sched_barrier(0);  // every load of the step is issued before the first product
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k0.v[s][e], q0.v[s][e], sc[0], 0, 0, 0);
+      sc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k1.v[s][e], q1.v[s][e], sc[1], 0, 0, 0);
+    }
 }
 
+// Pass 1: natural-log sum-exp of 16 scoring rows of one head over all keys.
 template <int D>
-__global__ __launch_bounds__(64) void score_colpass_f32(const float* __restrict__ Qs,
-                                                        const int32_t* __restrict__ q_rows,
-                                                        const float* __restrict__ K,
-                                                        const float* __restrict__ lse,
-                                                        float* __restrict__ score,
-                                                        int64_t score_stride_h, int rep, int n_qs,
-                                                        int Nk, int64_t q_stride_h,
-                                                        int64_t k_stride_h, float scale) {
-  __shared__ float qs[kF32Tile][D];
-  __shared__ float ls[kF32Tile];
-  const int kvh = blockIdx.y;
-  const int key = blockIdx.x * 64 + threadIdx.x;
-  const float* krow = K + kvh * k_stride_h + static_cast<int64_t>(min(key, Nk - 1)) * D;
-  float k[D];
+__global__ __launch_bounds__(kF32Threads) void score_rowpass_f32(const float* __restrict__ Qs,
+                                                                 const int32_t* __restrict__ q_rows,
+                                                                 const float* __restrict__ K,
+                                                                 float* __restrict__ lse, int rep, int n_qs,
+                                                                 int Nk, int64_t q_stride_h,
+                                                                 int64_t k_stride_h, float scale) {
+  __shared__ float s_m[kF32Waves][16], s_l[kF32Waves][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kg = lane >> 4;
+  const int h = blockIdx.y;
+  const int row = blockIdx.x * 16 + r;
+  int qr = min(row, n_qs - 1);
+  if (q_rows) qr = q_rows[qr];
+  F32Frag<D> q, k[2];
+  q.load(Qs + h * q_stride_h + static_cast<int64_t>(qr) * D, kg);
+  const float* Kh = K + (h / rep) * k_stride_h;
+  float m = -INFINITY, l = 0.f;
+  for (int k0 = wave * 32; k0 < Nk; k0 += kF32Waves * 32) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) k[d] = krow[d];
-  float sum = 0.f;
-  for (int r = 0; r < rep; ++r) {
-    const int h = kvh * rep + r;
-    const float* Qh = Qs + h * q_stride_h;
-    for (int r0 = 0; r0 < n_qs; r0 += kF32Tile) {
-      const int nt = min(kF32Tile, n_qs - r0);
-      __syncthreads();
-      for (int e = threadIdx.x; e < nt * D; e += 64) {
-        const int qr = q_rows ? q_rows[r0 + e / D] : r0 + e / D;
-        qs[e / D][e % D] = Qh[static_cast<int64_t>(qr) * D + e % D];
-      }
-      if (static_cast<int>(threadIdx.x) < nt) ls[threadIdx.x] = lse[static_cast<int64_t>(h) * n_qs + r0 + threadIdx.x];
-      __syncthreads();
-      for (int j = 0; j < nt; ++j) {
-        float dot = 0.f;
+    for (int t = 0; t < 2; ++t) k[t].load(Kh + static_cast<int64_t>(min(k0 + t * 16 + r, Nk - 1)) * D, kg);
+    f32x4 sc[2];
+    f32_products<D>(k[0], q, k[1], q, sc);
+    float mt = m;
 #pragma unroll
-        for (int d = 0; d < D; ++d) dot = fmaf(qs[j][d], k[d], dot);
-        sum += expf(dot * scale - ls[j]);
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sc[t][e] = k0 + t * 16 + kg * 4 + e < Nk ? sc[t][e] * scale : -INFINITY;
+        mt = fmaxf(mt, sc[t][e]);
       }
-    }
+    // a lane may not have seen a valid key yet: exp(-inf - -inf) is not wanted
+    const float m_use = mt == -INFINITY ? 0.f : mt;
+    l *= expf(m - m_use);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) l += expf(sc[t][e] - m_use);
+    m = mt;
   }
-  if (key < Nk) score[kvh * score_stride_h + key] = sum;
+  // the four lanes of a query column, then the waves
+#pragma unroll
+  for (int x = 16; x <= 32; x *= 2) {
+    const float m_o = __shfl_xor(m, x), l_o = __shfl_xor(l, x);
+    const float mt = fmaxf(m, m_o), m_use = mt == -INFINITY ? 0.f : mt;
+    l = l * expf(m - m_use) + l_o * expf(m_o - m_use);
+    m = mt;
+  }
+  if (kg == 0) {
+    s_m[wave][r] = m;
+    s_l[wave][r] = l;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 16 || row >= n_qs) return;
+  float M = s_m[0][r];  // wave 0 always has keys
+#pragma unroll
+  for (int w = 1; w < kF32Waves; ++w) M = fmaxf(M, s_m[w][r]);
+  float lt = 0.f;
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) lt += s_l[w][r] * expf(s_m[w][r] - M);
+  lse[static_cast<int64_t>(h) * n_qs + row] = M + logf(lt);
+}
+
+// Pass 2: column mass of 16 keys over the (query head of the group, 16-row tile) list.  lse: the
+// dense [head][n_qs] output of pass 1 (lse_rows NULL), or the caller's array, indexed like Qs.
+template <int D>
+__global__ __launch_bounds__(kF32Threads) void score_colpass_f32(const float* __restrict__ Qs,
+                                                                 const int32_t* __restrict__ q_rows,
+                                                                 const float* __restrict__ K,
+                                                                 const float* __restrict__ lse, int64_t lse_stride_h,
+                                                                 int lse_by_q_row, float* __restrict__ score,
+                                                                 int64_t score_stride_h, int rep, int n_qs,
+                                                                 int Nk, int64_t q_stride_h,
+                                                                 int64_t k_stride_h, float scale) {
+  __shared__ f32x4 s_sum[kF32Waves][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kg = lane >> 4;
+  const int kvh = blockIdx.y;
+  const int key0 = blockIdx.x * 16;
+  F32Frag<D> k, q[2];
+  k.load(K + kvh * k_stride_h + static_cast<int64_t>(min(key0 + r, Nk - 1)) * D, kg);
+  const int tiles = (n_qs + 15) / 16, n_units = rep * tiles;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int u0 = wave * 2; u0 < n_units; u0 += kF32Waves * 2) {
+    float ls[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int u = min(u0 + t, n_units - 1);
+      const int h = kvh * rep + u / tiles, row = (u % tiles) * 16 + r;
+      const int rowc = min(row, n_qs - 1);
+      const int qr = q_rows ? q_rows[rowc] : rowc;
+      q[t].load(Qs + h * q_stride_h + static_cast<int64_t>(qr) * D, kg);
+      const float x = lse[h * lse_stride_h + (lse_by_q_row ? qr : rowc)];
+      ls[t] = u0 + t < n_units && row < n_qs ? x : INFINITY;  // padding adds nothing
+    }
+    f32x4 sc[2];
+    f32_products<D>(k, q[0], k, q[1], sc);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] += expf(sc[t][e] * scale - ls[t]);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)  // over the 16 query columns
+#pragma unroll
+    for (int x = 1; x < 16; x *= 2) sum[e] += __shfl_xor(sum[e], x);
+  if (r == 0) s_sum[wave][kg] = sum;
+  __syncthreads();
+  if (threadIdx.x >= 4) return;
+  f32x4 tot = s_sum[0][threadIdx.x];
+#pragma unroll
+  for (int w = 1; w < kF32Waves; ++w) tot += s_sum[w][threadIdx.x];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int key = key0 + threadIdx.x * 4 + e;
+    if (key < Nk) score[kvh * score_stride_h + key] = tot[e];
+  }
+}
+
+// lse (caller's, indexed like Qs) or NULL: pass 1 fills ws_lse.  Scores of the nkr keys at k_r.
+template <int D>
+void score_f32(const float* q, const int32_t* q_rows, const float* k, const float* k_r, const float* lse,
+               int64_t lse_stride_h, float* ws_lse, float* out, int64_t out_stride_h, int Hq, int Hkv, int n_qs, int Nk,
+               int nkr, int64_t q_stride_h, int64_t k_stride_h, float scale, hipStream_t s) {
+  const int rep = Hq / Hkv;
+  if (lse == nullptr)
+    score_rowpass_f32<D><<<dim3(ceil_div(n_qs, 16), Hq), kF32Threads, 0, s>>>(q, q_rows, k, ws_lse, rep, n_qs, Nk,
+                                                                              q_stride_h, k_stride_h, scale);
+  score_colpass_f32<D><<<dim3(ceil_div(nkr, 16), Hkv), kF32Threads, 0, s>>>(
+      q, q_rows, k_r, lse ? lse : ws_lse, lse ? lse_stride_h : n_qs, lse != nullptr, out, out_stride_h, rep, n_qs, nkr,
+      q_stride_h, k_stride_h, scale);
 }
 
 struct WsLayout {
@@ -671,8 +752,7 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
       score_merge_rows<<<ceil_div(Hq * n_pad, 256), 256, 0, s>>>(ws_part, ws_lse, Hq, n_qs, n_pad, n_splits);
       PC_CHECK_LAUNCH("pc_score merge");
     } else {
-      score_import_lse<<<ceil_div(Hq * n_pad, 256), 256, 0, s>>>(lse, lse_stride_h, q_rows, ws_lse, Hq, n_qs, n_pad,
-                                                                 -1.4426950408889634f, -INFINITY);
+      score_import_lse<<<ceil_div(Hq * n_pad, 256), 256, 0, s>>>(lse, lse_stride_h, q_rows, ws_lse, Hq, n_qs, n_pad);
       PC_CHECK_LAUNCH("pc_score lse import");
     }
     const int n_key_blocks = ceil_div(nkr, kBlockRows);
@@ -697,27 +777,13 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
     const float* q = static_cast<const float*>(Qs);
     const float* k = static_cast<const float*>(K);
     const float* k_r = k + static_cast<int64_t>(key_begin) * D;
-    const float* lse_in = ws_lse;
-    if (lse != nullptr) {
-      score_import_lse<<<ceil_div(Hq * n_qs, 256), 256, 0, s>>>(lse, lse_stride_h, q_rows, ws_lse, Hq, n_qs, n_qs, 1.f,
-                                                                INFINITY);
-      PC_CHECK_LAUNCH("pc_score lse import");
-    } else {
-      const dim3 grid(ceil_div(n_qs, 64), Hq);
-      if (D == 64)
-        score_rowpass_f32<64><<<grid, 64, 0, s>>>(q, q_rows, k, ws_lse, rep, n_qs, Nk, q_stride_h, k_stride_h, scale);
-      else
-        score_rowpass_f32<128><<<grid, 64, 0, s>>>(q, q_rows, k, ws_lse, rep, n_qs, Nk, q_stride_h, k_stride_h, scale);
-      PC_CHECK_LAUNCH("pc_score row pass");
-    }
-    const dim3 grid(ceil_div(nkr, 64), Hkv);
     if (D == 64)
-      score_colpass_f32<64><<<grid, 64, 0, s>>>(q, q_rows, k_r, lse_in, per_head, per_head_stride, rep, n_qs, nkr,
-                                                  q_stride_h, k_stride_h, scale);
+      score_f32<64>(q, q_rows, k, k_r, lse, lse_stride_h, ws_lse, per_head, per_head_stride, Hq, Hkv, n_qs, Nk, nkr,
+                    q_stride_h, k_stride_h, scale, s);
     else
-      score_colpass_f32<128><<<grid, 64, 0, s>>>(q, q_rows, k_r, lse_in, per_head, per_head_stride, rep, n_qs, nkr,
-                                                   q_stride_h, k_stride_h, scale);
-    PC_CHECK_LAUNCH("pc_score column pass");
+      score_f32<128>(q, q_rows, k, k_r, lse, lse_stride_h, ws_lse, per_head, per_head_stride, Hq, Hkv, n_qs, Nk, nkr,
+                     q_stride_h, k_stride_h, scale, s);
+    PC_CHECK_LAUNCH("pc_score passes");
     if (share_heads) {
       score_reduce<<<ceil_div(nkr, 256), 256, 0, s>>>(ws_col, score + key_begin, score_stride_h, 1, Hkv, nkr, 1);
       PC_CHECK_LAUNCH("pc_score head sum");

@@ -326,6 +326,18 @@ def test_score_f32_config1():
     _score_check(w, w.Q, w.K)
 
 
+# edges of the fp32 passes' 16-row tiles and of the wave turns over keys (256 per turn)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_qs,nk", [(1, 1), (15, 17), (16, 16), (17, 31), (33, 257), (130, 515)])
+def test_score_f32_tile_edges(d, n_qs, nk):
+    Q, K, _ = _attn_case("f32", 6, 2, n_qs, nk, d, n_qs + nk)
+    w = synth.config1()
+    w.Hq, w.Hkv, w.D = 6, 2, d
+    _score_check(w, Q, K)
+    lse = torch.from_numpy(orc.frame_attn(Q, K, K, d ** -0.5)[1].astype(np.float32)).to(DEV)
+    _score_check(w, Q, K, share=True, lse=lse)
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("share", [False, True])
 def test_score_bf16_midsize(share, fold):
