@@ -60,6 +60,17 @@ __device__ __forceinline__ void stage_tile(const uint16_t* __restrict__ base_h, 
   }
 }
 
+// The query rows of one KV head are numbered through its `rep` query heads: row rho is row
+// rho % Nq of head kvh * rep + rho / Nq.  A tile of rows may span heads, so a frame that is no
+// multiple of the tile leaves at most one part-filled tile per KV head instead of one per head.
+struct RowAt {
+  int head, row;
+};
+__device__ __forceinline__ RowAt row_at(int rho, int kvh, int rep, int Nq) {
+  const int in_group = rho / Nq;
+  return {kvh * rep + in_group, rho - in_group * Nq};
+}
+
 // One phase of the software pipeline (see the kernel comment): 8 score products, then 8
 // value products, with one element of the probability stage behind each.
 // The probabilities are formed against the reference m_ref as it stands; no maximum is
@@ -187,36 +198,25 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  auto k_slot = [&](int t) { return (t & (kStages - 1)) * kTileBytes; };
-  auto v_slot = [&](int t) { return (kStages + (t & (kStages - 1))) * kTileBytes; };
+  auto k_slot = [](int t) { return (t & (kStages - 1)) * kTileBytes; };
+  auto v_slot = [](int t) { return (kStages + (t & (kStages - 1))) * kTileBytes; };
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  // logical order: key split slowest, then head, then row tile
-  const int Hq_tiles = static_cast<int>(gridDim.x) / n_splits;
-  const int split = L / Hq_tiles;
-  const int h = (L % Hq_tiles) / n_tiles_q, tile = L % n_tiles_q;
-  const int kvh = h / rep;
-  const int row0 = tile * kBM + wave * 32;
-  const bool active = row0 < Nq;  // wave-uniform
+  // logical order: key split slowest, then KV head, then row tile
+  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
+  const int split = L / tiles_all;
+  const int kvh = (L % tiles_all) / n_tiles_q, tile = L % n_tiles_q;
+  const int n_rows = rep * Nq;    // query rows of the KV head
+  const int rho = tile * kBM + wave * 32 + l32;   // the row this lane owns
+  const bool active = rho - l32 < n_rows;  // wave-uniform
+  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, Nq);
 
-  const uint16_t* Qh = Q + h * q_stride_h;
   const uint16_t* Kh = K + kvh * kv_stride_h;
   const uint16_t* Vh = V + kvh * kv_stride_h;
 
-  bf16x8 qf[8];
-  {
-    const int row = min(row0 + l32, Nq - 1);
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-      qf[s] = *reinterpret_cast<const bf16x8*>(Qh + static_cast<int64_t>(row) * kD + s * 16 + g * 8);
-    // Make the compiler retire these loads here: otherwise it guards every use of qf inside
-    // the loop with s_waitcnt vmcnt(7..0), which also drains the direct K/V loads in flight.
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
-  }
   f32x16 o[4];
 #pragma unroll
   for (int db = 0; db < 4; ++db)
@@ -251,30 +251,40 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     }
   }
 
-  // this work-group's share of the key tiles: [t0, t0 + n) of n_all (the host leaves no share empty)
+  // this work-group's share of the key tiles: n of n_all (the host leaves no share empty)
   const int n_all = (Nk + kBN - 1) / kBN;
   const int per = (n_all + n_splits - 1) / n_splits;
-  const int t0 = split * per;
-  const int n = min(per, n_all - t0);
-  const int key0 = t0 * kBN;
-  const bool tail = (Nk % kBN) != 0 && t0 + n == n_all;   // the ragged last tile is in this share
-  const int lim_a = Nk - (n_all - 1) * kBN - g * 4;  // last tile: first invalid key offset, half A
-  const int lim_b = lim_a - 32;
+  const int n = min(per, n_all - split * per);
+  const int key0 = split * per * kBN;
+  const int n_valid = Nk - key0;   // less than n tiles only where the ragged last tile is in this share
 
   // the V slot of "tile -1" is read once against zero probabilities: clear it
   for (int e = threadIdx.x; e < kTileBytes / 16; e += kPPThreads)
     reinterpret_cast<__attribute__((address_space(3))) u32x4*>(smem + v_slot(-1))[e] = u32x4{0u, 0u, 0u, 0u};
-  // Prologue, in order of need: K(0), V(0), K(1), then K(2), V(1), K(3), V(2).  Tiles past the
-  // end of the cache are fetched too (clamped rows, never read) so that every staging point
+  // Prologue, in order of need: K(0), V(0), K(1), the queries, then K(2), V(1), K(3), V(2).  Tiles past
+  // the end of the cache are fetched too (clamped rows, never read) so that every staging point
   // issues the same number of loads and the in-flight count can be waited on.
-  stage_tile<false>(Kh, key0, Nk, lds0 + k_slot(0), wave, lane);
-  stage_tile<true>(Vh, key0, Nk, lds0 + v_slot(0), wave, lane);
-  stage_tile<false>(Kh, key0 + kBN, Nk, lds0 + k_slot(1), wave, lane);
-  stage_tile<false>(Kh, key0 + 2 * kBN, Nk, lds0 + k_slot(2), wave, lane);
-  stage_tile<true>(Vh, key0 + kBN, Nk, lds0 + v_slot(1), wave, lane);
-  stage_tile<false>(Kh, key0 + 3 * kBN, Nk, lds0 + k_slot(3), wave, lane);
-  stage_tile<true>(Vh, key0 + 2 * kBN, Nk, lds0 + v_slot(2), wave, lane);
-  dma_wait_older();
+  auto stage_k = [&](int j) { stage_tile<false>(Kh, key0 + j * kBN, Nk, lds0 + k_slot(j), wave, lane); };
+  auto stage_v = [&](int j) { stage_tile<true>(Vh, key0 + j * kBN, Nk, lds0 + v_slot(j), wave, lane); };
+  stage_k(0);
+  stage_v(0);
+  stage_k(1);
+  bf16x8 qf[8];
+  {
+    const uint16_t* qrow = Q + at_row.head * q_stride_h + static_cast<int64_t>(at_row.row) * kD + g * 8;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
+    // Behind the first fetches, so that one memory latency covers all of them.
+    // Make the compiler retire these loads here: otherwise it guards every use of qf inside
+    // the loop with s_waitcnt vmcnt(7..0), which also drains the direct K/V loads in flight.
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
+  }
+  stage_k(2);
+  stage_v(1);
+  stage_k(3);
+  stage_v(2);
+  dma_wait_older();  // K(0), V(0), K(1)
   __syncthreads();
 
   auto mask_tail = [&](f32x16& sc, int lim) {
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
         neg_m[i] = -m_ref;
       }
     }
-    if (tail && n == 1) mask_tail(sA, lim_a);
+    if (n_valid < kBN) mask_tail(sA, n_valid - g * 4);
   }
 
   // Tile j lives in LDS slot j % 4.  The loop is unrolled four times so that every slot is a
@@ -312,12 +322,12 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     constexpr int u = decltype(slot_tag)::value;            // j % kStages
     constexpr int k_cur = u * kTileBytes, k_nxt = ((u + 1) & 3) * kTileBytes;
     constexpr int v_prev = (kStages + ((u + 3) & 3)) * kTileBytes, v_cur = (kStages + u) * kTileBytes;
-    const bool last = j + 1 == n;
+    const int left = n_valid - j * kBN;   // valid keys from this tile on
     // ---- phase 1: S_B(j), O += V_B(j-1) P_B(j-1)  |  P_A(j) ----
     if (active) {
       pipeline_phase<kUnitC>(smem + k_cur + 32 * kRowBytes, k_off, smem + v_prev + 32 * kRowBytes, v_off, qf, sB, pB, o, sA,
                      pA, m_ref, l_run, c, neg_m);
-      if (last && tail) mask_tail(sB, lim_b);
+      if (left < kBN) mask_tail(sB, left - 32 - g * 4);
     }
     // One barrier per tile: every wave is past K(j) and V(j-1), and K(j+1), V(j) (fetched
     // kStages - 1 tiles ago) have landed: each wave waited for its own share.
@@ -329,7 +339,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     // (after the last tile S_A is formed from a clamped tile and never used)
     if (active) {
       pipeline_phase<kUnitC>(smem + k_nxt, k_off, smem + v_cur, v_off, qf, sA, pA, o, sB, pB, m_ref, l_run, c, neg_m);
-      if (j + 2 == n && tail) mask_tail(sA, lim_a);
+      if (left < 2 * kBN) mask_tail(sA, left - kBN - g * 4);
     }
   };
   for (int j0 = 0; j0 < n; j0 += kStages) {
@@ -364,11 +374,11 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
       }
   }
   const float l_tot = wave_half_sum(l_run);
-  const int row = row0 + l32;
+  const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
   if (part_o != nullptr) {  // one of several key shares: un-normalised O, reference and sum for the merge
-    if (row < Nq) {
-      const int64_t at = (static_cast<int64_t>(split) * gridDim.x / n_splits / n_tiles_q + h) * Nq + row;
-      float* prow = part_o + at * kD;
+    if (rho < n_rows) {
+      const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+      float* prow = part_o + at_s * kD;
 #pragma unroll
       for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -378,13 +388,13 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
           for (int e = 0; e < 4; ++e) v[e] = o[db][a * 4 + e];
           *reinterpret_cast<f32x4*>(prow + db * 32 + a * 8 + g * 4) = v;
         }
-      if (g == 0) part_ml[at] = make_float2(m_ref, l_tot);
+      if (g == 0) part_ml[at_s] = make_float2(m_ref, l_tot);
     }
     return;
   }
   const float inv = 1.f / l_tot;
-  if (row < Nq) {
-    uint16_t* orow = O + h * o_stride_h + static_cast<int64_t>(row) * kD;
+  if (rho < n_rows) {
+    uint16_t* orow = O + at_row.head * o_stride_h + static_cast<int64_t>(at_row.row) * kD;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -395,8 +405,222 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
         *reinterpret_cast<u32x2*>(orow + db * 32 + a * 8 + g * 4) = out;
       }
     if (lse != nullptr && g == 0)
-      lse[static_cast<int64_t>(h) * Nq + row] = (m_ref + log2f(l_tot)) * 0.6931471805599453f;
+      lse[at] = (m_ref + log2f(l_tot)) * 0.6931471805599453f;
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// bf16 frame attention for small calls: 32 query rows per work-group, the 8 waves take the keys in
+// steps of 32 by turns, each through LDS of its own (a step's fragments go to registers at once, and
+// the next step is fetched behind them), so the loop has no barrier; (O, m, l) of the waves are
+// merged through LDS once.  Bound: latency.  Eight times as many work-groups as
+// attn_bf16_kernel makes of the same rows, each an eighth as long; K and V come through L2 once per
+// 32 rows instead of once per 256, which is why large calls do not take this form (a step of 8 x 32
+// keys takes 1.4 us with every compute unit at it: 0.78 PFLOP/s at most).  8/2 heads x 252 rows x
+// 1,179 keys: 34 us in 8 work-groups of 256 rows, 12.4 us un-split in 64 of these, 11.9 us with
+// three key shares.  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
+// ------------------------------------------------------------------------------------------
+constexpr int kSmallRows = 32;
+constexpr int kSmallKeys = 32;                                  // keys per wave and step
+constexpr int kSmallTileBytes = kSmallKeys * kRowBytes;
+constexpr int kSmallOBytes = kSmallRows * kD * 4;               // a wave's O on its way to the merge
+constexpr size_t kSmallSmem = 8 * (kSmallOBytes + kSmallRows * 8);
+static_assert(2 * kSmallTileBytes <= kSmallOBytes, "a wave stages K and V in the LDS of its merge piece");
+
+__global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
+    int64_t kv_stride_h, int64_t o_stride_h, float c, int n_tiles_q, int n_splits, float* __restrict__ part_o,
+    float2* __restrict__ part_ml) {
+  extern __shared__ __align__(16) uint8_t smem_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const lds_u8* lds = (lds_u8*)smem_raw + wave * kSmallOBytes;
+  const uint32_t lds_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
+  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
+  const int split = L / tiles_all;
+  const int kvh = (L % tiles_all) / n_tiles_q, tile = L % n_tiles_q;
+  const int n_rows = rep * Nq;
+  const int rho = tile * kSmallRows + l32;
+  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, Nq);
+  const uint16_t* Kh = K + kvh * kv_stride_h;
+  const uint16_t* Vh = V + kvh * kv_stride_h;
+
+  // this share's keys, whole steps but for the very last
+  const int steps_all = (Nk + kSmallKeys - 1) / kSmallKeys, per = (steps_all + n_splits - 1) / n_splits;
+  const int k_begin = split * per * kSmallKeys, k_end = min(k_begin + per * kSmallKeys, Nk);
+
+  // a step's 32 rows of K and of V, two 8-KB pieces of the wave's LDS
+  auto stage = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = i * 4 + (lane >> 4);
+      const int64_t at = static_cast<int64_t>(min(k0 + row, Nk - 1)) * kD;
+      dma_16B(Kh + at + k_chunk_pos(row, lane & 15) * 8, lds_w + i * 1024);
+      dma_16B(Vh + at + v_chunk_pos(row, lane & 15) * 8, lds_w + kSmallTileBytes + i * 1024);
+    }
+  };
+  const int k_first = k_begin + wave * kSmallKeys;
+  stage(k_first);
+  bf16x8 qf[8];
+  {
+    const uint16_t* qrow = Q + at_row.head * q_stride_h + static_cast<int64_t>(at_row.row) * kD + g * 8;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
+  }
+  int k_off[8], v_off[4];  // as in attn_bf16_kernel
+#pragma unroll
+  for (int s = 0; s < 8; ++s) k_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  {
+    const int r = lane & 15, G = (lane >> 4) & 1;
+    const int row = g * 4 + (r >> 2);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      const int dim = db * 32 + G * 16 + 4 * (r & 3);
+      v_off[db] = kSmallTileBytes + row * kRowBytes + v_chunk_pos(row, dim >> 3) * 16 + (dim & 7) * 2;
+    }
+  }
+  f32x16 o[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  float m = -INFINITY, l = 0.f;
+
+  for (int k0 = k_first; k0 < k_end; k0 += 8 * kSmallKeys) {
+    // This step's rows have landed (they are all that is in flight): take every fragment into
+    // registers, so that the next step's rows can be fetched into the same LDS at once.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bf16x8 kf[8], vf[2][4];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[s] = lds_frag(lds + k_off[s]);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) {
+        const lds_u8* src = lds + v_off[db] + ks * 16 * kRowBytes;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src)));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src + 8 * kRowBytes)));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          vf[ks][db][e] = lo[e];
+          vf[ks][db][4 + e] = hi[e];
+        }
+      }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[s]));
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(vf[ks][db]));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (k0 + 8 * kSmallKeys < k_end) stage(k0 + 8 * kSmallKeys);  // wave-uniform
+    f32x16 sc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], sc, 0, 0, 0);
+    if (k0 + kSmallKeys > k_end) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + (i >> 2) * 8 + g * 4 + (i & 3) >= k_end) sc[i] = -INFINITY;
+    }
+    float mx = sc[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sc[i]);
+    mx = wave_half_max(mx) * c;        // key k0 is valid: not -inf
+    if (__any(!(mx <= m + 8.f))) {     // the reference lags by at most 2^8 (always taken first: m = -inf)
+      const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+      m = m_new;
+    }
+    bf16x8 p[2];
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float e = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -m));
+      sum += e;
+      p[i >> 3][i & 7] = static_cast<__bf16>(e);
+    }
+    l += sum;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], p[ks], o[db], 0, 0, 0);
+  }
+  // a wave without keys still has its first fetch in flight
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  l = wave_half_sum(l);
+
+  // merge in wave order: a wave's O goes to the LDS its keys came through, piece i = accumulators
+  // 4 i .. 4 i + 3 of every lane; thread (wave w, lane) then adds up pieces w and w + 8
+  auto piece = [&](int w, int i) {
+    return reinterpret_cast<__attribute__((address_space(3))) f32x4*>((lds_u8*)smem_raw + w * kSmallOBytes + i * 1024 +
+                                                                      lane * 16);
+  };
+  auto* s_ml = reinterpret_cast<__attribute__((address_space(3))) float*>((lds_u8*)smem_raw + 8 * kSmallOBytes);
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *piece(wave, db * 4 + a) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
+  if (g == 0) {
+    s_ml[(wave * kSmallRows + l32) * 2] = m;
+    s_ml[(wave * kSmallRows + l32) * 2 + 1] = l;
+  }
+  __syncthreads();
+  float mw[8], M = -INFINITY, lt = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    mw[w] = s_ml[(w * kSmallRows + l32) * 2];
+    M = fmaxf(M, mw[w]);               // wave 0 always has keys: not -inf
+  }
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const float wt = __builtin_amdgcn_exp2f(mw[w] - M);   // 0 for a wave that had no keys
+    lt += wt * s_ml[(w * kSmallRows + l32) * 2 + 1];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 v = *piece(w, wave + 8 * t);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][e] += wt * v[e];
+    }
+  }
+  if (rho >= n_rows) return;
+  const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;
+  // piece i of a lane is dims 32 (i / 4) + 8 (i % 4) + 4 g .. + 3 of its row
+  if (part_o != nullptr) {
+    const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int i = wave + 8 * t;
+      *reinterpret_cast<f32x4*>(part_o + at_s * kD + (i >> 2) * 32 + (i & 3) * 8 + g * 4) = acc[t];
+    }
+    if (wave == 0 && g == 0) part_ml[at_s] = make_float2(M, lt);
+    return;
+  }
+  const float inv = 1.f / lt;
+  uint16_t* orow = O + at_row.head * o_stride_h + static_cast<int64_t>(at_row.row) * kD;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int i = wave + 8 * t;
+    u32x2 out;
+    out[0] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
+    out[1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
+    *reinterpret_cast<u32x2*>(orow + (i >> 2) * 32 + (i & 3) * 8 + g * 4) = out;
+  }
+  if (lse != nullptr && wave == 0 && g == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
 }
 
 // Merge of the key shares: O = sum_s e^(m_s - M) O_s / sum_s e^(m_s - M) l_s with M = max_s m_s
@@ -412,17 +636,35 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   const int c = threadIdx.x % kLanes;
   const int64_t n_rows = static_cast<int64_t>(Hq) * Nq;
   if (r >= n_rows) return;
-  float M = -INFINITY;
-  for (int s = 0; s < n_splits; ++s) M = fmaxf(M, part_ml[s * n_rows + r].x);
-  float l = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < n_splits; ++s) {
-    const float2 ml = part_ml[s * n_rows + r];
-    const float w = kF32 ? expf(ml.x - M) : __builtin_amdgcn_exp2f(ml.x - M);
-    l += w * ml.y;
-    const f32x4 v = *reinterpret_cast<const f32x4*>(part_o + (s * n_rows + r) * D + c * 4);
+  // lane s of the row holds share s (n_splits <= kLanes): one load each instead of a chain of them
+  float2 ml = make_float2(-INFINITY, 0.f);
+  if (c < n_splits) ml = part_ml[c * n_rows + r];
+  constexpr int kBatch = 4;   // partial rows in flight
+  auto load = [&](int s0, f32x4 (&v)[kBatch]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += w * v[e];
+    for (int i = 0; i < kBatch; ++i)
+      v[i] = *reinterpret_cast<const f32x4*>(part_o + (min(s0 + i, n_splits - 1) * n_rows + r) * D + c * 4);
+  };
+  f32x4 v[kBatch];
+  load(0, v);
+  float M = ml.x;
+#pragma unroll
+  for (int x = 1; x < kLanes; x *= 2) M = fmaxf(M, __shfl_xor(M, x, kLanes));
+  const float w_mine = kF32 ? expf(ml.x - M) : __builtin_amdgcn_exp2f(ml.x - M);   // 0 beyond the last share
+  float l = w_mine * ml.y;
+#pragma unroll
+  for (int x = 1; x < kLanes; x *= 2) l += __shfl_xor(l, x, kLanes);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0;;) {
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const float w = s0 + i < n_splits ? __shfl(w_mine, s0 + i, kLanes) : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += w * v[i][e];
+    }
+    s0 += kBatch;
+    if (s0 >= n_splits) break;
+    load(s0, v);
   }
   const float inv = 1.f / l;
   const int h = static_cast<int>(r / Nq), row = static_cast<int>(r % Nq);
@@ -439,25 +681,43 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   }
 }
 
-// How many shares to cut the keys into: none unless it fills the 256 compute units in whole
-// rounds noticeably better (e.g. 24 heads x 16 row tiles = 384 work-groups: 1.5 rounds -> 3 rounds
-// of half the length), never so fine that a share's prologue shows.
-int choose_key_splits(int base_blocks, int n_tiles) {
-  int best = 1;
-  double best_score = 0.0;
-  for (int s = 1; s <= 4; ++s) {
-    const int per = ceil_div(n_tiles, s);
-    if (s > 1 && (per < 16 || ceil_div(n_tiles, per) != s)) continue;
-    const int blocks = base_blocks * s, rounds = ceil_div(blocks, 256);
-    const double score = static_cast<double>(blocks) / (rounds * 256.0) * per / (per + 2.0) * (s == 1 ? 1.08 : 1.0);
-    if (score > best_score) {
-      best_score = score;
-      best = s;
+// How a bf16 call is cut: 32 or 256 query rows per work-group, and the key shares.  The estimates
+// are microseconds, fitted to 24 shapes from 0.1 to 974 GFLOP (2 to 24 heads, 64 to 4,032 rows, 150 to
+// 29,500 keys) in both forms with 1 to 16 shares: `start` is what a work-group costs beside its
+// steps, a step is 64 keys here and 8 x 32 keys there and gets slower as the compute units fill up,
+// a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
+// (512 bytes written and read per row and share).  The cut it picks is at most 4 % slower than the
+// best of them on any of the 24, 0.5 % on average.  Where the line lies, both sides measured: 8/2
+// heads x 252 rows x 1,179 keys, 11.9 us with 32 rows against 18.8 with 256 (and 34 un-split); 16/4
+// x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x 7,455,
+// 92.9 against 67.4.
+struct AttnPlan {
+  bool small;
+  int n_splits;
+};
+AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
+  AttnPlan best = {false, 1};
+  double best_cost = 1e30;
+  auto consider = [&](bool small, int tile_rows, int share_keys, int step_keys, double start, double per_step,
+                      double fill_step) {
+    const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
+    for (int s = 1; s <= std::min(max_splits, units); ++s) {
+      const int per = ceil_div(units, s);
+      if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      const int steps = ceil_div(per * share_keys, step_keys), rounds = ceil_div(base * s, 256);
+      const double merge = s == 1 ? 0.0 : 2.4 + 1.86e-4 * s * Hkv * rows;
+      const double cost = start + rounds * (per_step + fill_step * std::min(1.0, base * s / 256.0)) * steps +
+                          (rounds - 1) * 3.3 + merge;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = {small, s};
+      }
     }
-  }
+  };
+  consider(false, kBM, kBN, kBN, 8.1, 1.14, 0.33);
+  consider(true, kSmallRows, kSmallKeys, 8 * kSmallKeys, 6.0, 1.17, 0.19);
   return best;
 }
-
 // Workspace of n_splits key shares: the partial O rows, then the (m, l) pairs.
 size_t attn_partial_o_bytes(int Hq, int Nq, int D, int n_splits) {
   return align_up(static_cast<size_t>(n_splits) * Hq * Nq * D * sizeof(float), 256);
@@ -692,7 +952,9 @@ using namespace pc;
 extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
   if ((D != 64 && D != 128) || Hq <= 0 || Nq <= 0 || Nk <= 0) return 0;
   int splits = f32_key_splits(Hq, Nq, Nk);   // the call does not say which tier it will be
-  if (D == kD) splits = std::max(splits, choose_key_splits(Hq * ceil_div(Nq, kBM), ceil_div(Nk, kBN)));
+  if (D == kD)                               // ... nor how many KV heads there are
+    for (int rep = 1; rep <= Hq; ++rep)
+      if (Hq % rep == 0) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, kMaxKeySplits).n_splits);
   return attn_partial_bytes(Hq, Nq, D, splits);
 }
 
@@ -717,31 +979,31 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
                          reinterpret_cast<uintptr_t>(V) | reinterpret_cast<uintptr_t>(O);
     PC_REQUIRE(al % 16 == 0 && q_stride_h % 8 == 0 && kv_stride_h % 8 == 0 && o_stride_h % 8 == 0,
                PC_ERR_SHAPE, "pc_frame_attn: bf16 tensors and head strides must be 16-byte aligned");
-    const bool unit_c = scale * 1.4426950408889634f == 1.0f;
-    static std::atomic<uint64_t> lds_ok{0}, lds_ok_u{0};
-    if (int rc = unit_c ? allow_dynamic_lds(reinterpret_cast<const void*>(attn_bf16_kernel<true>), kSmemBytes, lds_ok_u, "pc_frame_attn")
-                        : allow_dynamic_lds(reinterpret_cast<const void*>(attn_bf16_kernel<false>), kSmemBytes, lds_ok, "pc_frame_attn"))
-      return rc;
-    const int n_tiles_q = ceil_div(Nq, kBM);
-    const float c = scale * 1.4426950408889634f;
     // Key shares need the caller's workspace for the partial results; without it (or with one
-    // that is too small or misaligned) the keys are not split, which is always valid.
-    int n_splits = choose_key_splits(Hq * n_tiles_q, ceil_div(Nk, kBN));
-    if (splits_that_fit(n_splits, Hq, Nq, D, ws, ws_bytes) != n_splits) n_splits = 1;
+    // that is misaligned or too small for two) the keys are not split, which is always valid.
+    const AttnPlan plan = plan_bf16(Hkv, rep * Nq, Nk, splits_that_fit(kMaxKeySplits, Hq, Nq, D, ws, ws_bytes));
+    const float c = scale * 1.4426950408889634f;
+    const bool unit_c = c == 1.0f;
+    const auto kernel = plan.small ? attn_bf16_small_kernel : unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
+    const size_t smem = plan.small ? kSmallSmem : kSmemBytes;
+    static std::atomic<uint64_t> lds_ok[3];
+    if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.small ? 2 : unit_c], "pc_frame_attn"))
+      return rc;
+    const int n_tiles_q = ceil_div(rep * Nq, plan.small ? kSmallRows : kBM);
     float* part_o = nullptr;
     float2* part_ml = nullptr;
-    if (n_splits > 1) {
+    if (plan.n_splits > 1) {
       part_o = static_cast<float*>(ws);
-      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, n_splits));
+      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, plan.n_splits));
     }
-    (unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>)<<<dim3(n_tiles_q * Hq * n_splits), kPPThreads, kSmemBytes, s>>>(
+    kernel<<<dim3(n_tiles_q * Hkv * plan.n_splits), kPPThreads, smem, s>>>(
         static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
         static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), lse, rep, Nq, Nk, q_stride_h,
-        kv_stride_h, o_stride_h, c, n_tiles_q, n_splits, part_o, part_ml);
-    if (n_splits > 1) {
+        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml);
+    if (plan.n_splits > 1) {
       PC_CHECK_LAUNCH("pc_frame_attn");
       attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((static_cast<int64_t>(Hq) * Nq + 7) / 8), 256, 0, s>>>(
-          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, n_splits);
+          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits);
     }
   } else {
     PC_REQUIRE(D == 64 || D == 128, PC_ERR_UNSUPPORTED, "pc_frame_attn: fp32 tier needs D=64 or 128, got %d", D);

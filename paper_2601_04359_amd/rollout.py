@@ -36,6 +36,15 @@ MODES = {"pow": pk.PC_BUDGET_POW, "norm": pk.PC_BUDGET_NORM, "half": pk.PC_BUDGE
          "slide": pk.PC_BUDGET_SLIDE, "dense": None}
 
 
+def _attn_workspace(Hq: int, n_frame: int, D: int, device):
+    """Room for the partial results of the key shares of an attention pass: four shares, and up to
+    sixteen where the rows are few (how many a call takes depends on its key count; a workspace that
+    is too small for them only means fewer)."""
+    import torch
+    rows = Hq * n_frame
+    return torch.empty(max(4 * rows, min(16 * rows, 1 << 17)) * (D * 4 + 8) + 1024, dtype=torch.uint8, device=device)
+
+
 class RollingLayer:
     """The packed K/V cache of one layer in HBM and its host-side segment table."""
 
@@ -70,9 +79,7 @@ class RollingLayer:
         self.slide_t_scale, self.shift = slide_t_scale, 0
         n_rows = min(n_score, n_frame)
         self.q_rows = ((torch.arange(n_rows, dtype=torch.int64) * n_frame) // n_rows).to(torch.int32).to(device)
-        # room for the partial results of up to four key shares (the split depends on the key
-        # count of the call; a workspace that is too small only means no split)
-        self._ws_attn = torch.empty(4 * Hq * n_frame * (D * 4 + 8) + 1024, dtype=torch.uint8, device=device)
+        self._ws_attn = _attn_workspace(Hq, n_frame, D, device)
         if mode != "dense":   # the full-cache baseline neither scores nor compacts
             self.score = torch.empty((hsel, capacity), dtype=torch.float32, device=device)
             self._ws_score = torch.empty(pk.pc_score_workspace_bytes(Hq, Hkv, n_rows, capacity, share_heads),
@@ -234,7 +241,7 @@ class RollingStack:
         self.nk = 0
         n_rows = min(n_score, n_frame)
         self.q_rows = ((torch.arange(n_rows, dtype=torch.int64) * n_frame) // n_rows).to(torch.int32).to(device)
-        self._ws_attn = torch.empty(4 * Hq * n_frame * (D * 4 + 8) + 1024, dtype=torch.uint8, device=device)
+        self._ws_attn = _attn_workspace(Hq, n_frame, D, device)
         self._ws_score = torch.empty(pk.pc_score_workspace_bytes(Hq, Hkv, n_rows, capacity, share_heads),
                                      dtype=torch.uint8, device=device)
         self._ws_compact = torch.empty(pk.pc_compact_batch_workspace_bytes(n_layers, Hkv, capacity, share_heads),

@@ -227,6 +227,38 @@ def test_frame_attn_bf16_key_shares_and_merge(hq, hkv, nq, nk, fold):
     assert (split.float() - whole.float()).abs().max().item() <= 2 ** -6   # two roundings of values of O(1)
 
 
+# Row tiles that span query heads (nq is no multiple of the tile), steps and tiles of the keys that are
+# empty, single or ragged, and both forms of the kernel: the first five shapes take 32 rows per
+# work-group (un-split, then in key shares), the last two 256 rows (in key shares, then un-split).
+# step: logits climb along the key axis, as above.  Every row is computed; the oracle checks the rows
+# at the tile edges and a stride of the others.
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
+@pytest.mark.parametrize("hq,hkv,nq,nk", [(2, 1, 33, 1), (3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 84, 255),
+                                          (2, 1, 184, 5000), (24, 8, 520, 2100), (16, 4, 2010, 2499)])
+def test_frame_attn_bf16_row_tiles_across_heads(hq, hkv, nq, nk, step, fold):
+    Q, K, V = _attn_case("bf16", hq, hkv, nq, nk, 128, nq + nk)
+    scale = 128 ** -0.5
+    if step:
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * (np.arange(nk) // 32) / (8.0 * scale)
+        Q, K = synth.to_bf16(Q), synth.to_bf16(K)
+    if fold:
+        Q, scale = _fold(Q, scale)
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(dev(Q, "bf16"), dev(K, "bf16"), dev(V, "bf16"), nk, scale, lse=lse)
+    rows = sorted({0, 1, nq // 2, nq - 2, nq - 1} | set(range(0, nq, 97)))
+    Ow, Lw = orc.frame_attn(np.ascontiguousarray(Q[:, rows]), K, V, scale)
+    err = np.abs(host(O)[:, rows].astype(np.float64) - Ow)
+    # a climb of 40 per half tile leaves all weight on the last keys: |O| reaches 4, where bf16 values
+    # lie 2^-6 apart (outputs and probabilities rounded once each); else |O| < 2 as in the other tests
+    tol = 2 ** -5 if step == 40.0 or nk < 40 else 2e-2
+    assert err.max() <= tol and err.mean() <= 2e-3, (err.max(), err.mean())
+    lw_ulp = np.maximum(1.0, np.abs(Lw)) * 2.0 ** -20     # fp32 products and logs of values up to |Lw|
+    assert (np.abs(host(lse)[:, rows].astype(np.float64) - Lw) <= np.maximum(1e-3, lw_ulp)).all()
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("seed", [0, 1, 2, 3])
 def test_frame_attn_bf16_error_bound_at_twice_the_workload_amplitude(seed, fold):
