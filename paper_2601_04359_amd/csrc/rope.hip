@@ -17,6 +17,28 @@ struct RopeFreq {
   uint8_t axis[kMaxPairs];     // which coordinate (0 = t, 1 = h, 2 = w) turns the pair
 };
 
+// The frequencies of the last (sections, base) this host thread asked for: a model uses one set, and
+// its pow() calls are a quarter of the host time of a small call.
+const RopeFreq& rope_freq(const int (&secs)[3], double base) {
+  thread_local RopeFreq fr;
+  thread_local int of_secs[3] = {-1, -1, -1};
+  thread_local double of_base = 0.0;
+  if (secs[0] == of_secs[0] && secs[1] == of_secs[1] && secs[2] == of_secs[2] && base == of_base) return fr;
+  int p = 0;
+  for (int a = 0; a < 3; ++a)
+    for (int i = 0; i < secs[a] / 2; ++i, ++p) {
+      fr.inv_freq[p] = pow(base, -2.0 * i / secs[a]);
+      fr.axis[p] = static_cast<uint8_t>(a);
+    }
+  for (; p < kMaxPairs; ++p) {
+    fr.inv_freq[p] = 0.0;
+    fr.axis[p] = 0;
+  }
+  for (int a = 0; a < 3; ++a) of_secs[a] = secs[a];
+  of_base = base;
+  return fr;
+}
+
 // Phase 1: cos/sin of the kTokPerBlock x (D/2) angles of this work-group, angle formed
 // and reduced in fp64 (positions reach hundreds of radians), kept as fp32 in LDS.
 // Phase 2: every thread rotates 16 bytes (8 bf16 = 4 pairs, or 4 fp32 = 2 pairs) per head.
@@ -155,17 +177,7 @@ extern "C" int pc_rope3d(void* x, int dtype, int H, int n, int D, int64_t stride
                  reinterpret_cast<uintptr_t>(x) % 16 == 0,
              PC_ERR_SHAPE, "pc_rope3d: x and its head stride must be 16-byte aligned");
 
-  RopeFreq fr;
-  int p = 0;
-  for (int a = 0; a < 3; ++a)
-    for (int i = 0; i < secs[a] / 2; ++i, ++p) {
-      fr.inv_freq[p] = pow(base, -2.0 * i / secs[a]);
-      fr.axis[p] = static_cast<uint8_t>(a);
-    }
-  for (; p < kMaxPairs; ++p) {
-    fr.inv_freq[p] = 0.0;
-    fr.axis[p] = 0;
-  }
+  const RopeFreq& fr = rope_freq(secs, base);
   // heads are dealt to grid.y in groups of four when there are many: more work-groups in flight
   // for the price of recomputing the (shared) sines and cosines
   const dim3 grid(ceil_div(n, kTokPerBlock), H >= 8 ? 2 : 1);
@@ -197,10 +209,9 @@ extern "C" int pc_rebase(void* K, int dtype, int Hkv, int D, int64_t k_stride_h,
              PC_ERR_SHAPE, "pc_rebase: a head stride is smaller than the rows it must hold");
   PC_REQUIRE((k_stride_h * (dtype == PC_BF16 ? 2 : 4)) % 16 == 0 && reinterpret_cast<uintptr_t>(K) % 16 == 0,
              PC_ERR_SHAPE, "pc_rebase: K and its head stride must be 16-byte aligned");
-  RebaseTable tab;
-  for (int i = 0; i < kMaxPairs; ++i) {
-    double ang = 0.0;
-    if (i < sec_t / 2) ang = -static_cast<double>(delta_t) * pow(base, -2.0 * i / sec_t);
+  RebaseTable tab = {};
+  for (int i = 0; i < sec_t / 2; ++i) {
+    const double ang = -static_cast<double>(delta_t) * pow(base, -2.0 * i / sec_t);
     tab.cs[i] = make_float2(static_cast<float>(cos(ang)), static_cast<float>(sin(ang)));
   }
   const int chunks_t = sec_t / elems;
