@@ -20,7 +20,10 @@
 // Each element of the product costs one exponential, so both passes are bound by the vector
 // pipe, not the matrix pipe; matrix and vector instructions overlap only inside one wave's
 // instruction stream, so every wave interleaves the 16 products of the next half tile with
-// the exponentials of the one before.
+// the exponentials of the one before.  Small calls take a form of either pass in which the eight
+// waves share 64 stationary rows and deal the streamed rows among them.  The scoring rows of a
+// KV head are numbered head after head, so a tile of them may span heads.
+#include <limits.h>
 #include <math.h>
 
 #include <algorithm>
@@ -39,9 +42,10 @@ constexpr int kTileRows = 64;        // streamed rows per LDS slot
 constexpr int kRowBytes = kD * 2;
 constexpr int kTileBytes = kTileRows * kRowBytes;
 constexpr int kStages = 4;
-constexpr int kLseSlotBytes = kTileRows * 4;
 constexpr size_t kRowSmem = kStages * kTileBytes;
-constexpr size_t kColSmem = kStages * (kTileBytes + kLseSlotBytes);
+constexpr int kPrepTiles = 64;       // tiles whose rows pass 2 prepares in LDS at a time
+constexpr int kPrepRows = (kPrepTiles + kStages) * kTileRows;
+constexpr size_t kColSmem = kStages * kTileBytes + kPrepRows * 12;
 constexpr int kMaxSplits = 32;       // key splits of pass 1
 constexpr int kMaxQSplits = 8;       // query splits of pass 2
 constexpr float kNoMax = -1e30f;     // finite stand-in for "no key seen yet"
@@ -157,26 +161,11 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   const int l32 = lane & 31, g = lane >> 5;
   // logical order: split slowest, so the work-groups of one XCD stream the same keys
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int split = L / (Hq * n_row_tiles);
-  const int h = (L / n_row_tiles) % Hq, tile = L % n_row_tiles;
-  const int kvh = h / rep;
+  const int Hkv = Hq / rep, split = L / (Hkv * n_row_tiles);
+  const int kvh = (L / n_row_tiles) % Hkv, tile = L % n_row_tiles;
+  const int n_rows = rep * n_qs;   // scoring rows of the KV head's group, numbered head after head
   const int row0 = tile * kBlockRows + wave * kWaveRows;
-  const uint16_t* Qh = Qs + h * q_stride_h;
   const uint16_t* Kh = K + kvh * k_stride_h;
-
-  bf16x8 qf[2][8];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    int row = min(row0 + b * 32 + l32, n_qs - 1);
-    if (q_rows) row = q_rows[row];
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-      qf[b][s] = *reinterpret_cast<const bf16x8*>(Qh + static_cast<int64_t>(row) * kD + s * 16 + g * 8);
-  }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
 
   const int n_tiles = (Nk + kTileRows - 1) / kTileRows;
   const int per = (n_tiles + n_splits - 1) / n_splits;
@@ -185,8 +174,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   if (n <= 0) {  // the host never launches an empty split; keep the partials defined anyway
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const int row = row0 + b * 32 + l32;
-      if (g == 0 && row < n_qs) part[(static_cast<int64_t>(split) * Hq + h) * n_qs + row] = make_float2(kNoMax, 0.f);
+      const int rho = row0 + b * 32 + l32;
+      if (g == 0 && rho < n_rows) part[(static_cast<int64_t>(split) * Hkv + kvh) * n_rows + rho] = make_float2(kNoMax, 0.f);
     }
     return;
   }
@@ -210,6 +199,20 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   stage(0);
   stage(1);
   stage(2);
+  bf16x8 qf[2][8];   // behind the first fetches: one memory latency covers both
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int rho = min(row0 + b * 32 + l32, n_rows - 1), in_group = rho / n_qs;
+    int row = rho - in_group * n_qs;
+    if (q_rows) row = q_rows[row];
+    const uint16_t* qrow = Qs + (kvh * rep + in_group) * q_stride_h + static_cast<int64_t>(row) * kD + g * 8;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[b][s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
   asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   __syncthreads();
   bf16x8 ring[4];
@@ -254,52 +257,83 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
     const float m_o = wave_half_swap(st.m[b]), l_o = wave_half_swap(st.l[b]);
     const float m = fmaxf(st.m[b], m_o);
     const float l = st.l[b] * __builtin_amdgcn_exp2f(st.m[b] - m) + l_o * __builtin_amdgcn_exp2f(m_o - m);
-    const int row = row0 + b * 32 + l32;
-    if (g == 0 && row < n_qs) part[(static_cast<int64_t>(split) * Hq + h) * n_qs + row] = make_float2(m, l);
+    const int rho = row0 + b * 32 + l32;
+    if (g == 0 && rho < n_rows) part[(static_cast<int64_t>(split) * Hkv + kvh) * n_rows + rho] = make_float2(m, l);
   }
 }
 
-// Merge the per-split (max, sum) pairs in split order: lse2 = log2 sum_j 2^(c * s_j), stored
-// NEGATED (pass 2 adds it).  The result is laid out [head][n_pad] with n_pad a multiple of the
-// streamed tile; the padding rows hold -inf so that they add nothing in pass 2.
-__global__ void score_merge_rows(const float2* __restrict__ part, float* __restrict__ lse2, int Hq, int n_qs,
-                                 int n_pad, int n_splits) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= Hq * n_pad) return;
-  const int h = r / n_pad, row = r % n_pad;
-  if (row >= n_qs) {
-    lse2[r] = -INFINITY;
-    return;
+// Negated base-2 normalisers of the scoring rows of KV head kvh (numbered head after head), from one of
+// three sources: an array of them (`ready`), the caller's natural-log LSE (`lse`, indexed like the rows
+// of Qs), or the row pass's n_splits (reference, sum) pairs, merged in split order: -log2 sum_j
+// 2^(c * s_j).  Rows past the last one give -inf: they add nothing.
+struct RowNorm {
+  const float* ready;        // [Hkv][rep * n_qs], or NULL
+  const float* lse;          // the caller's, or NULL
+  int64_t lse_stride_h;
+  const int32_t* q_rows;
+  const float2* part;        // [split][Hkv][rep * n_qs]
+  int64_t part_stride;       // Hkv * rep * n_qs
+  int n_splits, rep, n_qs;
+};
+// v[i]: row rho0 + i * step.  The loads of all of them are in flight together.
+template <int kN>
+__device__ __forceinline__ void row_norms(const RowNorm& a, int kvh, int rho0, int step, float (&v)[kN]) {
+  const int n_rows = a.rep * a.n_qs;
+  if (a.ready) {
+#pragma unroll
+    for (int i = 0; i < kN; ++i) v[i] = a.ready[static_cast<int64_t>(kvh) * n_rows + min(rho0 + i * step, n_rows - 1)];
+  } else if (a.lse) {
+    int head[kN], row[kN];
+#pragma unroll
+    for (int i = 0; i < kN; ++i) {
+      const int rho = min(rho0 + i * step, n_rows - 1), in_group = rho / a.n_qs;
+      head[i] = kvh * a.rep + in_group;
+      row[i] = rho - in_group * a.n_qs;
+      if (a.q_rows) row[i] = a.q_rows[row[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < kN; ++i) v[i] = a.lse[head[i] * a.lse_stride_h + row[i]];
+#pragma unroll
+    for (int i = 0; i < kN; ++i) v[i] *= -1.4426950408889634f;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kN; ++i) {
+      if (rho0 - static_cast<int>(threadIdx.x) + i * step >= n_rows) break;   // no thread has a row left
+      const float2* p = a.part + static_cast<int64_t>(kvh) * n_rows + min(rho0 + i * step, n_rows - 1);
+      constexpr int kBatch = 8;
+      float m = -INFINITY, l = 0.f;
+      for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
+        float2 x[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) x[q] = p[min(s0 + q, a.n_splits - 1) * a.part_stride];
+        float mb = m;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) mb = fmaxf(mb, x[q].x);
+        l *= exp2f(m - mb);       // first batch: 0 * exp2(-inf)
+        m = mb;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (s0 + q < a.n_splits && x[q].y > 0.f) l += x[q].y * exp2f(x[q].x - m);
+      }
+      v[i] = -(m + log2f(l));
+    }
   }
-  const int64_t n_rows = static_cast<int64_t>(Hq) * n_qs, at = static_cast<int64_t>(h) * n_qs + row;
-  float2 p[kMaxSplits];  // all partials first: the loads are independent and overlap
 #pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s) p[s] = s < n_splits ? part[s * n_rows + at] : make_float2(kNoMax, 0.f);
-  float m = -INFINITY;
-#pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s) m = fmaxf(m, p[s].x);
-  float l = 0.f;
-#pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s)
-    if (p[s].y > 0.f) l += p[s].y * exp2f(p[s].x - m);
-  lse2[r] = -(m + log2f(l));
+  for (int i = 0; i < kN; ++i)
+    if (rho0 + i * step >= n_rows) v[i] = -INFINITY;
 }
-
-// A caller's natural-log LSE, indexed like the rows of Qs, -> the dense [head][n_pad] layout
-// of pass 2 in base 2, negated (pass 2 adds it); padding rows hold -inf.
-__global__ void score_import_lse(const float* __restrict__ lse, int64_t lse_stride_h,
-                                 const int32_t* __restrict__ q_rows, float* __restrict__ out, int Hq, int n_qs,
-                                 int n_pad) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= Hq * n_pad) return;
-  const int h = r / n_pad, row = r % n_pad;
-  out[r] = row < n_qs ? lse[h * lse_stride_h + (q_rows ? q_rows[row] : row)] * -1.4426950408889634f : -INFINITY;
+// The `ready` array, for calls whose many work-groups would each do the same merging.
+__global__ __launch_bounds__(256) void score_row_norms(RowNorm a, float* __restrict__ out) {
+  const int rho = blockIdx.x * 256 + threadIdx.x, n_rows = a.rep * a.n_qs;
+  float v[1];
+  row_norms(a, blockIdx.y, rho, 0, v);
+  if (rho < n_rows) out[static_cast<int64_t>(blockIdx.y) * n_rows + rho] = v[0];
 }
 
 // ---- pass 2: column mass --------------------------------------------------------------------
 // S = Q K^T: a lane owns one key column of each stationary block and 16 of the 32 query rows
-// of the half tile.  The streamed operand is the list of (query head of the group, 64-row
-// tile) pairs; the normalisers of a tile travel through LDS beside it.
+// of the half tile.  The streamed operand is the scoring rows of the group, head after head, in
+// tiles of 64; where they lie and their normalisers are prepared in LDS before the loop.
 // nlq: the negated normalisers of the 16 query rows the lane holds.  kUnitC (c == 1): the
 // products were started from nlq, so s already holds s - lse2.
 template <bool kUnitC>
@@ -317,14 +351,14 @@ __device__ __forceinline__ void col_epilogue(int i, const f32x16 (&s)[2], const 
 
 template <bool kUnitC>
 __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
-    const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K,
-    const float* __restrict__ lse2, float* __restrict__ out, int64_t out_stride_h, int64_t out_stride_split,
-    int /*Hkv*/, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c, int n_key_blocks,
-    int n_qsplits) {
+    const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K, RowNorm norm,
+    float* __restrict__ out, int64_t out_stride_h, int64_t out_stride_split, int rep, int n_qs, int Nk, int64_t q_stride_h,
+    int64_t k_stride_h, float c, int n_key_blocks, int n_qsplits) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  constexpr int kLse0 = kStages * kTileBytes;
+  int64_t* s_src = reinterpret_cast<int64_t*>(smem_raw + kStages * kTileBytes);   // element offset of a row in Qs
+  float* s_norm = reinterpret_cast<float*>(s_src + kPrepRows);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
@@ -342,74 +376,86 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
     for (int s = 0; s < 8; ++s)
       kf[b][s] = *reinterpret_cast<const bf16x8*>(Kh + static_cast<int64_t>(key) * kD + s * 16 + g * 8);
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
 
-  const int tiles_per_head = (n_qs + kTileRows - 1) / kTileRows;
-  const int n_pad = tiles_per_head * kTileRows;
-  const int n_vt = rep * tiles_per_head;
+  const int n_rows = rep * n_qs, n_vt = (n_rows + kTileRows - 1) / kTileRows;
   const int per = (n_vt + n_qsplits - 1) / n_qsplits;
-  const int t_begin = min(qsplit * per, n_vt), t_end = min(t_begin + per, n_vt);
-  const int n = t_end - t_begin;
+  const int t_end = min((qsplit + 1) * per, n_vt);
+
+  int a_off[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  const int my_row = wave * 8 + (lane >> 4);   // this lane fetches rows my_row and my_row + 4 of a tile
+  struct Src {
+    int64_t at[2];
+  };
+  auto src_of = [&](int j) {
+    const int64_t* p = s_src + j * kTileRows + my_row;
+    return Src{{p[0], p[4]}};
+  };
+  auto stage = [&](int j, const Src& r) {
+    stage_rows([&](int, int i) { return Qs + r.at[i]; }, lds0 + (j & (kStages - 1)) * kTileBytes, wave, lane);
+  };
+  auto slot = [&](int j) { return smem + (j & (kStages - 1)) * kTileBytes; };
+  // normalisers of the 16 rows this lane holds in half `half` of tile j
+  auto load_lq = [&](int j, int half, f32x16& lq) {
+    const float* base = s_norm + j * kTileRows + half * 32 + g * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(base + q * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lq[q * 4 + e] = v[e];
+    }
+  };
 
   float colsum[2] = {0.f, 0.f};
-  if (n > 0) {
-    int a_off[8];
+  f32x16 sA[2], sB[2];
+  f32x16 lq;            // general path: normalisers of the half tile whose elements the epilogue takes
+  f32x16 initA, initB;  // kUnitC: start values of the next sA / sB products, fetched one phase ahead
+  auto startA = [&](int) -> const f32x16& { return initA; };
+  auto startB = [&](int) -> const f32x16& { return initB; };
+  for (int t0 = qsplit * per; t0 < t_end; t0 += kPrepTiles) {   // one turn but for thousands of scoring rows
+    const int n = min(kPrepTiles, t_end - t0);
+    // Sources and normalisers of the turn's rows, and of the kStages tiles after it that are fetched or
+    // looked up but never used.  In the loop no load but the direct ones is then in flight: the
+    // compiler waits for its own loads in order, which would drain the ring with them.
+    // (16/4 heads x 512 rows x 193,792 keys: 377 -> 364 us.)
+    constexpr int kBatch = 4;
+    for (int r0 = threadIdx.x; r0 < (n + kStages) * kTileRows; r0 += kBatch * kThreads) {
+      int head[kBatch], row[kBatch];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
-    // source row (within its head) of the two pieces this lane fetches for tile j
-    auto src_rows = [&](int j, int (&rows)[2]) {
-      const int vt = t_begin + min(j, n - 1);
-      const int r0 = (vt % tiles_per_head) * kTileRows;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = min(r0 + (wave * 2 + i) * 4 + (lane >> 4), n_qs - 1);
-        rows[i] = q_rows ? q_rows[row] : row;
+      for (int i = 0; i < kBatch; ++i) {
+        const int rho = min(t0 * kTileRows + r0 + i * kThreads, n_rows - 1), in_group = rho / n_qs;
+        head[i] = kvh * rep + in_group;
+        row[i] = rho - in_group * n_qs;
+        if (q_rows) row[i] = q_rows[row[i]];
       }
-    };
-    auto stage = [&](int j, const int (&rows)[2]) {
-      const int vt = t_begin + min(j, n - 1);
-      const int h = kvh * rep + vt / tiles_per_head;
-      const uint16_t* Qh = Qs + h * q_stride_h;
-      stage_rows([&](int, int i) { return Qh + static_cast<int64_t>(rows[i]) * kD; },
-                 lds0 + (j & (kStages - 1)) * kTileBytes, wave, lane);
-      if (wave == 0)
-        dma_4B(lse2 + static_cast<int64_t>(h) * n_pad + (vt % tiles_per_head) * kTileRows + lane,
-               lds0 + kLse0 + (j & (kStages - 1)) * kLseSlotBytes);
-    };
-    auto slot = [&](int j) { return smem + (j & (kStages - 1)) * kTileBytes; };
-    // normalisers of the 16 rows this lane holds in half `half` of tile j
-    auto load_lq = [&](int j, int half, f32x16& lq) {
-      const lds_u8* base = smem + kLse0 + (j & (kStages - 1)) * kLseSlotBytes + (half * 32 + g * 4) * 4;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(base + q * 32);
+      for (int i = 0; i < kBatch; ++i)
+        if (r0 + i * kThreads < (n + kStages) * kTileRows)
+          s_src[r0 + i * kThreads] = head[i] * q_stride_h + static_cast<int64_t>(row[i]) * kD;
+    }
+    __syncthreads();
+    stage(0, src_of(0));
+    stage(1, src_of(1));
+    stage(2, src_of(2));
+    for (int r0 = threadIdx.x; r0 < (n + kStages) * kTileRows; r0 += kBatch * kThreads) {
+      float v[kBatch];
+      row_norms(norm, kvh, t0 * kTileRows + r0, kThreads, v);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lq[q * 4 + e] = v[e];
-      }
-    };
-
-    f32x16 sA[2], sB[2];
-    f32x16 lq;            // general path: normalisers of the half tile whose elements the epilogue takes
-    f32x16 initA, initB;  // kUnitC: start values of the next sA / sB products, fetched one phase ahead
-    auto startA = [&](int) -> const f32x16& { return initA; };
-    auto startB = [&](int) -> const f32x16& { return initB; };
-    int rows[2];
-    src_rows(0, rows);
-    stage(0, rows);
-    src_rows(1, rows);
-    stage(1, rows);
-    src_rows(2, rows);
-    stage(2, rows);
-    src_rows(3, rows);
-    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // at least the first tile's pieces
+      for (int i = 0; i < kBatch; ++i)
+        if (r0 + i * kThreads < (n + kStages) * kTileRows) s_norm[r0 + i * kThreads] = v[i];
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // the first tile's pieces
     __syncthreads();
     if constexpr (kUnitC) {
       load_lq(0, 0, initA);
       load_lq(0, 1, initB);
     }
+    Src src = src_of(3);
     bf16x8 ring[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) ring[r] = lds_frag(slot(0) + a_off[r]);
@@ -418,12 +464,12 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
       constexpr int u = decltype(slot_tag)::value;
       dma_wait_all_but_newest();
       __syncthreads();  // tile j+1 has landed everywhere; slot of tile j-1 is free
-      stage(j + 3, rows);
-      src_rows(j + 4, rows);
-      if constexpr (kUnitC) load_lq((u + 1) & 3, 0, initA); else load_lq(u, 0, lq);
+      stage(j + 3, src);
+      src = src_of(j + 4);
+      if constexpr (kUnitC) load_lq(j + 1, 0, initA); else load_lq(j, 0, lq);
       stream_phase<kUnitC>(smem + u * kTileBytes + 32 * kRowBytes, smem + ((u + 1) & 3) * kTileBytes, a_off, kf, sB, startB,
                            [&](int i) { col_epilogue<kUnitC>(i, sA, lq, colsum, c); }, ring);
-      if constexpr (kUnitC) load_lq((u + 1) & 3, 1, initB); else load_lq(u, 1, lq);
+      if constexpr (kUnitC) load_lq(j + 1, 1, initB); else load_lq(j, 1, lq);
       if (j + 1 < n) {
         stream_phase<kUnitC>(smem + ((u + 1) & 3) * kTileBytes, smem + ((u + 1) & 3) * kTileBytes + 32 * kRowBytes, a_off, kf,
                              sA, startA, [&](int i) { col_epilogue<kUnitC>(i, sB, lq, colsum, c); }, ring);
@@ -441,7 +487,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
       if (j0 + 3 >= n) break;
       tile_body(j0 + 3, std::integral_constant<int, 3>{});
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no direct load may outlive the work-group
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no direct load may outlive the turn or the work-group
+    __syncthreads();
   }
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -451,26 +498,298 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
   }
 }
 
+// ---- both passes, small calls ---------------------------------------------------------------
+// A work-group has 64 stationary rows (every wave holds all of them as fragments); its 8 waves take
+// the streamed rows in steps of 32 by turns, each through an LDS double buffer of its own, two steps
+// ahead and without a barrier in the loop, and are merged through LDS once: the row pass cuts its
+// keys less often, and the column pass leaves no partial sums to add up in another launch.  The products
+// of a step and the exponentials of the one before are interleaved as in stream_phase.  Bound: latency
+// (5.5-6 us with one step, of which the launch is about 2).  8/2 heads x 100 rows x 1,804 keys: row
+// pass 9.5 us and its merge 3.5 -> 8.0 us, column pass 10.8 us and its reduction 3.8 -> 8.7 us.
+constexpr int kSmallStep = 32;
+constexpr int kSmallStepBytes = kSmallStep * kRowBytes;
+constexpr int kSmallRing = 8 * 2 * kSmallStepBytes;            // 8 waves x two steps
+constexpr int kSmallMaxRows = 2048;                            // scoring rows pass 2 prepares in LDS
+constexpr size_t kSmallRowSmem = kSmallRing + 8 * kWaveRows * 8;
+constexpr size_t kSmallColSmem = kSmallRing + kSmallMaxRows * 12 + 8 * kWaveRows * 4;
+
+// The rows of step i of a wave have landed when at most the next step's eight loads are in flight.
+// All eight fragments go to registers, so that the buffer can be refilled at once.
+__device__ __forceinline__ void small_fragments(const lds_u8* buf, const int (&a_off)[8], bool more_in_flight, bf16x8 (&f)[8]) {
+  if (more_in_flight)
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < 8; ++s) f[s] = lds_frag(buf + a_off[s]);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(f[s]));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+template <bool kInit, class Init, class Epi>
+__device__ __forceinline__ void small_phase(const bf16x8 (&f)[8], const bf16x8 (&st)[2][8], f32x16 (&acc)[2], Init&& init,
+                                            Epi&& epi) {
+  f32x16 zero;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if constexpr (kInit)
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s], st[b][s], s == 0 ? init(b) : acc[b], 0, 0, 0);
+      else
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s], st[b][s], s == 0 ? zero : acc[b], 0, 0, 0);
+      epi(s * 2 + b);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+__global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
+    const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K,
+    float2* __restrict__ part, int Hkv, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c,
+    int n_row_tiles, int n_splits) {
+  extern __shared__ __align__(16) uint8_t smem_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const lds_u8* ring = (lds_u8*)smem_raw + wave * 2 * kSmallStepBytes;
+  const uint32_t ring_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
+  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
+  const int split = L / (Hkv * n_row_tiles), kvh = (L / n_row_tiles) % Hkv, tile = L % n_row_tiles;
+  const int n_rows = rep * n_qs;
+  const uint16_t* Kh = K + kvh * k_stride_h;
+  const int steps_all = (Nk + kSmallStep - 1) / kSmallStep, per = (steps_all + n_splits - 1) / n_splits;
+  const int t_end = min((split + 1) * per, steps_all), t_first = split * per + wave;
+  const int n = t_first < t_end ? (t_end - t_first + 7) / 8 : 0;   // steps of this wave
+  auto stage = [&](int i) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int row = q * 4 + (lane >> 4);
+      const int key = min((t_first + i * 8) * kSmallStep + row, Nk - 1);
+      dma_16B(Kh + static_cast<int64_t>(key) * kD + k_chunk_pos(row, lane & 15) * 8,
+              ring_w + (i & 1) * kSmallStepBytes + q * 1024);
+    }
+  };
+  if (n > 0) stage(0);
+  if (n > 1) stage(1);
+  bf16x8 qf[2][8];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int rho = min(tile * kWaveRows + b * 32 + l32, n_rows - 1), in_group = rho / n_qs;
+    int row = rho - in_group * n_qs;
+    if (q_rows) row = q_rows[row];
+    const uint16_t* qrow = Qs + (kvh * rep + in_group) * q_stride_h + static_cast<int64_t>(row) * kD + g * 8;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[b][s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
+  int a_off[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+
+  RowState st;
+  st.m[0] = st.m[1] = kNoMax;
+  st.l[0] = st.l[1] = 0.f;
+  float psum[2] = {0.f, 0.f};
+  f32x16 sA[2], sB[2];
+  bf16x8 f[8];
+  auto fetch = [&](int i) {   // fragments of step i; step i + 2 into the buffer they came from
+    small_fragments(ring + (i & 1) * kSmallStepBytes, a_off, i + 1 < n, f);
+    if (i + 2 < n) stage(i + 2);
+  };
+  auto mask = [&](f32x16 (&sc)[2], int i) {
+    const int k0 = (t_first + i * 8) * kSmallStep;
+    if (k0 + kSmallStep > Nk) mask_keys(sc, k0, Nk, g);
+  };
+  auto body = [&](int i, f32x16 (&cur)[2], f32x16 (&nxt)[2]) {
+    mask(cur, i);
+    if (i + 1 < n) {
+      fetch(i + 1);
+      small_phase<false>(f, qf, nxt, NoInit{}, [&](int e) { row_epilogue(e, cur, st, psum, c); });
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) row_epilogue(e, cur, st, psum, c);
+    }
+    row_commit(cur, st, psum, c);
+  };
+  if (n > 0) {
+    fetch(0);
+    small_phase<false>(f, qf, sA, NoInit{}, [](int) {});
+    for (int i = 0; i < n; i += 2) {
+      body(i, sA, sB);
+      if (i + 1 < n) body(i + 1, sB, sA);
+    }
+  }
+  // merge: the halves of a wave, then the waves in order
+  float2* s_ml = reinterpret_cast<float2*>(smem_raw + kSmallRing);
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const float m_o = wave_half_swap(st.m[b]), l_o = wave_half_swap(st.l[b]);
+    const float m = fmaxf(st.m[b], m_o);
+    const float l = st.l[b] * __builtin_amdgcn_exp2f(st.m[b] - m) + l_o * __builtin_amdgcn_exp2f(m_o - m);
+    if (g == 0) s_ml[wave * kWaveRows + b * 32 + l32] = make_float2(m, l);
+  }
+  __syncthreads();
+  const int rho = tile * kWaveRows + threadIdx.x;
+  if (threadIdx.x >= kWaveRows || rho >= n_rows) return;
+  float m = kNoMax, l = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) m = fmaxf(m, s_ml[w * kWaveRows + threadIdx.x].x);
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const float2 v = s_ml[w * kWaveRows + threadIdx.x];
+    l += v.y * __builtin_amdgcn_exp2f(v.x - m);
+  }
+  part[(static_cast<int64_t>(split) * Hkv + kvh) * n_rows + rho] = make_float2(m, l);
+}
+
+template <bool kUnitC>
+__global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
+    const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K, RowNorm norm,
+    float* __restrict__ out, int64_t out_stride_h, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h,
+    float c, int n_key_blocks) {
+  extern __shared__ __align__(16) uint8_t smem_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const lds_u8* ring = (lds_u8*)smem_raw + wave * 2 * kSmallStepBytes;
+  const uint32_t ring_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
+  int64_t* s_src = reinterpret_cast<int64_t*>(smem_raw + kSmallRing);      // element offset of a row in Qs
+  float* s_norm = reinterpret_cast<float*>(smem_raw + kSmallRing + kSmallMaxRows * 8);
+  float* s_sum = s_norm + kSmallMaxRows;
+  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
+  const int kb = L % n_key_blocks, kvh = L / n_key_blocks;
+  const int key0 = kb * kWaveRows;
+  const uint16_t* Kh = K + kvh * k_stride_h;
+  const int n_rows = rep * n_qs, n_steps = (n_rows + kSmallStep - 1) / kSmallStep;
+  const int n = wave < n_steps ? (n_steps - wave + 7) / 8 : 0;   // steps of this wave: wave, wave + 8, ...
+
+  // a thread prepares the rows threadIdx.x + 512 i: every load of a stage is issued before its first use
+  constexpr int kPrep = kSmallMaxRows / kThreads;
+  int head[kPrep], row[kPrep];
+#pragma unroll
+  for (int i = 0; i < kPrep; ++i) {
+    const int r = min(static_cast<int>(threadIdx.x) + i * kThreads, n_rows - 1);
+    head[i] = kvh * rep + r / n_qs;
+    row[i] = r % n_qs;
+    if (q_rows) row[i] = q_rows[row[i]];
+  }
+  bf16x8 kf[2][8];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int key = min(key0 + b * 32 + l32, Nk - 1);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      kf[b][s] = *reinterpret_cast<const bf16x8*>(Kh + static_cast<int64_t>(key) * kD + s * 16 + g * 8);
+  }
+#pragma unroll
+  for (int i = 0; i < kPrep; ++i)
+    s_src[threadIdx.x + i * kThreads] = head[i] * q_stride_h + static_cast<int64_t>(row[i]) * kD;
+  __syncthreads();
+  auto stage = [&](int i) {
+    const int64_t* src = s_src + (wave + i * 8) * kSmallStep + (lane >> 4);
+    const uint32_t to = __builtin_amdgcn_readfirstlane(ring_w + (i & 1) * kSmallStepBytes);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      dma_16B(Qs + src[q * 4] + k_chunk_pos(q * 4 + (lane >> 4), lane & 15) * 8, to + q * 1024);
+  };
+  if (n > 0) stage(0);
+  if (n > 1) stage(1);
+  {
+    float v[kPrep];
+    row_norms(norm, kvh, threadIdx.x, kThreads, v);
+#pragma unroll
+    for (int i = 0; i < kPrep; ++i) s_norm[threadIdx.x + i * kThreads] = v[i];
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+  __syncthreads();
+
+  int a_off[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  auto load_lq = [&](int i, f32x16& lq) {   // normalisers of the 16 rows this lane holds of step i
+    const float* base = s_norm + (wave + i * 8) * kSmallStep + g * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(base + q * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lq[q * 4 + e] = v[e];
+    }
+  };
+  float colsum[2] = {0.f, 0.f};
+  f32x16 sA[2], sB[2], lq;
+  bf16x8 f[8];
+  auto init = [&](int) -> const f32x16& { return lq; };
+  auto fetch = [&](int i) {
+    small_fragments(ring + (i & 1) * kSmallStepBytes, a_off, i + 1 < n, f);
+    if (i + 2 < n) stage(i + 2);
+  };
+  auto body = [&](int i, f32x16 (&cur)[2], f32x16 (&nxt)[2]) {
+    if (!kUnitC) load_lq(i, lq);
+    if (i + 1 < n) {
+      fetch(i + 1);
+      if (kUnitC) load_lq(i + 1, lq);
+      small_phase<kUnitC>(f, kf, nxt, init, [&](int e) { col_epilogue<kUnitC>(e, cur, lq, colsum, c); });
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) col_epilogue<kUnitC>(e, cur, lq, colsum, c);
+    }
+  };
+  if (n > 0) {
+    fetch(0);
+    if (kUnitC) load_lq(0, lq);
+    small_phase<kUnitC>(f, kf, sA, init, [](int) {});
+    for (int i = 0; i < n; i += 2) {
+      body(i, sA, sB);
+      if (i + 1 < n) body(i + 1, sB, sA);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const float v = wave_half_sum(colsum[b]);
+    if (g == 0) s_sum[wave * kWaveRows + b * 32 + l32] = v;
+  }
+  __syncthreads();
+  const int key = key0 + threadIdx.x;
+  if (threadIdx.x >= kWaveRows || key >= Nk) return;
+  float v = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) v += s_sum[w * kWaveRows + threadIdx.x];
+  out[kvh * out_stride_h + key] = v;
+}
+
 // out[h][j] = sum over parts p of part[p][h][j] (p ascending); with share_heads the heads are
-// summed too, head 0 first, into out[j].
+// summed too, head 0 first, into out[j].  Latency-bound: the parts are loaded together.
 __global__ void score_reduce(const float* __restrict__ part, float* __restrict__ out, int64_t out_stride_h,
                              int n_parts, int Hkv, int Nk, int share_heads) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= Nk) return;
   const int64_t split_stride = static_cast<int64_t>(Hkv) * Nk;
+  auto head_sum = [&](int h) {
+    float v[kMaxQSplits];
+#pragma unroll
+    for (int p = 0; p < kMaxQSplits; ++p)
+      v[p] = p < n_parts ? part[p * split_stride + static_cast<int64_t>(h) * Nk + j] : 0.f;
+    float sh = 0.f;
+#pragma unroll
+    for (int p = 0; p < kMaxQSplits; ++p) sh += v[p];   // a missing part adds +0: the sum is unchanged
+    return sh;
+  };
   if (share_heads) {
     float s = 0.f;
-    for (int h = 0; h < Hkv; ++h) {
-      float sh = 0.f;
-      for (int p = 0; p < n_parts; ++p) sh += part[p * split_stride + static_cast<int64_t>(h) * Nk + j];
-      s += sh;
-    }
+#pragma unroll 4
+    for (int h = 0; h < Hkv; ++h) s += head_sum(h);
     out[j] = s;
   } else {
     const int h = blockIdx.y;
-    float sh = 0.f;
-    for (int p = 0; p < n_parts; ++p) sh += part[p * split_stride + static_cast<int64_t>(h) * Nk + j];
-    out[h * out_stride_h + j] = sh;
+    out[h * out_stride_h + j] = head_sum(h);
   }
 }
 
@@ -663,19 +982,69 @@ WsLayout ws_layout(int Hq, int Hkv, int n_qs, int Nk, int /*share_heads*/) {
   return w;
 }
 
-// Number of ways to split the streamed axis (n_tiles tiles) so that `base` x splits
-// work-groups fill the 256 compute units in whole rounds without making a work-group's
-// share so short that its three-tile prologue shows.
-int choose_splits(int base, int n_tiles, int max_splits) {
-  int best = 1;
-  double best_score = -1.0;
-  for (int s = 1; s <= std::min(max_splits, n_tiles); ++s) {
-    const int blocks = base * s, rounds = ceil_div(blocks, 256), per = ceil_div(n_tiles, s);
-    const double score = static_cast<double>(blocks) / (rounds * 256.0) * per / (per + 2.0);
-    if (score > best_score * 1.001) {
-      best_score = score;
-      best = s;
+// How the two passes of a bf16 call are cut: their form (512 stationary rows per work-group, or 64) and
+// the shares of the streamed axis.  The estimates are microseconds, fitted to 22 shapes (100 to 512
+// scoring rows, 2 to 24 heads, 596 to 100,000 keys) in both forms with every number of shares: `start`
+// is what a work-group costs beside its steps, a step gets slower as the compute units fill up, a
+// further round costs a new start, and pass 2 merges the row pass's shares.  Row pass: 1.6 % slower than
+// the best cut on average (at most 1 us); column pass: 0.3 %.  Where the lines lie, both sides measured
+// (16/4 heads unless stated): row pass, 512 rows a head x 2,633 keys 12.9 us with 64 rows against 18.5
+// with 512, x 7,199 22.4 against 23.9, x 20,000 56.6 against 46.5, 100 rows a head x 30,000 25.2
+// against 35.4; column pass, 8/2 heads, 100 x 1,804 8.7 us against 10.5, 6/2 heads, 330 x 3,000 11.8
+// against 12.1, 512 x 2,633 18.3 against 15.2.
+struct PassCost {
+  double start, step, step_filled, round;
+  double of(int blocks, int steps) const {
+    const int rounds = ceil_div(blocks, 256);
+    return start + rounds * (step + step_filled * std::min(1.0, blocks / 256.0)) * steps + (rounds - 1) * round;
+  }
+};
+struct RowPlan {
+  bool small;
+  int n_splits;
+};
+RowPlan plan_rows(int Hkv, int rows, int Nk) {
+  RowPlan best = {false, 1};
+  double best_cost = 1e30;
+  auto consider = [&](bool small, int block_rows, int share_keys, int steps_per, const PassCost& cost) {
+    const int base = Hkv * ceil_div(rows, block_rows), units = ceil_div(Nk, share_keys);
+    for (int s = 1; s <= std::min(kMaxSplits, units); ++s) {
+      const int per = ceil_div(units, s);
+      if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      const double c = cost.of(base * s, ceil_div(per, steps_per)) + s * (0.04 + 1.5e-4 * rows);
+      if (c < best_cost) {
+        best_cost = c;
+        best = {small, s};
+      }
     }
+  };
+  consider(false, kBlockRows, kTileRows, 1, {6.9, 1.49, 0.11, 4.3});
+  consider(true, kWaveRows, kSmallStep, 8, {6.1, 1.05, 0.13, 4.3});
+  return best;
+}
+struct ColPlan {
+  bool small, prepares;   // prepares: the work-groups form the normalisers of their rows themselves
+  int n_qsplits;
+};
+ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
+  const int n_vt = ceil_div(rows, kTileRows), base = Hkv * ceil_div(nkr, kBlockRows);
+  ColPlan best = {false, false, 1};
+  double best_cost = 1e30;
+  for (int s = 1; s <= std::min(kMaxQSplits, n_vt); ++s) {
+    const int per = ceil_div(n_vt, s);
+    if (ceil_div(n_vt, per) != s) continue;
+    const double reduce = s == 1 ? 0.0 : 1.9 + 3.9e-6 * s * Hkv * nkr;
+    const double c = PassCost{7.36, 1.12, 0.36, 4.46}.of(base * s, per) + reduce;
+    if (c < best_cost) {
+      best_cost = c;
+      // A few loads per thread, once per compute unit, are 3-5 us less than a launch in between.
+      best = {false, base * s <= 256 && per * n_splits <= 128, s};
+    }
+  }
+  if (rows <= kSmallMaxRows) {
+    const double c = PassCost{6.03, 1.45, -0.04, 4.46}.of(Hkv * ceil_div(nkr, kWaveRows), ceil_div(rows, 8 * kSmallStep)) +
+                     2.9e-4 * rows;   // the normalisers of all rows, in every work-group
+    if (c < best_cost) best = {true, true, 1};
   }
   return best;
 }
@@ -735,38 +1104,56 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
     // the column pass takes the affine step out of its loop (the row pass has no registers left
     // for the start values of its products and would gain nothing from rebuilding them per phase)
     const bool unit_c = c == 1.0f;
-    const auto col_kernel = unit_c ? score_colpass_bf16<true> : score_colpass_bf16<false>;
-    static std::atomic<uint64_t> row_ok{0}, col_ok[2];
-    if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(score_rowpass_bf16), kRowSmem, row_ok, "pc_score"))
-      return rc;
-    if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(col_kernel), kColSmem, col_ok[unit_c], "pc_score"))
-      return rc;
-    const int n_pad = padded_rows(n_qs);
-    if (lse == nullptr) {
-      const int n_row_tiles = ceil_div(n_qs, kBlockRows);
-      const int n_splits = choose_splits(n_row_tiles * Hq, ceil_div(Nk, kTileRows), kMaxSplits);
-      score_rowpass_bf16<<<n_row_tiles * Hq * n_splits, kThreads, kRowSmem, s>>>(
-          static_cast<const uint16_t*>(Qs), q_rows, static_cast<const uint16_t*>(K), ws_part, Hq, rep, n_qs, Nk,
-          q_stride_h, k_stride_h, c, n_row_tiles, n_splits);
-      PC_CHECK_LAUNCH("pc_score row pass");
-      score_merge_rows<<<ceil_div(Hq * n_pad, 256), 256, 0, s>>>(ws_part, ws_lse, Hq, n_qs, n_pad, n_splits);
-      PC_CHECK_LAUNCH("pc_score merge");
-    } else {
-      score_import_lse<<<ceil_div(Hq * n_pad, 256), 256, 0, s>>>(lse, lse_stride_h, q_rows, ws_lse, Hq, n_qs, n_pad);
-      PC_CHECK_LAUNCH("pc_score lse import");
-    }
-    const int n_key_blocks = ceil_div(nkr, kBlockRows);
-    const int n_qsplits = choose_splits(n_key_blocks * Hkv, rep * (n_pad / kTileRows), kMaxQSplits);
-    const bool direct = n_qsplits == 1 && !share_heads;
+    const uint16_t* q = static_cast<const uint16_t*>(Qs);
+    const uint16_t* k = static_cast<const uint16_t*>(K);
+    const uint16_t* k_r = k + static_cast<int64_t>(key_begin) * kD;
     float* score_r = score + key_begin;
-    col_kernel<<<n_key_blocks * Hkv * n_qsplits, kThreads, kColSmem, s>>>(
-        static_cast<const uint16_t*>(Qs), q_rows, static_cast<const uint16_t*>(K) + static_cast<int64_t>(key_begin) * kD,
-        ws_lse, direct ? score_r : ws_col, direct ? score_stride_h : nkr, static_cast<int64_t>(Hkv) * nkr, Hkv, rep,
-        n_qs, nkr, q_stride_h, k_stride_h, c, n_key_blocks, n_qsplits);
+    static std::atomic<uint64_t> row_ok[2], col_ok[4];
+    auto allow = [](auto kernel, size_t bytes, std::atomic<uint64_t>& done) {
+      return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes, done, "pc_score");
+    };
+    const RowPlan row = plan_rows(Hkv, rep * n_qs, Nk);
+    const ColPlan col = plan_cols(Hkv, rep * n_qs, nkr, lse ? 1 : row.n_splits);
+    if (lse == nullptr) {
+      const int n_row_tiles = ceil_div(rep * n_qs, row.small ? kWaveRows : kBlockRows);
+      if (row.small) {
+        if (int rc = allow(score_rowpass_small, kSmallRowSmem, row_ok[1])) return rc;
+        score_rowpass_small<<<n_row_tiles * Hkv * row.n_splits, kThreads, kSmallRowSmem, s>>>(
+            q, q_rows, k, ws_part, Hkv, rep, n_qs, Nk, q_stride_h, k_stride_h, c, n_row_tiles, row.n_splits);
+      } else {
+        if (int rc = allow(score_rowpass_bf16, kRowSmem, row_ok[0])) return rc;
+        score_rowpass_bf16<<<n_row_tiles * Hkv * row.n_splits, kThreads, kRowSmem, s>>>(
+            q, q_rows, k, ws_part, Hq, rep, n_qs, Nk, q_stride_h, k_stride_h, c, n_row_tiles, row.n_splits);
+      }
+      PC_CHECK_LAUNCH("pc_score row pass");
+    }
+    RowNorm norm = {nullptr, lse, lse_stride_h, q_rows, ws_part, static_cast<int64_t>(Hq) * n_qs, row.n_splits, rep, n_qs};
+    const bool direct = col.n_qsplits == 1 && !share_heads;
+    float* col_out = direct ? score_r : ws_col;
+    const int64_t col_stride = direct ? score_stride_h : nkr;
+    if (col.small) {
+      const auto kernel = unit_c ? score_colpass_small<true> : score_colpass_small<false>;
+      if (int rc = allow(kernel, kSmallColSmem, col_ok[2 + unit_c])) return rc;
+      const int n_key_blocks = ceil_div(nkr, kWaveRows);
+      kernel<<<n_key_blocks * Hkv, kThreads, kSmallColSmem, s>>>(q, q_rows, k_r, norm, col_out, col_stride, rep, n_qs, nkr,
+                                                                 q_stride_h, k_stride_h, c, n_key_blocks);
+    } else {
+      const auto kernel = unit_c ? score_colpass_bf16<true> : score_colpass_bf16<false>;
+      if (int rc = allow(kernel, kColSmem, col_ok[unit_c])) return rc;
+      if (!col.prepares) {
+        score_row_norms<<<dim3(ceil_div(rep * n_qs, 256), Hkv), 256, 0, s>>>(norm, ws_lse);
+        PC_CHECK_LAUNCH("pc_score normalisers");
+        norm.ready = ws_lse;
+      }
+      const int n_key_blocks = ceil_div(nkr, kBlockRows);
+      kernel<<<n_key_blocks * Hkv * col.n_qsplits, kThreads, kColSmem, s>>>(
+          q, q_rows, k_r, norm, col_out, col_stride, static_cast<int64_t>(Hkv) * nkr, rep, n_qs, nkr, q_stride_h,
+          k_stride_h, c, n_key_blocks, col.n_qsplits);
+    }
     PC_CHECK_LAUNCH("pc_score column pass");
     if (!direct) {
-      score_reduce<<<dim3(ceil_div(nkr, 256), share_heads ? 1 : Hkv), 256, 0, s>>>(ws_col, score_r, score_stride_h,
-                                                                                   n_qsplits, Hkv, nkr, share_heads);
+      score_reduce<<<dim3(ceil_div(nkr, 256), share_heads ? 1 : Hkv), 256, 0, s>>>(
+          ws_col, score_r, score_stride_h, col.n_qsplits, Hkv, nkr, share_heads);
       PC_CHECK_LAUNCH("pc_score reduce");
     }
     return PC_OK;

@@ -413,6 +413,41 @@ def test_score_bf16_row_reference_is_refreshed(step, fold):
     assert np.all(np.abs(got - want) <= 2e-7 + rel * want), (np.abs(got - want) / (want + 1e-30)).max()
 
 
+# Scoring rows numbered through the heads of a group (n_qs is no multiple of a tile, or smaller than
+# one), both forms of either pass: the first three shapes have 64 stationary rows per work-group in
+# both; the next has 512 in the column pass; then 512 in both, with the normalisers formed by the
+# column pass itself, by a launch of their own, and of more rows than it prepares at a time.  step:
+# logits climb along the key axis, as above.  The reference is the softmax in 64 bits, on the GPU.
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
+@pytest.mark.parametrize("hq,hkv,n_qs,nk", [(3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 33, 65), (16, 2, 20, 30000),
+                                            (16, 8, 600, 6000), (6, 2, 1100, 12000), (4, 2, 2100, 65000)])
+def test_score_bf16_rows_across_heads(hq, hkv, n_qs, nk, step, fold):
+    Q, K, _ = _attn_case("bf16", hq, hkv, n_qs, nk, 128, n_qs + nk)
+    scale = 128 ** -0.5
+    if step:
+        step *= min(1.0, 125 / (nk // 32))      # as steep as on 4,000 keys at most
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * (np.arange(nk) // 32) / (8.0 * scale)
+        Q, K = synth.to_bf16(Q), synth.to_bf16(K)
+    if fold:
+        Q, scale = _fold(Q, scale)
+    Qd, Kd = dev(Q, "bf16"), dev(K, "bf16")
+    want = torch.zeros((hkv, nk), dtype=torch.float64, device=DEV)
+    lse = torch.empty((hq, n_qs), dtype=torch.float64, device=DEV)
+    for h in range(hq):
+        s = (Qd[h].double() @ Kd[h * hkv // hq].double().t()) * scale
+        lse[h] = torch.logsumexp(s, dim=1)
+        want[h * hkv // hq] += torch.softmax(s, dim=1).sum(0)
+    # exponents of up to |logit| log2(e) are formed in fp32, twice (the product, the normaliser), and a
+    # caller's normaliser arrives rounded to fp32 besides
+    rel = max(2e-5, 6 * lse.abs().max().item() * 1.4427 * 2.0 ** -23)
+    for given in (None, lse.float()):
+        got = pk.pc_score(Qd, Kd, nk, scale, lse=given).double()
+        assert ((got - want).abs() <= 2e-7 + rel * want).all(), ((got - want).abs() / (want + 1e-30)).max().item()
+
+
 @pytest.mark.parametrize("fold", [False, True])
 def test_score_with_supplied_lse_matches_internal_pass(fold):
     w = synth.midsize()
