@@ -118,6 +118,22 @@ def test_rope3d_out_scale_is_applied_before_the_one_rounding(dtype):
         assert (got == orc.round_to_bf16(want)).mean() > 0.99
 
 
+# the whole range of the reduction: positions at both ends of int32, frequencies above one (base 0.5,
+# angles beyond 2^32); tokens and heads that are no multiple of a work-group's
+@pytest.mark.parametrize("base", [1e4, 0.5])
+@pytest.mark.parametrize("n,H,sections", [(3, 1, (16, 24, 24)), (5, 5, (32, 48, 48)), (4, 9, (64, 0, 64))])
+def test_rope3d_extreme_positions(n, H, sections, base):
+    rng = np.random.default_rng(n + H)
+    d = sum(sections)
+    x = rng.standard_normal((H, n, d)).astype(np.float32)
+    pos = rng.integers(-2 ** 31, 2 ** 31, (n, 3)).astype(np.int32)
+    pos[0], pos[1], pos[2] = -2 ** 31, 2 ** 31 - 1, (0, 1, -1)
+    xd = dev(x, None)
+    pk.pc_rope3d(xd, dev(pos, None), sections, base)
+    # frequencies of the two sides may differ in the last bit: 2^32 * 2^-52 radians, next to fp32's rounding
+    assert np.abs(host(xd) - orc.rope3d(x, pos, sections, base)).max() <= 4e-6
+
+
 def test_rope3d_negative_shift_undoes_rotation_and_head_stride():
     # a rebase by (-dt, 0, 0) (Eq. 9) is a rotation with negative position; also exercises
     # a head stride larger than n*D (capacity > rows)
@@ -415,12 +431,12 @@ def test_score_bf16_row_reference_is_refreshed(step, fold):
 
 # Scoring rows numbered through the heads of a group (n_qs is no multiple of a tile, or smaller than
 # one), both forms of either pass: the first three shapes have 64 stationary rows per work-group in
-# both; the next has 512 in the column pass; then 512 in both, with the normalisers formed by the
-# column pass itself, by a launch of their own, and of more rows than it prepares at a time.  step:
+# both; the next two have 512 in the column pass, which forms the normalisers of its rows itself or
+# finds them formed; then 512 in both, the last with more rows than it prepares at a time.  step:
 # logits climb along the key axis, as above.  The reference is the softmax in 64 bits, on the GPU.
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
-@pytest.mark.parametrize("hq,hkv,n_qs,nk", [(3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 33, 65), (16, 2, 20, 30000),
+@pytest.mark.parametrize("hq,hkv,n_qs,nk", [(3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 33, 65), (8, 2, 252, 1804), (16, 2, 20, 30000),
                                             (16, 8, 600, 6000), (6, 2, 1100, 12000), (4, 2, 2100, 65000)])
 def test_score_bf16_rows_across_heads(hq, hkv, n_qs, nk, step, fold):
     Q, K, _ = _attn_case("bf16", hq, hkv, n_qs, nk, 128, n_qs + nk)
