@@ -162,14 +162,14 @@ __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ sc
   select_wave<kItems>(score + sc_off + start, len, keep, out, start);
 }
 
-// One work-group of 256 threads per segment; thread t keeps the kItems CONSECUTIVE keys
+// One work-group of kThr threads per segment; thread t keeps the kItems CONSECUTIVE keys
 // [t kItems, (t+1) kItems) of the segment in registers as order-preserving integers.
 //   * The bits all keys share (sign, most of the exponent) are found with one AND / OR reduction
 //     and skipped.
 //   * The k-th largest key is then found eleven bits at a time: keys that still match the prefix
-//     vote into a 2,048-bin LDS histogram; a thread owns eight neighbouring bins, the 256 threads
+//     vote into a 2,048-bin LDS histogram; a thread owns 2,048 / kThr neighbouring bins, the threads
 //     take a suffix sum over their totals (wave scan + one exchange) and the thread whose bins
-//     contain the k-th key walks its eight.  With 4,032 keys over 2,048 bins the chosen bin
+//     contain the k-th key walks them.  With 4,032 keys over 2,048 bins the chosen bin
 //     nearly always holds a handful of keys: up to 64 are put into LDS and ranked against each
 //     other by every wave (no second pass over the histogram); more than 64 take another pass.
 //   * Output in ascending index order: with consecutive keys per thread a kept key's position is
@@ -179,31 +179,31 @@ __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ sc
 // The kernel is bound by its instruction count once a stack of layers fills the chip with these
 // work-groups, hence few, wide passes and no per-key cross-lane work.
 // Blocks also clear the in-place gather's ticket counters and flags (n_clear words).
-template <int kItems>
-__global__ __launch_bounds__(256) void select_block_kernel(const float* __restrict__ score,
+template <int kItems, int kThr>
+__global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restrict__ score,
                                                            int64_t score_stride_h,
                                                            int32_t* __restrict__ idx, int64_t idx_stride_h,
                                                            SegTable tab, int32_t* __restrict__ clear,
                                                            int n_clear, int hsel, int64_t score_stride_l,
                                                            int64_t idx_stride_l) {
-  constexpr int kBits = 11, kBins = 1 << kBits, kOwn = kBins / 256;  // bins per thread
-  static_assert(kOwn == 8, "a thread reads its bins with two 16-byte loads");
+  constexpr int kBits = 11, kBins = 1 << kBits, kOwn = kBins / kThr, kWaves = kThr / 64;  // bins per thread
+  static_assert(kOwn == 8 || kOwn == 2, "a thread reads its bins with two 16-byte loads or one of 8 bytes");
   __shared__ __align__(16) int s_hist[kBins];
-  __shared__ int s_wave_sum[4];
+  __shared__ int s_wave_sum[kWaves];
   __shared__ int s_pick[3];  // chosen digit, keys above it, keys in it
-  __shared__ uint32_t s_and[4], s_or[4];
+  __shared__ uint32_t s_and[kWaves], s_or[kWaves];
   __shared__ uint32_t s_cand[64];  // the keys of the chosen bin when they are few
   __shared__ int s_n_cand;
   const int s = blockIdx.x, h = blockIdx.y;
   {
     const int nb = gridDim.x * gridDim.y, b = h * gridDim.x + s;
-    for (int i = b * 256 + threadIdx.x; i < n_clear; i += nb * 256) clear[i] = 0;
+    for (int i = b * kThr + threadIdx.x; i < n_clear; i += nb * kThr) clear[i] = 0;
   }
   const int start = tab.start[s], len = tab.len[s], k = tab.keep[s];
   int32_t* out = idx + (h / hsel) * idx_stride_l + (h % hsel) * idx_stride_h + tab.dst[s];
   if (k <= 0) return;  // block-uniform
   if (!tab.prune[s]) {
-    for (int e = threadIdx.x; e < len; e += 256) out[e] = start + e;
+    for (int e = threadIdx.x; e < len; e += kThr) out[e] = start + e;
     return;
   }
   const float* sc = score + (h / hsel) * score_stride_l + (h % hsel) * score_stride_h + start;
@@ -248,13 +248,24 @@ __global__ __launch_bounds__(256) void select_block_kernel(const float* __restri
     s_and[wave] = k_and;
     s_or[wave] = k_or;
   }
-  int4* h4 = reinterpret_cast<int4*>(s_hist);
-  h4[2 * t] = make_int4(0, 0, 0, 0);  // this thread's own eight bins, cleared for the first pass
-  h4[2 * t + 1] = make_int4(0, 0, 0, 0);
+  auto clear_bins = [&] {  // this thread's own bins
+    if constexpr (kOwn == 8) {
+      reinterpret_cast<int4*>(s_hist)[2 * t] = make_int4(0, 0, 0, 0);
+      reinterpret_cast<int4*>(s_hist)[2 * t + 1] = make_int4(0, 0, 0, 0);
+    } else {
+      reinterpret_cast<int2*>(s_hist)[t] = make_int2(0, 0);
+    }
+  };
+  clear_bins();  // for the first pass
   if (t == 0) s_n_cand = 0;
   __syncthreads();
-  k_and = s_and[0] & s_and[1] & s_and[2] & s_and[3];
-  k_or = s_or[0] | s_or[1] | s_or[2] | s_or[3];
+  k_and = s_and[0];
+  k_or = s_or[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) {
+    k_and &= s_and[w];
+    k_or |= s_or[w];
+  }
   const uint32_t differ = k_and ^ k_or;
   int hi = differ ? 32 - __clz(differ) : 0;  // number of undecided low bits
   uint32_t prefix = hi >= 32 ? 0u : (k_or >> hi) << hi;
@@ -263,8 +274,7 @@ __global__ __launch_bounds__(256) void select_block_kernel(const float* __restri
   while (hi > 0) {
     const int width = min(kBits, hi), shift = hi - width;
     if (!cleared) {  // a further pass (rare): the bins are cleared behind the reads of the pass before
-      h4[2 * t] = make_int4(0, 0, 0, 0);
-      h4[2 * t + 1] = make_int4(0, 0, 0, 0);
+      clear_bins();
       __syncthreads();
     }
     cleared = false;
@@ -275,9 +285,15 @@ __global__ __launch_bounds__(256) void select_block_kernel(const float* __restri
       if (e0 + i < len && (key[i] & hi_mask) == (prefix & hi_mask))
         atomicAdd(&s_hist[(key[i] >> shift) & digit_mask], 1);
     __syncthreads();
-    const int4 lo4 = h4[2 * t], hi4 = h4[2 * t + 1];
-    const int c[kOwn] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
-    int mine = 0;  // votes for bins 8 t .. 8 t + 7
+    int c[kOwn];
+    if constexpr (kOwn == 8) {
+      const int4 lo4 = reinterpret_cast<const int4*>(s_hist)[2 * t], hi4 = reinterpret_cast<const int4*>(s_hist)[2 * t + 1];
+      c[0] = lo4.x, c[1] = lo4.y, c[2] = lo4.z, c[3] = lo4.w, c[4] = hi4.x, c[5] = hi4.y, c[6] = hi4.z, c[7] = hi4.w;
+    } else {
+      const int2 c2 = reinterpret_cast<const int2*>(s_hist)[t];
+      c[0] = c2.x, c[1] = c2.y;
+    }
+    int mine = 0;  // votes for this thread's bins
 #pragma unroll
     for (int j = 0; j < kOwn; ++j) mine += c[j];
     // suffix sums over the threads: above = matching keys with a digit beyond this thread's bins
@@ -286,7 +302,7 @@ __global__ __launch_bounds__(256) void select_block_kernel(const float* __restri
     if (lane == 0) s_wave_sum[wave] = incl;
     __syncthreads();
     int above = incl - mine;
-    for (int w = wave + 1; w < 4; ++w) above += s_wave_sum[w];
+    for (int w = wave + 1; w < kWaves; ++w) above += s_wave_sum[w];
     if (above < remaining && remaining <= above + mine) {  // exactly one thread: walk its bins downwards
       int ab = above, digit = 0, cnt = 0;
       bool found = false;
@@ -388,6 +404,7 @@ __global__ __launch_bounds__(256) void select_block_kernel(const float* __restri
 // the wave form is used from this many segments per call on (measured cross-over: 7-8 layers of 196
 // segments), when the longest pruned segment is longer than kRowsSelectMinLen
 constexpr int kRowsSelectMinUnits = PC_ROWS_SELECT_MIN_UNITS, kRowsSelectMinLen = PC_ROWS_SELECT_MIN_LEN;
+constexpr int kWideSelectMaxUnits = 256;  // segments that take 1,024 threads each (see the launch)
 // f(n - 1), ..., f(0) with compile-time row numbers; n in [0, 64] is wave-uniform
 template <class F>
 __device__ __forceinline__ void rows_down_from(int n, F&& f) {
@@ -954,15 +971,19 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
              n_seg * hsel * n_layers >= kRowsSelectMinUnits)
     select_rows_kernel<<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel,
                                              score_stride_l, idx_stride_layer);
-  else if (max_prune_len <= 256)
-    select_block_kernel<1><<<sgrid, 256, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel,
-                                                   score_stride_l, idx_stride_layer);
-  else if (max_prune_len <= 1024)
-    select_block_kernel<4><<<sgrid, 256, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel,
-                                                   score_stride_l, idx_stride_layer);
-  else if (max_prune_len <= PC_MAX_SELECT_LEN)
-    select_block_kernel<16><<<sgrid, 256, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel,
-                                                   score_stride_l, idx_stride_layer);
+  else if (max_prune_len <= PC_MAX_SELECT_LEN) {
+    // Long segments, and at most one per compute unit: 1,024 threads each, a quarter of the serial work
+    // per thread (4,032 keys: 100 segments 9.2 -> 8.1 us, 196 segments 9.1 -> 8.6; 300 segments 9.8 ->
+    // 10.2 and 1,000 keys 4.8 -> 5.9, where the work-group barriers cost more than that saves).
+    const bool wide = max_prune_len > 1024 && n_seg * hsel * n_layers <= kWideSelectMaxUnits;
+    const auto kernel = max_prune_len <= 256    ? select_block_kernel<1, 256>
+                        : max_prune_len <= 1024 ? select_block_kernel<4, 256>
+                        : wide                  ? select_block_kernel<4, 1024>
+                                                : select_block_kernel<16, 256>;
+    const int threads = wide ? 1024 : 256;
+    kernel<<<sgrid, threads, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel, score_stride_l,
+                                      idx_stride_layer);
+  }
   else
   {
     select_kernel<0><<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, hsel, score_stride_l,
