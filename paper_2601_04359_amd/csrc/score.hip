@@ -369,7 +369,8 @@ __device__ __forceinline__ void row_norms(const RowNorm& a, int kvh, int rho0, i
         for (int q = 0; q < kBatch; ++q)
           if (s0 + q < a.n_splits && x[q].y > 0.f) l += x[q].y * __builtin_amdgcn_exp2f(x[q].x - m);
       }
-      v[i] = -(m + log2f(l));
+      // the logarithm is taken of l's significand: an ulp of it is then far below one of the result
+      v[i] = -(m + (static_cast<float>(__builtin_amdgcn_frexp_expf(l)) + log2f(__builtin_amdgcn_frexp_mantf(l))));
     }
   }
 #pragma unroll
