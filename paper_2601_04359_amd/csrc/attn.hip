@@ -50,13 +50,13 @@ static_assert(kStages == 4, "dma_wait_older encodes 4 * (kStages - 2)");
 template <bool kIsV>
 __device__ __forceinline__ void stage_tile(const uint16_t* __restrict__ base_h, int k0, int Nk, uint32_t lds_tile,
                                            int wave, int lane) {
+  const RowWindow w = row_window(base_h, k0, Nk);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int row = (wave * 2 + i) * 4 + (lane >> 4);  // 4 rows per load
     const int pos = lane & 15;                          // chunk position inside the row
     const int chunk = kIsV ? v_chunk_pos(row, pos) : k_chunk_pos(row, pos);  // both maps are involutions
-    const int key = min(k0 + row, Nk - 1);
-    dma_16B(base_h + static_cast<int64_t>(key) * kD + chunk * 8, lds_tile + (wave * 2 + i) * 1024);
+    dma_16B_at(w.base, row_offset(w, row, chunk), lds_tile + (wave * 2 + i) * 1024);
   }
 }
 
@@ -274,18 +274,17 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     const uint16_t* qrow = Q + at_row.head * q_stride_h + static_cast<int64_t>(at_row.row) * kD + g * 8;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
-    // Behind the first fetches, so that one memory latency covers all of them.
-    // Make the compiler retire these loads here: otherwise it guards every use of qf inside
-    // the loop with s_waitcnt vmcnt(7..0), which also drains the direct K/V loads in flight.
+    // Behind the first fetches, so that one memory latency covers all of them.  Make the compiler
+    // retire these loads here (and with them, in order, the direct ones before): otherwise it guards
+    // every use of qf inside the loop with s_waitcnt vmcnt(7..0), which also drains the K/V loads.
 #pragma unroll
     for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
   }
+  __syncthreads();   // K(0), V(0), K(1) have landed: they were fetched before the queries
   stage_k(2);
   stage_v(1);
   stage_k(3);
   stage_v(2);
-  dma_wait_older();  // K(0), V(0), K(1)
-  __syncthreads();
 
   auto mask_tail = [&](f32x16& sc, int lim) {
 #pragma unroll
@@ -454,12 +453,12 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
 
   // a step's 32 rows of K and of V, two 8-KB pieces of the wave's LDS
   auto stage = [&](int k0) {
+    const RowWindow wk = row_window(Kh, k0, Nk), wv = row_window(Vh, k0, Nk);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int row = i * 4 + (lane >> 4);
-      const int64_t at = static_cast<int64_t>(min(k0 + row, Nk - 1)) * kD;
-      dma_16B(Kh + at + k_chunk_pos(row, lane & 15) * 8, lds_w + i * 1024);
-      dma_16B(Vh + at + v_chunk_pos(row, lane & 15) * 8, lds_w + kSmallTileBytes + i * 1024);
+      dma_16B_at(wk.base, row_offset(wk, row, k_chunk_pos(row, lane & 15)), lds_w + i * 1024);
+      dma_16B_at(wv.base, row_offset(wv, row, v_chunk_pos(row, lane & 15)), lds_w + kSmallTileBytes + i * 1024);
     }
   };
   const int k_first = k_begin + wave * kSmallKeys;

@@ -51,14 +51,29 @@ __device__ __forceinline__ void dma_16B(const void* src, uint32_t lds_base) {
       : "s"(lds_base), "v"(src)
       : "memory");
 }
-// One wave-wide 256-byte direct load: lane i's 4 bytes from `src` land at lds_base + 4 i.
-__device__ __forceinline__ void dma_4B(const void* src, uint32_t lds_base) {
+// The same from `base` (wave-uniform) + a byte offset per lane: no 64-bit address arithmetic in the
+// vector pipe.  A scalar register that a vector instruction wrote may be read as a load's base five
+// wait states later; the compiler does not look into the statement, so it brings them along.
+__device__ __forceinline__ void dma_16B_at(const void* base, uint32_t offset, uint32_t lds_base) {
   uint32_t saved_m0;
   asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off\n\ts_mov_b32 m0, %0"
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
       : "=&s"(saved_m0)
-      : "s"(lds_base), "v"(src)
+      : "s"(lds_base), "v"(offset), "s"(base)
       : "memory");
+}
+// Where rows k0, k0 + 1, ... of a [rows][128] bf16 array start, and the last of them that exists: rows
+// past the end are read as the last row (k0 itself may lie past it).
+struct RowWindow {
+  const uint16_t* base;
+  int last;
+};
+__device__ __forceinline__ RowWindow row_window(const uint16_t* rows, int k0, int n_rows) {
+  const int first = min(k0, n_rows - 1);
+  return {rows + static_cast<int64_t>(first) * 128, n_rows - 1 - first};
+}
+__device__ __forceinline__ uint32_t row_offset(const RowWindow& w, int row, int chunk) {
+  return min(row, w.last) * 256 + chunk * 16;
 }
 
 __device__ __forceinline__ bf16x8 lds_frag(const lds_u8* p) {

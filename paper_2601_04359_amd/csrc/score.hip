@@ -221,9 +221,13 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
 #pragma unroll
   for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
   auto stage = [&](int j) {  // tile j of this split (clamped: a repeat of the last tile is never read)
-    const int k0 = (t_begin + min(j, n - 1)) * kTileRows;
-    stage_rows([&](int row, int) { return Kh + static_cast<int64_t>(min(k0 + row, Nk - 1)) * kD; },
-               lds0 + (j & (kStages - 1)) * kTileBytes, wave, lane);
+    const RowWindow w = row_window(Kh, (t_begin + min(j, n - 1)) * kTileRows, Nk);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = (wave * 2 + i) * 4 + (lane >> 4);
+      dma_16B_at(w.base, row_offset(w, row, k_chunk_pos(row, lane & 15)),
+                 lds0 + (j & (kStages - 1)) * kTileBytes + (wave * 2 + i) * 1024);
+    }
   };
   auto slot = [&](int j) { return smem + (j & (kStages - 1)) * kTileBytes; };
 
@@ -615,12 +619,11 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
   const int t_end = min((split + 1) * per, steps_all), t_first = split * per + wave;
   const int n = t_first < t_end ? (t_end - t_first + 7) / 8 : 0;   // steps of this wave
   auto stage = [&](int i) {
+    const RowWindow w = row_window(Kh, (t_first + i * 8) * kSmallStep, Nk);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int row = q * 4 + (lane >> 4);
-      const int key = min((t_first + i * 8) * kSmallStep + row, Nk - 1);
-      dma_16B(Kh + static_cast<int64_t>(key) * kD + k_chunk_pos(row, lane & 15) * 8,
-              ring_w + (i & 1) * kSmallStepBytes + q * 1024);
+      dma_16B_at(w.base, row_offset(w, row, k_chunk_pos(row, lane & 15)), ring_w + (i & 1) * kSmallStepBytes + q * 1024);
     }
   };
   const RowPtrs qrow = row_ptrs(Qs, q_rows, tile * kWaveRows + l32, n_rows, n_qs, kvh * rep, q_stride_h);
