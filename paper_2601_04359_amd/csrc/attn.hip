@@ -622,8 +622,13 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   if (lse != nullptr && wave == 0 && g == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
 }
 
-// Merge of the key shares: O = sum_s e^(m_s - M) O_s / sum_s e^(m_s - M) l_s with M = max_s m_s
-// (bf16 tier: base 2, as its kernel keeps its references).  A thread owns four dims of one row.
+// ln(2^m l), rounded once: m may reach hundreds where l's logarithm is small
+__device__ __forceinline__ float natural_lse(float m, float l) {
+  return fmaf(m, 0.693147182464599609375f, fmaf(m, -1.90465429995776804525e-9f, logf(l)));
+}
+
+// Merge of the key shares: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s with M = max_s m_s.
+// A thread owns four dims of one row.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float2* __restrict__ part_ml,
@@ -649,7 +654,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   float M = ml.x;
 #pragma unroll
   for (int x = 1; x < kLanes; x *= 2) M = fmaxf(M, __shfl_xor(M, x, kLanes));
-  const float w_mine = kF32 ? expf(ml.x - M) : __builtin_amdgcn_exp2f(ml.x - M);   // 0 beyond the last share
+  const float w_mine = __builtin_amdgcn_exp2f(ml.x - M);   // 0 beyond the last share
   float l = w_mine * ml.y;
 #pragma unroll
   for (int x = 1; x < kLanes; x *= 2) l += __shfl_xor(l, x, kLanes);
@@ -670,7 +675,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   T* out = O + h * o_stride_h + static_cast<int64_t>(row) * D + c * 4;
   if constexpr (kF32) {
     store_f32x4(out, acc * inv);
-    if (lse != nullptr && c == 0) lse[r] = M + logf(l);
+    if (lse != nullptr && c == 0) lse[r] = natural_lse(M, l);
   } else {
     u32x2 packed;
     packed[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
@@ -736,11 +741,12 @@ int splits_that_fit(int want, int Hq, int Nq, int D, const void* ws, size_t ws_b
 
 // ------------------------------------------------------------------------------------------
 // fp32 tier: the 16x16x4 fp32 MFMA (fp32 operands and accumulation throughout; 2,048 FLOP in 32
-// cycles, twice the rate of scalar FMAs).  Bound: matrix rate when the chip is full, latency at
-// the few-hundred-token sizes this tier is used at, so the work is cut fine: a work-group owns 16
-// query rows, its 8 waves take the keys in groups of 32 by turns (no LDS, no barrier in the loop)
-// and merge their (O, m, l) through LDS once; when that leaves compute units idle the host cuts
-// the keys into shares as well (f32_key_splits).
+// cycles, twice the rate of scalar FMAs).  Bound: matrix rate and the loads of K and V when the chip
+// is full, latency at the few-hundred-token sizes this tier is used at, so the work is cut fine: a
+// work-group owns 16 kR query rows (numbered through the heads of the KV head, as above), its 8 waves
+// take the keys in steps of 32 / kR by turns (no LDS, no barrier in the loop) and merge their
+// (O, m, l) through LDS once; when that leaves compute units idle the host cuts the keys into shares
+// as well (plan_f32).  kR = 2 loads K and V half as often per product, kR = 1 starts and ends sooner.
 //   * S^T = K Q^T: lane (r = l % 16, kg = l / 16) holds key row r, dims 16 s + 4 kg .. + 3 as one
 //     16-byte load; the four MFMAs of step s contract over (kg, element e), the same permutation
 //     of the head dimension on both operands.
@@ -749,189 +755,269 @@ int splits_that_fit(int want, int Hq, int Nq, int D, const void* ws, size_t ws_b
 //     (product e contracts over keys 4 kg + e).
 //   * V is the A operand through 16-byte loads too: row r of output block (db, e) stands for dim
 //     64 db + 4 r + e, so a lane's accumulators are whole 16-byte pieces of its output row.
-// Measured (8/2 heads, 252 rows, 1,804 keys, D = 128; 1.86 GFLOP, 12 us at the rate a large fp32
-// product reaches): one thread per row with K / V broadcast from LDS and plain FMA 3,945 us a call,
-// this kernel 38 us with two key shares and 56 us without; 24/8 heads, 1,000 rows, 8,000 keys:
-// 1,179 us, 83 TFLOP/s (K and V come through L2 once per 16 rows).
+//   * Softmax in base 2: a score is s (c + c_lo) with one rounding, c + c_lo = scale * log2(e).
+// Measured: 8/2 heads, 252 rows, 1,804 keys, D = 128 (1.86 GFLOP, 12 us at the rate a large fp32
+// product reaches) 30 us a call with kR = 2 and four key shares, 37 with kR = 1 and two, 3,945 with
+// one thread per row and plain FMA; 24/8 heads, 1,000 rows, 8,000 keys 874 us against 1,220
+// (112 TFLOP/s); 8/2 heads, 60 rows, 300 keys 13 us against 10.
 // ------------------------------------------------------------------------------------------
 constexpr int kMaxKeySplits = 16;
 constexpr int kF32Waves = 8;
 constexpr int kF32Threads = 64 * kF32Waves;
-constexpr int kF32Rows = 16;        // query rows per work-group
-constexpr int kF32Keys = 32;        // keys per wave and step (two 16-key MFMA tiles)
-
-template <int D>
+template <int D, int kR>
 constexpr size_t f32_smem_bytes() {
-  return sizeof(float) * kF32Waves * kF32Rows * (D + 2);
+  return sizeof(float) * kF32Waves * 16 * kR * (D + 2);
 }
 
-template <int D>
+template <int D, int kR>
 __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
-    int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split,
+    int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split, int n_tiles_q, int n_splits,
     float* __restrict__ part_o, float2* __restrict__ part_ml) {
-  constexpr int kS = D / 16, kB = D / 64;
+  static_assert(kR == 1 || kR == 2, "a step is two 16 x 16 products");
+  constexpr int kS = D / 16, kB = D / 64, kF32Rows = 16 * kR, kT = 2 / kR, kF32Keys = 16 * kT;  // kT: key blocks
   extern __shared__ __align__(16) uint8_t smem_raw[];
   float* s_o = reinterpret_cast<float*>(smem_raw);        // [wave][row][D]
   float* s_m = s_o + kF32Waves * kF32Rows * D;            // [wave][row]
   float* s_l = s_m + kF32Waves * kF32Rows;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
-  const int h = blockIdx.y, kvh = h / rep, split = blockIdx.z;
-  const int row0 = blockIdx.x * kF32Rows;
+  // logical order: key split slowest, then KV head, then row tile: the work-groups of one XCD (one L2)
+  // read the same keys
+  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
+  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
+  const int split = L / tiles_all, kvh = L % tiles_all / n_tiles_q;
+  const int row0 = L % n_tiles_q * kF32Rows, n_rows = rep * Nq;
   const float* Kh = K + kvh * kv_stride_h;
   const float* Vh = V + kvh * kv_stride_h;
   const int k_begin = split * keys_per_split, k_end = min(k_begin + keys_per_split, Nk);
 
-  f32x4 q[kS];
-  {
-    const float* qrow = Q + h * q_stride_h + static_cast<int64_t>(min(row0 + r, Nq - 1)) * D + kg * 4;
+  f32x4 q[kR][kS];
 #pragma unroll
-    for (int s = 0; s < kS; ++s) q[s] = load_f32x4(qrow + s * 16);
+  for (int t = 0; t < kR; ++t) {
+    const RowAt at = row_at(min(row0 + t * 16 + r, n_rows - 1), kvh, rep, Nq);
+    const float* qrow = Q + at.head * q_stride_h + static_cast<int64_t>(at.row) * D + kg * 4;
+#pragma unroll
+    for (int s = 0; s < kS; ++s) q[t][s] = load_f32x4(qrow + s * 16);
   }
-  f32x4 o[kB][4];
+  f32x4 o[kR][kB][4];
 #pragma unroll
-  for (int b = 0; b < kB; ++b)
+  for (int t = 0; t < kR; ++t)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+    for (int b = 0; b < kB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[t][b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m[kR], l[kR];
+#pragma unroll
+  for (int t = 0; t < kR; ++t) {
+    m[t] = -INFINITY;
+    l[t] = 0.f;
+  }
+  const float c = scale * 1.4426950408889634f;
+  const float c_lo = fmaf(scale, 1.92596299e-8f, fmaf(scale, 1.4426950216293335f, -c));
 
   // Software pipeline: the V loads of a step fly during its score products, the K loads of the
   // next step (into the registers those products just freed) during its softmax and value products.
-  f32x4 kf[2][kS], v[2][4][kB];
+  // Rows of a step lie at 32-bit offsets from its first one (a scalar); past the end: the last row.
+  f32x4 kf[kT][kS], v[kT][4][kB];
   auto load_k = [&](int k0) {
+    const int first = min(k0, Nk - 1), last = Nk - 1 - first;
+    const float* base = Kh + static_cast<int64_t>(first) * D;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const float* krow = Kh + static_cast<int64_t>(min(k0 + t * 16 + r, Nk - 1)) * D + kg * 4;
+    for (int u = 0; u < kT; ++u) {
+      const uint32_t at = min(u * 16 + r, last) * D + kg * 4;
 #pragma unroll
-      for (int s = 0; s < kS; ++s) kf[t][s] = load_f32x4(krow + s * 16);
+      for (int s = 0; s < kS; ++s) kf[u][s] = load_f32x4(base + at + s * 16);
     }
   };
   load_k(k_begin + wave * kF32Keys);
   for (int k0 = k_begin + wave * kF32Keys; k0 < k_end; k0 += kF32Waves * kF32Keys) {
+    const int last = Nk - 1 - k0;
+    const float* v_base = Vh + static_cast<int64_t>(k0) * D;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int u = 0; u < kT; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float* vrow = Vh + static_cast<int64_t>(min(k0 + t * 16 + kg * 4 + e, Nk - 1)) * D + r * 4;
+        const uint32_t at = min(u * 16 + kg * 4 + e, last) * D + r * 4;
 #pragma unroll
-        for (int b = 0; b < kB; ++b) v[t][e][b] = load_f32x4(vrow + b * 64);
+        for (int b = 0; b < kB; ++b) v[u][e][b] = load_f32x4(v_base + at + b * 64);
       }
     __builtin_amdgcn_sched_barrier(0);
-    f32x4 sc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    f32x4 sc[kR][kT];   // two independent products, interleaved
+#pragma unroll
+    for (int t = 0; t < kR; ++t)
+#pragma unroll
+      for (int u = 0; u < kT; ++u) sc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kS; ++s)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][s][e], q[s][e], sc[t], 0, 0, 0);
+        for (int t = 0; t < kR; ++t)
+#pragma unroll
+          for (int u = 0; u < kT; ++u)
+            sc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][s][e], q[t][s][e], sc[t][u], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     load_k(k0 + kF32Waves * kF32Keys);  // past the end: clamped rows, never used
     __builtin_amdgcn_sched_barrier(0);
-    float mx = -INFINITY;
+    float mx[kR];
+    bool lags = false;   // a reference may lag by 2^8 (always taken first: m = -inf)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < kR; ++t) {
+      mx[t] = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sc[t][e] = k0 + t * 16 + kg * 4 + e < k_end ? sc[t][e] * scale : -INFINITY;
-        mx = fmaxf(mx, sc[t][e]);
+      for (int u = 0; u < kT; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[t][u][e] = fmaf(sc[t][u][e], c, sc[t][u][e] * c_lo);
+        if (k0 + kF32Keys > k_end) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k0 + u * 16 + kg * 4 + e >= k_end) sc[t][u][e] = -INFINITY;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx[t] = fmaxf(mx[t], sc[t][u][e]);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = wave_half_max(mx);
-    const float m_new = fmaxf(m, mx);      // finite: key k0 itself is inside the share
-    const float alpha = expf(m - m_new);   // exp(-inf) = 0 on the first step
-    float sum = 0.f;
+      mx[t] = fmaxf(mx[t], __shfl_xor(mx[t], 16));
+      mx[t] = wave_half_max(mx[t]);      // finite: key k0 itself is inside the share
+      lags = lags || !(mx[t] <= m[t] + 8.f);
+    }
+    if (__any(lags)) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < kR; ++t) {
+        const float m_new = fmaxf(m[t], mx[t]), alpha = __builtin_amdgcn_exp2f(m[t] - m_new);
+        l[t] *= alpha;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sc[t][e] = expf(sc[t][e] - m_new);
-        sum += sc[t][e];
+        for (int b = 0; b < kB; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[t][b][e] *= alpha;
+        m[t] = m_new;
       }
-    l = l * alpha + sum;
-    m = m_new;
+    }
 #pragma unroll
-    for (int b = 0; b < kB; ++b)
+    for (int t = 0; t < kR; ++t) {
+      float sum = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[b][e] *= alpha;
+      for (int u = 0; u < kT; ++u)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int e = 0; e < 4; ++e) {
+          sc[t][u][e] = __builtin_amdgcn_exp2f(sc[t][u][e] - m[t]);
+          sum += sc[t][u][e];
+        }
+      l[t] += sum;
+    }
+#pragma unroll
+    for (int u = 0; u < kT; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int b = 0; b < kB; ++b)
 #pragma unroll
           for (int x = 0; x < 4; ++x)
-            o[b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[t][e][b][x], sc[t][e], o[b][x], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < kR; ++t)
+              o[t][b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][e][b][x], sc[t][u][e], o[t][b][x], 0, 0, 0);
   }
-  l += __shfl_xor(l, 16);
-  l = wave_half_sum(l);
 
-  // accumulator element (b, x, i) of lane (q = r, kg) is dim 64 b + 16 kg + 4 i + x of query row r
-  float* mine = s_o + (wave * kF32Rows + r) * D + kg * 16;
+  // accumulator element (b, x, i) of lane (q = r, kg) is dim 64 b + 16 kg + 4 i + x of its query row
 #pragma unroll
-  for (int b = 0; b < kB; ++b)
+  for (int t = 0; t < kR; ++t) {
+    l[t] += __shfl_xor(l[t], 16);
+    l[t] = wave_half_sum(l[t]);
+    const int row = wave * kF32Rows + t * 16 + r;
+    float* mine = s_o + row * D + kg * 16;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4*>(mine + b * 64 + i * 4) = f32x4{o[b][0][i], o[b][1][i], o[b][2][i], o[b][3][i]};
-  if (kg == 0) {
-    s_m[wave * kF32Rows + r] = m;
-    s_l[wave * kF32Rows + r] = l;
+    for (int b = 0; b < kB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(mine + b * 64 + i * 4) =
+            f32x4{o[t][b][0][i], o[t][b][1][i], o[t][b][2][i], o[t][b][3][i]};
+    if (kg == 0) {
+      s_m[row] = m[t];
+      s_l[row] = l[t];
+    }
   }
   __syncthreads();
-  // merge in wave order: a thread owns four dims of one row
-  const int row = threadIdx.x / (D / 4), c = threadIdx.x % (D / 4);
-  if (row >= kF32Rows || row0 + row >= Nq) return;
-  float M = -INFINITY;
+  // merge in wave order: a thread owns four dims of a row, of every kPass-th
+  constexpr int kPass = kF32Threads / (D / 4);   // rows per pass
+  const int col = threadIdx.x % (D / 4) * 4;
 #pragma unroll
-  for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, s_m[w * kF32Rows + row]);
-  float lt = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int row = threadIdx.x / (D / 4); row < kF32Rows; row += kPass) {
+    const int rho = row0 + row;
+    if (rho >= n_rows) return;
+    float M = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < kF32Waves; ++w) {
-    const float wt = expf(s_m[w * kF32Rows + row] - M);   // 0 for a wave that had no keys
-    lt += wt * s_l[w * kF32Rows + row];
-    acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + c * 4);
+    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, s_m[w * kF32Rows + row]);
+    float lt = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+      const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);   // 0 for a wave that had no keys
+      lt += wt * s_l[w * kF32Rows + row];
+      acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + col);
+    }
+    const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
+    if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
+      const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+      *reinterpret_cast<f32x4*>(part_o + at_s * D + col) = acc;
+      if (col == 0) part_ml[at_s] = make_float2(M, lt);
+    } else {
+      const RowAt to = row_at(rho, kvh, rep, Nq);
+      store_f32x4(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * D + col, acc * (1.f / lt));
+      if (lse != nullptr && col == 0) lse[at] = natural_lse(M, lt);
+    }
   }
-  if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
-    const int64_t at = (static_cast<int64_t>(split) * gridDim.y + h) * Nq + row0 + row;
-    *reinterpret_cast<f32x4*>(part_o + at * D + c * 4) = acc;
-    if (c == 0) part_ml[at] = make_float2(M, lt);
-    return;
-  }
-  store_f32x4(O + h * o_stride_h + static_cast<int64_t>(row0 + row) * D + c * 4, acc * (1.f / lt));
-  if (lse != nullptr && c == 0) lse[static_cast<int64_t>(h) * Nq + row0 + row] = M + logf(lt);
 }
 
-// Key shares of the fp32 tier.  A work-group takes its share in steps of 8 x 32 keys; two
-// work-groups fit a compute unit (their LDS).  Shares pay while they fill idle compute units, at
-// the price of a merge launch (3-4 us) and of the partial rows.
-int f32_key_splits(int Hq, int Nq, int Nk) {
-  const int blocks = ceil_div(Nq, kF32Rows) * Hq, steps = ceil_div(Nk, kF32Waves * kF32Keys);
-  return std::max(1, std::min(std::min(256 / blocks, steps / 2), kMaxKeySplits));
+// How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 13 shapes (2 to 24 heads, 40
+// to 1,000 rows, 100 to 8,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it
+// picks is the best of them on 12 and 4 % off on the last.  A step's waves contend for the matrix
+// pipes and the loads, so a part-filled step costs its part.
+struct F32Plan {
+  int kr, n_splits;
+};
+F32Plan plan_f32(int Hkv, int rows, int Nk, int D, int max_splits) {
+  F32Plan best = {1, 1};
+  double best_cost = 1e30;
+  const double f = D / 128.0;
+  for (int kr = 1; kr <= 2; ++kr) {
+    const int blocks = ceil_div(rows, 16 * kr) * Hkv, units = ceil_div(Nk, 32 / kr);
+    for (int s = 1; s <= std::min(max_splits, units); ++s) {
+      const int per = ceil_div(units, s);
+      if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      const double merge = s == 1 ? 0.0 : 2.2 + 8.6e-4 * s * Hkv * rows * f;
+      const double cost = (kr == 1 ? 2.1 : 3.5) + 3.4 * f +
+                          ceil_div(blocks * s, 256) * (kr == 1 ? 7.0 : 5.15) * f * per / kF32Waves + merge;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = {kr, s};
+      }
+    }
+  }
+  return best;
 }
 
 template <int D>
 int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, int Nq, int Nk, int64_t q_stride_h,
              int64_t kv_stride_h, int64_t o_stride_h, float scale, float* O, float* lse, void* ws, size_t ws_bytes,
              hipStream_t s) {
-  static std::atomic<uint64_t> lds_ok{0};
-  if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<D>), f32_smem_bytes<D>(), lds_ok,
-                                 "pc_frame_attn"))
+  const F32Plan plan = plan_f32(Hq / rep, rep * Nq, Nk, D, splits_that_fit(kMaxKeySplits, Hq, Nq, D, ws, ws_bytes));
+  const auto kernel = plan.kr == 2 ? attn_f32_kernel<D, 2> : attn_f32_kernel<D, 1>;
+  const size_t smem = plan.kr == 2 ? f32_smem_bytes<D, 2>() : f32_smem_bytes<D, 1>();
+  static std::atomic<uint64_t> lds_ok[2];
+  if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.kr - 1], "pc_frame_attn"))
     return rc;
-  int n_splits = splits_that_fit(f32_key_splits(Hq, Nq, Nk), Hq, Nq, D, ws, ws_bytes);
-  // whole steps per share, and as many shares as that leaves (none is empty)
-  const int per = ceil_div(ceil_div(Nk, kF32Keys), n_splits) * kF32Keys;
-  n_splits = ceil_div(Nk, per);
+  const int n_tiles_q = ceil_div(rep * Nq, 16 * plan.kr), n_splits = plan.n_splits, unit = 32 / plan.kr;
+  const int keys_per_split = ceil_div(ceil_div(Nk, unit), n_splits) * unit;
   float* part_o = nullptr;
   float2* part_ml = nullptr;
   if (n_splits > 1) {
     part_o = static_cast<float*>(ws);
     part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, n_splits));
   }
-  attn_f32_kernel<D><<<dim3(ceil_div(Nq, kF32Rows), Hq, n_splits), kF32Threads, f32_smem_bytes<D>(), s>>>(
-      Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, per, part_o, part_ml);
+  kernel<<<n_tiles_q * (Hq / rep) * n_splits, kF32Threads, smem, s>>>(
+      Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, keys_per_split, n_tiles_q, n_splits,
+      part_o, part_ml);
   PC_CHECK_LAUNCH("pc_frame_attn");
   if (n_splits > 1) {
     constexpr int kRowsPerBlock = 256 / (D / 4);
@@ -950,10 +1036,12 @@ using namespace pc;
 
 extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
   if ((D != 64 && D != 128) || Hq <= 0 || Nq <= 0 || Nk <= 0) return 0;
-  int splits = f32_key_splits(Hq, Nq, Nk);   // the call does not say which tier it will be
-  if (D == kD)                               // ... nor how many KV heads there are
-    for (int rep = 1; rep <= Hq; ++rep)
-      if (Hq % rep == 0) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, kMaxKeySplits).n_splits);
+  int splits = 1;   // the call does not say which tier it will be, nor how many KV heads there are
+  for (int rep = 1; rep <= Hq; ++rep) {
+    if (Hq % rep != 0) continue;
+    splits = std::max(splits, plan_f32(Hq / rep, rep * Nq, Nk, D, kMaxKeySplits).n_splits);
+    if (D == kD) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, kMaxKeySplits).n_splits);
+  }
   return attn_partial_bytes(Hq, Nq, D, splits);
 }
 

@@ -320,8 +320,9 @@ def test_frame_attn_f32_shapes(d, nq, nk):
 
 # edges of the fp32 kernel's 16-row tiles, 32-key steps and key shares (17 rows x 5,000 keys: shares)
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("nq,nk", [(15, 31), (16, 32), (17, 33), (31, 255), (32, 256), (33, 257), (17, 5000)])
+@pytest.mark.parametrize("nq,nk", [(15, 31), (16, 32), (17, 33), (31, 255), (32, 256), (33, 257), (17, 5000), (301, 2501)])
 def test_frame_attn_f32_tile_edges_and_key_shares(d, nq, nk):
+    # 16 query rows per work-group, 32 in the last shape; tiles of rows that span the three heads
     Q, K, V = _attn_case("f32", 3, 1, nq, nk, d, d + nq + nk)
     _attn_check("f32", Q, K, V, d ** -0.5)
     # without a workspace the keys are not cut: the same sums in another order
@@ -329,6 +330,24 @@ def test_frame_attn_f32_tile_edges_and_key_shares(d, nq, nk):
     b = pk.pc_frame_attn(dev(Q, None), dev(K, None), dev(V, None), nk, d ** -0.5,
                          ws=torch.empty(16, dtype=torch.uint8, device=DEV))
     assert (a - b).abs().max().item() <= 2e-6   # two fp32 results of |O| < 4, each within a few 2^-24 |O| of exact
+
+
+@pytest.mark.parametrize("nq,nk", [(70, 900), (301, 2501)])
+@pytest.mark.parametrize("step", [0.05, 0.6, 40.0])
+def test_frame_attn_f32_reference_is_refreshed(nq, nk, step):
+    # logits that climb along the key axis: the reference lags by up to 2^8 before the rows are rescaled
+    Q, K, V = _attn_case("f32", 3, 1, nq, nk, 128, 9)
+    Q[..., 0] = 8.0
+    K *= 0.1
+    K[..., 0] = step * (np.arange(nk) // 32) / (8.0 * 128 ** -0.5)
+    lse = torch.empty((3, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(dev(Q, None), dev(K, None), dev(V, None), nk, 128 ** -0.5, lse=lse)
+    rows = sorted({0, 15, 16, 31, 32, nq - 1} | set(range(0, nq, 37)))
+    Ow, Lw = orc.frame_attn(Q[:, rows], K, V, 128 ** -0.5)
+    # a logit L is an fp32 sum of products of magnitude L: its error is a few L 2^-24, and so is p's
+    rel = 8 * max(1.0, np.abs(Lw).max()) * 2.0 ** -24
+    assert np.abs(host(O)[:, rows] - Ow).max() <= 4 * rel + 1e-6
+    assert np.abs(host(lse)[:, rows] - Lw).max() <= rel
 
 
 def test_frame_attn_f32_takes_buffers_that_are_not_16_byte_aligned():
