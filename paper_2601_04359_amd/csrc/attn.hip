@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
     int64_t kv_stride_h, int64_t o_stride_h, float c, int n_tiles_q, int n_splits, float* __restrict__ part_o,
-    float2* __restrict__ part_ml) {
+    float2* __restrict__ part_ml, int n_whole, int64_t row_whole) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -204,11 +204,14 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  // logical order: key split slowest, then KV head, then row tile
-  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
-  const int split = L / tiles_all;
-  const int kvh = (L % tiles_all) / n_tiles_q, tile = L % n_tiles_q;
+  // Row tiles in the order (KV head, tile).  The first n_whole of them (whole rounds of the chip) walk
+  // all keys; the rest are cut into n_splits key shares, share slowest.
+  const bool whole = static_cast<int>(blockIdx.x) < n_whole;
+  const int n_cut = (static_cast<int>(gridDim.x) - n_whole) / n_splits;   // row tiles that are cut
+  const int L = whole ? xcd_contiguous_index(blockIdx.x, n_whole)
+                      : xcd_contiguous_index(blockIdx.x - n_whole, gridDim.x - n_whole);
+  const int split = whole ? 0 : L / n_cut, unit = whole ? L : n_whole + L % n_cut;
+  const int kvh = unit / n_tiles_q, tile = unit % n_tiles_q;
   const int n_rows = rep * Nq;    // query rows of the KV head
   const int rho = tile * kBM + wave * 32 + l32;   // the row this lane owns
   const bool active = rho - l32 < n_rows;  // wave-uniform
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 
   // this work-group's share of the key tiles: n of n_all (the host leaves no share empty)
   const int n_all = (Nk + kBN - 1) / kBN;
-  const int per = (n_all + n_splits - 1) / n_splits;
+  const int per = whole ? n_all : (n_all + n_splits - 1) / n_splits;
   const int n = min(per, n_all - split * per);
   const int key0 = split * per * kBN;
   const int n_valid = Nk - key0;   // less than n tiles only where the ragged last tile is in this share
@@ -374,9 +377,10 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   }
   const float l_tot = wave_half_sum(l_run);
   const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
-  if (part_o != nullptr) {  // one of several key shares: un-normalised O, reference and sum for the merge
+  if (part_o != nullptr && !whole) {  // one of several key shares: un-normalised O, reference and sum for the merge
     if (rho < n_rows) {
-      const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+      const int64_t n_all_rows = static_cast<int64_t>((n_whole + n_cut) / n_tiles_q) * n_rows;
+      const int64_t at_s = split * (n_all_rows - row_whole) + at - row_whole;
       float* prow = part_o + at_s * kD;
 #pragma unroll
       for (int db = 0; db < 4; ++db)
@@ -430,7 +434,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
     int64_t kv_stride_h, int64_t o_stride_h, float c, int n_tiles_q, int n_splits, float* __restrict__ part_o,
-    float2* __restrict__ part_ml) {
+    float2* __restrict__ part_ml, int /*n_whole*/, int64_t /*row_whole*/) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -628,17 +632,19 @@ __device__ __forceinline__ float natural_lse(float m, float l) {
 }
 
 // Merge of the key shares: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s with M = max_s m_s.
-// A thread owns four dims of one row.
+// A thread owns four dims of one row.  The rows in front of row_whole (numbered over all heads) were
+// not cut.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float2* __restrict__ part_ml,
                                                          T* __restrict__ O, float* __restrict__ lse,
-                                                         int Hq, int Nq, int64_t o_stride_h, int n_splits) {
+                                                         int Hq, int Nq, int64_t o_stride_h, int n_splits,
+                                                         int64_t row_whole) {
   constexpr bool kF32 = sizeof(T) == 4;
   constexpr int kLanes = D / 4;  // threads per row
   const int64_t r = static_cast<int64_t>(blockIdx.x) * (256 / kLanes) + threadIdx.x / kLanes;
   const int c = threadIdx.x % kLanes;
-  const int64_t n_rows = static_cast<int64_t>(Hq) * Nq;
+  const int64_t n_rows = static_cast<int64_t>(Hq) * Nq - row_whole;
   if (r >= n_rows) return;
   // lane s of the row holds share s (n_splits <= kLanes): one load each instead of a chain of them
   float2 ml = make_float2(-INFINITY, 0.f);
@@ -671,17 +677,18 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     load(s0, v);
   }
   const float inv = 1.f / l;
-  const int h = static_cast<int>(r / Nq), row = static_cast<int>(r % Nq);
+  const int64_t at = row_whole + r;
+  const int h = static_cast<int>(at / Nq), row = static_cast<int>(at % Nq);
   T* out = O + h * o_stride_h + static_cast<int64_t>(row) * D + c * 4;
   if constexpr (kF32) {
     store_f32x4(out, acc * inv);
-    if (lse != nullptr && c == 0) lse[r] = natural_lse(M, l);
+    if (lse != nullptr && c == 0) lse[at] = natural_lse(M, l);
   } else {
     u32x2 packed;
     packed[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
     packed[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
     *reinterpret_cast<u32x2*>(out) = packed;
-    if (lse != nullptr && c == 0) lse[r] = (M + log2f(l)) * 0.6931471805599453f;
+    if (lse != nullptr && c == 0) lse[at] = (M + log2f(l)) * 0.6931471805599453f;
   }
 }
 
@@ -695,12 +702,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 // heads x 252 rows x 1,179 keys, 11.9 us with 32 rows against 18.8 with 256 (and 34 un-split); 16/4
 // x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x 7,455,
 // 92.9 against 67.4.
+// Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
+// rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
+// third of the partial rows and a round less: 363 us, 381 with all of them cut).
 struct AttnPlan {
   bool small;
   int n_splits;
+  int n_whole;   // row tiles that are not cut (n_splits > 1)
 };
 AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
-  AttnPlan best = {false, 1};
+  AttnPlan best = {false, 1, 0};
   double best_cost = 1e30;
   auto consider = [&](bool small, int tile_rows, int share_keys, int step_keys, double start, double per_step,
                       double fill_step) {
@@ -714,7 +725,17 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
                           (rounds - 1) * 3.3 + merge;
       if (cost < best_cost) {
         best_cost = cost;
-        best = {small, s};
+        best = {small, s, 0};
+      }
+      const int whole = base / 256 * 256, cut = base - whole;
+      if (small || s == 1 || whole == 0 || cut == 0) continue;
+      const int cut_rounds = ceil_div(cut * s, 256);
+      const double part = start + whole / 256 * (per_step + fill_step) * ceil_div(Nk, step_keys) +
+                          cut_rounds * (per_step + fill_step * std::min(1.0, cut * s / 256.0)) * steps +
+                          (whole / 256 + cut_rounds - 1) * 3.3 + 2.4 + 1.86e-4 * s * cut * tile_rows;
+      if (part < best_cost) {
+        best_cost = part;
+        best = {small, s, whole};
       }
     }
   };
@@ -1023,7 +1044,7 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
     constexpr int kRowsPerBlock = 256 / (D / 4);
     const int64_t rows = static_cast<int64_t>(Hq) * Nq;
     attn_merge_kernel<float, D><<<static_cast<unsigned>((rows + kRowsPerBlock - 1) / kRowsPerBlock), 256, 0, s>>>(
-        part_o, part_ml, O, lse, Hq, Nq, o_stride_h, n_splits);
+        part_o, part_ml, O, lse, Hq, Nq, o_stride_h, n_splits, 0);
     PC_CHECK_LAUNCH("pc_frame_attn merge");
   }
   return PC_OK;
@@ -1083,14 +1104,18 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
       part_o = static_cast<float*>(ws);
       part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, plan.n_splits));
     }
-    kernel<<<dim3(n_tiles_q * Hkv * plan.n_splits), kPPThreads, smem, s>>>(
+    const int n_tiles = n_tiles_q * Hkv;
+    // the first row that is cut, numbered over all heads
+    const int64_t row_whole = static_cast<int64_t>(plan.n_whole / n_tiles_q) * rep * Nq + plan.n_whole % n_tiles_q * kBM;
+    kernel<<<dim3(plan.n_whole + (n_tiles - plan.n_whole) * plan.n_splits), kPPThreads, smem, s>>>(
         static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
         static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), lse, rep, Nq, Nk, q_stride_h,
-        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml);
+        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml, plan.n_whole, row_whole);
     if (plan.n_splits > 1) {
       PC_CHECK_LAUNCH("pc_frame_attn");
-      attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((static_cast<int64_t>(Hq) * Nq + 7) / 8), 256, 0, s>>>(
-          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits);
+      const int64_t rows = static_cast<int64_t>(Hq) * Nq - row_whole;
+      attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((rows + 7) / 8), 256, 0, s>>>(
+          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits, row_whole);
     }
   } else {
     PC_REQUIRE(D == 64 || D == 128, PC_ERR_UNSUPPORTED, "pc_frame_attn: fp32 tier needs D=64 or 128, got %d", D);

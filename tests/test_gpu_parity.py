@@ -245,13 +245,15 @@ def test_frame_attn_bf16_key_shares_and_merge(hq, hkv, nq, nk, fold):
 
 # Row tiles that span query heads (nq is no multiple of the tile), steps and tiles of the keys that are
 # empty, single or ragged, and both forms of the kernel: the first five shapes take 32 rows per
-# work-group (un-split, then in key shares), the last two 256 rows (in key shares, then un-split).
+# work-group (un-split, then in key shares), the others 256 rows (in key shares; un-split; a whole
+# round of row tiles un-split and the rest in key shares).
 # step: logits climb along the key axis, as above.  Every row is computed; the oracle checks the rows
 # at the tile edges and a stride of the others.
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
 @pytest.mark.parametrize("hq,hkv,nq,nk", [(2, 1, 33, 1), (3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 84, 255),
-                                          (2, 1, 184, 5000), (24, 8, 520, 2100), (16, 4, 2010, 2499)])
+                                          (2, 1, 184, 5000), (24, 8, 520, 2100), (16, 4, 2010, 2499),
+                                          (24, 8, 2901, 2100)])
 def test_frame_attn_bf16_row_tiles_across_heads(hq, hkv, nq, nk, step, fold):
     Q, K, V = _attn_case("bf16", hq, hkv, nq, nk, 128, nq + nk)
     scale = 128 ** -0.5
