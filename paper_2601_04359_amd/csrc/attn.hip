@@ -14,7 +14,7 @@
 //     (and the accumulators rescaled) only when one of its row sums runs away.
 //   * With scale = ln 2 (the caller multiplied Q by scale * log2(e), e.g. while rotating it)
 //     the affine step c*s - m is taken out of the loop: see kUnitC below.
-// fp32 tier (D = 64 or 128): fp32 MFMA, sixteen query rows per work-group (see attn_f32_kernel).
+// fp32 tier (D = 64 or 128): fp32 MFMA, 16 or 32 query rows per work-group (see attn_f32_kernel).
 #include <math.h>
 
 #include <algorithm>
