@@ -241,3 +241,16 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert p.returncode != 0 and "ONE GPU" in p.stderr and p.stdout.strip() == ""
+
+
+def test_tables_marshal_the_same_from_any_kind_of_number():
+    # plain and numpy integers are packed in one pass, everything else is converted one by one
+    plain = [(0, 4, pk.PC_SEG_TEXT, -1), (4, 9, pk.PC_SEG_COND, 0), (13, 9, pk.PC_SEG_FRAME, 1)]
+    want = pk.pc_compact_plan(plain, [4, 9, 5])
+    assert want == ([(0, 4, pk.PC_SEG_TEXT, -1), (4, 9, pk.PC_SEG_COND, 0), (13, 5, pk.PC_SEG_FRAME, 1)], 18)
+    for conv in (lambda v: v, np.int64, np.int32, float, np.float64):
+        segs = [tuple(conv(v) for v in s) for s in plain]
+        assert pk.pc_compact_plan(segs, [conv(4), conv(9), conv(5)]) == want
+        assert pk.pc_compact_plan([list(s) for s in segs], (conv(4), conv(9), conv(5))) == want
+    assert pk.pc_compact_plan([(0, 4, pk.PC_SEG_TEXT)], [4]) == ([(0, 4, pk.PC_SEG_TEXT, 0)], 4)   # frame left out
+    assert pk.pc_compact_plan([], []) == ([], 0)
