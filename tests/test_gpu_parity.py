@@ -313,6 +313,25 @@ def test_frame_attn_bf16_closed_forms():
     assert np.array_equal(O1, np.broadcast_to(V[0, 5], O1.shape))   # one key -> that value row
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shares", [0.5, 2, 3.5])
+def test_frame_attn_takes_as_many_key_shares_as_the_workspace_holds(shares, dtype):
+    # the call would take about ten shares; a workspace for fewer means fewer, a misaligned one none
+    hq, nq, nk, d = 2, 184, 5000, 128
+    Q, K, V = _attn_case(dtype, hq, 1, nq, nk, d, 21)
+    Qd, Kd, Vd = dev(Q, dtype), dev(K, dtype), dev(V, dtype)
+    n = int(shares * hq * nq * (d * 4 + 8)) + 512
+    buf = torch.full((n + 4096,), 255, dtype=torch.uint8, device=DEV)
+    Ow, Lw = orc.frame_attn(Q, K, V, d ** -0.5)
+    for off in (0, 8):
+        lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+        O = pk.pc_frame_attn(Qd, Kd, Vd, nk, d ** -0.5, lse=lse, ws=buf[off:off + n])
+        tol = 2e-2 if dtype == "bf16" else 1e-5
+        assert np.abs(host(O).astype(np.float64) - Ow).max() <= tol
+        assert np.abs(host(lse).astype(np.float64) - Lw).max() <= tol
+        assert (buf[off + n:] == 255).all()     # nothing behind the workspace was written
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nk", [(1, 1), (64, 336), (70, 33), (130, 191)])
 def test_frame_attn_f32_shapes(d, nq, nk):
