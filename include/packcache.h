@@ -339,6 +339,8 @@ int pc_mask_scores(float* score, int Hsel, int Nk, int64_t score_stride_h, const
  *   compute units badly; the shares' partial results are merged from the workspace.  A smaller one
  *   means fewer shares; without it, or if it is not 16-byte aligned, the keys are not cut: always
  *   valid, the result differs by rounding only.
+ * Nk >= 1, Nq >= 1.  Errors: PC_ERR_NULL, PC_ERR_DTYPE, PC_ERR_SHAPE, PC_ERR_UNSUPPORTED,
+ * PC_ERR_HIP.
  */
 size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D);
 int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq, int Hkv,
