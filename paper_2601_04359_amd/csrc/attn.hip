@@ -34,7 +34,11 @@ constexpr int kTileBytes = kBN * kRowBytes;
 constexpr int kStages = 4;           // LDS slots per operand: tile t lives in slot t % kStages
 constexpr size_t kSmemBytes = 2 * kStages * kTileBytes;
 constexpr float kRescaleTrigger = 1024.f;  // row sum of a half tile that forces a new reference maximum
+constexpr float kLowestStart = -4096.f;    // lowest reference that products start from (see pipeline_phase)
 constexpr int kRing = 4;
+// The reference of a query that has seen no key, or only keys of a score -inf: finite, so that such
+// keys weigh exp2(-inf) = 0 and what has been summed (zeros) merges like any other share.
+constexpr float kNoRef = -3.402823466e38f;
 
 // ---- LDS tile layout ---------------------------------------------------------------------------
 // K tiles use the fragment-read swizzle of lds_dma.h.  V is read with transposing loads
@@ -82,11 +86,17 @@ __device__ __forceinline__ RowAt row_at(int rho, int kvh, int rep, int Nq) {
 // lane, which holds one query), so a score arrives as s - m_ref and the probability is a bare
 // exp2: one vector instruction per element fewer.  When the reference moves, the scores that
 // were started from the old one are shifted by the difference.
+// Keys of a score -inf, or of a mask value far below the rest, weigh nothing, and a wave may see a half
+// tile of nothing else before its first real key.  c general: a reference of -inf makes the row sum
+// NaN or inf, so every half tile is redone until there is a finite one, and a redo without one adds
+// zeros.  kUnitC: products must not start from such a reference (inf - inf, or a score lost in the
+// rounding of -m_ref: an ulp at kLowestStart is 2^-11): they start from zero instead, and while any
+// query of the wave is in that state (low_ref) every half tile is redone.
 template <bool kUnitC>
 __device__ __forceinline__ void pipeline_phase(
     const lds_u8* k_half, const int (&k_off)[8], const lds_u8* v_half, const int (&v_off)[4],
     const bf16x8 (&qf)[8], f32x16& s_nxt, const bf16x8 (&p_mm)[2], f32x16 (&o)[4], const f32x16& s_cur,
-    bf16x8 (&p_cur)[2], float& m_ref, float& l_run, float c, f32x16& neg_m) {
+    bf16x8 (&p_cur)[2], float& m_ref, float& l_run, float c, f32x16& neg_m, bool& low_ref) {
   // fragment k: 0..7 -> K rows, contraction step k; 8..15 -> V^T (key step (k-8)/4, block (k-8)%4)
   auto frag = [&](int k) -> bf16x8 {
     if (k < 8) {
@@ -142,24 +152,30 @@ __device__ __forceinline__ void pipeline_phase(
 #pragma unroll
   for (int half = 0; half < 2; ++half) asm volatile("" : "+v"(p_cur[half]));
   asm volatile("" : "+v"(psum));
-  if (__any(!(psum <= kRescaleTrigger))) {  // also catches inf and NaN
+  if ((kUnitC && low_ref) || __any(!(psum <= kRescaleTrigger))) {  // also catches inf and NaN
     float mx = s_cur[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s_cur[i]);
-    // unit c: s_cur already holds s - m_ref, so the new reference lies max(0, max s_cur) above the old one
-    const float m_new = kUnitC ? m_ref + fmaxf(0.f, wave_half_max(mx)) : fmaxf(m_ref, wave_half_max(mx) * c);
-    const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+    mx = wave_half_max(mx);
+    // unit c: s_cur holds s - start, and so do the scores just formed; start is the reference or zero
+    const float start = kUnitC ? -neg_m[0] : 0.f;
+    const float m_new = fmaxf(m_ref, kUnitC ? start + mx : mx * c);
+    const bool none = m_new == -INFINITY;   // no key of a finite score yet
+    const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+    const float m_use = none ? 0.f : m_new - start;
     psum = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      pv[i] = kUnitC ? __builtin_amdgcn_exp2f(s_cur[i] - (m_new - m_ref)) : __builtin_amdgcn_exp2f(fmaf(s_cur[i], c, -m_new));
+      pv[i] = kUnitC ? __builtin_amdgcn_exp2f(s_cur[i] - m_use) : __builtin_amdgcn_exp2f(fmaf(s_cur[i], c, -m_use));
       psum += pv[i];
     }
-    if constexpr (kUnitC) {   // the scores just formed were started from the old reference
+    if constexpr (kUnitC) {
+      const float start_new = m_new >= kLowestStart ? m_new : 0.f;
+      low_ref = __any(!(m_new >= kLowestStart));
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        s_acc[i] -= m_new - m_ref;
-        neg_m[i] = -m_new;
+        s_acc[i] -= start_new - start;
+        neg_m[i] = -start_new;
       }
     }
 #pragma unroll
@@ -235,6 +251,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
       pB[ks][e] = static_cast<__bf16>(0.f);
     }
   float m_ref = -INFINITY, l_run = 0.f;
+  bool low_ref = false;   // wave-uniform
   f32x16 neg_m;
 #pragma unroll
   for (int i = 0; i < 16; ++i) neg_m[i] = 0.f;
@@ -308,10 +325,12 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sA[i]);
     m_ref = wave_half_max(mx) * c;
     if constexpr (kUnitC) {
+      const float start = m_ref >= kLowestStart ? m_ref : 0.f;
+      low_ref = __any(!(m_ref >= kLowestStart));
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        sA[i] -= m_ref;
-        neg_m[i] = -m_ref;
+        sA[i] -= start;
+        neg_m[i] = -start;
       }
     }
     if (n_valid < kBN) mask_tail(sA, n_valid - g * 4);
@@ -328,7 +347,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     // ---- phase 1: S_B(j), O += V_B(j-1) P_B(j-1)  |  P_A(j) ----
     if (active) {
       pipeline_phase<kUnitC>(smem + k_cur + 32 * kRowBytes, k_off, smem + v_prev + 32 * kRowBytes, v_off, qf, sB, pB, o, sA,
-                     pA, m_ref, l_run, c, neg_m);
+                     pA, m_ref, l_run, c, neg_m, low_ref);
       if (left < kBN) mask_tail(sB, left - 32 - g * 4);
     }
     // One barrier per tile: every wave is past K(j) and V(j-1), and K(j+1), V(j) (fetched
@@ -340,7 +359,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     // ---- phase 2: S_A(j+1), O += V_A(j) P_A(j)  |  P_B(j) ----
     // (after the last tile S_A is formed from a clamped tile and never used)
     if (active) {
-      pipeline_phase<kUnitC>(smem + k_nxt, k_off, smem + v_cur, v_off, qf, sA, pA, o, sB, pB, m_ref, l_run, c, neg_m);
+      pipeline_phase<kUnitC>(smem + k_nxt, k_off, smem + v_cur, v_off, qf, sA, pA, o, sB, pB, m_ref, l_run, c, neg_m,
+                             low_ref);
       if (left < 2 * kBN) mask_tail(sA, left - kBN - g * 4);
     }
   };
@@ -492,7 +512,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = kNoRef, l = 0.f;
 
   for (int k0 = k_first; k0 < k_end; k0 += 8 * kSmallKeys) {
     // This step's rows have landed (they are all that is in flight): take every fragment into
@@ -537,8 +557,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     float mx = sc[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sc[i]);
-    mx = wave_half_max(mx) * c;        // key k0 is valid: not -inf
-    if (__any(!(mx <= m + 8.f))) {     // the reference lags by at most 2^8 (always taken first: m = -inf)
+    mx = wave_half_max(mx) * c;
+    if (__any(!(mx <= m + 8.f))) {     // the reference lags by at most 2^8
       const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
@@ -586,12 +606,12 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
     mw[w] = s_ml[(w * kSmallRows + l32) * 2];
-    M = fmaxf(M, mw[w]);               // wave 0 always has keys: not -inf
+    M = fmaxf(M, mw[w]);
   }
   f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
-    const float wt = __builtin_amdgcn_exp2f(mw[w] - M);   // 0 for a wave that had no keys
+    const float wt = __builtin_amdgcn_exp2f(mw[w] - M);
     lt += wt * s_ml[(w * kSmallRows + l32) * 2 + 1];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -832,11 +852,14 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
   float m[kR], l[kR];
 #pragma unroll
   for (int t = 0; t < kR; ++t) {
-    m[t] = -INFINITY;
+    m[t] = kNoRef;
     l[t] = 0.f;
   }
-  const float c = scale * 1.4426950408889634f;
-  const float c_lo = fmaf(scale, 1.92596299e-8f, fmaf(scale, 1.4426950216293335f, -c));
+  // c is rounded down and c_lo above zero: a score of -inf then stays -inf (and is no NaN)
+  float c = scale * 1.4426950408889634f;
+  auto rest = [&] { return fmaf(scale, 1.92596299e-8f, fmaf(scale, 1.4426950216293335f, -c)); };
+  if (rest() < 0.f) c = __uint_as_float(__float_as_uint(c) - 1);
+  const float c_lo = fmaxf(rest(), 1.17549435e-38f);
 
   // Software pipeline: the V loads of a step fly during its score products, the K loads of the
   // next step (into the registers those products just freed) during its softmax and value products.
@@ -883,7 +906,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     load_k(k0 + kF32Waves * kF32Keys);  // past the end: clamped rows, never used
     __builtin_amdgcn_sched_barrier(0);
     float mx[kR];
-    bool lags = false;   // a reference may lag by 2^8 (always taken first: m = -inf)
+    bool lags = false;   // a reference may lag by 2^8
 #pragma unroll
     for (int t = 0; t < kR; ++t) {
       mx[t] = -INFINITY;
@@ -900,7 +923,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
         for (int e = 0; e < 4; ++e) mx[t] = fmaxf(mx[t], sc[t][u][e]);
       }
       mx[t] = fmaxf(mx[t], __shfl_xor(mx[t], 16));
-      mx[t] = wave_half_max(mx[t]);      // finite: key k0 itself is inside the share
+      mx[t] = wave_half_max(mx[t]);
       lags = lags || !(mx[t] <= m[t] + 8.f);
     }
     if (__any(lags)) {
@@ -973,7 +996,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kF32Waves; ++w) {
-      const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);   // 0 for a wave that had no keys
+      const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);
       lt += wt * s_l[w * kF32Rows + row];
       acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + col);
     }

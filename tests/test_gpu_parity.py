@@ -381,6 +381,56 @@ def test_frame_attn_f32_takes_buffers_that_are_not_16_byte_aligned():
     assert np.abs(host(O) - Ow).max() <= 1e-5
 
 
+def _masked_reference(Q, K, V, keep, scale, rows):
+    """(O rows, lse rows, importances) of the unmasked keys alone, in 64 bits on the GPU."""
+    hq, hkv = Q.shape[0], K.shape[0]
+    O, L = [], []
+    mass = torch.zeros((hkv, int(keep.sum())), dtype=torch.float64, device=DEV)
+    for h in range(hq):
+        s = Q[h, rows].double() @ K[h * hkv // hq, keep].double().t() * scale
+        p = torch.softmax(s, dim=1)
+        O.append(p @ V[h * hkv // hq, keep].double())
+        L.append(torch.logsumexp(s, dim=1))
+        mass[h * hkv // hq] += p.sum(0)
+    return torch.stack(O), torch.stack(L), mass
+
+
+# A caller that masks keys through a coordinate of its own (the queries carry a constant there): their
+# logits are -inf, the type's lowest value times a constant, or far below the rest.  Steps, waves, half
+# tiles and key shares that hold nothing else, first and last ones among them: 32 rows per work-group
+# un-split and in shares, 256 un-split and in four shares of 1,920 keys; fp32 with 16 and 32.
+@pytest.mark.parametrize("value", [float("-inf"), "lowest", -3e5])
+@pytest.mark.parametrize("masked", [slice(3, None, 5), slice(40, 300), slice(0, 140), slice(1900, 2040), slice(0, -3), slice(5, None)])
+@pytest.mark.parametrize("dtype,d,fold,hq,hkv,nq,nk", [
+    ("bf16", 128, False, 8, 2, 252, 1804), ("bf16", 128, True, 8, 2, 252, 1804), ("bf16", 128, False, 2, 1, 184, 5000),
+    ("bf16", 128, False, 16, 4, 4032, 2048), ("bf16", 128, True, 16, 4, 4032, 2048),
+    ("bf16", 128, False, 16, 4, 1008, 7455), ("bf16", 128, True, 16, 4, 1008, 7455),
+    ("f32", 64, False, 2, 1, 64, 336), ("f32", 128, False, 2, 1, 33, 336), ("f32", 128, False, 8, 2, 252, 1804),
+    ("f32", 64, False, 3, 1, 301, 2501)])
+def test_masked_keys_weigh_nothing(dtype, d, fold, hq, hkv, nq, nk, masked, value):
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K, V = (dev(x, dtype) for x in _attn_case(dtype, hq, hkv, nq, nk, d, nq + nk))
+    Q[..., 0] = 4.0
+    scale = d ** -0.5
+    if fold:
+        Q, scale = (Q.double() * q_fold(scale)).to(td), LN2
+    keep = torch.ones(nk, dtype=torch.bool, device=DEV)
+    keep[masked] = False
+    K[:, ~keep, 0] = torch.finfo(td).min if value == "lowest" else value
+    rows = torch.arange(0, nq, max(1, nq // 40), device=DEV)
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, lse=lse)
+    Ow, Lw, mass = _masked_reference(Q, K, V, keep, scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs().max().item()
+    # with three keys left |O| reaches 4, as in the tests of climbing logits above
+    tol = (2 ** -5 if keep.sum() < 40 else 2e-2, 1e-3) if dtype == "bf16" else (1e-5, 1e-5)
+    assert not O.isnan().any() and err.max().item() <= tol[0] and lerr <= tol[1], (err.max().item(), lerr)
+    score = pk.pc_score(Q[:, rows].contiguous(), K, nk, scale).double()
+    rel = max(2e-5, 6 * Lw.abs().max().item() * 1.4427 * 2.0 ** -23)      # as in the tests of pc_score
+    assert (score[:, ~keep] == 0).all()
+    assert ((score[:, keep] - mass).abs() <= 2e-7 + rel * mass).all()
+
+
 def test_frame_attn_capacity_larger_than_rows():
     # K/V live in buffers with spare capacity (head stride > Nk*D), as a cache does
     Q, K, V = _attn_case("bf16", 4, 2, 100, 300, 128, 11)
