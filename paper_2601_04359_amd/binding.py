@@ -9,7 +9,7 @@ import ctypes as C
 import os
 import struct
 from itertools import chain
-from typing import Sequence
+from typing import Iterable, Sequence
 
 __all__ = [
     "PC_F32", "PC_BF16", "PC_SEG_TEXT", "PC_SEG_COND", "PC_SEG_FRAME", "PC_SEG_SELF",
@@ -164,11 +164,11 @@ def _workspace(nbytes: int, like):
 
 def _seg_array(segments: Sequence[Sequence[int]]):
     n = len(segments)
-    if n and set(map(len, segments)) == {4}:
-        try:    # one pass in C: a table of 49 segments in 4 us instead of 22
+    try:
+        if n and set(map(len, segments)) == {4}:    # one pass in C: a table of 49 segments in 4 us instead of 22
             return (pc_segment * n).from_buffer_copy(struct.pack(f"{4 * n}i", *chain.from_iterable(segments)))
-        except struct.error:
-            pass    # not plain 32-bit integers: convert one by one
+    except (struct.error, TypeError):
+        pass    # rows without a length, or not plain 32-bit integers: convert one by one
     arr = (pc_segment * max(n, 1))()
     for i, s in enumerate(segments):
         arr[i] = pc_segment(*[int(v) for v in s])
@@ -181,12 +181,12 @@ def _seg_tuples(arr, n: int) -> list[tuple[int, int, int, int]]:
     return list(zip(flat, flat, flat, flat))
 
 
-def _budget_array(budgets: Sequence[int], n: int):
-    if n and len(budgets) == n:
-        try:
+def _budget_array(budgets: Iterable[int], n: int):
+    try:
+        if n and len(budgets) == n:
             return (C.c_int32 * n).from_buffer_copy(struct.pack(f"{n}i", *budgets))
-        except struct.error:
-            pass
+    except (struct.error, TypeError):
+        pass    # as above
     return (C.c_int32 * max(n, 1))(*[int(v) for v in budgets])
 
 

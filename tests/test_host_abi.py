@@ -254,3 +254,22 @@ def test_tables_marshal_the_same_from_any_kind_of_number():
         assert pk.pc_compact_plan([list(s) for s in segs], (conv(4), conv(9), conv(5))) == want
     assert pk.pc_compact_plan([(0, 4, pk.PC_SEG_TEXT)], [4]) == ([(0, 4, pk.PC_SEG_TEXT, 0)], 4)   # frame left out
     assert pk.pc_compact_plan([], []) == ([], 0)
+
+
+def test_tables_may_be_tensors_and_iterators():
+    import torch
+    plain = [(0, 4, pk.PC_SEG_TEXT, -1), (4, 9, pk.PC_SEG_COND, 0), (13, 9, pk.PC_SEG_FRAME, 1)]
+    budgets = [4, 9, 5]
+    want = pk.pc_compact_plan(plain, budgets)
+    for make in (iter, lambda b: map(int, b), lambda b: (v for v in b), np.array, torch.tensor,
+                 lambda b: torch.tensor(b, dtype=torch.float32), lambda b: torch.tensor(b, dtype=torch.uint8),
+                 lambda b: [torch.tensor(float(v)) for v in b], lambda b: [str(v) for v in b], dict.fromkeys):
+        assert pk.pc_compact_plan(plain, make(budgets)) == want
+        assert pk.pc_masked_budgets(plain, make(budgets), np.ones(22, np.uint8)) == budgets
+    for make in (lambda t: [iter(s) for s in t], lambda t: [map(int, s) for s in t], np.array, torch.tensor,
+                 lambda t: torch.tensor(t, dtype=torch.float64), lambda t: list(torch.tensor(t, dtype=torch.float32)),
+                 lambda t: [[torch.tensor(float(v)) for v in s] for s in t]):
+        assert pk.pc_compact_plan(make(plain), budgets) == want
+    for bad in (5, None, [4, 9, None], [4, 9, "x"], [4, 9, 5, 6]):     # refused before as now
+        with pytest.raises((TypeError, ValueError, IndexError)):
+            pk.pc_compact_plan(plain, bad)
