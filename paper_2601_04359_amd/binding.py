@@ -116,11 +116,15 @@ def _dtype_code(t) -> int:
 
 
 def _stream() -> int:
-    """The current stream's handle.  The raw query costs 0.2 us; building the Stream object of
-    torch.cuda.current_stream() costs ten times that, once per call of this module."""
+    """The current stream's handle.  torch's internal raw query costs 0.2 us; building the Stream object
+    of torch.cuda.current_stream() costs ten times that, once per call of this module.  A torch that
+    lacks the raw query is asked the public way."""
     import torch
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

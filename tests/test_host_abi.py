@@ -273,3 +273,16 @@ def test_tables_may_be_tensors_and_iterators():
     for bad in (5, None, [4, 9, None], [4, 9, "x"], [4, 9, 5, 6]):     # refused before as now
         with pytest.raises((TypeError, ValueError, IndexError)):
             pk.pc_compact_plan(plain, bad)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_query_falls_back_to_the_public_one(monkeypatch, missing):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 12, raising=False)
+    assert binding._stream() == 12
+    monkeypatch.delattr(torch._C, missing)
+    assert binding._stream() == 4711
