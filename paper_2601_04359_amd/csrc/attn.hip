@@ -712,6 +712,21 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   }
 }
 
+// Workspace of n_splits key shares of `rows` query rows: the partial O rows, then the (m, l) pairs.
+size_t attn_partial_o_bytes(int64_t rows, int D, int n_splits) {
+  return align_up(static_cast<size_t>(n_splits) * rows * D * sizeof(float), 256);
+}
+size_t attn_partial_bytes(int64_t rows, int D, int n_splits) {
+  return n_splits <= 1 ? 0
+                       : attn_partial_o_bytes(rows, D, n_splits) +
+                             align_up(static_cast<size_t>(n_splits) * rows * sizeof(float2), 256);
+}
+// What of the caller's workspace key shares may use: nothing of one that is not 16-byte aligned.
+size_t usable_bytes(const void* ws, size_t ws_bytes) {
+  return ws == nullptr || reinterpret_cast<uintptr_t>(ws) % 16 != 0 ? 0 : ws_bytes;
+}
+constexpr int kMaxKeySplits = 16;
+
 // How a bf16 call is cut: 32 or 256 query rows per work-group, and the key shares.  The estimates
 // are microseconds, fitted to 24 shapes from 0.1 to 974 GFLOP (2 to 24 heads, 64 to 4,032 rows, 150 to
 // 29,500 keys) in both forms with 1 to 16 shares: `start` is what a work-group costs beside its
@@ -725,27 +740,30 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
 // rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
 // third of the partial rows and a round less: 363 us, 381 with all of them cut).
+// A cut whose partial rows do not fit ws_bytes is not considered; no shares always fit.
 struct AttnPlan {
   bool small;
   int n_splits;
-  int n_whole;   // row tiles that are not cut (n_splits > 1)
+  int n_whole;        // row tiles that are not cut (n_splits > 1)
+  int64_t row_whole;  // rows in front of the first that is cut, numbered over all heads
 };
-AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
-  AttnPlan best = {false, 1, 0};
+AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
+  AttnPlan best = {false, 1, 0, 0};
   double best_cost = 1e30;
   auto consider = [&](bool small, int tile_rows, int share_keys, int step_keys, double start, double per_step,
                       double fill_step) {
     const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
-    for (int s = 1; s <= std::min(max_splits, units); ++s) {
+    const int64_t all_rows = static_cast<int64_t>(Hkv) * rows;
+    for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
       const int steps = ceil_div(per * share_keys, step_keys), rounds = ceil_div(base * s, 256);
       const double merge = s == 1 ? 0.0 : 2.4 + 1.86e-4 * s * Hkv * rows;
       const double cost = start + rounds * (per_step + fill_step * std::min(1.0, base * s / 256.0)) * steps +
                           (rounds - 1) * 3.3 + merge;
-      if (cost < best_cost) {
+      if (cost < best_cost && attn_partial_bytes(all_rows, kD, s) <= ws_bytes) {
         best_cost = cost;
-        best = {small, s, 0};
+        best = {small, s, 0, 0};
       }
       const int whole = base / 256 * 256, cut = base - whole;
       if (small || s == 1 || whole == 0 || cut == 0) continue;
@@ -753,9 +771,11 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
       const double part = start + whole / 256 * (per_step + fill_step) * ceil_div(Nk, step_keys) +
                           cut_rounds * (per_step + fill_step * std::min(1.0, cut * s / 256.0)) * steps +
                           (whole / 256 + cut_rounds - 1) * 3.3 + 2.4 + 1.86e-4 * s * cut * tile_rows;
-      if (part < best_cost) {
+      const int tiles_q = base / Hkv;
+      const int64_t row_whole = static_cast<int64_t>(whole / tiles_q) * rows + whole % tiles_q * tile_rows;
+      if (part < best_cost && attn_partial_bytes(all_rows - row_whole, kD, s) <= ws_bytes) {
         best_cost = part;
-        best = {small, s, whole};
+        best = {small, s, whole, row_whole};
       }
     }
   };
@@ -763,23 +783,6 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, int max_splits) {
   consider(true, kSmallRows, kSmallKeys, 8 * kSmallKeys, 6.0, 1.17, 0.19);
   return best;
 }
-// Workspace of n_splits key shares: the partial O rows, then the (m, l) pairs.
-size_t attn_partial_o_bytes(int Hq, int Nq, int D, int n_splits) {
-  return align_up(static_cast<size_t>(n_splits) * Hq * Nq * D * sizeof(float), 256);
-}
-size_t attn_partial_bytes(int Hq, int Nq, int D, int n_splits) {
-  return n_splits <= 1 ? 0
-                       : attn_partial_o_bytes(Hq, Nq, D, n_splits) +
-                             align_up(static_cast<size_t>(n_splits) * Hq * Nq * sizeof(float2), 256);
-}
-// The largest number of shares not above `want` whose partial results fit the caller's workspace
-// (1, no shares, without one: always valid).
-int splits_that_fit(int want, int Hq, int Nq, int D, const void* ws, size_t ws_bytes) {
-  if (ws == nullptr || reinterpret_cast<uintptr_t>(ws) % 16 != 0) return 1;
-  while (want > 1 && attn_partial_bytes(Hq, Nq, D, want) > ws_bytes) --want;
-  return want;
-}
-
 // ------------------------------------------------------------------------------------------
 // fp32 tier: the 16x16x4 fp32 MFMA (fp32 operands and accumulation throughout; 2,048 FLOP in 32
 // cycles, twice the rate of scalar FMAs).  Bound: matrix rate and the loads of K and V when the chip
@@ -802,7 +805,6 @@ int splits_that_fit(int want, int Hq, int Nq, int D, const void* ws, size_t ws_b
 // one thread per row and plain FMA; 24/8 heads, 1,000 rows, 8,000 keys 874 us against 1,220
 // (112 TFLOP/s); 8/2 heads, 60 rows, 300 keys 13 us against 10.
 // ------------------------------------------------------------------------------------------
-constexpr int kMaxKeySplits = 16;
 constexpr int kF32Waves = 8;
 constexpr int kF32Threads = 64 * kF32Waves;
 template <int D, int kR>
@@ -1020,15 +1022,16 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
 struct F32Plan {
   int kr, n_splits;
 };
-F32Plan plan_f32(int Hkv, int rows, int Nk, int D, int max_splits) {
+F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
   F32Plan best = {1, 1};
   double best_cost = 1e30;
   const double f = D / 128.0;
   for (int kr = 1; kr <= 2; ++kr) {
     const int blocks = ceil_div(rows, 16 * kr) * Hkv, units = ceil_div(Nk, 32 / kr);
-    for (int s = 1; s <= std::min(max_splits, units); ++s) {
+    for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      if (attn_partial_bytes(static_cast<int64_t>(Hkv) * rows, D, s) > ws_bytes) break;
       const double merge = s == 1 ? 0.0 : 2.2 + 8.6e-4 * s * Hkv * rows * f;
       const double cost = (kr == 1 ? 2.1 : 3.5) + 3.4 * f +
                           ceil_div(blocks * s, 256) * (kr == 1 ? 7.0 : 5.15) * f * per / kF32Waves + merge;
@@ -1045,7 +1048,7 @@ template <int D>
 int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, int Nq, int Nk, int64_t q_stride_h,
              int64_t kv_stride_h, int64_t o_stride_h, float scale, float* O, float* lse, void* ws, size_t ws_bytes,
              hipStream_t s) {
-  const F32Plan plan = plan_f32(Hq / rep, rep * Nq, Nk, D, splits_that_fit(kMaxKeySplits, Hq, Nq, D, ws, ws_bytes));
+  const F32Plan plan = plan_f32(Hq / rep, rep * Nq, Nk, D, usable_bytes(ws, ws_bytes));
   const auto kernel = plan.kr == 2 ? attn_f32_kernel<D, 2> : attn_f32_kernel<D, 1>;
   const size_t smem = plan.kr == 2 ? f32_smem_bytes<D, 2>() : f32_smem_bytes<D, 1>();
   static std::atomic<uint64_t> lds_ok[2];
@@ -1053,11 +1056,12 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
     return rc;
   const int n_tiles_q = ceil_div(rep * Nq, 16 * plan.kr), n_splits = plan.n_splits, unit = 32 / plan.kr;
   const int keys_per_split = ceil_div(ceil_div(Nk, unit), n_splits) * unit;
+  const int64_t rows = static_cast<int64_t>(Hq) * Nq;
   float* part_o = nullptr;
   float2* part_ml = nullptr;
   if (n_splits > 1) {
     part_o = static_cast<float*>(ws);
-    part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, n_splits));
+    part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(rows, D, n_splits));
   }
   kernel<<<n_tiles_q * (Hq / rep) * n_splits, kF32Threads, smem, s>>>(
       Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, keys_per_split, n_tiles_q, n_splits,
@@ -1065,7 +1069,6 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
   PC_CHECK_LAUNCH("pc_frame_attn");
   if (n_splits > 1) {
     constexpr int kRowsPerBlock = 256 / (D / 4);
-    const int64_t rows = static_cast<int64_t>(Hq) * Nq;
     attn_merge_kernel<float, D><<<static_cast<unsigned>((rows + kRowsPerBlock - 1) / kRowsPerBlock), 256, 0, s>>>(
         part_o, part_ml, O, lse, Hq, Nq, o_stride_h, n_splits, 0);
     PC_CHECK_LAUNCH("pc_frame_attn merge");
@@ -1083,10 +1086,10 @@ extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
   int splits = 1;   // the call does not say which tier it will be, nor how many KV heads there are
   for (int rep = 1; rep <= Hq; ++rep) {
     if (Hq % rep != 0) continue;
-    splits = std::max(splits, plan_f32(Hq / rep, rep * Nq, Nk, D, kMaxKeySplits).n_splits);
-    if (D == kD) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, kMaxKeySplits).n_splits);
+    splits = std::max(splits, plan_f32(Hq / rep, rep * Nq, Nk, D, SIZE_MAX).n_splits);
+    if (D == kD) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, SIZE_MAX).n_splits);
   }
-  return attn_partial_bytes(Hq, Nq, D, splits);
+  return attn_partial_bytes(static_cast<int64_t>(Hq) * Nq, D, splits);
 }
 
 extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq,
@@ -1112,7 +1115,7 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
                PC_ERR_SHAPE, "pc_frame_attn: bf16 tensors and head strides must be 16-byte aligned");
     // Key shares need the caller's workspace for the partial results; without it (or with one
     // that is misaligned or too small for two) the keys are not split, which is always valid.
-    const AttnPlan plan = plan_bf16(Hkv, rep * Nq, Nk, splits_that_fit(kMaxKeySplits, Hq, Nq, D, ws, ws_bytes));
+    const AttnPlan plan = plan_bf16(Hkv, rep * Nq, Nk, usable_bytes(ws, ws_bytes));
     const float c = scale * 1.4426950408889634f;
     const bool unit_c = c == 1.0f;
     const auto kernel = plan.small ? attn_bf16_small_kernel : unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
@@ -1121,24 +1124,22 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.small ? 2 : unit_c], "pc_frame_attn"))
       return rc;
     const int n_tiles_q = ceil_div(rep * Nq, plan.small ? kSmallRows : kBM);
+    const int64_t rows_cut = static_cast<int64_t>(Hq) * Nq - plan.row_whole;
     float* part_o = nullptr;
     float2* part_ml = nullptr;
     if (plan.n_splits > 1) {
       part_o = static_cast<float*>(ws);
-      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(Hq, Nq, D, plan.n_splits));
+      part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(rows_cut, D, plan.n_splits));
     }
     const int n_tiles = n_tiles_q * Hkv;
-    // the first row that is cut, numbered over all heads
-    const int64_t row_whole = static_cast<int64_t>(plan.n_whole / n_tiles_q) * rep * Nq + plan.n_whole % n_tiles_q * kBM;
     kernel<<<dim3(plan.n_whole + (n_tiles - plan.n_whole) * plan.n_splits), kPPThreads, smem, s>>>(
         static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
         static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), lse, rep, Nq, Nk, q_stride_h,
-        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml, plan.n_whole, row_whole);
+        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml, plan.n_whole, plan.row_whole);
     if (plan.n_splits > 1) {
       PC_CHECK_LAUNCH("pc_frame_attn");
-      const int64_t rows = static_cast<int64_t>(Hq) * Nq - row_whole;
-      attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((rows + 7) / 8), 256, 0, s>>>(
-          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits, row_whole);
+      attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((rows_cut + 7) / 8), 256, 0, s>>>(
+          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits, plan.row_whole);
     }
   } else {
     PC_REQUIRE(D == 64 || D == 128, PC_ERR_UNSUPPORTED, "pc_frame_attn: fp32 tier needs D=64 or 128, got %d", D);

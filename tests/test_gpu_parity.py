@@ -332,6 +332,22 @@ def test_frame_attn_takes_as_many_key_shares_as_the_workspace_holds(shares, dtyp
         assert (buf[off + n:] == 255).all()     # nothing behind the workspace was written
 
 
+def test_frame_attn_workspace_holds_the_rows_that_are_cut():
+    # 8 x 34 row tiles: the 256 of the first round walk all keys, the last 4,095 rows are cut; a workspace
+    # for 16 shares of those rows (half of what two shares of every row would take) changes nothing
+    hq, hkv, nq, nk, d = 24, 8, 2901, 2100, 128
+    Q, K, V = (dev(x, "bf16") for x in _attn_case("bf16", hq, hkv, nq, nk, d, 22))
+    n_cut = hq * nq - (7 * 3 * nq + 18 * 256)
+    n = 16 * n_cut * (d * 4 + 8) + 512
+    buf = torch.full((n + 4096,), 255, dtype=torch.uint8, device=DEV)
+    ample = torch.empty(4 * hq * nq * (d * 4 + 8) * 4, dtype=torch.uint8, device=DEV)
+    none = torch.empty(16, dtype=torch.uint8, device=DEV)
+    O, Oa, On = (pk.pc_frame_attn(Q, K, V, nk, d ** -0.5, ws=ws) for ws in (buf[:n], ample, none))
+    assert torch.equal(O, Oa) and (buf[n:] == 255).all()
+    flat, flat_n = O.reshape(-1, d), On.reshape(-1, d)
+    assert torch.equal(flat[:-n_cut], flat_n[:-n_cut]) and not torch.equal(flat[-n_cut:], flat_n[-n_cut:])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nk", [(1, 1), (64, 336), (70, 33), (130, 191)])
 def test_frame_attn_f32_shapes(d, nq, nk):
