@@ -334,14 +334,16 @@ int pc_mask_scores(float* score, int Hsel, int Nk, int64_t score_stride_h, const
  *   pc_rope3d) is the same computation on the bf16 kernel's shorter loop: the scores start
  *   from minus the running reference inside the matrix product and the probability is a bare
  *   exp2.
- *   ws  dev or NULL: optional.  With a workspace of pc_frame_attn_workspace_bytes (0 where it
- *   would not help) the keys may be cut into shares when the row tiles alone fill the 256
- *   compute units badly; the shares' partial results are merged from the workspace.  A smaller one
- *   means fewer shares; without it, or if it is not 16-byte aligned, the keys are not cut: always
- *   valid, the result differs by rounding only.
+ *   ws  dev or NULL: optional.  With a workspace the keys may be cut into shares when the row
+ *   tiles alone fill the 256 compute units badly; the shares' partial results are merged from the
+ *   workspace.  pc_frame_attn_workspace_bytes_for says what the call would use (0 where shares do
+ *   not help), pc_frame_attn_workspace_bytes the most that either dtype and any number of KV heads
+ *   would.  A smaller one means fewer shares; without it, or if it is not 16-byte aligned, the
+ *   keys are not cut: always valid, the result differs by rounding only.
  * Nk >= 1, Nq >= 1.  Errors: PC_ERR_NULL, PC_ERR_DTYPE, PC_ERR_SHAPE, PC_ERR_UNSUPPORTED,
  * PC_ERR_HIP.
  */
+size_t pc_frame_attn_workspace_bytes_for(int dtype, int Hq, int Hkv, int Nq, int Nk, int D);
 size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D);
 int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq, int Hkv,
                   int Nq, int Nk, int D, int64_t q_stride_h, int64_t kv_stride_h,

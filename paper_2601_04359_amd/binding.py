@@ -17,6 +17,7 @@ __all__ = [
     "PackCacheError", "lib", "lib_path", "pc_version", "pc_strerror", "pc_budget", "pc_rope3d", "pc_rebase",
     "pc_score", "pc_score_workspace_bytes", "pc_compact_plan", "pc_compact", "pc_compact_batch", "pc_compact_batch_workspace_bytes", "PC_COMPACT_SELECT", "PC_COMPACT_GATHER", "PC_SCALE_FOLDED", "folded_q_scale", "pc_masked_budgets", "pc_mask_scores", "pc_compact_status",
     "pc_compact_workspace_bytes", "pc_compact_prepared", "pc_compact_static", "pc_compact_static_capacity", "pc_frame_attn", "pc_frame_attn_workspace_bytes",
+    "pc_frame_attn_workspace_bytes_for",
     "segment_budgets",
 ]
 
@@ -95,6 +96,8 @@ def lib() -> C.CDLL:
         L.pc_compact_static.argtypes = L.pc_compact.argtypes[:-3] + [vp]
         L.pc_frame_attn_workspace_bytes.restype = sz
         L.pc_frame_attn_workspace_bytes.argtypes = [C.c_int] * 4
+        L.pc_frame_attn_workspace_bytes_for.restype = sz
+        L.pc_frame_attn_workspace_bytes_for.argtypes = [C.c_int] * 6
         L.pc_frame_attn.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i64,
                                     i64, i64, C.c_float, vp, vp, vp, sz, vp]
         _LIB = L
@@ -413,7 +416,13 @@ def pc_compact_prepared(K, V, pos, score, segments, budgets, ws, share_heads: bo
 
 
 def pc_frame_attn_workspace_bytes(Hq: int, Nq: int, Nk: int, D: int) -> int:
+    """Enough for either dtype and any number of KV heads."""
     return lib().pc_frame_attn_workspace_bytes(Hq, Nq, Nk, D)
+
+
+def pc_frame_attn_workspace_bytes_for(dtype: int, Hq: int, Hkv: int, Nq: int, Nk: int, D: int) -> int:
+    """What a call of this dtype (PC_F32 / PC_BF16) and these sizes uses."""
+    return lib().pc_frame_attn_workspace_bytes_for(dtype, Hq, Hkv, Nq, Nk, D)
 
 
 def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):
@@ -426,7 +435,7 @@ def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):
     if O is None:
         O = torch.empty_like(Q)
     if ws is None:
-        nws = pc_frame_attn_workspace_bytes(Hq, Nq, Nk, D)
+        nws = pc_frame_attn_workspace_bytes_for(_dtype_code(Q), Hq, Hkv, Nq, Nk, D)
         if nws:
             ws = _workspace(nws, Q)
     if K.stride(0) != V.stride(0):

@@ -15,7 +15,9 @@
 //   * With scale = ln 2 (the caller multiplied Q by scale * log2(e), e.g. while rotating it)
 //     the affine step c*s - m is taken out of the loop: see kUnitC below.
 // fp32 tier (D = 64 or 128): fp32 MFMA, 16 or 32 query rows per work-group (see attn_f32_kernel).
+#include <limits.h>
 #include <math.h>
+#include <stdint.h>
 
 #include <algorithm>
 #include <type_traits>
@@ -1018,13 +1020,16 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
 // How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 13 shapes (2 to 24 heads, 40
 // to 1,000 rows, 100 to 8,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it
 // picks is the best of them on 12 and 4 % off on the last.  A step's waves contend for the matrix
-// pipes and the loads, so a part-filled step costs its part.
+// pipes and the loads, so a part-filled step costs its part.  Shares that save less than those 4 % are
+// not worth the workspace (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
 struct F32Plan {
   int kr, n_splits;
 };
 F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
   F32Plan best = {1, 1};
   double best_cost = 1e30;
+  F32Plan uncut = best;
+  double uncut_cost = best_cost;
   const double f = D / 128.0;
   for (int kr = 1; kr <= 2; ++kr) {
     const int blocks = ceil_div(rows, 16 * kr) * Hkv, units = ceil_div(Nk, 32 / kr);
@@ -1039,9 +1044,13 @@ F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
         best_cost = cost;
         best = {kr, s};
       }
+      if (s == 1 && cost < uncut_cost) {
+        uncut_cost = cost;
+        uncut = {kr, s};
+      }
     }
   }
-  return best;
+  return best_cost > 0.96 * uncut_cost ? uncut : best;
 }
 
 template <int D>
@@ -1081,15 +1090,31 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
 
 using namespace pc;
 
-extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
-  if ((D != 64 && D != 128) || Hq <= 0 || Nq <= 0 || Nk <= 0) return 0;
-  int splits = 1;   // the call does not say which tier it will be, nor how many KV heads there are
-  for (int rep = 1; rep <= Hq; ++rep) {
-    if (Hq % rep != 0) continue;
-    splits = std::max(splits, plan_f32(Hq / rep, rep * Nq, Nk, D, SIZE_MAX).n_splits);
-    if (D == kD) splits = std::max(splits, plan_bf16(Hq / rep, rep * Nq, Nk, SIZE_MAX).n_splits);
+extern "C" size_t pc_frame_attn_workspace_bytes_for(int dtype, int Hq, int Hkv, int Nq, int Nk, int D) {
+  if (Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0 || Nq <= 0 || Nk <= 0 || static_cast<int64_t>(Hq) * Nq > INT_MAX) return 0;
+  const int rows = Hq / Hkv * Nq;
+  const int64_t all_rows = static_cast<int64_t>(Hq) * Nq;
+  if (dtype == PC_BF16 && D == kD) {
+    const AttnPlan plan = plan_bf16(Hkv, rows, Nk, SIZE_MAX);
+    return attn_partial_bytes(all_rows - plan.row_whole, D, plan.n_splits);
   }
-  return attn_partial_bytes(static_cast<int64_t>(Hq) * Nq, D, splits);
+  if (dtype == PC_F32 && (D == 64 || D == 128))
+    return attn_partial_bytes(all_rows, D, plan_f32(Hkv, rows, Nk, D, SIZE_MAX).n_splits);
+  return 0;
+}
+
+extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
+  size_t most = 0;   // over both tiers and every number of KV heads
+  auto consider = [&](int Hkv) {
+    most = std::max({most, pc_frame_attn_workspace_bytes_for(PC_F32, Hq, Hkv, Nq, Nk, D),
+                     pc_frame_attn_workspace_bytes_for(PC_BF16, Hq, Hkv, Nq, Nk, D)});
+  };
+  for (int64_t i = 1; i * i <= Hq; ++i)
+    if (Hq % i == 0) {
+      consider(static_cast<int>(i));
+      consider(static_cast<int>(Hq / i));
+    }
+  return most;
 }
 
 extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq,

@@ -348,6 +348,19 @@ def test_frame_attn_workspace_holds_the_rows_that_are_cut():
     assert torch.equal(flat[:-n_cut], flat_n[:-n_cut]) and not torch.equal(flat[-n_cut:], flat_n[-n_cut:])
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,nq,nk,d", [("bf16", 8, 2, 252, 1804, 128), ("bf16", 16, 4, 1008, 7455, 128),
+                                                  ("bf16", 24, 8, 4032, 2100, 128), ("f32", 8, 2, 252, 1804, 128),
+                                                  ("f32", 2, 1, 64, 336, 64)])
+def test_frame_attn_takes_the_same_cut_in_the_workspace_it_asks_for(dtype, hq, hkv, nq, nk, d):
+    Q, K, V = (dev(x, dtype) for x in _attn_case(dtype, hq, hkv, nq, nk, d, 23))
+    n = pk.pc_frame_attn_workspace_bytes_for(pk.PC_BF16 if dtype == "bf16" else pk.PC_F32, hq, hkv, nq, nk, d)
+    assert n > 0
+    buf = torch.full((n + 4096,), 255, dtype=torch.uint8, device=DEV)
+    ample = torch.empty(16 * hq * nq * (d * 4 + 8) + 512, dtype=torch.uint8, device=DEV)
+    a, b, c = (pk.pc_frame_attn(Q, K, V, nk, d ** -0.5, ws=ws) for ws in (buf[:n], ample, None))
+    assert torch.equal(a, b) and torch.equal(a, c) and (buf[n:] == 255).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nk", [(1, 1), (64, 336), (70, 33), (130, 191)])
 def test_frame_attn_f32_shapes(d, nq, nk):

@@ -286,3 +286,39 @@ def test_stream_query_falls_back_to_the_public_one(monkeypatch, missing):
     assert binding._stream() == 12
     monkeypatch.delattr(torch._C, missing)
     assert binding._stream() == 4711
+
+
+def test_attention_asks_for_no_workspace_it_would_not_use(monkeypatch):
+    import torch
+    # full caches of frames 24 and 48, 16/4 heads: 252 row tiles fill the chip, nothing is cut in either dtype
+    for nk in (97024, 193792):
+        assert pk.pc_frame_attn_workspace_bytes(16, 4032, nk, 128) == 0
+    # 24/8 heads: 384 row tiles, the 128 behind the first round in two shares of 512 + 8 bytes a row
+    assert pk.pc_frame_attn_workspace_bytes_for(pk.PC_BF16, 24, 8, 4032, 8320, 128) <= 2 * 128 * 256 * 520 + 512
+    # one query covers every dtype and number of KV heads
+    rng = np.random.default_rng(1)
+    for _ in range(200):
+        hq, nq, nk = int(rng.choice([2, 6, 8, 16, 24])), int(rng.integers(1, 4100)), int(rng.integers(1, 60000))
+        d = int(rng.choice([64, 128]))
+        every = [pk.pc_frame_attn_workspace_bytes_for(t, hq, hkv, nq, nk, d) for t in (pk.PC_F32, pk.PC_BF16)
+                 for hkv in range(1, hq + 1)]
+        assert pk.pc_frame_attn_workspace_bytes(hq, nq, nk, d) == max(every)
+    for bad in ((pk.PC_BF16, 3, 2, 10, 10, 128), (pk.PC_BF16, 2, 0, 10, 10, 128), (pk.PC_BF16, 2, 1, 10, 10, 64),
+                (pk.PC_F32, 2, 1, 0, 10, 64), (pk.PC_F32, 2, 1, 10, 10, 96), (7, 2, 1, 10, 10, 128)):
+        assert pk.pc_frame_attn_workspace_bytes_for(*bad) == 0
+    # and a call without a workspace takes one of its own dtype's and head count's size
+    class Enough(Exception):
+        pass
+    def stop():
+        raise Enough
+    taken = []
+    monkeypatch.setattr(binding, "_workspace", lambda n, like: taken.append(n) or torch.empty(16, dtype=torch.uint8))
+    monkeypatch.setattr(binding, "_stream", stop)      # the last thing before the library call
+    for dtype, code in ((torch.float32, pk.PC_F32), (torch.bfloat16, pk.PC_BF16)):
+        for hq, hkv, nq, nk in ((16, 4, 4032, 193792), (8, 2, 252, 1179), (24, 8, 2901, 2100)):
+            Q, K, V = (torch.empty((h, n, 128), dtype=dtype, device="meta") for h, n in ((hq, nq), (hkv, nk), (hkv, nk)))
+            taken.clear()
+            with pytest.raises(Enough):
+                pk.pc_frame_attn(Q, K, V, nk, 0.1)
+            need = pk.pc_frame_attn_workspace_bytes_for(code, hq, hkv, nq, nk, 128)
+            assert taken == ([need] if need else [])
