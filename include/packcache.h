@@ -339,7 +339,8 @@ int pc_mask_scores(float* score, int Hsel, int Nk, int64_t score_stride_h, const
  *   workspace.  pc_frame_attn_workspace_bytes_for says what the call would use (0 where shares do
  *   not help), pc_frame_attn_workspace_bytes the most that either dtype and any number of KV heads
  *   would.  A smaller one means fewer shares; without it, or if it is not 16-byte aligned, the
- *   keys are not cut: always valid, the result differs by rounding only.
+ *   keys are not cut: always valid, the result differs by rounding only. Calls that may overlap on
+ *   the GPU must not share a workspace: one call's merge would read another's partial results.
  * Nk >= 1, Nq >= 1.  Errors: PC_ERR_NULL, PC_ERR_DTYPE, PC_ERR_SHAPE, PC_ERR_UNSUPPORTED,
  * PC_ERR_HIP.
  */

@@ -426,7 +426,8 @@ def pc_frame_attn_workspace_bytes_for(dtype: int, Hq: int, Hkv: int, Nq: int, Nk
 
 
 def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):
-    """Q [Hq][Nq][D], K/V [Hkv][>=Nk][D] -> O [Hq][Nq][D] (same dtype)."""
+    """Q [Hq][Nq][D], K/V [Hkv][>=Nk][D] -> O [Hq][Nq][D] (same dtype).  ws: workspace for key shares,
+    not to be shared by calls that may overlap; None: one of the call's own, from torch's allocator."""
     import torch
     Hq, Nq, D = Q.shape
     Hkv = K.shape[0]

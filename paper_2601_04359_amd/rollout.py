@@ -36,15 +36,6 @@ MODES = {"pow": pk.PC_BUDGET_POW, "norm": pk.PC_BUDGET_NORM, "half": pk.PC_BUDGE
          "slide": pk.PC_BUDGET_SLIDE, "dense": None}
 
 
-def _attn_workspace(Hq: int, n_frame: int, D: int, device):
-    """Room for the partial results of the key shares of an attention pass: four shares, and up to
-    sixteen where the rows are few (how many a call takes depends on its key count; a workspace that
-    is too small for them only means fewer)."""
-    import torch
-    rows = Hq * n_frame
-    return torch.empty(max(4 * rows, min(16 * rows, 1 << 17)) * (D * 4 + 8) + 1024, dtype=torch.uint8, device=device)
-
-
 class RollingLayer:
     """The packed K/V cache of one layer in HBM and its host-side segment table."""
 
@@ -79,7 +70,6 @@ class RollingLayer:
         self.slide_t_scale, self.shift = slide_t_scale, 0
         n_rows = min(n_score, n_frame)
         self.q_rows = ((torch.arange(n_rows, dtype=torch.int64) * n_frame) // n_rows).to(torch.int32).to(device)
-        self._ws_attn = _attn_workspace(Hq, n_frame, D, device)
         if mode != "dense":   # the full-cache baseline neither scores nor compacts
             self.score = torch.empty((hsel, capacity), dtype=torch.float32, device=device)
             self._ws_score = torch.empty(pk.pc_score_workspace_bytes(Hq, Hkv, n_rows, capacity, share_heads),
@@ -188,8 +178,10 @@ class RollingLayer:
                                                budgets, share_heads=self.share_heads, ws=self._ws_compact)
 
     def attend(self, Q, O=None, lse=None):
-        """The (rotated) queries Q over the cache as it stands -> O (and the log-sum-exp)."""
-        return pk.pc_frame_attn(Q, self.K, self.V, self.nk, self.call_scale, O=O, lse=lse, ws=self._ws_attn)
+        """The (rotated) queries Q over the cache as it stands -> O (and the log-sum-exp).  It only reads
+        the cache, and each call's key shares go to a workspace of its own: passes on several streams
+        or from several threads may overlap."""
+        return pk.pc_frame_attn(Q, self.K, self.V, self.nk, self.call_scale, O=O, lse=lse)
 
     def step(self, Q, O=None, q_pos=None, lse=None):
         """Queries Q [Hq][n_frame][D] of the frame being generated -> O.  q_pos (int32
@@ -241,7 +233,6 @@ class RollingStack:
         self.nk = 0
         n_rows = min(n_score, n_frame)
         self.q_rows = ((torch.arange(n_rows, dtype=torch.int64) * n_frame) // n_rows).to(torch.int32).to(device)
-        self._ws_attn = _attn_workspace(Hq, n_frame, D, device)
         self._ws_score = torch.empty(pk.pc_score_workspace_bytes(Hq, Hkv, n_rows, capacity, share_heads),
                                      dtype=torch.uint8, device=device)
         self._ws_compact = torch.empty(pk.pc_compact_batch_workspace_bytes(n_layers, Hkv, capacity, share_heads),
@@ -277,9 +268,9 @@ class RollingStack:
         return (prunable[0][0], prunable[-1][0] + prunable[-1][1]) if prunable else None
 
     def attend(self, layer: int, Q, O=None, lse=None):
-        """Layer `layer`'s (rotated) queries over its cache as it stands -> O (and the log-sum-exp)."""
-        return pk.pc_frame_attn(Q, self.K[layer], self.V[layer], self.nk, self.call_scale, O=O, lse=lse,
-                                ws=self._ws_attn)
+        """Layer `layer`'s (rotated) queries over its cache as it stands -> O (and the log-sum-exp).  As
+        RollingLayer.attend: calls may overlap."""
+        return pk.pc_frame_attn(Q, self.K[layer], self.V[layer], self.nk, self.call_scale, O=O, lse=lse)
 
     def score_layer(self, layer: int, Q, lse=None) -> None:
         """Importance of layer `layer`'s cached keys under Q (lse: the log-sum-exp attend() gave for

@@ -450,3 +450,54 @@ def test_rolling_stack_repacks_all_layers_at_the_step_boundary_like_the_oracle(m
             assert np.array_equal(host(stack.pos[l, :, :nk]), w["pos"]), f"layer {l} step {i + 1}: kept set differs"
             assert np.array_equal(host(stack.K[l, :, :nk]).astype(np.float64), w["K"])
             assert np.array_equal(host(stack.V[l, :, :nk]).astype(np.float64), w["V"])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_attention_passes_over_one_cache_may_overlap(dtype):
+    # 1,804 keys under 8/2 heads x 252 rows are cut into key shares in both dtypes; passes with queries of
+    # their own on two streams, with nothing between them that orders them
+    layer = RollingLayer(8, 2, 128, capacity=1804, n_frame=252, scale=128 ** -0.5, mode="pow", b_min=32, n_score=100,
+                         dtype=dtype, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(8)
+    for t in (layer.K, layer.V):
+        t.normal_(generator=gen)
+    layer.segments, layer.nk = [(0, 1804, pk.PC_SEG_COND, 0)], 1804
+    code = pk.PC_BF16 if dtype == torch.bfloat16 else pk.PC_F32
+    assert pk.pc_frame_attn_workspace_bytes_for(code, 8, 2, 252, 1804, 128) > 0
+    Q = torch.empty((24, 8, 252, 128), dtype=dtype, device=DEV).normal_(generator=gen)
+    want = [layer.attend(q) for q in Q]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [torch.empty_like(q) for q in Q]
+    for i, q in enumerate(Q):
+        with torch.cuda.stream(streams[i % 2]):
+            layer.attend(q, O=got[i])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_attention_of_a_rolling_cache_replays_from_a_hip_graph():
+    # the workspace of a recorded call belongs to the graph; eager passes run between the replays
+    layer = RollingLayer(8, 2, 128, capacity=1804, n_frame=252, scale=128 ** -0.5, mode="pow", b_min=32, n_score=100,
+                         device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9)
+    for t in (layer.K, layer.V):
+        t.normal_(generator=gen)
+    layer.segments, layer.nk = [(0, 1804, pk.PC_SEG_COND, 0)], 1804
+    Q = torch.empty((4, 8, 252, 128), dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    want = [layer.attend(q) for q in Q]
+    q, O = Q[0].clone(), torch.empty_like(Q[0])
+    layer.attend(q, O=O)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.attend(q, O=O)
+    for i in (1, 2, 3, 0):
+        q.copy_(Q[i])
+        O.zero_()
+        graph.replay()
+        assert torch.equal(layer.attend(Q[3 - i]), want[3 - i])
+        torch.cuda.synchronize()
+        assert torch.equal(O, want[i]), i

@@ -322,3 +322,19 @@ def test_attention_asks_for_no_workspace_it_would_not_use(monkeypatch):
                 pk.pc_frame_attn(Q, K, V, nk, 0.1)
             need = pk.pc_frame_attn_workspace_bytes_for(code, hq, hkv, nq, nk, 128)
             assert taken == ([need] if need else [])
+
+
+def test_rolling_caches_give_every_attention_call_its_own_workspace(monkeypatch):
+    import torch
+    from paper_2601_04359_amd import rollout
+    taken = []
+    monkeypatch.setattr(rollout.pk, "pc_frame_attn", lambda *a, ws=None, **kw: taken.append(ws))
+    kw = dict(capacity=600, n_frame=252, scale=0.1, device="cpu")
+    layer, stack = rollout.RollingLayer(8, 2, 128, **kw), rollout.RollingStack(2, 8, 2, 128, **kw)
+    Q = torch.empty((8, 252, 128), dtype=torch.bfloat16)
+    for _ in range(2):
+        layer.attend(Q)
+        stack.attend(0, Q)
+        stack.attend(1, Q)
+    given = [w.data_ptr() for w in taken if w is not None]
+    assert len(taken) == 6 and len(set(given)) == len(given)
