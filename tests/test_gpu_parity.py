@@ -505,6 +505,25 @@ def test_score_f32_tile_edges(d, n_qs, nk):
     _score_check(w, Q, K, share=True, lse=lse)
 
 
+# 1 to 18 units of 16 scoring rows per KV head: 1 to 7 waves and all eight; rows of several heads in one
+# unit (n_qs below 16 and just above it); rows picked by index, the log-sum-exp a view with a larger stride
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rep,n_qs", [(1, 1), (3, 5), (1, 17), (4, 9), (2, 31), (3, 37), (8, 25), (4, 72)])
+def test_score_f32_few_scoring_rows(d, rep, n_qs):
+    hkv, nk, nq = 2, 333, 3 * n_qs
+    Q, K, _ = _attn_case("f32", rep * hkv, hkv, nq, nk, d, rep + n_qs)
+    picked = np.arange(n_qs)[::-1] * 3 + 1
+    scale = d ** -0.5
+    lse_all = orc.frame_attn(Q, K, K, scale)[1].astype(np.float32)
+    lse = torch.zeros((rep * hkv, nq + 7), dtype=torch.float32, device=DEV)
+    lse[:, :nq] = torch.from_numpy(lse_all).to(DEV)
+    rows = torch.from_numpy(picked.astype(np.int32)).to(DEV)
+    want = orc.score(np.ascontiguousarray(Q[:, picked]), K, scale)
+    for given in (None, lse[:, :nq]):
+        got = host(pk.pc_score(dev(Q, None), dev(K, None), nk, scale, lse=given, q_rows=rows)).astype(np.float64)
+        assert np.all(np.abs(got - want) <= 2e-7 + 2e-5 * want)      # as in _score_check
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("share", [False, True])
 def test_score_bf16_midsize(share, fold):
