@@ -5,6 +5,8 @@
 // work-group and the general fp64 sine and cosine.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace pc {
@@ -13,6 +15,7 @@ namespace {
 constexpr int kMaxPairs = 128;    // D <= 256
 constexpr int kTokPerBlock = 4;   // tokens per work-group
 constexpr int kThreads = 256;
+constexpr int kHeadsInFlight = 4;  // loads of several heads are issued before any is used
 
 struct RopeFreq {
   double inv_freq[kMaxPairs];  // base^(-2i/s) of every pair, section by section
@@ -102,10 +105,9 @@ __global__ __launch_bounds__(kThreads) void rope3d_kernel(T* __restrict__ x, int
   __syncthreads();
 
   constexpr int kElems = 16 / sizeof(T);  // elements per 16-byte chunk
-  constexpr int kHeadsInFlight = 4;       // loads of several heads are issued before any is used
   const int chunks_per_row = D / kElems;
   const int per_group = kTokPerBlock * chunks_per_row, total = per_group * ((H + kHeadsInFlight - 1) / kHeadsInFlight);
-  for (int e = threadIdx.x; e < total; e += kThreads) {
+  for (int e = blockIdx.y * kThreads + threadIdx.x; e < total; e += gridDim.y * kThreads) {
     const int h0 = e / per_group * kHeadsInFlight, t = e % per_group / chunks_per_row, c = e % chunks_per_row;
     const int tok = tok0 + t;
     if (tok >= n) continue;
@@ -211,7 +213,12 @@ extern "C" int pc_rope3d(void* x, int dtype, int H, int n, int D, int64_t stride
              PC_ERR_SHAPE, "pc_rope3d: x and its head stride must be 16-byte aligned");
 
   const RopeFreq& fr = rope_freq(secs, base);
-  const dim3 grid(ceil_div(n, kTokPerBlock));
+  // Few tokens of many heads (a stack's keys): the heads are dealt to grid.y, up to a work-group per compute
+  // unit, each forming the angles anew (D = 128, fp32, 3 tokens: 224 heads 29.3 us without, 3.8 with; 16 heads
+  // 4.5 and 3.6).
+  const int chunks = ceil_div(H, kHeadsInFlight) * kTokPerBlock * (D / (dtype == PC_BF16 ? 8 : 4));
+  const int blocks = ceil_div(n, kTokPerBlock);
+  const dim3 grid(blocks, std::min(ceil_div(chunks, kThreads), ceil_div(256, blocks)));
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == PC_BF16)
     rope3d_kernel<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<uint16_t*>(x), H, n, D, stride_h, pos, fr, out_scale);

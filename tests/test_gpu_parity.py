@@ -134,6 +134,24 @@ def test_rope3d_extreme_positions(n, H, sections, base):
     assert np.abs(host(xd) - orc.rope3d(x, pos, sections, base)).max() <= 4e-6
 
 
+# few tokens of many heads: the heads dealt over several work-groups per token block, the last one part-filled
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,n,sections", [(224, 3, (32, 48, 48)), (113, 64, (32, 48, 48)), (67, 1, (64, 96, 96)),
+                                          (33, 30, (32, 32, 32)), (41, 260, (16, 24, 24))])
+def test_rope3d_many_heads(dtype, H, n, sections):
+    rng = np.random.default_rng(H + n)
+    x = rng.standard_normal((H, n, sum(sections))).astype(np.float32)
+    x = synth.to_bf16(x) if dtype == "bf16" else x
+    pos = rng.integers(0, 700, (n, 3)).astype(np.int32)
+    buf = torch.full((H, n + 2, sum(sections)), 7.0, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device=DEV)
+    buf[:, :n] = dev(x, dtype)
+    pk.pc_rope3d(buf[:, :n], dev(pos, None), sections, 1e4)
+    want = orc.rope3d(x, pos, sections, 1e4)
+    tol = 2.0 ** -8 if dtype == "bf16" else 2e-6      # as above: one rounding of the result
+    assert np.all(np.abs(host(buf[:, :n]).astype(np.float64) - want) <= tol * np.abs(want) + 1e-6)
+    assert (buf[:, n:] == 7).all()
+
+
 def test_rope3d_negative_shift_undoes_rotation_and_head_stride():
     # a rebase by (-dt, 0, 0) (Eq. 9) is a rotation with negative position; also exercises
     # a head stride larger than n*D (capacity > rows)
