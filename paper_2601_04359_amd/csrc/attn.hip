@@ -1020,8 +1020,8 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
 // How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 13 shapes (2 to 24 heads, 40
 // to 1,000 rows, 100 to 8,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it
 // picks is the best of them on 12 and 4 % off on the last.  A step's waves contend for the matrix
-// pipes and the loads, so a part-filled step costs its part.  Shares that save less than those 4 % are
-// not worth the workspace (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
+// pipes and the loads, so a part-filled step costs its part.  Shares that need more than 16 MB of workspace
+// have to save more than those 4 % (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
 struct F32Plan {
   int kr, n_splits;
 };
@@ -1050,7 +1050,8 @@ F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
       }
     }
   }
-  return best_cost > 0.96 * uncut_cost ? uncut : best;
+  const bool large = attn_partial_bytes(static_cast<int64_t>(Hkv) * rows, D, best.n_splits) > (16u << 20);
+  return large && best_cost > 0.96 * uncut_cost ? uncut : best;
 }
 
 template <int D>
