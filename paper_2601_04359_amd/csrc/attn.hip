@@ -808,14 +808,13 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
 // (112 TFLOP/s); 8/2 heads, 60 rows, 300 keys 13 us against 10.
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 8;
-constexpr int kF32Threads = 64 * kF32Waves;
 template <int D, int kR>
 constexpr size_t f32_smem_bytes() {
   return sizeof(float) * kF32Waves * 16 * kR * (D + 2);
 }
 
-template <int D, int kR>
-__global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
+template <int D, int kR, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
     int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split, int n_tiles_q, int n_splits,
@@ -824,8 +823,8 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
   constexpr int kS = D / 16, kB = D / 64, kF32Rows = 16 * kR, kT = 2 / kR, kF32Keys = 16 * kT;  // kT: key blocks
   extern __shared__ __align__(16) uint8_t smem_raw[];
   float* s_o = reinterpret_cast<float*>(smem_raw);        // [wave][row][D]
-  float* s_m = s_o + kF32Waves * kF32Rows * D;            // [wave][row]
-  float* s_l = s_m + kF32Waves * kF32Rows;
+  float* s_m = s_o + kWaves * kF32Rows * D;               // [wave][row]
+  float* s_l = s_m + kWaves * kF32Rows;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
   // logical order: key split slowest, then KV head, then row tile: the work-groups of one XCD (one L2)
@@ -880,7 +879,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     }
   };
   load_k(k_begin + wave * kF32Keys);
-  for (int k0 = k_begin + wave * kF32Keys; k0 < k_end; k0 += kF32Waves * kF32Keys) {
+  for (int k0 = k_begin + wave * kF32Keys; k0 < k_end; k0 += kWaves * kF32Keys) {
     const int last = Nk - 1 - k0;
     const float* v_base = Vh + static_cast<int64_t>(k0) * D;
 #pragma unroll
@@ -907,7 +906,7 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
           for (int u = 0; u < kT; ++u)
             sc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][s][e], q[t][s][e], sc[t][u], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    load_k(k0 + kF32Waves * kF32Keys);  // past the end: clamped rows, never used
+    load_k(k0 + kWaves * kF32Keys);  // past the end: clamped rows, never used
     __builtin_amdgcn_sched_barrier(0);
     float mx[kR];
     bool lags = false;   // a reference may lag by 2^8
@@ -972,6 +971,20 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
   for (int t = 0; t < kR; ++t) {
     l[t] += __shfl_xor(l[t], 16);
     l[t] = wave_half_sum(l[t]);
+    if constexpr (kWaves == 1) {   // nothing to merge
+      const int rho = row0 + t * 16 + r;
+      if (rho >= n_rows) continue;
+      const RowAt to = row_at(rho, kvh, rep, Nq);
+      float* out = O + to.head * o_stride_h + static_cast<int64_t>(to.row) * D + kg * 16;
+      const float inv = 1.f / l[t];
+#pragma unroll
+      for (int b = 0; b < kB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          store_f32x4(out + b * 64 + i * 4, f32x4{o[t][b][0][i], o[t][b][1][i], o[t][b][2][i], o[t][b][3][i]} * inv);
+      if (lse != nullptr && kg == 0) lse[static_cast<int64_t>(kvh) * n_rows + rho] = natural_lse(m[t], l[t]);
+      continue;
+    }
     const int row = wave * kF32Rows + t * 16 + r;
     float* mine = s_o + row * D + kg * 16;
 #pragma unroll
@@ -985,9 +998,10 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
       s_l[row] = l[t];
     }
   }
+  if constexpr (kWaves == 1) return;
   __syncthreads();
   // merge in wave order: a thread owns four dims of a row, of every kPass-th
-  constexpr int kPass = kF32Threads / (D / 4);   // rows per pass
+  constexpr int kPass = 64 * kWaves / (D / 4);   // rows per pass
   const int col = threadIdx.x % (D / 4) * 4;
 #pragma unroll
   for (int row = threadIdx.x / (D / 4); row < kF32Rows; row += kPass) {
@@ -995,11 +1009,11 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
     if (rho >= n_rows) return;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, s_m[w * kF32Rows + row]);
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w * kF32Rows + row]);
     float lt = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) {
+    for (int w = 0; w < kWaves; ++w) {
       const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);
       lt += wt * s_l[w * kF32Rows + row];
       acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + col);
@@ -1022,11 +1036,14 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
 // picks is the best of them on 12 and 4 % off on the last.  A step's waves contend for the matrix
 // pipes and the loads, so a part-filled step costs its part.  Shares that need more than 16 MB of workspace
 // have to save more than those 4 % (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
+// The keys of one step need one wave and no merge (16/4 heads, 4,032 rows, 32 keys, D = 64: 33.3 us with
+// eight waves, 15.1 with one; 3 keys, D = 128: 49.5 and 26.1).
 struct F32Plan {
-  int kr, n_splits;
+  int kr, n_splits, waves;
 };
 F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
-  F32Plan best = {1, 1};
+  if (Nk <= 32) return {1, 1, 1};
+  F32Plan best = {1, 1, kF32Waves};
   double best_cost = 1e30;
   F32Plan uncut = best;
   double uncut_cost = best_cost;
@@ -1042,11 +1059,11 @@ F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
                           ceil_div(blocks * s, 256) * (kr == 1 ? 7.0 : 5.15) * f * per / kF32Waves + merge;
       if (cost < best_cost) {
         best_cost = cost;
-        best = {kr, s};
+        best = {kr, s, kF32Waves};
       }
       if (s == 1 && cost < uncut_cost) {
         uncut_cost = cost;
-        uncut = {kr, s};
+        uncut = {kr, s, kF32Waves};
       }
     }
   }
@@ -1059,11 +1076,14 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
              int64_t kv_stride_h, int64_t o_stride_h, float scale, float* O, float* lse, void* ws, size_t ws_bytes,
              hipStream_t s) {
   const F32Plan plan = plan_f32(Hq / rep, rep * Nq, Nk, D, usable_bytes(ws, ws_bytes));
-  const auto kernel = plan.kr == 2 ? attn_f32_kernel<D, 2> : attn_f32_kernel<D, 1>;
-  const size_t smem = plan.kr == 2 ? f32_smem_bytes<D, 2>() : f32_smem_bytes<D, 1>();
+  const auto kernel = plan.waves == 1 ? attn_f32_kernel<D, 1, 1>
+                      : plan.kr == 2  ? attn_f32_kernel<D, 2, kF32Waves>
+                                      : attn_f32_kernel<D, 1, kF32Waves>;
+  const size_t smem = plan.waves == 1 ? 0 : plan.kr == 2 ? f32_smem_bytes<D, 2>() : f32_smem_bytes<D, 1>();
   static std::atomic<uint64_t> lds_ok[2];
-  if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.kr - 1], "pc_frame_attn"))
-    return rc;
+  if (smem != 0)
+    if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.kr - 1], "pc_frame_attn"))
+      return rc;
   const int n_tiles_q = ceil_div(rep * Nq, 16 * plan.kr), n_splits = plan.n_splits, unit = 32 / plan.kr;
   const int keys_per_split = ceil_div(ceil_div(Nk, unit), n_splits) * unit;
   const int64_t rows = static_cast<int64_t>(Hq) * Nq;
@@ -1073,7 +1093,7 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
     part_o = static_cast<float*>(ws);
     part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(rows, D, n_splits));
   }
-  kernel<<<n_tiles_q * (Hq / rep) * n_splits, kF32Threads, smem, s>>>(
+  kernel<<<n_tiles_q * (Hq / rep) * n_splits, 64 * plan.waves, smem, s>>>(
       Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, keys_per_split, n_tiles_q, n_splits,
       part_o, part_ml);
   PC_CHECK_LAUNCH("pc_frame_attn");

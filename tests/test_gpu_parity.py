@@ -400,6 +400,17 @@ def test_frame_attn_f32_tile_edges_and_key_shares(d, nq, nk):
     assert (a - b).abs().max().item() <= 2e-6   # two fp32 results of |O| < 4, each within a few 2^-24 |O| of exact
 
 
+# at most one step of keys: one wave, written without a merge; row tiles that span heads, strided output
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,hkv,nq,nk", [(1, 1, 1, 1), (3, 1, 17, 3), (6, 2, 37, 17), (8, 2, 252, 31), (2, 1, 16, 32)])
+def test_frame_attn_f32_few_keys(d, hq, hkv, nq, nk):
+    Q, K, V = _attn_case("f32", hq, hkv, nq, nk, d, nq + nk)
+    _attn_check("f32", Q, K, V, d ** -0.5)
+    buf = torch.full((hq, nq + 3, d), 7.0, dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(dev(Q, None), dev(K, None), dev(V, None), nk, d ** -0.5, O=buf[:, :nq])
+    assert np.abs(host(O) - orc.frame_attn(Q, K, V, d ** -0.5)[0]).max() <= 1e-5 and (buf[:, nq:] == 7).all()
+
+
 @pytest.mark.parametrize("nq,nk", [(70, 900), (301, 2501)])
 @pytest.mark.parametrize("step", [0.05, 0.6, 40.0])
 def test_frame_attn_f32_reference_is_refreshed(nq, nk, step):
@@ -452,7 +463,7 @@ def _masked_reference(Q, K, V, keep, scale, rows):
     ("bf16", 128, False, 8, 2, 252, 1804), ("bf16", 128, True, 8, 2, 252, 1804), ("bf16", 128, False, 2, 1, 184, 5000),
     ("bf16", 128, False, 16, 4, 4032, 2048), ("bf16", 128, True, 16, 4, 4032, 2048),
     ("bf16", 128, False, 16, 4, 1008, 7455), ("bf16", 128, True, 16, 4, 1008, 7455),
-    ("f32", 64, False, 2, 1, 64, 336), ("f32", 128, False, 2, 1, 33, 336), ("f32", 128, False, 8, 2, 252, 1804),
+    ("f32", 64, False, 2, 1, 64, 336), ("f32", 128, False, 2, 1, 33, 336), ("f32", 64, False, 2, 1, 20, 30), ("f32", 128, False, 8, 2, 252, 1804),
     ("f32", 64, False, 3, 1, 301, 2501)])
 def test_masked_keys_weigh_nothing(dtype, d, fold, hq, hkv, nq, nk, masked, value):
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -463,6 +474,7 @@ def test_masked_keys_weigh_nothing(dtype, d, fold, hq, hkv, nq, nk, masked, valu
         Q, scale = (Q.double() * q_fold(scale)).to(td), LN2
     keep = torch.ones(nk, dtype=torch.bool, device=DEV)
     keep[masked] = False
+    keep[-1] |= not keep.any()      # a table shorter than the mask keeps its last key
     K[:, ~keep, 0] = torch.finfo(td).min if value == "lowest" else value
     rows = torch.arange(0, nq, max(1, nq // 40), device=DEV)
     lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
