@@ -66,15 +66,39 @@ __device__ __forceinline__ void stage_tile(const uint16_t* __restrict__ base_h, 
   }
 }
 
+// Division by a number that the host knows, for 0 <= n < 2^31: n / d = n m >> sh with sh = 31 + ceil(log2 d)
+// and m = floor(2^sh / d) + 1 (m d exceeds 2^sh by at most 2^(sh - 31), which n times is below 2^sh).
+struct Divisor {
+  uint32_t m;
+  int sh, d;
+  explicit Divisor(int by) : sh(31), d(by) {
+    while (sh < 62 && (1ll << (sh - 31)) < by) ++sh;
+    m = static_cast<uint32_t>((1ull << sh) / by + 1);
+  }
+  __device__ __forceinline__ int of(int n) const {
+    return static_cast<int>(static_cast<uint64_t>(static_cast<uint32_t>(n)) * m >> sh);
+  }
+};
+
 // The query rows of one KV head are numbered through its `rep` query heads: row rho is row
 // rho % Nq of head kvh * rep + rho / Nq.  A tile of rows may span heads, so a frame that is no
 // multiple of the tile leaves at most one part-filled tile per KV head instead of one per head.
 struct RowAt {
   int head, row;
 };
-__device__ __forceinline__ RowAt row_at(int rho, int kvh, int rep, int Nq) {
-  const int in_group = rho / Nq;
-  return {kvh * rep + in_group, rho - in_group * Nq};
+__device__ __forceinline__ RowAt row_at(int rho, int kvh, int rep, const Divisor& by_nq) {
+  const int in_group = by_nq.of(rho);
+  return {kvh * rep + in_group, rho - in_group * by_nq.d};
+}
+
+// The key share of work-group L, shares of n_units work-groups one after another; L becomes the unit.  By
+// subtraction: calls that are not cut (L < n_units) pay nothing for it.  A division by a number that is not
+// known is 0.2 us at the front of every work-group, and there were four of them (16/4 heads x 4,032 rows x 64
+// keys 14.0 us with them, 13.4 without; 8/2 x 17 rows x 64 keys 6.3 and 5.6).
+__device__ __forceinline__ int take_share(int& L, int n_units) {
+  int share = 0;
+  for (; L >= n_units; L -= n_units) ++share;   // at most kMaxKeySplits - 1 times
+  return share;
 }
 
 // One phase of the software pipeline (see the kernel comment): 8 score products, then 8
@@ -210,9 +234,9 @@ __device__ __forceinline__ void pipeline_phase(
 template <bool kUnitC>
 __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
-    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
-    int64_t kv_stride_h, int64_t o_stride_h, float c, int n_tiles_q, int n_splits, float* __restrict__ part_o,
-    float2* __restrict__ part_ml, int n_whole, int64_t row_whole) {
+    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
+    int64_t kv_stride_h, int64_t o_stride_h, float c, Divisor by_tiles_q, int n_whole, int n_cut, int share_tiles,
+    float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t row_whole, int64_t rows_cut) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -222,18 +246,18 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  // Row tiles in the order (KV head, tile).  The first n_whole of them (whole rounds of the chip) walk
-  // all keys; the rest are cut into n_splits key shares, share slowest.
+  // Row tiles in the order (KV head, tile).  The first n_whole of them (whole rounds of the chip, or all)
+  // walk all keys; the other n_cut are cut into shares of share_tiles key tiles, share slowest.
   const bool whole = static_cast<int>(blockIdx.x) < n_whole;
-  const int n_cut = (static_cast<int>(gridDim.x) - n_whole) / n_splits;   // row tiles that are cut
-  const int L = whole ? xcd_contiguous_index(blockIdx.x, n_whole)
-                      : xcd_contiguous_index(blockIdx.x - n_whole, gridDim.x - n_whole);
-  const int split = whole ? 0 : L / n_cut, unit = whole ? L : n_whole + L % n_cut;
-  const int kvh = unit / n_tiles_q, tile = unit % n_tiles_q;
-  const int n_rows = rep * Nq;    // query rows of the KV head
+  int unit = whole ? xcd_contiguous_index(blockIdx.x, n_whole)
+                   : xcd_contiguous_index(blockIdx.x - n_whole, gridDim.x - n_whole);
+  const int split = whole ? 0 : take_share(unit, n_cut);
+  if (!whole) unit += n_whole;
+  const int kvh = by_tiles_q.of(unit), tile = unit - kvh * by_tiles_q.d;
+  const int n_rows = rep * by_nq.d;    // query rows of the KV head
   const int rho = tile * kBM + wave * 32 + l32;   // the row this lane owns
   const bool active = rho - l32 < n_rows;  // wave-uniform
-  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, Nq);
+  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, by_nq);
 
   const uint16_t* Kh = K + kvh * kv_stride_h;
   const uint16_t* Vh = V + kvh * kv_stride_h;
@@ -275,7 +299,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 
   // this work-group's share of the key tiles: n of n_all (the host leaves no share empty)
   const int n_all = (Nk + kBN - 1) / kBN;
-  const int per = whole ? n_all : (n_all + n_splits - 1) / n_splits;
+  const int per = whole ? n_all : share_tiles;
   const int n = min(per, n_all - split * per);
   const int key0 = split * per * kBN;
   const int n_valid = Nk - key0;   // less than n tiles only where the ragged last tile is in this share
@@ -399,10 +423,9 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   }
   const float l_tot = wave_half_sum(l_run);
   const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
-  if (part_o != nullptr && !whole) {  // one of several key shares: un-normalised O, reference and sum for the merge
+  if (!whole) {  // one of several key shares: un-normalised O, reference and sum for the merge
     if (rho < n_rows) {
-      const int64_t n_all_rows = static_cast<int64_t>((n_whole + n_cut) / n_tiles_q) * n_rows;
-      const int64_t at_s = split * (n_all_rows - row_whole) + at - row_whole;
+      const int64_t at_s = split * rows_cut + at - row_whole;
       float* prow = part_o + at_s * kD;
 #pragma unroll
       for (int db = 0; db < 4; ++db)
@@ -454,28 +477,26 @@ static_assert(2 * kSmallTileBytes <= kSmallOBytes, "a wave stages K and V in the
 
 __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
-    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
-    int64_t kv_stride_h, int64_t o_stride_h, float c, int n_tiles_q, int n_splits, float* __restrict__ part_o,
-    float2* __restrict__ part_ml, int /*n_whole*/, int64_t /*row_whole*/) {
+    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
+    int64_t kv_stride_h, int64_t o_stride_h, float c, Divisor by_tiles_q, int n_tiles, int share_steps,
+    float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   const lds_u8* lds = (lds_u8*)smem_raw + wave * kSmallOBytes;
   const uint32_t lds_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
-  const int split = L / tiles_all;
-  const int kvh = (L % tiles_all) / n_tiles_q, tile = L % n_tiles_q;
-  const int n_rows = rep * Nq;
+  int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);   // n_tiles row tiles per share
+  const int split = take_share(unit, n_tiles);
+  const int kvh = by_tiles_q.of(unit), tile = unit - kvh * by_tiles_q.d;
+  const int n_rows = rep * by_nq.d;
   const int rho = tile * kSmallRows + l32;
-  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, Nq);
+  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, by_nq);
   const uint16_t* Kh = K + kvh * kv_stride_h;
   const uint16_t* Vh = V + kvh * kv_stride_h;
 
   // this share's keys, whole steps but for the very last
-  const int steps_all = (Nk + kSmallKeys - 1) / kSmallKeys, per = (steps_all + n_splits - 1) / n_splits;
-  const int k_begin = split * per * kSmallKeys, k_end = min(k_begin + per * kSmallKeys, Nk);
+  const int k_begin = split * share_steps * kSmallKeys, k_end = min(k_begin + share_steps * kSmallKeys, Nk);
 
   // a step's 32 rows of K and of V, two 8-KB pieces of the wave's LDS
   auto stage = [&](int k0) {
@@ -626,7 +647,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;
   // piece i of a lane is dims 32 (i / 4) + 8 (i % 4) + 4 g .. + 3 of its row
   if (part_o != nullptr) {
-    const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+    const int64_t at_s = split * rows_all + at;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int i = wave + 8 * t;
@@ -816,9 +837,9 @@ constexpr size_t f32_smem_bytes() {
 template <int D, int kR, int kWaves>
 __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    float* __restrict__ O, float* __restrict__ lse, int rep, int Nq, int Nk, int64_t q_stride_h,
-    int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split, int n_tiles_q, int n_splits,
-    float* __restrict__ part_o, float2* __restrict__ part_ml) {
+    float* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
+    int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split, Divisor by_tiles_q, int n_tiles,
+    float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
   static_assert(kR == 1 || kR == 2, "a step is two 16 x 16 products");
   constexpr int kS = D / 16, kB = D / 64, kF32Rows = 16 * kR, kT = 2 / kR, kF32Keys = 16 * kT;  // kT: key blocks
   extern __shared__ __align__(16) uint8_t smem_raw[];
@@ -829,10 +850,9 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
   const int r = lane & 15, kg = lane >> 4;
   // logical order: key split slowest, then KV head, then row tile: the work-groups of one XCD (one L2)
   // read the same keys
-  const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int tiles_all = static_cast<int>(gridDim.x) / n_splits;
-  const int split = L / tiles_all, kvh = L % tiles_all / n_tiles_q;
-  const int row0 = L % n_tiles_q * kF32Rows, n_rows = rep * Nq;
+  int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);
+  const int split = take_share(unit, n_tiles), kvh = by_tiles_q.of(unit);
+  const int row0 = (unit - kvh * by_tiles_q.d) * kF32Rows, n_rows = rep * by_nq.d;
   const float* Kh = K + kvh * kv_stride_h;
   const float* Vh = V + kvh * kv_stride_h;
   const int k_begin = split * keys_per_split, k_end = min(k_begin + keys_per_split, Nk);
@@ -840,7 +860,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
   f32x4 q[kR][kS];
 #pragma unroll
   for (int t = 0; t < kR; ++t) {
-    const RowAt at = row_at(min(row0 + t * 16 + r, n_rows - 1), kvh, rep, Nq);
+    const RowAt at = row_at(min(row0 + t * 16 + r, n_rows - 1), kvh, rep, by_nq);
     const float* qrow = Q + at.head * q_stride_h + static_cast<int64_t>(at.row) * D + kg * 4;
 #pragma unroll
     for (int s = 0; s < kS; ++s) q[t][s] = load_f32x4(qrow + s * 16);
@@ -974,7 +994,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     if constexpr (kWaves == 1) {   // nothing to merge
       const int rho = row0 + t * 16 + r;
       if (rho >= n_rows) continue;
-      const RowAt to = row_at(rho, kvh, rep, Nq);
+      const RowAt to = row_at(rho, kvh, rep, by_nq);
       float* out = O + to.head * o_stride_h + static_cast<int64_t>(to.row) * D + kg * 16;
       const float inv = 1.f / l[t];
 #pragma unroll
@@ -1020,11 +1040,11 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     }
     const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
     if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
-      const int64_t at_s = static_cast<int64_t>(split) * (tiles_all / n_tiles_q) * n_rows + at;
+      const int64_t at_s = split * rows_all + at;
       *reinterpret_cast<f32x4*>(part_o + at_s * D + col) = acc;
       if (col == 0) part_ml[at_s] = make_float2(M, lt);
     } else {
-      const RowAt to = row_at(rho, kvh, rep, Nq);
+      const RowAt to = row_at(rho, kvh, rep, by_nq);
       store_f32x4(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * D + col, acc * (1.f / lt));
       if (lse != nullptr && col == 0) lse[at] = natural_lse(M, lt);
     }
@@ -1093,9 +1113,10 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
     part_o = static_cast<float*>(ws);
     part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(rows, D, n_splits));
   }
-  kernel<<<n_tiles_q * (Hq / rep) * n_splits, 64 * plan.waves, smem, s>>>(
-      Q, K, V, O, lse, rep, Nq, Nk, q_stride_h, kv_stride_h, o_stride_h, scale, keys_per_split, n_tiles_q, n_splits,
-      part_o, part_ml);
+  const int n_tiles = n_tiles_q * (Hq / rep);
+  kernel<<<n_tiles * n_splits, 64 * plan.waves, smem, s>>>(Q, K, V, O, lse, rep, Divisor(Nq), Nk, q_stride_h,
+                                                           kv_stride_h, o_stride_h, scale, keys_per_split,
+                                                           Divisor(n_tiles_q), n_tiles, part_o, part_ml, rows);
   PC_CHECK_LAUNCH("pc_frame_attn");
   if (n_splits > 1) {
     constexpr int kRowsPerBlock = 256 / (D / 4);
@@ -1163,12 +1184,6 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     // that is misaligned or too small for two) the keys are not split, which is always valid.
     const AttnPlan plan = plan_bf16(Hkv, rep * Nq, Nk, usable_bytes(ws, ws_bytes));
     const float c = scale * 1.4426950408889634f;
-    const bool unit_c = c == 1.0f;
-    const auto kernel = plan.small ? attn_bf16_small_kernel : unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
-    const size_t smem = plan.small ? kSmallSmem : kSmemBytes;
-    static std::atomic<uint64_t> lds_ok[3];
-    if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.small ? 2 : unit_c], "pc_frame_attn"))
-      return rc;
     const int n_tiles_q = ceil_div(rep * Nq, plan.small ? kSmallRows : kBM);
     const int64_t rows_cut = static_cast<int64_t>(Hq) * Nq - plan.row_whole;
     float* part_o = nullptr;
@@ -1178,14 +1193,34 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
       part_ml = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + attn_partial_o_bytes(rows_cut, D, plan.n_splits));
     }
     const int n_tiles = n_tiles_q * Hkv;
-    kernel<<<dim3(plan.n_whole + (n_tiles - plan.n_whole) * plan.n_splits), kPPThreads, smem, s>>>(
-        static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
-        static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), lse, rep, Nq, Nk, q_stride_h,
-        kv_stride_h, o_stride_h, c, n_tiles_q, plan.n_splits, part_o, part_ml, plan.n_whole, plan.row_whole);
+    const auto* q = static_cast<const uint16_t*>(Q);
+    const auto* k = static_cast<const uint16_t*>(K);
+    const auto* v = static_cast<const uint16_t*>(V);
+    auto* o = static_cast<uint16_t*>(O);
+    static std::atomic<uint64_t> lds_ok[3];
+    auto allow = [](auto kernel, size_t bytes, std::atomic<uint64_t>& done) {
+      return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes, done, "pc_frame_attn");
+    };
+    if (plan.small) {
+      if (int rc = allow(attn_bf16_small_kernel, kSmallSmem, lds_ok[2])) return rc;
+      const int share_steps = ceil_div(ceil_div(Nk, kSmallKeys), plan.n_splits);
+      attn_bf16_small_kernel<<<n_tiles * plan.n_splits, kPPThreads, kSmallSmem, s>>>(
+          q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_tiles,
+          share_steps, part_o, part_ml, rows_cut);
+    } else {
+      const bool unit_c = c == 1.0f;
+      const auto kernel = unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
+      if (int rc = allow(kernel, kSmemBytes, lds_ok[unit_c])) return rc;
+      const int n_whole = plan.n_splits > 1 ? plan.n_whole : n_tiles, n_cut = n_tiles - n_whole;
+      const int share_tiles = ceil_div(ceil_div(Nk, kBN), plan.n_splits);
+      kernel<<<n_whole + n_cut * plan.n_splits, kPPThreads, kSmemBytes, s>>>(
+          q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_whole,
+          n_cut, share_tiles, part_o, part_ml, plan.row_whole, rows_cut);
+    }
     if (plan.n_splits > 1) {
       PC_CHECK_LAUNCH("pc_frame_attn");
       attn_merge_kernel<uint16_t, kD><<<static_cast<unsigned>((rows_cut + 7) / 8), 256, 0, s>>>(
-          part_o, part_ml, static_cast<uint16_t*>(O), lse, Hq, Nq, o_stride_h, plan.n_splits, plan.row_whole);
+          part_o, part_ml, o, lse, Hq, Nq, o_stride_h, plan.n_splits, plan.row_whole);
     }
   } else {
     PC_REQUIRE(D == 64 || D == 128, PC_ERR_UNSUPPORTED, "pc_frame_attn: fp32 tier needs D=64 or 128, got %d", D);
