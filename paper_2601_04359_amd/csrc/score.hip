@@ -843,8 +843,18 @@ __global__ void score_reduce(const float* __restrict__ part, float* __restrict__
   };
   if (share_heads) {
     float s = 0.f;
+    if (n_parts == 1) {   // the usual one: a load per head, eight heads together
+      for (int h0 = 0; h0 < Hkv; h0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = h0 + i < Hkv ? part[static_cast<int64_t>(h0 + i) * Nk + j] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += v[i];
+      }
+    } else {
 #pragma unroll 4
-    for (int h = 0; h < Hkv; ++h) s += head_sum(h);
+      for (int h = 0; h < Hkv; ++h) s += head_sum(h);
+    }
     out[j] = s;
   } else {
     const int h = blockIdx.y;
