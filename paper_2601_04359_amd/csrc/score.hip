@@ -843,7 +843,7 @@ __global__ void score_reduce(const float* __restrict__ part, float* __restrict__
   };
   if (share_heads) {
     float s = 0.f;
-    if (n_parts == 1) {   // the usual one: a load per head, eight heads together
+    if (n_parts == 1) {   // the usual call (16/16 heads x 64 rows x 64 keys 13.3 us by head_sum, 9.4 like this)
       for (int h0 = 0; h0 < Hkv; h0 += 8) {
         float v[8];
 #pragma unroll
@@ -1124,7 +1124,9 @@ WsLayout ws_layout(int Hq, int Hkv, int n_qs, int Nk, int /*share_heads*/) {
 // the shares of the streamed axis.  The estimates are microseconds, fitted to 22 shapes (100 to 512
 // scoring rows, 2 to 24 heads, 596 to 100,000 keys) in both forms with every number of shares: `start`
 // is what a work-group costs beside its steps, a step gets slower as the compute units fill up, a
-// further round costs a new start, and pass 2 merges the row pass's shares.  Row pass: 1.6 % slower than
+// further round costs a new start, and pass 2 merges the row pass's shares, itself or behind a launch of
+// 2-5 us that does (8/2 heads, 512 rows a head x 20,000 keys: 57.4 us with 32 shares of 512 rows, 60.1 with 4
+// of 64 rows, which a merge priced by the share alone had picked).  Row pass: 1.6 % slower than
 // the best cut on average (at most 1 us); column pass: 0.3 %.  Where the lines lie, both sides measured
 // (16/4 heads unless stated): row pass, 512 rows a head x 2,633 keys 12.9 us with 64 rows against 18.5
 // with 512, x 7,199 22.4 against 23.9, x 20,000 56.6 against 46.5, 100 rows a head x 30,000 25.2
@@ -1149,7 +1151,8 @@ RowPlan plan_rows(int Hkv, int rows, int Nk, bool unit_c) {
     for (int s = 1; s <= std::min(kMaxSplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
-      const double c = cost.of(base * s, ceil_div(per, steps_per)) + s * (0.04 + 1.5e-4 * rows);
+      // pass 2 merges the shares, by itself or behind a launch that does
+      const double c = cost.of(base * s, ceil_div(per, steps_per)) + std::min(s * (0.04 + 1.5e-4 * rows), 2.0 + 0.09 * s);
       if (c < best_cost) {
         best_cost = c;
         best = {small, s};
