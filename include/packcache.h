@@ -166,6 +166,10 @@ int pc_rebase(void* K, int dtype, int Hkv, int D, int64_t k_stride_h, int32_t* p
  * PC_ERR_HIP.
  */
 size_t pc_score_workspace_bytes(int Hq, int Hkv, int n_qs, int Nk, int share_heads);
+/* Host only: how a bf16 call is cut.  n_scored: keys that get a score.  cut[0], cut[1]: scoring rows per
+ * work-group and key shares of the row pass (0, 0 when it is skipped); cut[2], cut[3]: keys per work-group
+ * and query shares of the column pass; cut[4]: 1 where that pass forms the normalisers itself. */
+int pc_score_cut(int Hq, int Hkv, int n_qs, int Nk, int n_scored, float scale, int lse_given, int32_t cut[5]);
 int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hkv, int n_qs, int Nk,
              int D, int64_t q_stride_h, int64_t k_stride_h, const int32_t* q_rows, float scale,
              const float* lse, int64_t lse_stride_h, float* score, int64_t score_stride_h,
@@ -341,9 +345,12 @@ int pc_mask_scores(float* score, int Hsel, int Nk, int64_t score_stride_h, const
  *   would.  A smaller one means fewer shares; without it, or if it is not 16-byte aligned, the
  *   keys are not cut: always valid, the result differs by rounding only. Calls that may overlap on
  *   the GPU must not share a workspace: one call's merge would read another's partial results.
+ * pc_frame_attn_cut (host only) tells how a call with ws_bytes of workspace is cut: cut[0] query
+ *   rows per work-group, cut[1] key shares, cut[2] row tiles that walk all keys when the rest is cut.
  * Nk >= 1, Nq >= 1.  Errors: PC_ERR_NULL, PC_ERR_DTYPE, PC_ERR_SHAPE, PC_ERR_UNSUPPORTED,
  * PC_ERR_HIP.
  */
+int pc_frame_attn_cut(int dtype, int Hq, int Hkv, int Nq, int Nk, int D, size_t ws_bytes, int32_t cut[3]);
 size_t pc_frame_attn_workspace_bytes_for(int dtype, int Hq, int Hkv, int Nq, int Nk, int D);
 size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D);
 int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq, int Hkv,

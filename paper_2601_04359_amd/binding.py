@@ -17,7 +17,7 @@ __all__ = [
     "PackCacheError", "lib", "lib_path", "pc_version", "pc_strerror", "pc_budget", "pc_rope3d", "pc_rebase",
     "pc_score", "pc_score_workspace_bytes", "pc_compact_plan", "pc_compact", "pc_compact_batch", "pc_compact_batch_workspace_bytes", "PC_COMPACT_SELECT", "PC_COMPACT_GATHER", "PC_SCALE_FOLDED", "folded_q_scale", "pc_masked_budgets", "pc_mask_scores", "pc_compact_status",
     "pc_compact_workspace_bytes", "pc_compact_prepared", "pc_compact_static", "pc_compact_static_capacity", "pc_frame_attn", "pc_frame_attn_workspace_bytes",
-    "pc_frame_attn_workspace_bytes_for",
+    "pc_frame_attn_workspace_bytes_for", "pc_frame_attn_cut", "pc_score_cut",
     "segment_budgets",
 ]
 
@@ -98,6 +98,8 @@ def lib() -> C.CDLL:
         L.pc_frame_attn_workspace_bytes.argtypes = [C.c_int] * 4
         L.pc_frame_attn_workspace_bytes_for.restype = sz
         L.pc_frame_attn_workspace_bytes_for.argtypes = [C.c_int] * 6
+        L.pc_frame_attn_cut.argtypes = [C.c_int] * 6 + [sz, i32p]
+        L.pc_score_cut.argtypes = [C.c_int] * 5 + [C.c_float, C.c_int, i32p]
         L.pc_frame_attn.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i64,
                                     i64, i64, C.c_float, vp, vp, vp, sz, vp]
         _LIB = L
@@ -244,6 +246,15 @@ def pc_rebase(K, pos, row0: int, n_rows: int, delta_t: int, sections: Sequence[i
 
 def pc_score_workspace_bytes(Hq: int, Hkv: int, n_qs: int, Nk: int, share_heads: bool = False) -> int:
     return lib().pc_score_workspace_bytes(Hq, Hkv, n_qs, Nk, int(share_heads))
+
+
+def pc_score_cut(Hq: int, Hkv: int, n_qs: int, Nk: int, scale: float, lse_given: bool = False,
+                 n_scored: int | None = None) -> tuple[int, ...]:
+    """How a bf16 call is cut: (rows per work-group, key shares) of the row pass, (keys per work-group, query
+    shares) of the column pass, and whether that one forms the normalisers."""
+    cut = (C.c_int32 * 5)()
+    _check(lib().pc_score_cut(Hq, Hkv, n_qs, Nk, Nk if n_scored is None else n_scored, float(scale), int(lse_given), cut))
+    return tuple(cut)
 
 
 def pc_score(Qs, K, Nk: int, scale: float, lse=None, score=None, share_heads: bool = False, ws=None,
@@ -423,6 +434,13 @@ def pc_frame_attn_workspace_bytes(Hq: int, Nq: int, Nk: int, D: int) -> int:
 def pc_frame_attn_workspace_bytes_for(dtype: int, Hq: int, Hkv: int, Nq: int, Nk: int, D: int) -> int:
     """What a call of this dtype (PC_F32 / PC_BF16) and these sizes uses."""
     return lib().pc_frame_attn_workspace_bytes_for(dtype, Hq, Hkv, Nq, Nk, D)
+
+
+def pc_frame_attn_cut(dtype: int, Hq: int, Hkv: int, Nq: int, Nk: int, D: int, ws_bytes: int) -> tuple[int, ...]:
+    """How a call is cut: (query rows per work-group, key shares, row tiles that are not cut)."""
+    cut = (C.c_int32 * 3)()
+    _check(lib().pc_frame_attn_cut(dtype, Hq, Hkv, Nq, Nk, D, int(ws_bytes), cut))
+    return tuple(cut)
 
 
 def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):

@@ -1159,6 +1159,26 @@ extern "C" size_t pc_frame_attn_workspace_bytes(int Hq, int Nq, int Nk, int D) {
   return most;
 }
 
+extern "C" int pc_frame_attn_cut(int dtype, int Hq, int Hkv, int Nq, int Nk, int D, size_t ws_bytes, int32_t* cut) {
+  PC_REQUIRE(cut, PC_ERR_NULL, "pc_frame_attn_cut: cut is NULL");
+  PC_REQUIRE(Hq > 0 && Hkv > 0 && Hq % Hkv == 0 && Nq >= 1 && Nk >= 1 && static_cast<int64_t>(Hq) * Nq <= INT_MAX,
+             PC_ERR_SHAPE, "pc_frame_attn_cut: Hq=%d Hkv=%d Nq=%d Nk=%d", Hq, Hkv, Nq, Nk);
+  const int rows = Hq / Hkv * Nq;
+  if (dtype == PC_BF16 && D == kD) {
+    const AttnPlan plan = plan_bf16(Hkv, rows, Nk, ws_bytes);
+    cut[0] = plan.small ? kSmallRows : kBM;
+    cut[1] = plan.n_splits;
+    cut[2] = plan.n_whole;
+  } else {
+    PC_REQUIRE(dtype == PC_F32 && (D == 64 || D == 128), PC_ERR_UNSUPPORTED, "pc_frame_attn_cut: dtype %d, D=%d", dtype, D);
+    const F32Plan plan = plan_f32(Hkv, rows, Nk, D, ws_bytes);
+    cut[0] = 16 * plan.kr;
+    cut[1] = plan.n_splits;
+    cut[2] = 0;
+  }
+  return PC_OK;
+}
+
 extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dtype, int Hq,
                              int Hkv, int Nq, int Nk, int D, int64_t q_stride_h,
                              int64_t kv_stride_h, int64_t o_stride_h, float scale, void* O,

@@ -1202,6 +1202,21 @@ extern "C" size_t pc_score_workspace_bytes(int Hq, int Hkv, int n_qs, int Nk, in
   return ws_layout(Hq, Hkv, n_qs, Nk, share_heads).total;
 }
 
+extern "C" int pc_score_cut(int Hq, int Hkv, int n_qs, int Nk, int n_scored, float scale, int lse_given, int32_t* cut) {
+  PC_REQUIRE(cut, PC_ERR_NULL, "pc_score_cut: cut is NULL");
+  PC_REQUIRE(Hq > 0 && Hkv > 0 && Hq % Hkv == 0 && n_qs >= 1 && Nk >= 1 && n_scored >= 1 && n_scored <= Nk, PC_ERR_SHAPE,
+             "pc_score_cut: Hq=%d Hkv=%d n_qs=%d Nk=%d n_scored=%d", Hq, Hkv, n_qs, Nk, n_scored);
+  const int rows = Hq / Hkv * n_qs;
+  const RowPlan row = plan_rows(Hkv, rows, Nk, scale * 1.4426950408889634f == 1.0f);
+  const ColPlan col = plan_cols(Hkv, rows, n_scored, lse_given ? 1 : row.n_splits);
+  cut[0] = lse_given ? 0 : row.small ? kWaveRows : kBlockRows;
+  cut[1] = lse_given ? 0 : row.n_splits;
+  cut[2] = col.small ? kWaveRows : kBlockRows;
+  cut[3] = col.n_qsplits;
+  cut[4] = col.prepares;
+  return PC_OK;
+}
+
 extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hkv, int n_qs,
                         int Nk, int D, int64_t q_stride_h, int64_t k_stride_h,
                         const int32_t* q_rows, float scale, const float* lse, int64_t lse_stride_h, float* score,

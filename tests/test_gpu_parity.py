@@ -187,6 +187,20 @@ def _fold(Q, scale):
     return synth.to_bf16((Q.astype(np.float64) * q_fold(scale)).astype(np.float32)), LN2
 
 
+def _masked_reference(Q, K, V, keep, scale, rows):
+    """(O rows, lse rows, importances) of the unmasked keys alone, in 64 bits on the GPU."""
+    hq, hkv = Q.shape[0], K.shape[0]
+    O, L = [], []
+    mass = torch.zeros((hkv, int(keep.sum())), dtype=torch.float64, device=DEV)
+    for h in range(hq):
+        s = Q[h, rows].double() @ K[h * hkv // hq, keep].double().t() * scale
+        p = torch.softmax(s, dim=1)
+        O.append(p @ V[h * hkv // hq, keep].double())
+        L.append(torch.logsumexp(s, dim=1))
+        mass[h * hkv // hq] += p.sum(0)
+    return torch.stack(O), torch.stack(L), mass
+
+
 def _attn_check(dtype, Q, K, V, scale, fold=False):
     if fold:
         Q, scale = _fold(Q, scale)
@@ -261,17 +275,20 @@ def test_frame_attn_bf16_key_shares_and_merge(hq, hkv, nq, nk, fold):
     assert (split.float() - whole.float()).abs().max().item() <= 2 ** -6   # two roundings of values of O(1)
 
 
+ATTN_ACROSS_HEADS = [(2, 1, 33, 1), (3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 84, 255), (2, 1, 184, 5000),
+                     (24, 8, 520, 2100), (16, 4, 2010, 2499), (24, 8, 2901, 2100)]
+ATTN_256_ROWS_UNCUT = [(16, 4, 3990, nk) for nk in (1, 31, 33, 64, 65, 128, 129, 192, 193, 2499)]
+
+
 # Row tiles that span query heads (nq is no multiple of the tile), steps and tiles of the keys that are
 # empty, single or ragged, and both forms of the kernel: the first five shapes take 32 rows per
-# work-group (un-split, then in key shares), the others 256 rows (in key shares; un-split; a whole
-# round of row tiles un-split and the rest in key shares).
+# work-group (four un-split, one in key shares), the others 256 rows (in key shares twice; a whole round of
+# row tiles un-split and the rest in key shares).  test_host_abi.py pins these forms.
 # step: logits climb along the key axis, as above.  Every row is computed; the oracle checks the rows
 # at the tile edges and a stride of the others.
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
-@pytest.mark.parametrize("hq,hkv,nq,nk", [(2, 1, 33, 1), (3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 84, 255),
-                                          (2, 1, 184, 5000), (24, 8, 520, 2100), (16, 4, 2010, 2499),
-                                          (24, 8, 2901, 2100)])
+@pytest.mark.parametrize("hq,hkv,nq,nk", ATTN_ACROSS_HEADS)
 def test_frame_attn_bf16_row_tiles_across_heads(hq, hkv, nq, nk, step, fold):
     Q, K, V = _attn_case("bf16", hq, hkv, nq, nk, 128, nq + nk)
     scale = 128 ** -0.5
@@ -293,6 +310,34 @@ def test_frame_attn_bf16_row_tiles_across_heads(hq, hkv, nq, nk, step, fold):
     assert err.max() <= tol and err.mean() <= 2e-3, (err.max(), err.mean())
     lw_ulp = np.maximum(1.0, np.abs(Lw)) * 2.0 ** -20     # fp32 products and logs of values up to |Lw|
     assert (np.abs(host(lse)[:, rows].astype(np.float64) - Lw) <= np.maximum(1e-3, lw_ulp)).all()
+
+
+# 256 rows per work-group with all keys: walks of one, two, three and four tiles of 64, whole and ragged, a
+# last half tile with no key, fewer keys than a half tile; many tiles once.  step: logits climb along the
+# key axis by so much per half tile (0.05: the first reference stands throughout).
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step", [0.0, 0.05, 0.6, 40.0])
+@pytest.mark.parametrize("hq,hkv,nq,nk", ATTN_256_ROWS_UNCUT)
+def test_frame_attn_bf16_256_rows_and_few_keys(hq, hkv, nq, nk, step, fold):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nk)
+    Q, K, V = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((hq, nq), (hkv, nk), (hkv, nk)))
+    scale = 128 ** -0.5
+    if step:
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * (torch.arange(nk, device=DEV) // 32) / (8.0 * scale)
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, lse=lse, ws=torch.empty(16, dtype=torch.uint8, device=DEV))
+    rows = torch.tensor(sorted({0, 1, nq - 1} | set(range(0, nq, 61))), device=DEV)
+    Ow, Lw, _ = _masked_reference(Q, K, V, torch.ones(nk, dtype=torch.bool, device=DEV), scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs()
+    # tolerances as in the test above: with all weight on few keys |O| reaches 4
+    assert err.max().item() <= (2 ** -5 if step == 40.0 or nk < 40 else 2e-2) and err.mean().item() <= 2e-3
+    assert (lerr <= torch.clamp(Lw.abs().clamp(min=1.0) * 2.0 ** -20, min=1e-3)).all()
 
 
 @pytest.mark.parametrize("fold", [False, True])
@@ -439,20 +484,6 @@ def test_frame_attn_f32_takes_buffers_that_are_not_16_byte_aligned():
     assert np.abs(host(O) - Ow).max() <= 1e-5
 
 
-def _masked_reference(Q, K, V, keep, scale, rows):
-    """(O rows, lse rows, importances) of the unmasked keys alone, in 64 bits on the GPU."""
-    hq, hkv = Q.shape[0], K.shape[0]
-    O, L = [], []
-    mass = torch.zeros((hkv, int(keep.sum())), dtype=torch.float64, device=DEV)
-    for h in range(hq):
-        s = Q[h, rows].double() @ K[h * hkv // hq, keep].double().t() * scale
-        p = torch.softmax(s, dim=1)
-        O.append(p @ V[h * hkv // hq, keep].double())
-        L.append(torch.logsumexp(s, dim=1))
-        mass[h * hkv // hq] += p.sum(0)
-    return torch.stack(O), torch.stack(L), mass
-
-
 # A caller that masks keys through a coordinate of its own (the queries carry a constant there): their
 # logits are -inf, the type's lowest value times a constant, or far below the rest.  Steps, waves, half
 # tiles and key shares that hold nothing else, first and last ones among them: 32 rows per work-group
@@ -597,6 +628,12 @@ def test_score_bf16_row_reference_is_refreshed(step, fold):
     assert np.all(np.abs(got - want) <= 2e-7 + rel * want), (np.abs(got - want) / (want + 1e-30)).max()
 
 
+SCORE_ACROSS_HEADS = [(3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 33, 65), (8, 2, 252, 1804), (16, 2, 20, 30000),
+                      (16, 8, 600, 6000), (6, 2, 1100, 12000), (4, 2, 2100, 65000)]
+SCORE_512_FEW_KEYS = [(16, 4, 3990, nk) for nk in (1, 33, 64, 65, 129, 300)]
+SCORE_512_FEW_ROWS = [(2, 1, n, 60000) for n in (1, 30, 50, 96, 130)]
+
+
 # Scoring rows numbered through the heads of a group (n_qs is no multiple of a tile, or smaller than
 # one), both forms of either pass: the first three shapes have 64 stationary rows per work-group in
 # both; the next two have 512 in the column pass, which forms the normalisers of its rows itself or
@@ -604,8 +641,7 @@ def test_score_bf16_row_reference_is_refreshed(step, fold):
 # logits climb along the key axis, as above.  The reference is the softmax in 64 bits, on the GPU.
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("step", [0.0, 0.6, 40.0])
-@pytest.mark.parametrize("hq,hkv,n_qs,nk", [(3, 1, 31, 33), (6, 2, 43, 257), (2, 1, 33, 65), (8, 2, 252, 1804), (16, 2, 20, 30000),
-                                            (16, 8, 600, 6000), (6, 2, 1100, 12000), (4, 2, 2100, 65000)])
+@pytest.mark.parametrize("hq,hkv,n_qs,nk", SCORE_ACROSS_HEADS)
 def test_score_bf16_rows_across_heads(hq, hkv, n_qs, nk, step, fold):
     Q, K, _ = _attn_case("bf16", hq, hkv, n_qs, nk, 128, n_qs + nk)
     scale = 128 ** -0.5
@@ -629,6 +665,31 @@ def test_score_bf16_rows_across_heads(hq, hkv, n_qs, nk, step, fold):
     rel = max(2e-5, 6 * lse.abs().max().item() * 1.4427 * 2.0 ** -23)
     for given in (None, lse.float()):
         got = pk.pc_score(Qd, Kd, nk, scale, lse=given).double()
+        assert ((got - want).abs() <= 2e-7 + rel * want).all(), ((got - want).abs() / (want + 1e-30)).max().item()
+
+
+# The 512-row passes at their shortest: row pass with one to three key tiles per share, column pass with one
+# to five tiles of scoring rows, and a last block with a single key
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step", [0.0, 0.6])
+@pytest.mark.parametrize("hq,hkv,n_qs,nk", SCORE_512_FEW_KEYS + SCORE_512_FEW_ROWS)
+def test_score_bf16_short_512_row_passes(hq, hkv, n_qs, nk, step, fold):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n_qs + nk)
+    Q, K = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((hq, n_qs), (hkv, nk)))
+    scale = 128 ** -0.5
+    if step:
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * min(1.0, 125 / max(1, nk // 32)) * (torch.arange(nk, device=DEV) // 32) / (8.0 * scale)
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K = Q.bfloat16(), K.bfloat16()
+    rows = torch.arange(n_qs, device=DEV)
+    _, lse, want = _masked_reference(Q, K, K, torch.ones(nk, dtype=torch.bool, device=DEV), scale, rows)
+    rel = max(2e-5, 6 * lse.abs().max().item() * 1.4427 * 2.0 ** -23)     # as in the test above
+    for given in (None, lse.float()):
+        got = pk.pc_score(Q, K, nk, scale, lse=given).double()
         assert ((got - want).abs() <= 2e-7 + rel * want).all(), ((got - want).abs() / (want + 1e-30)).max().item()
 
 

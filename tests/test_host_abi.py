@@ -338,3 +338,40 @@ def test_rolling_caches_give_every_attention_call_its_own_workspace(monkeypatch)
         stack.attend(1, Q)
     given = [w.data_ptr() for w in taken if w is not None]
     assert len(taken) == 6 and len(set(given)) == len(given)
+
+
+def test_parity_shapes_take_the_forms_they_are_meant_for(L):
+    """Which kernel form and how many shares the shapes of test_gpu_parity.py take, so that a change of the
+    estimates does not move them off what their tests say they cover."""
+    import test_gpu_parity as g
+    ample, ln2 = 1 << 40, pk.PC_SCALE_FOLDED
+    attn = lambda shape, ws=ample: pk.pc_frame_attn_cut(pk.PC_BF16, *shape, 128, ws)
+    cuts = [attn(s) for s in g.ATTN_ACROSS_HEADS]
+    assert cuts[:4] == [(32, 1, 0)] * 4 and cuts[4][0] == 32 and cuts[4][1] > 1
+    assert all(c[0] == 256 and c[1] > 1 for c in cuts[5:]) and [c[2] for c in cuts[5:]] == [0, 0, 256]
+    assert all(attn(s, 0) == (256, 1, 0) for s in g.ATTN_256_ROWS_UNCUT)
+    # masked keys: 32 rows in shares, 256 rows un-split and in four shares of 1,920 keys, fp32 with 16 and 32
+    assert attn((2, 1, 184, 5000))[:2] == (32, 10) and attn((16, 4, 4032, 2048)) == (256, 1, 0)
+    assert attn((16, 4, 1008, 7455)) == (256, 4, 0)
+    f32 = lambda shape, d: pk.pc_frame_attn_cut(pk.PC_F32, *shape, d, ample)
+    assert f32((2, 1, 64, 336), 64)[0] == 16 and f32((8, 2, 252, 1804), 128)[0] == 32
+    score = lambda shape, scale=0.088, lse=False: pk.pc_score_cut(*shape, scale, lse)
+    for scale in (0.088, ln2):
+        cuts = [score(s, scale) for s in g.SCORE_ACROSS_HEADS]
+        assert all((c[0], c[2]) == (64, 64) for c in cuts[:3])
+        assert [(c[0], c[2], c[4]) for c in cuts[3:5]] == [(64, 512, 1), (64, 512, 0)]
+        assert all((c[0], c[2]) == (512, 512) for c in cuts[5:])
+        per_share = [-(-(-(-s[3] // 64)) // score(s, scale)[1]) for s in g.SCORE_512_FEW_KEYS]
+        assert all(score(s, scale)[0] == 512 for s in g.SCORE_512_FEW_KEYS) and {1, 2, 3} <= set(per_share)
+        for s in g.SCORE_512_FEW_ROWS:
+            assert score(s, scale)[2:4] == (512, 1) and score(s, scale, True)[:4] == (0, 0, 512, 1)
+
+
+def test_cut_queries_refuse_what_the_calls_refuse(L):
+    for bad in ((pk.PC_BF16, 3, 2, 10, 10, 128), (pk.PC_BF16, 2, 1, 0, 10, 128), (pk.PC_BF16, 2, 1, 10, 10, 64), (5, 2, 1, 10, 10, 128)):
+        with pytest.raises(pk.PackCacheError):
+            pk.pc_frame_attn_cut(*bad, 0)
+    for bad in ((3, 2, 10, 10), (2, 1, 0, 10), (2, 1, 10, 0)):
+        with pytest.raises(pk.PackCacheError):
+            pk.pc_score_cut(*bad, 0.1)
+    assert L.pc_frame_attn_cut(pk.PC_BF16, 2, 1, 10, 10, 128, 0, None) == -1 and L.pc_score_cut(2, 1, 10, 10, 10, 0.1, 0, None) == -1
