@@ -465,8 +465,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 // attn_bf16_kernel makes of the same rows, each an eighth as long; K and V come through L2 once per
 // 32 rows instead of once per 256, which is why large calls do not take this form (a step of 8 x 32
 // keys takes 1.4 us with every compute unit at it: 0.78 PFLOP/s at most).  8/2 heads x 252 rows x
-// 1,179 keys: 34 us in 8 work-groups of 256 rows, 12.4 us un-split in 64 of these, 11.9 us with
-// three key shares.  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
+// 1,179 keys: 34 us in 8 work-groups of 256 rows, 12.4 us un-split in 64 of these (three key shares took
+// 11.9; the estimate picks one).  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
 // ------------------------------------------------------------------------------------------
 constexpr int kSmallRows = 32;
 constexpr int kSmallKeys = 32;                                  // keys per wave and step
@@ -757,7 +757,7 @@ constexpr int kMaxKeySplits = 16;
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
 // (512 bytes written and read per row and share).  The cut it picks is at most 4 % slower than the
 // best of them on any of the 24, 0.5 % on average.  Where the line lies, both sides measured: 8/2
-// heads x 252 rows x 1,179 keys, 11.9 us with 32 rows against 18.8 with 256 (and 34 un-split); 16/4
+// heads x 252 rows x 1,179 keys, 12.4 us with 32 rows against 18.8 with 256 (and 34 un-split); 16/4
 // x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x 7,455,
 // 92.9 against 67.4.
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the

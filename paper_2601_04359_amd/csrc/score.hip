@@ -50,8 +50,10 @@ constexpr int kMaxSplits = 32;       // key splits of pass 1
 constexpr int kMaxQSplits = 8;       // query splits of pass 2
 constexpr float kNoMax = -1e30f;     // finite stand-in for "no key seen yet"
 
-// Every staging point issues at most three direct loads per wave; waiting until at most two
-// are in flight leaves only (part of) the newest point outstanding.
+// Every staging point issues kTileLoads direct loads per wave and nothing else is in flight in the loops:
+// waiting until at most that many are leaves only the newest point outstanding.
+constexpr int kTileLoads = kTileBytes / (kThreads * 16);
+static_assert(kTileLoads == 2, "dma_wait_all_but_newest encodes it");
 __device__ __forceinline__ void dma_wait_all_but_newest() { asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); }
 
 // Fetch the two 1-KB pieces of a 64-row tile this wave is responsible for; src(row) is the
