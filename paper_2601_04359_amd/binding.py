@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+from functools import lru_cache
 from itertools import chain
 from typing import Iterable, Sequence
 
@@ -436,6 +437,11 @@ def pc_frame_attn_workspace_bytes_for(dtype: int, Hq: int, Hkv: int, Nq: int, Nk
     return lib().pc_frame_attn_workspace_bytes_for(dtype, Hq, Hkv, Nq, Nk, D)
 
 
+@lru_cache(maxsize=1024)    # a function of its (plain) numbers alone, and the layers of a step ask the same
+def _attn_workspace_bytes(*sizes: int) -> int:
+    return pc_frame_attn_workspace_bytes_for(*sizes)
+
+
 def pc_frame_attn_cut(dtype: int, Hq: int, Hkv: int, Nq: int, Nk: int, D: int, ws_bytes: int) -> tuple[int, ...]:
     """How a call is cut: (query rows per work-group, key shares, row tiles that are not cut)."""
     cut = (C.c_int32 * 3)()
@@ -453,15 +459,16 @@ def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):
         _rows_dense(t, nm)
     if O is None:
         O = torch.empty_like(Q)
+    dtype = _dtype_code(Q)
     if ws is None:
-        nws = pc_frame_attn_workspace_bytes_for(_dtype_code(Q), Hq, Hkv, Nq, Nk, D)
+        nws = _attn_workspace_bytes(dtype, Hq, Hkv, Nq, int(Nk), D)
         if nws:
             ws = _workspace(nws, Q)
     if K.stride(0) != V.stride(0):
         raise PackCacheError(-2, "K and V must share their head stride")
     if lse is not None and (tuple(lse.shape) != (Hq, Nq) or not lse.is_contiguous()):
         raise PackCacheError(-2, f"lse must be a contiguous fp32 [{Hq}][{Nq}] tensor")
-    _check(lib().pc_frame_attn(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _dtype_code(Q), Hq, Hkv, Nq, Nk, D,
+    _check(lib().pc_frame_attn(Q.data_ptr(), K.data_ptr(), V.data_ptr(), dtype, Hq, Hkv, Nq, Nk, D,
                                Q.stride(0), K.stride(0), O.stride(0), float(scale), O.data_ptr(), _ptr(lse),
                                _ptr(ws), 0 if ws is None else ws.numel(), _stream()))
     return O
