@@ -435,7 +435,8 @@ def test_frame_attn_f32_shapes(d, nq, nk):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nk", [(15, 31), (16, 32), (17, 33), (31, 255), (32, 256), (33, 257), (17, 5000), (301, 2501)])
 def test_frame_attn_f32_tile_edges_and_key_shares(d, nq, nk):
-    # 16 query rows per work-group, 32 in the last shape; tiles of rows that span the three heads
+    # 16 query rows per work-group, 32 in the last shape at D = 128; the first two shapes are one wave's step;
+    # tiles of rows that span the three heads
     Q, K, V = _attn_case("f32", 3, 1, nq, nk, d, d + nq + nk)
     _attn_check("f32", Q, K, V, d ** -0.5)
     # without a workspace the keys are not cut: the same sums in another order

@@ -355,6 +355,8 @@ def test_parity_shapes_take_the_forms_they_are_meant_for(L):
     assert attn((16, 4, 1008, 7455)) == (256, 4, 0)
     f32 = lambda shape, d: pk.pc_frame_attn_cut(pk.PC_F32, *shape, d, ample)
     assert f32((2, 1, 64, 336), 64)[0] == 16 and f32((8, 2, 252, 1804), 128)[0] == 32
+    assert f32((3, 1, 301, 2501), 64)[0] == 16 and f32((3, 1, 301, 2501), 128)[0] == 32
+    assert f32((3, 1, 17, 5000), 64)[1] > 1 and f32((3, 1, 16, 32), 64) == (16, 1, 0)
     score = lambda shape, scale=0.088, lse=False: pk.pc_score_cut(*shape, scale, lse)
     for scale in (0.088, ln2):
         cuts = [score(s, scale) for s in g.SCORE_ACROSS_HEADS]
