@@ -18,6 +18,7 @@
 //            chunks with a lower ticket, which are already running and whose loads wait on
 //            nothing.
 //   A stack of layers is handled by the same two launches (layer strides).
+//   small    caches of a few thousand rows take one launch instead (compact_fused_kernel).
 #include <limits.h>
 #include <stddef.h>
 
@@ -405,11 +406,11 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
 // segments), when the longest pruned segment is longer than kRowsSelectMinLen
 constexpr int kRowsSelectMinUnits = PC_ROWS_SELECT_MIN_UNITS, kRowsSelectMinLen = PC_ROWS_SELECT_MIN_LEN;
 constexpr int kWideSelectMaxUnits = 256;  // segments that take 1,024 threads each (see the launch)
-// f(n - 1), ..., f(0) with compile-time row numbers; n in [0, 64] is wave-uniform
-template <class F>
+// f(n - 1), ..., f(0) with compile-time row numbers; n in [0, kRows] is wave-uniform
+template <int kRows, class F>
 __device__ __forceinline__ void rows_down_from(int n, F&& f) {
 #pragma unroll
-  for (int i = 63; i >= 0; --i) {
+  for (int i = kRows - 1; i >= 0; --i) {
     asm volatile("" : "+s"(n));  // one scalar compare here, not 64 lane masks kept from sweep to sweep
     if (i < n) f(i);
   }
@@ -420,25 +421,14 @@ __device__ __forceinline__ int lanes_below(uint64_t mask, int base) {  // base +
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), base));
 }
 
-__global__ __launch_bounds__(64) void select_rows_kernel(
-    const float* __restrict__ score, int64_t score_stride_h, int32_t* __restrict__ idx, int64_t idx_stride_h,
-    SegTable tab, int32_t* __restrict__ clear, int n_clear, int hsel, int64_t score_stride_l, int64_t idx_stride_l) {
-  constexpr int kRows = PC_MAX_SELECT_LEN / 64;                     // 64 full rows at most
-  constexpr int kBits = 11, kBins = 1 << kBits, kOwn = kBins / 64;  // 32 bins per lane
-  static_assert(kRows == 64, "rows_down_from covers 64 rows");
-  __shared__ __align__(16) int hist[kBins];
-  const int lane = threadIdx.x;
-  const int s = blockIdx.x, h = blockIdx.y;  // wave-uniform, like everything read from the table
-  for (int i = (h * gridDim.x + s) * 64 + lane; i < n_clear; i += gridDim.x * gridDim.y * 64) clear[i] = 0;
-  const int layer = __builtin_amdgcn_readfirstlane(h / hsel), head = __builtin_amdgcn_readfirstlane(h % hsel);
-  const int start = tab.start[s], len = tab.len[s], k = tab.keep[s];
-  int32_t* out = idx + layer * idx_stride_l + head * idx_stride_h + tab.dst[s];
-  if (k <= 0) return;
-  if (!tab.prune[s]) {
-    for (int e = lane; e < len; e += 64) out[e] = start + e;
-    return;
-  }
-  const float* sc = score + layer * score_stride_l + head * score_stride_h + start;
+// The k best of the len scores at sc, by one wave: store(at, source row) for the at-th of them in
+// ascending row order.  kRows x 64 keys at most (plus the ragged row); hist: 2^kBits words of LDS of the
+// wave's own.
+template <int kRows, int kBits, class Store>
+__device__ __forceinline__ void select_rows(const float* __restrict__ sc, int len, int k, int start, int* hist,
+                                            Store&& store) {
+  constexpr int kBins = 1 << kBits, kOwn = kBins / 64;  // bins per lane
+  const int lane = threadIdx.x & 63;
   uint32_t* cand = reinterpret_cast<uint32_t*>(hist);  // the candidates reuse the histogram's first words
   auto wave_sync = [] {  // LDS written by other lanes of this wave becomes visible; nothing moves across
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -457,10 +447,10 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(sc), 0, len * 4, 0x00020000);
     const int lane_bytes = lane * 4;
-    rows_down_from(n_full, [&](int i) {
+    rows_down_from<kRows>(n_full, [&](int i) {
       v[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_bytes, i * 256, 0));
     });
-    rows_down_from(n_full, [&](int i) {
+    rows_down_from<kRows>(n_full, [&](int i) {
       asm volatile("" : "+v"(v[i]));  // the conversion stays in this sweep, behind all the loads
       key[i] = order_key(v[i]);
     });
@@ -470,7 +460,7 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
   // bit operation per key), then an OR over the lanes
   const uint32_t key0 = __builtin_amdgcn_readfirstlane(n_full > 0 ? key[0] : key_r);
   uint32_t differ = in_tail ? key_r ^ key0 : 0u;
-  rows_down_from(n_full, [&](int i) { differ |= key[i] ^ key0; });
+  rows_down_from<kRows>(n_full, [&](int i) { differ |= key[i] ^ key0; });
   differ = wave_or(differ);  // the same in every lane: scalar from here on
   int hi = differ ? 32 - __clz(differ) : 0;  // number of undecided low bits
   uint32_t prefix = hi >= 32 ? 0u : (key0 >> hi) << hi;
@@ -492,11 +482,11 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
     };
     if (first) {  // every key matches the shared prefix
       if (in_tail) vote(key_r);
-      rows_down_from(n_full, [&](int i) { vote(key[i]); });
+      rows_down_from<kRows>(n_full, [&](int i) { vote(key[i]); });
     } else {
       const uint32_t hi_mask = 0xFFFFFFFFu << hi;  // hi < 32 after the first pass
       if (in_tail && (key_r & hi_mask) == prefix) vote(key_r);
-      rows_down_from(n_full, [&](int i) {
+      rows_down_from<kRows>(n_full, [&](int i) {
         if ((key[i] & hi_mask) == prefix) vote(key[i]);
       });
     }
@@ -540,7 +530,7 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
         }
       };
       collect(key_r, in_tail && (key_r & lo_mask) == prefix);
-      rows_down_from(n_full, [&](int i) { collect(key[i], (key[i] & lo_mask) == prefix); });
+      rows_down_from<kRows>(n_full, [&](int i) { collect(key[i], (key[i] & lo_mask) == prefix); });
       wave_sync();
       n_cand = min(n_cand, 64);
       const bool has = lane < n_cand;
@@ -570,10 +560,10 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
       after += popc64(bk);
       const int at = lanes_below(bk, k - after);
       if (keep && static_cast<uint32_t>(at) < static_cast<uint32_t>(k))
-        *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(out) + static_cast<uint32_t>(at) * 4u) = lane_start + row * 64;
+        store(at, lane_start + row * 64);
     };
     put(in_tail && key_r >= prefix, n_full);
-    rows_down_from(n_full, [&](int i) { put(key[i] >= prefix, i); });
+    rows_down_from<kRows>(n_full, [&](int i) { put(key[i] >= prefix, i); });
   } else {
     int eq_after = 0;
     auto put = [&](uint32_t kv, bool valid, int row) {
@@ -586,11 +576,34 @@ __global__ __launch_bounds__(64) void select_rows_kernel(
       after += popc64(bk);
       const int at = lanes_below(bk, k - after);
       if (keep && static_cast<uint32_t>(at) < static_cast<uint32_t>(k))
-        *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(out) + static_cast<uint32_t>(at) * 4u) = lane_start + row * 64;
+        store(at, lane_start + row * 64);
     };
     put(key_r, in_tail, n_full);
-    rows_down_from(n_full, [&](int i) { put(key[i], true, i); });
+    rows_down_from<kRows>(n_full, [&](int i) { put(key[i], true, i); });
   }
+}
+
+__global__ __launch_bounds__(64) void select_rows_kernel(
+    const float* __restrict__ score, int64_t score_stride_h, int32_t* __restrict__ idx, int64_t idx_stride_h,
+    SegTable tab, int32_t* __restrict__ clear, int n_clear, int hsel, int64_t score_stride_l, int64_t idx_stride_l) {
+  constexpr int kRows = PC_MAX_SELECT_LEN / 64;                     // 64 full rows at most
+  constexpr int kBits = 11;
+  __shared__ __align__(16) int hist[1 << kBits];
+  const int lane = threadIdx.x;
+  const int s = blockIdx.x, h = blockIdx.y;  // wave-uniform, like everything read from the table
+  for (int i = (h * gridDim.x + s) * 64 + lane; i < n_clear; i += gridDim.x * gridDim.y * 64) clear[i] = 0;
+  const int layer = __builtin_amdgcn_readfirstlane(h / hsel), head = __builtin_amdgcn_readfirstlane(h % hsel);
+  const int start = tab.start[s], len = tab.len[s], k = tab.keep[s];
+  int32_t* out = idx + layer * idx_stride_l + head * idx_stride_h + tab.dst[s];
+  if (k <= 0) return;
+  if (!tab.prune[s]) {
+    for (int e = lane; e < len; e += 64) out[e] = start + e;
+    return;
+  }
+  select_rows<kRows, kBits>(score + layer * score_stride_l + head * score_stride_h + start, len, k, start, hist,
+                            [&](int at, int row) {
+                              *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(out) + static_cast<uint32_t>(at) * 4u) = row;
+                            });
 }
 
 // ---- gather ----------------------------------------------------------------------------------
@@ -738,6 +751,128 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     }
   }
   if (pdst >= 0) pos_o[pdst] = pval;
+}
+
+// ---- small caches: select and move in ONE launch ------------------------------------------------
+// A cache of a few thousand rows is two or three memory latencies of work, and the hand-over between
+// two launches (and, in place, between the work-groups of one) costs more than the work.  Here a
+// work-group owns a COLUMN SLICE of one (layer, KV head): a few neighbouring 16-byte chunks of every
+// row of K or of V (or the positions).  Slices never touch each other's bytes, so the in-place move
+// needs no order between work-groups: each one selects for itself (a wave per segment, kept rows in
+// LDS), then walks the packed rows upwards, loads of a pass before its stores.
+constexpr int kFusedThreads = 1024, kFusedWaves = kFusedThreads / 64;
+constexpr int kFusedBits = 8;         // bins of a wave's histogram: 1 KB of LDS each
+constexpr int kFusedSelRows = 16;     // segments of up to 1,024 scores (and a ragged row)
+constexpr int kFusedMaxLen = kFusedSelRows * 64;
+constexpr int kFusedMaxRows = 8192;   // kept rows in LDS
+constexpr int kFusedPasses = 4;       // pieces a thread has in flight
+
+template <int kCap>
+struct FusedTable {  // rows fit 16 bits each: a segment is {start | len << 16, keep | dst << 16}
+  uint2 seg[kCap];
+};
+struct FusedArgs {
+  const u32x4* K;
+  const u32x4* V;
+  const int32_t* pos;
+  u32x4* Ko;
+  u32x4* Vo;
+  int32_t* pos_o;
+  const float* score;
+  int32_t* idx_out;    // or null
+  int32_t* abort;      // cleared when in place, or null
+  int64_t in_stride_c, out_stride_c, in_stride_lc, out_stride_lc;       // 16-byte chunks
+  int64_t pos_stride_h, pos_out_stride_h, pos_stride_l, pos_out_stride_l;
+  int64_t score_stride_h, score_stride_l, idx_stride_h, idx_stride_l;
+  int n_seg, n_out, row0;  // packed rows below row0 stay where they are (0 out of place)
+  int Hkv, hsel, log_chunks, log_slices;  // a slice is 2^log_chunks chunks, a row 2^log_slices slices
+};
+
+// Microseconds of the launch, fitted to 90 shapes (64 to 1,000 tokens per frame, 2 to 47 frames, within
+// 13 %): every round of 16 segments is a chain of a load and a histogram's steps, and a compute unit moves
+// one piece of a row per 3 clocks whatever its width.  Two launches take 8.3 to 11.5 in place and 7.1 to
+// 8.5 out of place where this one takes 4.8 to 9 (252-token frames, 6 of them, 4 heads: 10.3 -> 7.0 and
+// 7.6 -> 6.7; the same for 28 layers: 31 -> 22.6), and the launch saved is 3 on the host.  Out of place
+// many layers are better off with whole rows (28 layers x 8 heads, 600 x 3: 83 against 101).
+inline bool fused_pays(int n_seg, int max_len, int n_moved, int heads, bool in_place) {
+  const float us = 2.2f + 2.4f * ceil_div(n_seg, kFusedWaves) + 1.5f / 1024 * max_len + 2.4f / 1024 * n_moved;
+  return in_place ? us <= 10.f && heads <= kMaxTicketHeads : us <= 9.f && heads <= 112;
+}
+// Slices of 64 bytes waste half of every cache line they touch and pay only while few work-groups run (8
+// heads 6.2 against 6.5 us, 24 heads 8.2 against 6.8 for 128-byte slices); those pay up to one
+// work-group per compute unit (48 heads: 8.1 against 9.1 for whole rows).
+inline bool fused_slices_pay(int chunks, int work_groups) {
+  return chunks >= 8 ? work_groups <= 256 : chunks == 4 && work_groups <= 64;
+}
+
+template <int cpr /* 16-byte chunks per row */, int kCap>
+__global__ __launch_bounds__(kFusedThreads) void compact_fused_kernel(FusedArgs a, FusedTable<kCap> tab) {
+  __shared__ int32_t s_idx[kFusedMaxRows];
+  __shared__ __align__(16) int s_hist[kFusedWaves][1 << kFusedBits];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int kv_units = (a.Hkv * 2) << a.log_slices, l = blockIdx.y, u = blockIdx.x;
+  const bool is_pos = u >= kv_units;
+  const int h = is_pos ? u - kv_units : u >> (a.log_slices + 1);
+  const int hs = a.hsel == 1 ? 0 : h;
+  if (a.abort != nullptr && l == 0 && u == 0 && t == 0) *a.abort = 0;
+  const int row0 = is_pos && a.idx_out ? 0 : a.row0;
+  const float* sc = a.score + l * a.score_stride_l + hs * a.score_stride_h;
+  for (int s = wave; s < a.n_seg; s += kFusedWaves) {
+    const uint2 g = tab.seg[s];
+    const int start = g.x & 0xFFFF, len = g.x >> 16, keep = g.y & 0xFFFF, dst = g.y >> 16;
+    if (keep == 0 || dst + keep <= row0) continue;  // wave-uniform
+    if (keep == len)
+      for (int e = lane; e < len; e += 64) s_idx[dst + e] = start + e;
+    else
+      select_rows<kFusedSelRows, kFusedBits>(sc + start, len, keep, start, s_hist[wave],
+                                             [&](int at, int row) { s_idx[dst + at] = row; });
+  }
+  __syncthreads();
+
+  if (is_pos) {  // 12-byte rows, one component per thread
+    const int32_t* in = a.pos + l * a.pos_stride_l + hs * a.pos_stride_h;
+    int32_t* out = a.pos_o + l * a.pos_out_stride_l + hs * a.pos_out_stride_h;
+    if (a.idx_out)
+      for (int r = t; r < a.n_out; r += kFusedThreads)
+        a.idx_out[l * a.idx_stride_l + hs * a.idx_stride_h + r] = s_idx[r];
+    const int n = (a.n_out - a.row0) * 3;
+    for (int e0 = t; e0 < n + t; e0 += kFusedThreads * kFusedPasses) {  // the same trip count for every thread
+      int32_t v[kFusedPasses];
+#pragma unroll
+      for (int i = 0; i < kFusedPasses; ++i) {
+        const int e = e0 + i * kFusedThreads;
+        if (e < n) v[i] = in[s_idx[a.row0 + e / 3] * 3 + e % 3];
+      }
+#pragma unroll
+      for (int i = 0; i < kFusedPasses; ++i) asm volatile("" : "+v"(v[i]));
+      __syncthreads();  // every row of this pass is in registers; later passes read rows above it
+#pragma unroll
+      for (int i = 0; i < kFusedPasses; ++i) {
+        const int e = e0 + i * kFusedThreads;
+        if (e < n) out[a.row0 * 3 + e] = v[i];
+      }
+    }
+    return;
+  }
+  const int slice = u & ((1 << a.log_slices) - 1);
+  const bool is_v = (u >> a.log_slices) & 1;
+  const int ch = (slice << a.log_chunks) + (t & ((1 << a.log_chunks) - 1)), rows_per_pass = kFusedThreads >> a.log_chunks;
+  const u32x4* in = (is_v ? a.V : a.K) + l * a.in_stride_lc + h * a.in_stride_c + ch;
+  u32x4* out = (is_v ? a.Vo : a.Ko) + l * a.out_stride_lc + h * a.out_stride_c + ch;
+  for (int r0 = a.row0; r0 < a.n_out; r0 += rows_per_pass * kFusedPasses) {
+    const int row = r0 + (t >> a.log_chunks);
+    u32x4 v[kFusedPasses];
+#pragma unroll
+    for (int i = 0; i < kFusedPasses; ++i)
+      if (row + i * rows_per_pass < a.n_out) v[i] = in[static_cast<int64_t>(s_idx[row + i * rows_per_pass]) * cpr];
+#pragma unroll
+    for (int i = 0; i < kFusedPasses; ++i) asm volatile("" : "+v"(v[i]));
+    __syncthreads();  // as above
+#pragma unroll
+    for (int i = 0; i < kFusedPasses; ++i)
+      if (row + i * rows_per_pass < a.n_out) out[static_cast<int64_t>(row + i * rows_per_pass) * cpr] = v[i];
+  }
 }
 
 // score of a masked token -> -1: below every real score (sums of probabilities are >= 0), so
@@ -960,6 +1095,52 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
   const int64_t idx_stride_layer = idx_out ? idx_stride_l : static_cast<int64_t>(hsel) * nk_in;
   GatherSync* sync = reinterpret_cast<GatherSync*>(wsb + lay.sync_off);
   int32_t* flags = reinterpret_cast<int32_t*>(wsb + lay.flags_off);
+
+  const int row_chunks = row_bytes / 16;
+  int row0 = 0;  // in place, packed rows below it stay where they are
+  if (in_place) {
+    row0 = nk_out;
+    for (int s = n_seg - 1; s >= 0; --s)
+      if (plan[s].len < seg_in[s].len) row0 = plan[s].start;
+  }
+  if (phases == (PC_COMPACT_SELECT | PC_COMPACT_GATHER) && max_prune_len <= kFusedMaxLen && nk_in <= 0xFFFF &&
+      nk_out <= kFusedMaxRows && fused_pays(n_seg, max_prune_len, nk_out - row0, n_layers * Hkv, in_place)) {
+    FusedArgs a;
+    a.K = static_cast<const u32x4*>(K), a.V = static_cast<const u32x4*>(V), a.pos = pos;
+    a.Ko = static_cast<u32x4*>(K_out), a.Vo = static_cast<u32x4*>(V_out), a.pos_o = pos_out;
+    a.score = score, a.idx_out = idx_out, a.abort = in_place ? static_cast<int32_t*>(ws) : nullptr;
+    a.in_stride_c = kv_stride_h * elt / 16, a.out_stride_c = kv_out_stride_h * elt / 16;
+    a.in_stride_lc = kv_stride_l * elt / 16, a.out_stride_lc = kv_out_stride_l * elt / 16;
+    a.pos_stride_h = pos_stride_h, a.pos_out_stride_h = pos_out_stride_h;
+    a.pos_stride_l = pos_stride_l, a.pos_out_stride_l = pos_out_stride_l;
+    a.score_stride_h = score_stride_h, a.score_stride_l = score_stride_l;
+    a.idx_stride_h = idx_stride_h, a.idx_stride_l = idx_stride_l;
+    a.n_seg = n_seg, a.n_out = nk_out, a.Hkv = Hkv, a.hsel = hsel;
+    a.row0 = row0;
+    a.log_slices = 0;
+    while (a.log_slices < 5 && fused_slices_pay(row_chunks >> (a.log_slices + 1), (n_layers * Hkv * 2) << (a.log_slices + 1)))
+      ++a.log_slices;
+    a.log_chunks = (row_chunks == 16 ? 4 : 5) - a.log_slices;
+    const dim3 grid(((Hkv * 2) << a.log_slices) + hsel, n_layers);
+    auto fill = [&](auto& ft) {
+      for (int s = 0; s < n_seg; ++s)
+        ft.seg[s] = make_uint2(static_cast<uint32_t>(seg_in[s].start) | static_cast<uint32_t>(seg_in[s].len) << 16,
+                               static_cast<uint32_t>(plan[s].len) | static_cast<uint32_t>(plan[s].start) << 16);
+    };
+    if (n_seg <= 24) {
+      FusedTable<24> ft;
+      fill(ft);
+      if (row_bytes == 256) compact_fused_kernel<16, 24><<<grid, kFusedThreads, 0, st>>>(a, ft);
+      else compact_fused_kernel<32, 24><<<grid, kFusedThreads, 0, st>>>(a, ft);
+    } else {
+      FusedTable<PC_MAX_SEGMENTS> ft;
+      fill(ft);
+      if (row_bytes == 256) compact_fused_kernel<16, PC_MAX_SEGMENTS><<<grid, kFusedThreads, 0, st>>>(a, ft);
+      else compact_fused_kernel<32, PC_MAX_SEGMENTS><<<grid, kFusedThreads, 0, st>>>(a, ft);
+    }
+    PC_CHECK_LAUNCH("pc_compact");
+    return PC_OK;
+  }
 
   const dim3 sgrid(n_seg, hsel * n_layers);
   // the select kernel also clears the in-place gather's counters and flags (contiguous in ws)

@@ -851,6 +851,39 @@ def test_compact_long_segment_generic_select_and_negative_zero():
     assert np.array_equal(host(Kd[:, :nko]), Kw) and np.array_equal(host(pd[:, :nko]), pw)
 
 
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("lens,D,dtype,Hkv,share", [
+    ([5, 1, 2, 3], 128, "bf16", 1, False),                       # frames shorter than a wave
+    ([16, 64, 63, 64, 65, 64], 64, "f32", 2, False),             # around one row of 64 keys
+    ([0, 1023, 1024, 7], 128, "bf16", 2, True),                  # the longest segments the one-launch form takes
+    ([0, 1023, 1025, 7], 128, "bf16", 2, False),                 # one key more: two launches
+    ([3] + [70] * 23, 128, "f32", 1, False),                     # 24 segments: the short table, two rounds of waves
+    ([3] + [70] * 24, 128, "bf16", 24, False),                   # 25: the long table; many heads, wide slices
+    ([0] + [130] * 16 + [0, 200], 128, "bf16", 2, False),        # empty segments between others
+])
+def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv, share, in_place):
+    rng = np.random.default_rng(sum(lens) + Hkv)
+    segs, at = [], 0
+    for i, n in enumerate(lens):
+        segs.append((at, n, pk.PC_SEG_TEXT if i == 0 else pk.PC_SEG_FRAME, i))
+        at += n
+    hsel = 1 if share else Hkv
+    sc = np.round(np.exp(rng.standard_normal((hsel, at))) * 64).astype(np.float32) / 64     # with ties
+    budgets = [n if i == 0 else (0, n, n // 3, max(1, n - 1), 1)[(i + 2) % 5] for i, n in enumerate(lens)]
+    K, V = (orc.round_to_bf16(rng.standard_normal((Hkv, at, D))).astype(np.float32) for _ in range(2))
+    pos = rng.integers(0, 10000, (hsel, at, 3)).astype(np.int32)
+    Kw, Vw, pw, iw, sw = orc.compact(K, V, pos, sc, segs, budgets, share_heads=share)
+    Kd, Vd, pd = dev(K, dtype), dev(V, dtype), dev(pos, None)
+    nk = sw[-1][0] + sw[-1][1]
+    idx = torch.full((hsel, nk), -1, dtype=torch.int32, device=DEV)
+    out = None if in_place else (torch.empty_like(Kd), torch.empty_like(Vd), torch.empty_like(pd))
+    sg, nko = pk.pc_compact(Kd, Vd, pd, dev(sc, None), segs, budgets, share_heads=share, out=out, idx=idx)
+    Ko, Vo, po = out or (Kd, Vd, pd)
+    assert sg == sw and nko == nk and np.array_equal(host(idx), iw)
+    assert np.array_equal(host(Ko[:, :nk]), Kw) and np.array_equal(host(Vo[:, :nk]), Vw)
+    assert np.array_equal(host(po[:, :nk]), pw)
+
+
 def test_in_place_compaction_repeated_random_budgets():
     # the in-place ordering protocol against the out-of-place result, many budget patterns
     w = synth.midsize(n_past=9, gh=16, gw=21, n_text=24)
