@@ -1,6 +1,8 @@
-"""ctypes binding of libpackcache.so: same names as the C ABI, argument marshalling only.
+"""Binding of libpackcache.so: same names as the C ABI, argument marshalling only.
 
-PyTorch supplies device memory and the current stream; every step of the path runs in the
+Calls with plain arguments (strided GPU tensors, built-in numbers, lists and tuples of them) are
+marshalled by the compiled half of this module, _marshal; everything else, and what the checks refuse,
+goes through ctypes here.  Both make the same call into the same library.  PyTorch supplies device memory and the current stream; every step of the path runs in the
 library's HIP kernels.  A missing library raises: there is no fallback.
 """
 from __future__ import annotations
@@ -8,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+import sys
 from functools import lru_cache
 from itertools import chain
 from typing import Iterable, Sequence
@@ -37,6 +40,7 @@ def folded_q_scale(scale: float) -> float:
 PC_MAX_SEGMENTS = 120
 
 _LIB = None
+_NATIVE = None    # the compiled half, once the library and torch are loaded; False: not there
 
 
 class PackCacheError(RuntimeError):
@@ -104,7 +108,24 @@ def lib() -> C.CDLL:
         L.pc_frame_attn.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i64,
                                     i64, i64, C.c_float, vp, vp, vp, sz, vp]
         _LIB = L
+    if _NATIVE is None and "torch" in sys.modules:
+        _bind_native(_LIB)
     return _LIB
+
+
+def _bind_native(L) -> None:
+    """Hands the loaded entry points to the compiled half.  Where it was not built, or torch lacks the raw
+    stream query, every call takes the path through ctypes."""
+    global _NATIVE
+    try:
+        import torch
+        from . import _marshal
+        entries = [C.cast(f, C.c_void_p).value for f in (L.pc_rope3d, L.pc_score, L.pc_compact, L.pc_compact_batch,
+                                                         L.pc_frame_attn, L.pc_frame_attn_workspace_bytes_for, L.pc_budget)]
+        _marshal.bind(*entries, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _NATIVE = _marshal
+    except (ImportError, AttributeError):
+        _NATIVE = False
 
 
 def _check(status: int) -> None:
@@ -209,6 +230,10 @@ def pc_strerror(status: int) -> str:
 
 
 def pc_budget(mode: int, n_frame_tokens: int, n_past: int, gamma: float = 0.0, b_min: int = 0) -> list[int]:
+    if _NATIVE:
+        r = _NATIVE.budget(mode, n_frame_tokens, n_past, gamma, b_min)
+        if r.__class__ is list:
+            return r
     out = (C.c_int32 * max(n_past, 1))()
     _check(lib().pc_budget(mode, n_frame_tokens, n_past, float(gamma), b_min, out))
     return out[:n_past]
@@ -217,6 +242,10 @@ def pc_budget(mode: int, n_frame_tokens: int, n_past: int, gamma: float = 0.0, b
 def segment_budgets(segments: Sequence[Sequence[int]], by_distance: Sequence[int]) -> list[int]:
     """Budget per segment from budgets per temporal distance: the newest FRAME segment in
     the table is at distance 1.  Non-FRAME segments get their own length."""
+    if _NATIVE:
+        r = _NATIVE.segment_budgets(segments, by_distance)
+        if r is not None:
+            return r
     frames = [i for i, s in enumerate(segments) if s[2] == PC_SEG_FRAME]
     out = [int(s[1]) for s in segments]
     for d, i in enumerate(reversed(frames), start=1):
@@ -224,10 +253,38 @@ def segment_budgets(segments: Sequence[Sequence[int]], by_distance: Sequence[int
     return out
 
 
+def _past_frames(segments) -> int:
+    """How many past frames a table holds."""
+    n = _NATIVE.past_frames(segments) if _NATIVE else None
+    return sum(1 for s in segments if s[2] == PC_SEG_FRAME) if n is None else n
+
+
+def _prunable_span(segments, budgets):
+    """Rows from the first to the last past frame that is over its budget; None if none is."""
+    span = _NATIVE.prunable_span(segments, budgets) if _NATIVE else None
+    if span is None:
+        over = [s for s, b in zip(segments, budgets) if s[2] == PC_SEG_FRAME and b < s[1]]
+        return (over[0][0], over[-1][0] + over[-1][1]) if over else None
+    return span or None
+
+
+def _rows(K, V, pos, dim: int, start: int, n: int):
+    """Rows start .. start + n - 1 of the three, as views."""
+    views = _NATIVE.rows(K, V, pos, dim, start, n) if _NATIVE else None
+    if views is None:
+        at = (slice(None),) * dim + (slice(start, start + n),)
+        return K[at], V[at], pos[at]
+    return views
+
+
 def pc_rope3d(x, pos, sections: Sequence[int], base: float = 10000.0, out_scale: float = 1.0) -> None:
     """x [H][n][D] (bf16/fp32, device) rotated in place by pos int32 [n][3] and multiplied by
     out_scale before the one rounding (folded_q_scale(scale) for queries that go to pc_score /
     pc_frame_attn with scale = PC_SCALE_FOLDED)."""
+    if _NATIVE:
+        r = _NATIVE.rope3d(x, pos, sections, base, out_scale)
+        if r is not None:
+            return _check(r)
     H, n, D = x.shape
     _rows_dense(x, "x")
     _check(lib().pc_rope3d(x.data_ptr(), _dtype_code(x), H, n, D, x.stride(0), pos.data_ptr(),
@@ -264,6 +321,11 @@ def pc_score(Qs, K, Nk: int, scale: float, lse=None, score=None, share_heads: bo
     picks the rows of Qs that score; None: all of them.  lse (fp32 [Hq][rows], optional) is
     indexed like the rows of Qs.  key_range = (begin, end): only these keys get a score (all of
     them still count in the softmax); the rest of `score` is left as it is."""
+    if _NATIVE and score is not None:
+        r = _NATIVE.score(Qs, K, Nk, scale, lse, score, share_heads, ws, q_rows, key_range)
+        if r is not None:
+            _check(r)
+            return score
     import torch
     Hq, n_qs, D = Qs.shape
     if q_rows is not None:
@@ -324,6 +386,12 @@ def pc_compact_workspace_bytes(Hkv: int, Nk_in: int, share_heads: bool = False) 
 def pc_compact(K, V, pos, score, segments, budgets, share_heads: bool = False, out=None, idx=None, ws=None):
     """Select and compact.  out = None compacts in place; out = (K_out, V_out, pos_out)
     writes there.  Returns (segments_out, Nk_out)."""
+    if _NATIVE:
+        r = _NATIVE.compact(K, V, pos, score, segments, budgets, share_heads, out, idx, ws)
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            _check(r)
     Hkv, _, D = K.shape
     _check_kv_layout(K, V, pos, out, share_heads)
     n = len(segments)
@@ -377,6 +445,12 @@ def pc_compact_batch(K, V, pos, score, segments, budgets, share_heads: bool = Fa
     layer axis.  phases: PC_COMPACT_SELECT, PC_COMPACT_GATHER or both (the two halves of
     pc_compact_batch_phase, for callers that overlap them on two streams; pass the same ws to
     both); stream: a torch stream (default: the current one).  Returns (segments_out, Nk_out)."""
+    if _NATIVE and phases == 3 and stream is None:
+        r = _NATIVE.compact_batch(K, V, pos, score, segments, budgets, share_heads, out, idx, ws)
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            _check(r)
     L, Hkv, _, D = K.shape
     _check_kv_layout(K, V, pos, out, share_heads, layer_axis=True)
     if ws is None and (int(phases) != 3 or stream is not None):
@@ -452,6 +526,11 @@ def pc_frame_attn_cut(dtype: int, Hq: int, Hkv: int, Nq: int, Nk: int, D: int, w
 def pc_frame_attn(Q, K, V, Nk: int, scale: float, O=None, lse=None, ws=None):
     """Q [Hq][Nq][D], K/V [Hkv][>=Nk][D] -> O [Hq][Nq][D] (same dtype).  ws: workspace for key shares,
     not to be shared by calls that may overlap; None: one of the call's own, from torch's allocator."""
+    if _NATIVE and O is not None:
+        r = _NATIVE.frame_attn(Q, K, V, Nk, scale, O, lse, ws)
+        if r is not None:
+            _check(r)
+            return O
     import torch
     Hq, Nq, D = Q.shape
     Hkv = K.shape[0]

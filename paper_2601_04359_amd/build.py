@@ -1,4 +1,4 @@
-"""Builds libpackcache.so (gfx950) in-tree with hipcc.  `python -m paper_2601_04359_amd.build`"""
+"""Builds libpackcache.so (gfx950) in-tree with hipcc, and the compiled half of the binding with g++.  `python -m paper_2601_04359_amd.build`"""
 from __future__ import annotations
 
 import os
@@ -11,6 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB_DIR = os.path.join(PKG, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libpackcache.so")
+MARSHAL_PATH = os.path.join(PKG, "_marshal.so")
 SOURCES = ["host.cpp", "rope.hip", "attn.hip", "score.hip", "compact.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,6 +24,19 @@ def _run(cmd):
     if p.returncode != 0:
         raise RuntimeError("command failed: " + " ".join(cmd) + "\n" + out)
     return out
+
+
+def build_marshal() -> str:
+    """The compiled half of the binding: host code against Python's and torch's headers."""
+    import sysconfig
+    import torch
+    at = os.path.dirname(torch.__file__)
+    lib = os.path.join(at, "lib")
+    return _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"),
+                 "-I" + os.path.join(at, "include"), "-I" + os.path.join(at, "include", "torch", "csrc", "api", "include"),
+                 "-I" + sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                 os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH,
+                 "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-Wl,-rpath," + lib])
 
 
 def build_library(verbose: bool = False) -> str:
@@ -40,6 +54,7 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         logs = list(ex.map(one, zip(SOURCES, objs)))
     logs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH]))
+    logs.append(build_marshal())
     if verbose:
         print("\n".join(l for l in logs if l))
     return LIB_PATH

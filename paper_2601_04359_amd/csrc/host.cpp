@@ -1,5 +1,6 @@
 // Host-only half of libpackcache: status strings, budgets (Sec. 3.4, Eq. 4-8) and the
 // segment bookkeeping of compaction.  No device work happens in this file.
+#include <float.h>
 #include <math.h>
 #include <string.h>
 
@@ -145,20 +146,29 @@ int active_window(int b_one, int w, int q_min) {
   return static_cast<int>(std::min<int64_t>(w, b_one / q_min));
 }
 
-// t_d = q_min + floor(free * num_d / den) with exact integers; leftovers to d = 1.
-void waterfill(int b_one, int q_min, const std::vector<BigU>& num, const BigU& den, int n_total,
-               int32_t* out) {
-  const int w = static_cast<int>(num.size());
+// t_d = q_min + floor(free * num_d / den) with exact integers; leftovers to d = 1.  share(d, free) is that
+// floor for d = 0 .. w - 1.
+template <class Share>
+void waterfill(int b_one, int q_min, int w, int n_total, Share&& share, int32_t* out) {
   const int64_t free_tokens = static_cast<int64_t>(b_one) - static_cast<int64_t>(w) * q_min;
   int64_t sum = 0;
   for (int d = 0; d < w; ++d) {
-    BigU a = num[d];
-    a.mul_small(static_cast<uint64_t>(free_tokens));
-    out[d] = static_cast<int32_t>(q_min + static_cast<int64_t>(floor_div_small_quotient(a, den)));
+    out[d] = static_cast<int32_t>(q_min + static_cast<int64_t>(share(d, static_cast<uint64_t>(free_tokens))));
     sum += out[d];
   }
   if (w > 0) out[0] += static_cast<int32_t>(b_one - sum);
   for (int d = w; d < n_total; ++d) out[d] = 0;
+}
+
+// floor(t) for t >= 0 known to within 2^-20, if that settles it.  The budgets' products are good to 2^-21 in
+// extended precision (below 2^31, at most kApproxTerms steps of relative error 2^-64), so the big integers are
+// needed only next to a whole number: 47 shares of Eq. 6 38 -> 2 us.
+constexpr int kApproxTerms = LDBL_MANT_DIG >= 64 ? 1024 : 0;
+bool floor_settled(long double t, uint64_t* q) {
+  constexpr long double kMargin = 1.0L / (1 << 20);
+  *q = static_cast<uint64_t>(t);
+  const long double r = t - static_cast<long double>(*q);
+  return r < 1.0L - kMargin && (r > kMargin || *q == 0);
 }
 
 }  // namespace
@@ -205,43 +215,62 @@ extern "C" int pc_budget(int mode, int n_frame_tokens, int n_past, double gamma,
 
   if (mode == PC_BUDGET_POW) {
     uint64_t mant;
-    int shift;
+    int shift, p_d = 0;
     dyadic(gamma, &mant, &shift);
-    BigU p(static_cast<uint64_t>(N));  // N * mant^d
+    BigU p(static_cast<uint64_t>(N));  // N * mant^p_d
+    long double approx = N;            // N * gamma^d
     for (int d = 1; d <= n_past; ++d) {
-      p.mul_small(mant);
-      const size_t s = static_cast<size_t>(shift) * d;
-      int64_t b = s >= p.bits() ? 0 : static_cast<int64_t>(p.shr_to_u64(s));
-      b = std::max<int64_t>(b, b_min);
+      approx *= gamma;
+      uint64_t q;
+      if (d > kApproxTerms || !floor_settled(approx, &q)) {
+        for (; p_d < d; ++p_d) p.mul_small(mant);
+        const size_t s = static_cast<size_t>(shift) * d;
+        q = s >= p.bits() ? 0 : p.shr_to_u64(s);
+      }
+      const int64_t b = std::max<int64_t>(static_cast<int64_t>(q), b_min);
       budget_out[d - 1] = static_cast<int32_t>(std::min<int64_t>(b, N));
     }
     return PC_OK;
   }
 
   const int we = active_window(N, n_past, b_min);
-  std::vector<BigU> num(we);
-  BigU den;
-  if (mode == PC_BUDGET_NORM) {
-    // rho^d / sum_j rho^j with rho = mant / 2^shift: scale both by 2^(shift * we).
-    uint64_t mant;
-    int shift;
-    dyadic(gamma, &mant, &shift);
-    BigU pw(1);
-    for (int d = 1; d <= we; ++d) {
-      pw.mul_small(mant);
-      num[d - 1] = pw;
-      num[d - 1].shl(static_cast<size_t>(shift) * (we - d));
-      den.add(num[d - 1]);
-    }
-  } else {  // PC_BUDGET_HALF: 2^-min(d, we-1), scaled by 2^(we-1); the shares sum to one
-    for (int d = 1; d <= we; ++d) {
-      num[d - 1] = BigU(1);
-      num[d - 1].shl(static_cast<size_t>(we - 1 - std::min(d, we - 1)));
-    }
-    den = BigU(1);
-    den.shl(static_cast<size_t>(std::max(we - 1, 0)));
+  if (mode == PC_BUDGET_HALF) {  // 2^-min(d, we-1); the shares sum to one
+    waterfill(N, b_min, we, n_past, [&](int d, uint64_t free_tokens) {
+      const int s = std::min(d + 1, we - 1);
+      return s < 64 ? free_tokens >> s : 0;
+    }, budget_out);
+    return PC_OK;
   }
-  waterfill(N, b_min, num, den, n_past, budget_out);
+  // PC_BUDGET_NORM: rho^d / sum_j rho^j
+  bool settled = we <= kApproxTerms / 3 - 2;
+  if (settled) {
+    std::vector<long double> pw(we);
+    long double x = 1, total = 0;
+    for (int d = 0; d < we; ++d) total += pw[d] = x *= gamma;
+    waterfill(N, b_min, we, n_past, [&](int d, uint64_t free_tokens) {
+      uint64_t q = 0;
+      settled = settled && floor_settled(static_cast<long double>(free_tokens) * pw[d] / total, &q);
+      return q;
+    }, budget_out);
+  }
+  if (settled) return PC_OK;
+  // rho = mant / 2^shift: numerators and denominator scaled by 2^(shift * we)
+  std::vector<BigU> num(we);
+  BigU den, pw(1);
+  uint64_t mant;
+  int shift;
+  dyadic(gamma, &mant, &shift);
+  for (int d = 1; d <= we; ++d) {
+    pw.mul_small(mant);
+    num[d - 1] = pw;
+    num[d - 1].shl(static_cast<size_t>(shift) * (we - d));
+    den.add(num[d - 1]);
+  }
+  waterfill(N, b_min, we, n_past, [&](int d, uint64_t free_tokens) {
+    BigU a = num[d];
+    a.mul_small(free_tokens);
+    return floor_div_small_quotient(a, den);
+  }, budget_out);
   return PC_OK;
 }
 

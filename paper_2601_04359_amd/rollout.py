@@ -82,8 +82,7 @@ class RollingLayer:
         """Views of the next n free rows: (K rows, V rows, pos rows [Hsel][n][3])."""
         if self.nk + n > self.capacity:
             raise ValueError(f"cache capacity {self.capacity} < {self.nk} + {n}")
-        a = self.nk
-        return self.K[:, a:a + n], self.V[:, a:a + n], self.pos[:, a:a + n]
+        return pk._rows(self.K, self.V, self.pos, 1, self.nk, n)
 
     def commit(self, n: int, kind: int, frame: int, rotate_with=None, valid=None) -> None:
         """Make the n reserved rows part of the cache.  rotate_with: int32 [n][3] device
@@ -150,9 +149,9 @@ class RollingLayer:
     # ---- one frame step -----------------------------------------------------------------------
     def budgets(self) -> list[int]:
         """Budget of every segment for the cache as it stands (anchors: their length)."""
-        n_past = sum(1 for s in self.segments if s[2] == pk.PC_SEG_FRAME)
         if self.mode == "dense":
             return [s[1] for s in self.segments]
+        n_past = pk._past_frames(self.segments)
         if self.mode == "pow":
             per_d = pk.pc_budget(pk.PC_BUDGET_POW, self.n_frame, n_past, self.gamma, self.b_min)
         else:
@@ -166,12 +165,11 @@ class RollingLayer:
         if self.mode == "dense":
             return
         budgets = self.budgets()
-        if all(b >= s[1] for s, b in zip(self.segments, budgets) if s[2] == pk.PC_SEG_FRAME):
-            return   # every frame is within its budget: nothing to score, nothing to move
         # only segments that lose rows at this step need scores (anchors never do, a frame that sits at
         # its budget does not either): the scoring covers the span from the first to the last of them
-        prunable = [s for s, b in zip(self.segments, budgets) if s[2] == pk.PC_SEG_FRAME and b < s[1]]
-        span = (prunable[0][0], prunable[-1][0] + prunable[-1][1])
+        span = pk._prunable_span(self.segments, budgets)
+        if span is None:
+            return   # every frame is within its budget: nothing to score, nothing to move
         pk.pc_score(Q, self.K, self.nk, self.call_scale, lse=lse, score=self.score, share_heads=self.share_heads,
                     ws=self._ws_score, q_rows=self.q_rows, key_range=span)
         self.segments, self.nk = pk.pc_compact(self.K, self.V, self.pos, self.score, self.segments,
@@ -242,8 +240,7 @@ class RollingStack:
         """Views of the next n free rows of every layer: K, V [L][Hkv][n][D], pos [L][Hsel][n][3]."""
         if self.nk + n > self.capacity:
             raise ValueError(f"cache capacity {self.capacity} < {self.nk} + {n}")
-        a = self.nk
-        return self.K[:, :, a:a + n], self.V[:, :, a:a + n], self.pos[:, :, a:a + n]
+        return pk._rows(self.K, self.V, self.pos, 2, self.nk, n)
 
     def commit(self, n: int, kind: int, frame: int, rotate_with=None) -> None:
         """Make the n reserved rows part of every layer's cache; rotate_with (int32 [n][3], device)
@@ -256,16 +253,12 @@ class RollingStack:
         self.nk = a + n
 
     def budgets(self) -> list[int]:
-        n_past = sum(1 for s in self.segments if s[2] == pk.PC_SEG_FRAME)
+        n_past = pk._past_frames(self.segments)
         if self.mode == "pow":
             per_d = pk.pc_budget(pk.PC_BUDGET_POW, self.n_frame, n_past, self.gamma, self.b_min)
         else:
             per_d = pk.pc_budget(MODES[self.mode], self.budget_tokens, n_past, self.gamma, self.b_min)
         return pk.segment_budgets(self.segments, per_d)
-
-    def _prunable_span(self, budgets):
-        prunable = [s for s, b in zip(self.segments, budgets) if s[2] == pk.PC_SEG_FRAME and b < s[1]]
-        return (prunable[0][0], prunable[-1][0] + prunable[-1][1]) if prunable else None
 
     def attend(self, layer: int, Q, O=None, lse=None):
         """Layer `layer`'s (rotated) queries over its cache as it stands -> O (and the log-sum-exp).  As
@@ -275,7 +268,7 @@ class RollingStack:
     def score_layer(self, layer: int, Q, lse=None) -> None:
         """Importance of layer `layer`'s cached keys under Q (lse: the log-sum-exp attend() gave for
         the same queries over the same cache; without it pc_score takes its extra pass)."""
-        span = self._prunable_span(self.budgets())
+        span = pk._prunable_span(self.segments, self.budgets())
         if span is None:
             return
         pk.pc_score(Q, self.K[layer], self.nk, self.call_scale, lse=lse, score=self.score[layer],
@@ -285,7 +278,7 @@ class RollingStack:
         """End of the frame step: every layer keeps, per past frame, its top-budget keys; one
         select launch and one gather launch for the whole stack, in place."""
         budgets = self.budgets()
-        if self._prunable_span(budgets) is None:
+        if pk._prunable_span(self.segments, budgets) is None:
             return
         self.segments, self.nk = pk.pc_compact_batch(self.K, self.V, self.pos, self.score, self.segments, budgets,
                                                      share_heads=self.share_heads, ws=self._ws_compact)

@@ -1300,3 +1300,80 @@ def test_step_captured_in_a_hip_graph_replays_to_the_eager_result():
         for i, (g, x) in enumerate(zip(got, want)):
             assert torch.equal(g, x), f"replay {replay}: output {i} differs from the eager run"
     pk.pc_compact_status(ws_c)
+
+
+def _marshalled_calls():
+    """Every call that the compiled half of the binding takes, as (name, call); a call makes its own outputs."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(4)
+    rand = lambda *shape: torch.randn(shape, device=DEV, generator=gen).to(torch.bfloat16)
+    Q, K, V = rand(4, 40, 128), rand(2, 90, 128), rand(2, 90, 128)
+    pos_q = torch.randint(0, 500, (40, 3), dtype=torch.int32, device=DEV, generator=gen)
+    pos = torch.randint(0, 500, (2, 90, 3), dtype=torch.int32, device=DEV, generator=gen)
+    sc = torch.rand((2, 90), device=DEV, generator=gen)
+    rows = torch.arange(0, 40, 3, dtype=torch.int32, device=DEV)
+    segs, budgets = [(0, 10, pk.PC_SEG_TEXT, -1), (10, 50, pk.PC_SEG_FRAME, 1), (60, 25, pk.PC_SEG_FRAME, 2)], [10, 20, 25]
+    empty = lambda n: torch.empty(n, dtype=torch.uint8, device=DEV)
+
+    def rope(x=None, sections=(32, 48, 48)):
+        x = Q.clone() if x is None else x
+        return pk.pc_rope3d(x, pos_q, sections, 1e4, out_scale=2), x
+
+    def score(K=K, **kw):
+        out = torch.zeros((2, 90), device=DEV)
+        r = pk.pc_score(Q, K, 90, 0.1, score=out, ws=empty(pk.pc_score_workspace_bytes(4, 2, 14, 90)), q_rows=rows,
+                        key_range=(10, 85), **kw)
+        return r is out, out
+
+    def compact(K=K, budgets=budgets, **kw):
+        k, v, p = K.clone(), V.clone(), pos.clone()
+        r = pk.pc_compact(k, v, p, sc, segs, budgets, ws=empty(pk.pc_compact_workspace_bytes(2, 85)), **kw)
+        return r, k[:, :r[1]], v[:, :r[1]], p[:, :r[1]]
+
+    def batch(idx=True, **kw):
+        k, v, p, s = (torch.stack([t, t.flip(0)]) for t in (K, V, pos, sc))
+        i = torch.zeros((2, 2, 55), dtype=torch.int32, device=DEV)
+        r = pk.pc_compact_batch(k, v, p, s, segs, budgets, idx=i, ws=empty(pk.pc_compact_batch_workspace_bytes(2, 2, 85)), **kw)
+        return r, k[:, :, :r[1]], v[:, :, :r[1]], p[:, :, :r[1]], i
+
+    def attn(Q=Q, V=V, **kw):
+        O, lse = torch.zeros_like(Q), torch.zeros(Q.shape[:2], device=DEV)
+        r = pk.pc_frame_attn(Q, K, V, 85, 0.1, O=O, lse=lse, **kw)
+        return r is O, O, lse
+
+    calls = dict(rope3d=rope, score=score, compact=compact, compact_batch=batch, frame_attn=attn)
+    refused = [lambda: rope(sections=(32, 48, 40)), lambda: rope(x=Q.transpose(0, 1)), lambda: score(K=K[..., :64]),
+               lambda: compact(K=K.to(torch.float16)), lambda: compact(budgets=[10, -1, 25]),
+               lambda: compact(out=(K.clone(), V.clone()[:, :80], pos.clone())), lambda: batch(share_heads=True),
+               lambda: attn(V=torch.cat([V, V], dim=1))]
+    return calls, refused
+
+
+def test_plain_calls_are_marshalled_alike_by_both_halves_of_the_binding(monkeypatch):
+    from paper_2601_04359_amd import binding
+    calls, refused = _marshalled_calls()
+    pk.pc_budget(pk.PC_BUDGET_POW, 10, 1, 0.5, 0)
+    native, seen = binding._NATIVE, []
+    assert native
+
+    class Spy:
+        def __getattr__(self, name):
+            f = getattr(native, name)
+            return lambda *a: seen.append((name, f(*a))) or seen[-1][1]
+
+    def outcome(call):
+        try:
+            return call()
+        except pk.PackCacheError as e:
+            return e.status, str(e)
+
+    same = lambda a, b: torch.equal(a, b) if torch.is_tensor(a) else a == b
+    for name, call in [*calls.items(), *((None, r) for r in refused)]:
+        seen.clear()
+        monkeypatch.setattr(binding, "_NATIVE", Spy())
+        got = outcome(call)
+        assert name is None or any(n == name and r is not None for n, r in seen)   # no fallback for a plain call
+        monkeypatch.setattr(binding, "_NATIVE", False)
+        want = outcome(call)
+        assert len(got) == len(want) and all(same(a, b) for a, b in zip(got, want)), (name, got, want)
+        assert name is not None or isinstance(want[0], int)

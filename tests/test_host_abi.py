@@ -256,6 +256,22 @@ def test_tables_marshal_the_same_from_any_kind_of_number():
     assert pk.pc_compact_plan([], []) == ([], 0)
 
 
+@pytest.mark.parametrize("gamma", [0.5, 1.0, 0.25, 0.75, 0.85, 1 - 2.0 ** -53, float(np.nextafter(0.5, 1)), 2.0 ** -40, 5e-324])
+def test_budgets_are_exact_next_to_whole_numbers(gamma):
+    # products that are whole numbers, or miss one by less than extended precision resolves, settle exactly
+    from fractions import Fraction
+    g = Fraction(gamma)
+    for n in (1, 7, 64, 4032, 4096, 2 ** 31 - 1):
+        for n_past in (1, 6, 47):
+            want = [min(n, max(3, int(n * g ** d))) for d in range(1, n_past + 1)]
+            assert pk.pc_budget(pk.PC_BUDGET_POW, n, n_past, gamma, 3) == want
+            for mode, w in ((pk.PC_BUDGET_NORM, lambda d: g ** d / sum(g ** j for j in range(1, n_past + 1))),
+                            (pk.PC_BUDGET_HALF, lambda d: Fraction(1, 2 ** min(d, n_past - 1)))):
+                want = [int(n * w(d)) for d in range(1, n_past + 1)]
+                want[0] += n - sum(want)
+                assert pk.pc_budget(mode, n, n_past, gamma, 0) == want
+
+
 def test_tables_may_be_tensors_and_iterators():
     import torch
     plain = [(0, 4, pk.PC_SEG_TEXT, -1), (4, 9, pk.PC_SEG_COND, 0), (13, 9, pk.PC_SEG_FRAME, 1)]
