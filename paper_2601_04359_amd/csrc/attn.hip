@@ -66,20 +66,6 @@ __device__ __forceinline__ void stage_tile(const uint16_t* __restrict__ base_h, 
   }
 }
 
-// Division by a number that the host knows, for 0 <= n < 2^31: n / d = n m >> sh with sh = 31 + ceil(log2 d)
-// and m = floor(2^sh / d) + 1 (m d exceeds 2^sh by at most 2^(sh - 31), which n times is below 2^sh).
-struct Divisor {
-  uint32_t m;
-  int sh, d;
-  explicit Divisor(int by) : sh(31), d(by) {
-    while (sh < 62 && (1ll << (sh - 31)) < by) ++sh;
-    m = static_cast<uint32_t>((1ull << sh) / by + 1);
-  }
-  __device__ __forceinline__ int of(int n) const {
-    return static_cast<int>(static_cast<uint64_t>(static_cast<uint32_t>(n)) * m >> sh);
-  }
-};
-
 // The query rows of one KV head are numbered through its `rep` query heads: row rho is row
 // rho % Nq of head kvh * rep + rho / Nq.  A tile of rows may span heads, so a frame that is no
 // multiple of the tile leaves at most one part-filled tile per KV head instead of one per head.

@@ -111,14 +111,14 @@ struct RowState {
 struct RowPtrs {
   const uint16_t* p[2];
 };
-__device__ __forceinline__ RowPtrs row_ptrs(const uint16_t* Qs, const int32_t* q_rows, int rho, int n_rows, int n_qs,
-                                            int head0, int64_t q_stride_h) {
+__device__ __forceinline__ RowPtrs row_ptrs(const uint16_t* Qs, const int32_t* q_rows, int rho, int n_rows,
+                                            const Divisor& by_qs, int head0, int64_t q_stride_h) {
   int head[2], row[2];
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const int r = min(rho + b * 32, n_rows - 1), in_group = r / n_qs;
+    const int r = min(rho + b * 32, n_rows - 1), in_group = by_qs.of(r);
     head[b] = head0 + in_group;
-    row[b] = r - in_group * n_qs;
+    row[b] = r - in_group * by_qs.d;
     if (q_rows) row[b] = q_rows[row[b]];
   }
 #pragma unroll
@@ -190,8 +190,8 @@ __device__ __forceinline__ void mask_keys(f32x16 (&s)[2], int k0, int Nk, int g)
 template <bool kUnitC>
 __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
     const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K,
-    float2* __restrict__ part, int Hq, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c,
-    int n_row_tiles, int n_splits) {
+    float2* __restrict__ part, int rep, Divisor by_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c,
+    Divisor by_tiles, Divisor by_heads, int per) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -200,14 +200,13 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   const int l32 = lane & 31, g = lane >> 5;
   // logical order: split slowest, so the work-groups of one XCD stream the same keys
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int Hkv = Hq / rep, split = L / (Hkv * n_row_tiles);
-  const int kvh = (L / n_row_tiles) % Hkv, tile = L % n_row_tiles;
-  const int n_rows = rep * n_qs;   // scoring rows of the KV head's group, numbered head after head
+  const int unit = by_tiles.of(L), tile = L - unit * by_tiles.d, Hkv = by_heads.d;
+  const int split = by_heads.of(unit), kvh = unit - split * Hkv;
+  const int n_rows = rep * by_qs.d;   // scoring rows of the KV head's group, numbered head after head
   const int row0 = tile * kBlockRows + wave * kWaveRows;
   const uint16_t* Kh = K + kvh * k_stride_h;
 
   const int n_tiles = (Nk + kTileRows - 1) / kTileRows;
-  const int per = (n_tiles + n_splits - 1) / n_splits;
   const int t_begin = min(split * per, n_tiles), t_end = min(t_begin + per, n_tiles);
   const int n = t_end - t_begin;
   if (n <= 0) {  // the host never launches an empty split; keep the partials defined anyway
@@ -239,7 +238,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   f32x16 sA[2], sB[2];
 
   float psum[2] = {0.f, 0.f};
-  const RowPtrs qrow = row_ptrs(Qs, q_rows, row0 + l32, n_rows, n_qs, kvh * rep, q_stride_h);
+  const RowPtrs qrow = row_ptrs(Qs, q_rows, row0 + l32, n_rows, by_qs, kvh * rep, q_stride_h);
   stage(0);
   stage(1);
   stage(2);
@@ -333,12 +332,13 @@ struct RowNorm {
   const int32_t* q_rows;
   const float2* part;        // [split][Hkv][rep * n_qs]
   int64_t part_stride;       // Hkv * rep * n_qs
-  int n_splits, rep, n_qs;
+  int n_splits, rep;
+  Divisor by_qs;             // by n_qs
 };
 // v[i]: row rho0 + i * step.  The loads of all of them are in flight together.
 template <int kN>
 __device__ __forceinline__ void row_norms(const RowNorm& a, int kvh, int rho0, int step, float (&v)[kN]) {
-  const int n_rows = a.rep * a.n_qs;
+  const int n_rows = a.rep * a.by_qs.d;
   if (a.ready) {
 #pragma unroll
     for (int i = 0; i < kN; ++i) v[i] = a.ready[static_cast<int64_t>(kvh) * n_rows + min(rho0 + i * step, n_rows - 1)];
@@ -346,9 +346,9 @@ __device__ __forceinline__ void row_norms(const RowNorm& a, int kvh, int rho0, i
     int head[kN], row[kN];
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
-      const int rho = min(rho0 + i * step, n_rows - 1), in_group = rho / a.n_qs;
+      const int rho = min(rho0 + i * step, n_rows - 1), in_group = a.by_qs.of(rho);
       head[i] = kvh * a.rep + in_group;
-      row[i] = rho - in_group * a.n_qs;
+      row[i] = rho - in_group * a.by_qs.d;
       if (a.q_rows) row[i] = a.q_rows[row[i]];
     }
 #pragma unroll
@@ -385,7 +385,7 @@ __device__ __forceinline__ void row_norms(const RowNorm& a, int kvh, int rho0, i
 }
 // The `ready` array, for calls whose many work-groups would each do the same merging.
 __global__ __launch_bounds__(256) void score_row_norms(RowNorm a, float* __restrict__ out) {
-  const int rho = blockIdx.x * 256 + threadIdx.x, n_rows = a.rep * a.n_qs;
+  const int rho = blockIdx.x * 256 + threadIdx.x, n_rows = a.rep * a.by_qs.d;
   float v[1];
   row_norms(a, blockIdx.y, rho, 0, v);
   if (rho < n_rows) out[static_cast<int64_t>(blockIdx.y) * n_rows + rho] = v[0];
@@ -413,8 +413,8 @@ __device__ __forceinline__ void col_epilogue(int i, const f32x16 (&s)[2], const 
 template <bool kUnitC>
 __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
     const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K, RowNorm norm,
-    float* __restrict__ out, int64_t out_stride_h, int64_t out_stride_split, int rep, int n_qs, int Nk, int64_t q_stride_h,
-    int64_t k_stride_h, float c, int n_key_blocks, int n_qsplits) {
+    float* __restrict__ out, int64_t out_stride_h, int64_t out_stride_split, int rep, Divisor by_qs, int Nk,
+    int64_t q_stride_h, int64_t k_stride_h, float c, Divisor by_blocks, Divisor by_qsplits, int per) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   lds_u8* smem = (lds_u8*)smem_raw;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -425,7 +425,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
   const int l32 = lane & 31, g = lane >> 5;
   // logical order: (kv head, query split) slowest, so the work-groups of one XCD stream the same queries
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int kb = L % n_key_blocks, qsplit = (L / n_key_blocks) % n_qsplits, kvh = L / (n_key_blocks * n_qsplits);
+  const int unit = by_blocks.of(L), kb = L - unit * by_blocks.d;
+  const int kvh = by_qsplits.of(unit), qsplit = unit - kvh * by_qsplits.d;
   const int key0 = kb * kBlockRows + wave * kWaveRows;
   const uint16_t* Kh = K + kvh * k_stride_h;
 
@@ -438,8 +439,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
       kf[b][s] = *reinterpret_cast<const bf16x8*>(Kh + static_cast<int64_t>(key) * kD + s * 16 + g * 8);
   }
 
-  const int n_rows = rep * n_qs, n_vt = (n_rows + kTileRows - 1) / kTileRows;
-  const int per = (n_vt + n_qsplits - 1) / n_qsplits;
+  const int n_rows = rep * by_qs.d, n_vt = (n_rows + kTileRows - 1) / kTileRows;
   const int t_end = min((qsplit + 1) * per, n_vt);
 
   int a_off[8];
@@ -485,9 +485,9 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
       int head[kBatch], row[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        const int rho = min(t0 * kTileRows + r0 + i * kThreads, n_rows - 1), in_group = rho / n_qs;
+        const int rho = min(t0 * kTileRows + r0 + i * kThreads, n_rows - 1), in_group = by_qs.of(rho);
         head[i] = kvh * rep + in_group;
-        row[i] = rho - in_group * n_qs;
+        row[i] = rho - in_group * by_qs.d;
         if (q_rows) row[i] = q_rows[row[i]];
       }
       float v[kBatch];
@@ -561,14 +561,16 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
 // the streamed rows in steps of 32 by turns, each through an LDS double buffer of its own, two steps
 // ahead and without a barrier in the loop, and are merged through LDS once: the row pass cuts its
 // keys less often, and the column pass leaves no partial sums to add up in another launch.  The products
-// of a step and the exponentials of the one before are interleaved as in stream_phase.  Bound: latency
-// (5.5-6 us with one step, of which the launch is about 2).  8/2 heads x 100 rows x 1,804 keys: row
-// pass 9.5 us and its merge 3.5 -> 8.0 us, column pass 10.8 us and its reduction 3.8 -> 8.7 us.
+// of a step and the exponentials of the one before are interleaved as in stream_phase.  Bound: latency.
+// The stationary rows come through LDS: each wave fetching all 64 as fragments (32 bytes of each of 32 rows
+// per load, 128 KB per work-group) was a third of the call.  8/2 heads x 100 rows x 1,804 keys: both
+// passes 16.1 -> 10.9 us, the column pass alone 8.6 -> 5.4; 2/1 x 64 x 300 14.7 -> 9.1.
 constexpr int kSmallStep = 32;
 constexpr int kSmallStepBytes = kSmallStep * kRowBytes;
 constexpr int kSmallRing = 8 * 2 * kSmallStepBytes;            // 8 waves x two steps
 constexpr int kSmallMaxRows = 2048;                            // scoring rows pass 2 prepares in LDS
-constexpr size_t kSmallRowSmem = kSmallRing + 8 * kWaveRows * 8;
+constexpr int kSmallMergeRows = 3 * 8 * kSmallStep;            // the same with the row pass's shares to merge
+constexpr size_t kSmallRowSmem = kSmallRing + 8 * kWaveRows * 8 + kWaveRows * kRowBytes;
 constexpr size_t kSmallColSmem = kSmallRing + kSmallMaxRows * 12 + 8 * kWaveRows * 4;
 
 // The rows of step i of a wave have landed when at most the next step's eight loads are in flight.
@@ -605,8 +607,8 @@ __device__ __forceinline__ void small_phase(const bf16x8 (&f)[8], const bf16x8 (
 
 __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
     const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K,
-    float2* __restrict__ part, int Hkv, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c,
-    int n_row_tiles, int n_splits) {
+    float2* __restrict__ part, int rep, Divisor by_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h, float c,
+    Divisor by_tiles, Divisor by_heads, int per) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -614,10 +616,11 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
   const lds_u8* ring = (lds_u8*)smem_raw + wave * 2 * kSmallStepBytes;
   const uint32_t ring_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int split = L / (Hkv * n_row_tiles), kvh = (L / n_row_tiles) % Hkv, tile = L % n_row_tiles;
-  const int n_rows = rep * n_qs;
+  const int unit = by_tiles.of(L), tile = L - unit * by_tiles.d, Hkv = by_heads.d;
+  const int split = by_heads.of(unit), kvh = unit - split * Hkv;
+  const int n_rows = rep * by_qs.d;
   const uint16_t* Kh = K + kvh * k_stride_h;
-  const int steps_all = (Nk + kSmallStep - 1) / kSmallStep, per = (steps_all + n_splits - 1) / n_splits;
+  const int steps_all = (Nk + kSmallStep - 1) / kSmallStep;
   const int t_end = min((split + 1) * per, steps_all), t_first = split * per + wave;
   const int n = t_first < t_end ? (t_end - t_first + 7) / 8 : 0;   // steps of this wave
   auto stage = [&](int i) {
@@ -628,22 +631,43 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
       dma_16B_at(w.base, row_offset(w, row, k_chunk_pos(row, lane & 15)), ring_w + (i & 1) * kSmallStepBytes + q * 1024);
     }
   };
-  const RowPtrs qrow = row_ptrs(Qs, q_rows, tile * kWaveRows + l32, n_rows, n_qs, kvh * rep, q_stride_h);
-  if (n > 0) stage(0);
-  if (n > 1) stage(1);
-  bf16x8 qf[2][8];
+  // The stationary rows go through LDS once (every wave holds all of them: 16 KB instead of 128 from L2),
+  // eight per wave; their indices are scalar loads, which direct loads are not waited for.
+  const lds_u8* q_tile = (lds_u8*)smem_raw + kSmallRing + 8 * kWaveRows * 8;
+  {
+    int64_t at[8];
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
+    for (int j = 0; j < 8; ++j) {
+      const int rho = min(tile * kWaveRows + wave * 8 + j, n_rows - 1), in_group = by_qs.of(rho);
+      int row = rho - in_group * by_qs.d;
+      if (q_rows) row = q_rows[row];
+      at[j] = (kvh * rep + in_group) * q_stride_h + static_cast<int64_t>(row) * kD;
+    }
+    if (n > 0) stage(0);
+    const uint32_t to = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(q_tile)) + wave * 8 * kRowBytes;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[b][s] = *reinterpret_cast<const bf16x8*>(qrow.p[b] + g * 8 + s * 16);
+    for (int i = 0; i < 2; ++i) {
+      const int64_t* four = at + i * 4;
+      const int which = lane >> 4, row = wave * 8 + i * 4 + which;
+      const int64_t src = which == 0 ? four[0] : which == 1 ? four[1] : which == 2 ? four[2] : four[3];
+      dma_16B(Qs + src + k_chunk_pos(row, lane & 15) * 8, to + i * 1024);
+    }
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
+  if (n > 1) {
+    stage(1);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  __syncthreads();
   int a_off[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  bf16x8 qf[2][8];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[b][s] = lds_frag(q_tile + b * 32 * kRowBytes + a_off[s]);
 
   RowState st;
   st.m[0] = st.m[1] = kNoMax;
@@ -664,6 +688,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
     if (i + 1 < n) {
       fetch(i + 1);
       small_phase<false>(f, qf, nxt, NoInit{}, [&](int e) { row_epilogue(e, cur, st, psum, c); });
+    } else if (i == 0) {   // the only step: there is no reference yet, so row_commit forms its sums
+      psum[0] = psum[1] = INFINITY;
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) row_epilogue(e, cur, st, psum, c);
@@ -705,8 +731,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_small(
 template <bool kUnitC>
 __global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
     const uint16_t* __restrict__ Qs, const int32_t* __restrict__ q_rows, const uint16_t* __restrict__ K, RowNorm norm,
-    float* __restrict__ out, int64_t out_stride_h, int rep, int n_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h,
-    float c, int n_key_blocks) {
+    float* __restrict__ out, int64_t out_stride_h, int rep, Divisor by_qs, int Nk, int64_t q_stride_h, int64_t k_stride_h,
+    float c, Divisor by_blocks) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -717,12 +743,23 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
   float* s_norm = reinterpret_cast<float*>(smem_raw + kSmallRing + kSmallMaxRows * 8);
   float* s_sum = s_norm + kSmallMaxRows;
   const int L = xcd_contiguous_index(blockIdx.x, gridDim.x);
-  const int kb = L % n_key_blocks, kvh = L / n_key_blocks;
-  const int key0 = kb * kWaveRows;
+  const int kvh = by_blocks.of(L), key0 = (L - kvh * by_blocks.d) * kWaveRows;
   const uint16_t* Kh = K + kvh * k_stride_h;
-  const int n_rows = rep * n_qs, n_steps = (n_rows + kSmallStep - 1) / kSmallStep;
+  const int n_rows = rep * by_qs.d, n_steps = (n_rows + kSmallStep - 1) / kSmallStep;
   const int n = wave < n_steps ? (n_steps - wave + 7) / 8 : 0;   // steps of this wave: wave, wave + 8, ...
 
+  // The stationary keys go through LDS once (every wave holds all of them), eight per wave: keys 0..31 lie
+  // in the second step's buffer of wave 0, 32..63 in that of wave 1, which is filled only behind them.
+  auto key_half = [&](int b) { return (lds_u8*)smem_raw + b * 2 * kSmallStepBytes + kSmallStepBytes; };
+  {
+    const RowWindow w = row_window(Kh, key0, Nk);
+    const uint32_t to = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(key_half(wave >> 2))) + (wave & 3) * 8 * kRowBytes;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = wave * 8 + i * 4 + (lane >> 4);
+      dma_16B_at(w.base, row_offset(w, row, k_chunk_pos(row, lane & 15)), to + i * 1024);
+    }
+  }
   // a thread prepares the rows threadIdx.x + 512 i; everything is loaded before anything is waited for
   constexpr int kPrep = kSmallMaxRows / kThreads;
   int head[kPrep], row[kPrep];
@@ -730,17 +767,10 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
   for (int i = 0; i < kPrep; ++i) {
     if (i * kThreads >= n_steps * kSmallStep) break;   // uniform
     const int r = min(static_cast<int>(threadIdx.x) + i * kThreads, n_rows - 1);
-    head[i] = kvh * rep + r / n_qs;
-    row[i] = r % n_qs;
+    const int in_group = by_qs.of(r);
+    head[i] = kvh * rep + in_group;
+    row[i] = r - in_group * by_qs.d;
     if (q_rows) row[i] = q_rows[row[i]];
-  }
-  bf16x8 kf[2][8];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int key = min(key0 + b * 32 + l32, Nk - 1);
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-      kf[b][s] = *reinterpret_cast<const bf16x8*>(Kh + static_cast<int64_t>(key) * kD + s * 16 + g * 8);
   }
   {
     float v[kPrep];
@@ -752,10 +782,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
       s_norm[threadIdx.x + i * kThreads] = v[i];
     }
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   auto stage = [&](int i) {
     const int64_t* src = s_src + (wave + i * 8) * kSmallStep + (lane >> 4);
@@ -770,11 +797,24 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_small(
       dma_16B(Qs + at[q] + k_chunk_pos(q * 4 + (lane >> 4), lane & 15) * 8, to + q * 1024);
   };
   if (n > 0) stage(0);
-  if (n > 1) stage(1);
 
   int a_off[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s) a_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  bf16x8 kf[2][8];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[b][s] = lds_frag(key_half(b) + a_off[s]);
+  if (n_steps > 8) {   // second steps: every wave has its keys
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (n > 1) stage(1);
+  }
   auto load_lq = [&](int i, f32x16& lq) {   // normalisers of the 16 rows this lane holds of step i
     const float* base = s_norm + (wave + i * 8) * kSmallStep + g * 4;
 #pragma unroll
@@ -1123,17 +1163,18 @@ WsLayout ws_layout(int Hq, int Hkv, int n_qs, int Nk, int /*share_heads*/) {
 }
 
 // How the two passes of a bf16 call are cut: their form (512 stationary rows per work-group, or 64) and
-// the shares of the streamed axis.  The estimates are microseconds, fitted to 22 shapes (100 to 512
-// scoring rows, 2 to 24 heads, 596 to 100,000 keys) in both forms with every number of shares: `start`
-// is what a work-group costs beside its steps, a step gets slower as the compute units fill up, a
-// further round costs a new start, and pass 2 merges the row pass's shares, itself or behind a launch of
-// 2-5 us that does (8/2 heads, 512 rows a head x 20,000 keys: 57.4 us with 32 shares of 512 rows, 60.1 with 4
-// of 64 rows, which a merge priced by the share alone had picked).  Row pass: 1.6 % slower than
-// the best cut on average (at most 1 us); column pass: 0.3 %.  Where the lines lie, both sides measured
-// (16/4 heads unless stated): row pass, 512 rows a head x 2,633 keys 12.9 us with 64 rows against 18.5
-// with 512, x 7,199 22.4 against 23.9, x 20,000 56.6 against 46.5, 100 rows a head x 30,000 25.2
-// against 35.4; column pass, 8/2 heads, 100 x 1,804 8.7 us against 10.5, 6/2 heads, 330 x 3,000 11.8
-// against 12.1, 512 x 2,633 18.3 against 15.2.
+// the shares of the streamed axis.  The estimates are microseconds, fitted to 63 shapes (100 to 512
+// scoring rows a head, 8 to 24 heads, 600 to 20,000 keys) in both forms with every number of shares that
+// makes 64 to 768 work-groups: `start` is what a work-group costs beside its steps, a step gets slower as
+// the compute units fill up, a further round costs a new start, and pass 2 merges the row pass's
+// shares, itself or behind a launch of 2-5 us that does.  The row pass it picks is 0.9 % off the best on
+// average.  Where the lines lie, both sides measured (16/4 heads unless stated): row pass, both passes of
+// the call with 64 rows against 512: 100 rows a head x 4,500 keys 19.4 / 25.3 us, 330 x 2,600 24.5 / 27.4,
+// 330 x 12,000 49.7 / 51.5, 512 x 12,000 65.7 / 65.6, 512 x 20,000 98.4 / 96.6; column pass, fed with
+// log-sum-exps: 100 x 7,200 10.7 / 12.9, 100 x 12,000 16.1 / 15.4, 330 x 2,600 11.5 / 15.4, 330 x 7,200
+// 20.0 / 18.5, 512 x 2,600 14.4 / 15.8, 512 x 4,500 25.6 / 18.7.  With shares to merge in every
+// work-group the column pass keeps to three steps of 64 keys' form: there it gains 2-4 us (8/2 heads, 170
+// x 1,804 14.3 / 18.2), with 2,048 rows 0.5 or nothing (8/2, 512 x 4,500 27.2 / 26.5).
 struct PassCost {
   double start, step, step_filled, round;
   double of(int blocks, int steps) const {
@@ -1145,6 +1186,9 @@ struct RowPlan {
   bool small;
   int n_splits;
 };
+// Forming the normalisers in the column pass's work-groups: a few loads per thread, once per compute unit,
+// are 1-2 us less than a launch in between; with 16 shares of 1,024 rows they are 2-6 us more.
+bool merges_in_pass_2(int rows_here, int n_splits) { return ceil_div(rows_here, kThreads) * n_splits <= 16; }
 RowPlan plan_rows(int Hkv, int rows, int Nk, bool unit_c) {
   RowPlan best = {false, 1};
   double best_cost = 1e30;
@@ -1161,8 +1205,8 @@ RowPlan plan_rows(int Hkv, int rows, int Nk, bool unit_c) {
       }
     }
   };
-  consider(false, kBlockRows, kTileRows, 1, {6.9, unit_c ? 1.38 : 1.49, 0.11, 4.3});
-  consider(true, kWaveRows, kSmallStep, 8, {6.1, 1.05, 0.13, 4.3});
+  consider(false, kBlockRows, kTileRows, 1, {6.9, unit_c ? 1.29 : 1.40, 0.08, 4.5});
+  consider(true, kWaveRows, kSmallStep, 8, {4.5, 0.85, 0.05, 4.3});
   return best;
 }
 struct ColPlan {
@@ -1171,9 +1215,6 @@ struct ColPlan {
 };
 ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
   const int n_vt = ceil_div(rows, kTileRows), base = Hkv * ceil_div(nkr, kBlockRows);
-  // Forming the normalisers in the work-groups: a few loads per thread, once per compute unit, are 1-2 us
-  // less than a launch in between; with 16 shares of 1,024 rows they are 2-6 us more.
-  auto few_loads = [&](int rows_here) { return ceil_div(rows_here, kThreads) * n_splits <= 16; };
   ColPlan best = {false, false, 1};
   double best_cost = 1e30;
   for (int s = 1; s <= std::min(kMaxQSplits, n_vt); ++s) {
@@ -1183,13 +1224,13 @@ ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
     const double c = PassCost{7.36, 1.12, 0.36, 4.46}.of(base * s, per) + reduce;
     if (c < best_cost) {
       best_cost = c;
-      best = {false, base * s <= 256 && few_loads((per + kStages) * kTileRows), s};
+      best = {false, base * s <= 256 && merges_in_pass_2((per + kStages) * kTileRows, n_splits), s};
     }
   }
-  if (rows <= kSmallMaxRows) {
-    const double c = PassCost{6.03, 1.45, -0.04, 4.46}.of(Hkv * ceil_div(nkr, kWaveRows), ceil_div(rows, 8 * kSmallStep)) +
+  if (rows <= (n_splits > 1 ? kSmallMergeRows : kSmallMaxRows)) {
+    const double c = PassCost{3.7, 1.2, 0.0, 2.0}.of(Hkv * ceil_div(nkr, kWaveRows), ceil_div(rows, 8 * kSmallStep)) +
                      2.9e-4 * rows;   // the normalisers of all rows, in every work-group
-    if (c < best_cost) best = {true, few_loads(rows), 1};
+    if (c < best_cost) best = {true, merges_in_pass_2(rows, n_splits), 1};
   }
   return best;
 }
@@ -1271,6 +1312,7 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
     auto allow = [](auto kernel, size_t bytes, std::atomic<uint64_t>& done) {
       return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes, done, "pc_score");
     };
+    const Divisor by_qs(n_qs);
     const RowPlan row = plan_rows(Hkv, rep * n_qs, Nk, unit_c);
     const ColPlan col = plan_cols(Hkv, rep * n_qs, nkr, lse ? 1 : row.n_splits);
     if (lse == nullptr) {
@@ -1278,16 +1320,18 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
       if (row.small) {
         if (int rc = allow(score_rowpass_small, kSmallRowSmem, row_ok[2])) return rc;
         score_rowpass_small<<<n_row_tiles * Hkv * row.n_splits, kThreads, kSmallRowSmem, s>>>(
-            q, q_rows, k, ws_part, Hkv, rep, n_qs, Nk, q_stride_h, k_stride_h, c, n_row_tiles, row.n_splits);
+            q, q_rows, k, ws_part, rep, by_qs, Nk, q_stride_h, k_stride_h, c, Divisor(n_row_tiles), Divisor(Hkv),
+            ceil_div(ceil_div(Nk, kSmallStep), row.n_splits));
       } else {
         const auto kernel = unit_c ? score_rowpass_bf16<true> : score_rowpass_bf16<false>;
         if (int rc = allow(kernel, kRowSmem, row_ok[unit_c])) return rc;
         kernel<<<n_row_tiles * Hkv * row.n_splits, kThreads, kRowSmem, s>>>(
-            q, q_rows, k, ws_part, Hq, rep, n_qs, Nk, q_stride_h, k_stride_h, c, n_row_tiles, row.n_splits);
+            q, q_rows, k, ws_part, rep, by_qs, Nk, q_stride_h, k_stride_h, c, Divisor(n_row_tiles), Divisor(Hkv),
+            ceil_div(ceil_div(Nk, kTileRows), row.n_splits));
       }
       PC_CHECK_LAUNCH("pc_score row pass");
     }
-    RowNorm norm = {nullptr, lse, lse_stride_h, q_rows, ws_part, static_cast<int64_t>(Hq) * n_qs, row.n_splits, rep, n_qs};
+    RowNorm norm = {nullptr, lse, lse_stride_h, q_rows, ws_part, static_cast<int64_t>(Hq) * n_qs, row.n_splits, rep, by_qs};
     const bool direct = col.n_qsplits == 1 && !share_heads;
     float* col_out = direct ? score_r : ws_col;
     const int64_t col_stride = direct ? score_stride_h : nkr;
@@ -1300,15 +1344,16 @@ extern "C" int pc_score(const void* Qs, const void* K, int dtype, int Hq, int Hk
       const auto kernel = unit_c ? score_colpass_small<true> : score_colpass_small<false>;
       if (int rc = allow(kernel, kSmallColSmem, col_ok[2 + unit_c])) return rc;
       const int n_key_blocks = ceil_div(nkr, kWaveRows);
-      kernel<<<n_key_blocks * Hkv, kThreads, kSmallColSmem, s>>>(q, q_rows, k_r, norm, col_out, col_stride, rep, n_qs, nkr,
-                                                                 q_stride_h, k_stride_h, c, n_key_blocks);
+      kernel<<<n_key_blocks * Hkv, kThreads, kSmallColSmem, s>>>(q, q_rows, k_r, norm, col_out, col_stride, rep, by_qs, nkr,
+                                                                 q_stride_h, k_stride_h, c, Divisor(n_key_blocks));
     } else {
       const auto kernel = unit_c ? score_colpass_bf16<true> : score_colpass_bf16<false>;
       if (int rc = allow(kernel, kColSmem, col_ok[unit_c])) return rc;
       const int n_key_blocks = ceil_div(nkr, kBlockRows);
       kernel<<<n_key_blocks * Hkv * col.n_qsplits, kThreads, kColSmem, s>>>(
-          q, q_rows, k_r, norm, col_out, col_stride, static_cast<int64_t>(Hkv) * nkr, rep, n_qs, nkr, q_stride_h,
-          k_stride_h, c, n_key_blocks, col.n_qsplits);
+          q, q_rows, k_r, norm, col_out, col_stride, static_cast<int64_t>(Hkv) * nkr, rep, by_qs, nkr, q_stride_h,
+          k_stride_h, c, Divisor(n_key_blocks), Divisor(col.n_qsplits),
+          ceil_div(ceil_div(rep * n_qs, kTileRows), col.n_qsplits));
     }
     PC_CHECK_LAUNCH("pc_score column pass");
     if (!direct) {
