@@ -107,6 +107,7 @@ def lib() -> C.CDLL:
         L.pc_score_cut.argtypes = [C.c_int] * 5 + [C.c_float, C.c_int, i32p]
         L.pc_frame_attn.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i64,
                                     i64, i64, C.c_float, vp, vp, vp, sz, vp]
+        L.pc_last_error_detail()    # touches the library's thread-local storage (see build.build_marshal)
         _LIB = L
     if _NATIVE is None and "torch" in sys.modules:
         _bind_native(_LIB)
