@@ -451,14 +451,16 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 // attn_bf16_kernel makes of the same rows, each an eighth as long; K and V come through L2 once per
 // 32 rows instead of once per 256, which is why large calls do not take this form (a step of 8 x 32
 // keys takes 1.4 us with every compute unit at it: 0.78 PFLOP/s at most).  8/2 heads x 252 rows x
-// 1,179 keys: 34 us in 8 work-groups of 256 rows, 12.4 us un-split in 64 of these (three key shares took
-// 11.9; the estimate picks one).  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
+// 1,179 keys: 34 us in 8 work-groups of 256 rows, 10.2 us un-split in 64 of these (11.3 before the query rows
+// came through LDS; 2/1 x 184 x 900 8.9 -> 7.8).  The loop runs at what a compute unit draws from L2 (128 KB a
+// step in 1.17 us).  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
 // ------------------------------------------------------------------------------------------
 constexpr int kSmallRows = 32;
 constexpr int kSmallKeys = 32;                                  // keys per wave and step
 constexpr int kSmallTileBytes = kSmallKeys * kRowBytes;
 constexpr int kSmallOBytes = kSmallRows * kD * 4;               // a wave's O on its way to the merge
-constexpr size_t kSmallSmem = 8 * (kSmallOBytes + kSmallRows * 8);
+constexpr int kSmallMlBytes = 8 * kSmallRows * 8;
+constexpr size_t kSmallSmem = 8 * kSmallOBytes + kSmallMlBytes + kSmallRows * kRowBytes;
 static_assert(2 * kSmallTileBytes <= kSmallOBytes, "a wave stages K and V in the LDS of its merge piece");
 
 __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
@@ -495,18 +497,24 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     }
   };
   const int k_first = k_begin + wave * kSmallKeys;
-  stage(k_first);
-  bf16x8 qf[8];
+  // The query rows go through LDS once, four per wave: every wave holds all of them, and as fragments from
+  // memory (32 bytes of each row per load) they were 64 KB per work-group.
+  const lds_u8* q_tile = (lds_u8*)smem_raw + 8 * kSmallOBytes + kSmallMlBytes;
   {
-    const uint16_t* qrow = Q + at_row.head * q_stride_h + static_cast<int64_t>(at_row.row) * kD + g * 8;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
+    const int row = wave * 4 + (lane >> 4);
+    const RowAt from = row_at(min(tile * kSmallRows + row, n_rows - 1), kvh, rep, by_nq);
+    dma_16B(Q + from.head * q_stride_h + static_cast<int64_t>(from.row) * kD + k_chunk_pos(row, lane & 15) * 8,
+            static_cast<uint32_t>(reinterpret_cast<uintptr_t>(q_tile)) + wave * 1024);
   }
+  stage(k_first);
   int k_off[8], v_off[4];  // as in attn_bf16_kernel
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  asm volatile("s_waitcnt vmcnt(16)" ::: "memory");   // this wave's queries: the 16 loads behind them are its first keys
+  __syncthreads();
+  bf16x8 qf[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) qf[s] = lds_frag(q_tile + k_off[s]);
   {
     const int r = lane & 15, G = (lane >> 4) & 1;
     const int row = g * 4 + (r >> 2);
@@ -741,11 +749,11 @@ constexpr int kMaxKeySplits = 16;
 // 29,500 keys) in both forms with 1 to 16 shares: `start` is what a work-group costs beside its
 // steps, a step is 64 keys here and 8 x 32 keys there and gets slower as the compute units fill up,
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
-// (512 bytes written and read per row and share).  The cut it picks is at most 4 % slower than the
-// best of them on any of the 24, 0.5 % on average.  Where the line lies, both sides measured: 8/2
-// heads x 252 rows x 1,179 keys, 12.4 us with 32 rows against 18.8 with 256 (and 34 un-split); 16/4
-// x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x 7,455,
-// 92.9 against 67.4.
+// (512 bytes written and read per row and share).  On 144 further shapes (2/1 to 24/8 heads, 64 to 1,000
+// rows, 300 to 8,000 keys) the cut it picks is 0.75 % off the best on average.  Where the line lies, both
+// sides measured: 8/2 heads x 252 rows x 1,179 keys, 10.2 us with 32 rows against 18.8 with 256 (and 34
+// un-split); 16/4 x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x
+// 7,455, 92.9 against 67.4.
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
 // rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
 // third of the partial rows and a round less: 363 us, 381 with all of them cut).
@@ -789,7 +797,7 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
     }
   };
   consider(false, kBM, kBN, kBN, 8.1, 1.14, 0.33);
-  consider(true, kSmallRows, kSmallKeys, 8 * kSmallKeys, 6.0, 1.17, 0.19);
+  consider(true, kSmallRows, kSmallKeys, 8 * kSmallKeys, 4.9, 1.17, 0.19);
   return best;
 }
 // ------------------------------------------------------------------------------------------
