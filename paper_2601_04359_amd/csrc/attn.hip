@@ -301,18 +301,27 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   stage_k(0);
   stage_v(0);
   stage_k(1);
+  // The wave's 32 query rows, whole rows through the slots that nothing is staged in yet (those of K(2),
+  // K(3), V(1), V(2): half a slot per wave), behind the first fetches: one memory latency covers all of them.
   bf16x8 qf[8];
   {
-    const uint16_t* qrow = Q + at_row.head * q_stride_h + static_cast<int64_t>(at_row.row) * kD + g * 8;
+    constexpr int kFree[4] = {2, 3, kStages + 1, kStages + 2};
+    const int slot = (wave >> 1) == 0 ? kFree[0] : (wave >> 1) == 1 ? kFree[1] : (wave >> 1) == 2 ? kFree[2] : kFree[3];
+    const int at = slot * kTileBytes + (wave & 1) * 32 * kRowBytes;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + s * 16);
-    // Behind the first fetches, so that one memory latency covers all of them.  Make the compiler
-    // retire these loads here (and with them, in order, the direct ones before): otherwise it guards
-    // every use of qf inside the loop with s_waitcnt vmcnt(7..0), which also drains the K/V loads.
+    for (int i = 0; i < 8; ++i) {
+      const int row = i * 4 + (lane >> 4);
+      const RowAt from = row_at(min(rho - l32 + row, n_rows - 1), kvh, rep, by_nq);
+      dma_16B(Q + from.head * q_stride_h + static_cast<int64_t>(from.row) * kD + k_chunk_pos(row, lane & 15) * 8,
+              __builtin_amdgcn_readfirstlane(lds0 + at + i * 1024));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = lds_frag(smem + at + k_off[s]);
 #pragma unroll
     for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
   }
-  __syncthreads();   // K(0), V(0), K(1) have landed: they were fetched before the queries
+  __syncthreads();   // K(0), V(0), K(1) have landed; every wave has its queries and the slots are free
   stage_k(2);
   stage_v(1);
   stage_k(3);
