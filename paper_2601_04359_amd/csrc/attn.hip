@@ -243,7 +243,6 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   const int n_rows = rep * by_nq.d;    // query rows of the KV head
   const int rho = tile * kBM + wave * 32 + l32;   // the row this lane owns
   const bool active = rho - l32 < n_rows;  // wave-uniform
-  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, by_nq);
 
   const uint16_t* Kh = K + kvh * kv_stride_h;
   const uint16_t* Vh = V + kvh * kv_stride_h;
@@ -394,9 +393,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
     if (j0 + 3 >= n) break;
     tile_body(j0 + 3, std::integral_constant<int, 3>{});
   }
-  if (!active) return;
   // ---- drain: O += V_B(n-1) P_B(n-1) ----
-  {
+  if (active) {
     const lds_u8* v_half = smem + v_slot(n - 1) + 32 * kRowBytes;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
@@ -418,35 +416,52 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   }
   const float l_tot = wave_half_sum(l_run);
   const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
+  // The output leaves through LDS in whole rows: a lane holds 4 dims of its row at a time, 32 rows apart.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // tiles past the end may still be landing
+  __syncthreads();
+  if (!active) return;
+  const int rows_w = min(32, n_rows - (rho - l32));   // rows of this wave that exist
+  lds_u8* mine = smem + wave * kTileBytes;
   if (!whole) {  // one of several key shares: un-normalised O, reference and sum for the merge
-    if (rho < n_rows) {
-      const int64_t at_s = split * rows_cut + at - row_whole;
-      float* prow = part_o + at_s * kD;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = o[db][a * 4 + e];
-          *reinterpret_cast<f32x4*>(prow + db * 32 + a * 8 + g * 4) = v;
-        }
-      if (g == 0) part_ml[at_s] = make_float2(m_ref, l_tot);
-    }
-    return;
-  }
-  const float inv = 1.f / l_tot;
-  if (rho < n_rows) {
-    uint16_t* orow = O + at_row.head * o_stride_h + static_cast<int64_t>(at_row.row) * kD;
+    const int64_t first = split * rows_cut + at - l32 - row_whole;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        u32x2 out;
-        out[0] = pack_bf16x2(o[db][a * 4 + 0] * inv, o[db][a * 4 + 1] * inv);
-        out[1] = pack_bf16x2(o[db][a * 4 + 2] * inv, o[db][a * 4 + 3] * inv);
-        *reinterpret_cast<u32x2*>(orow + db * 32 + a * 8 + g * 4) = out;
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = o[db][a * 4 + e];
+        *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(mine + l32 * 512 + ((db * 8 + a * 2 + g) ^ l32) * 16) = v;
       }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int row = i * 2 + g;
+      const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(mine + row * 512 + l32 * 16);
+      if (row < rows_w) *reinterpret_cast<f32x4*>(part_o + (first + row) * kD + (l32 ^ row) * 4) = v;
+    }
+    if (g == 0 && l32 < rows_w) part_ml[first + l32] = make_float2(m_ref, l_tot);
+    return;
+  }
+  const float inv = 1.f / l_tot;
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      u32x2 out;
+      out[0] = pack_bf16x2(o[db][a * 4 + 0] * inv, o[db][a * 4 + 1] * inv);
+      out[1] = pack_bf16x2(o[db][a * 4 + 2] * inv, o[db][a * 4 + 3] * inv);
+      *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(mine + l32 * kRowBytes + k_chunk_pos(l32, db * 4 + a) * 16 + g * 8) = out;
+    }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = i * 4 + (lane >> 4), chunk = k_chunk_pos(row, lane & 15);
+    const u32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(mine + row * kRowBytes + (lane & 15) * 16);
+    if (row < rows_w) {
+      const RowAt to = row_at(rho - l32 + row, kvh, rep, by_nq);
+      *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + chunk * 8) = v;
+    }
+  }
+  if (rho < n_rows) {
     if (lse != nullptr && g == 0)
       lse[at] = (m_ref + log2f(l_tot)) * 0.6931471805599453f;
   }
