@@ -502,8 +502,6 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   const int split = take_share(unit, n_tiles);
   const int kvh = by_tiles_q.of(unit), tile = unit - kvh * by_tiles_q.d;
   const int n_rows = rep * by_nq.d;
-  const int rho = tile * kSmallRows + l32;
-  const RowAt at_row = row_at(min(rho, n_rows - 1), kvh, rep, by_nq);
   const uint16_t* Kh = K + kvh * kv_stride_h;
   const uint16_t* Vh = V + kvh * kv_stride_h;
 
@@ -627,64 +625,61 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   l = wave_half_sum(l);
 
   // merge in wave order: a wave's O goes to the LDS its keys came through, piece i = accumulators
-  // 4 i .. 4 i + 3 of every lane; thread (wave w, lane) then adds up pieces w and w + 8
-  auto piece = [&](int w, int i) {
+  // 4 i .. 4 i + 3 of every lane = dims 8 i + 4 g .. + 3 of its row, lanes permuted by i so that the reads
+  // below use every bank; a thread then adds up eight dims of a row, and a row leaves whole.
+  auto piece = [&](int w, int i, int of_lane) {
     return reinterpret_cast<__attribute__((address_space(3))) f32x4*>((lds_u8*)smem_raw + w * kSmallOBytes + i * 1024 +
-                                                                      lane * 16);
+                                                                      (of_lane ^ i) * 16);
   };
   auto* s_ml = reinterpret_cast<__attribute__((address_space(3))) float*>((lds_u8*)smem_raw + 8 * kSmallOBytes);
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int a = 0; a < 4; ++a)
-      *piece(wave, db * 4 + a) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
+      *piece(wave, db * 4 + a, lane) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
   if (g == 0) {
     s_ml[(wave * kSmallRows + l32) * 2] = m;
     s_ml[(wave * kSmallRows + l32) * 2 + 1] = l;
   }
   __syncthreads();
+  const int row = threadIdx.x >> 4, i = threadIdx.x & 15, rho = tile * kSmallRows + row;
   float mw[8], M = -INFINITY, lt = 0.f;
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
-    mw[w] = s_ml[(w * kSmallRows + l32) * 2];
+    mw[w] = s_ml[(w * kSmallRows + row) * 2];
     M = fmaxf(M, mw[w]);
   }
   f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
     const float wt = __builtin_amdgcn_exp2f(mw[w] - M);
-    lt += wt * s_ml[(w * kSmallRows + l32) * 2 + 1];
+    lt += wt * s_ml[(w * kSmallRows + row) * 2 + 1];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const f32x4 v = *piece(w, wave + 8 * t);
+      const f32x4 v = *piece(w, i, t * 32 + row);
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[t][e] += wt * v[e];
     }
   }
   if (rho >= n_rows) return;
   const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;
-  // piece i of a lane is dims 32 (i / 4) + 8 (i % 4) + 4 g .. + 3 of its row
   if (part_o != nullptr) {
     const int64_t at_s = split * rows_all + at;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int i = wave + 8 * t;
-      *reinterpret_cast<f32x4*>(part_o + at_s * kD + (i >> 2) * 32 + (i & 3) * 8 + g * 4) = acc[t];
-    }
-    if (wave == 0 && g == 0) part_ml[at_s] = make_float2(M, lt);
+    for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4*>(part_o + at_s * kD + i * 8 + t * 4) = acc[t];
+    if (i == 0) part_ml[at_s] = make_float2(M, lt);
     return;
   }
   const float inv = 1.f / lt;
-  uint16_t* orow = O + at_row.head * o_stride_h + static_cast<int64_t>(at_row.row) * kD;
+  const RowAt to = row_at(rho, kvh, rep, by_nq);
+  u32x4 out;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const int i = wave + 8 * t;
-    u32x2 out;
-    out[0] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
-    out[1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
-    *reinterpret_cast<u32x2*>(orow + (i >> 2) * 32 + (i & 3) * 8 + g * 4) = out;
+    out[t * 2] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
+    out[t * 2 + 1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
   }
-  if (lse != nullptr && wave == 0 && g == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
+  *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + i * 8) = out;
+  if (lse != nullptr && i == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
 }
 
 // ln(2^m l), rounded once: m may reach hundreds where l's logarithm is small
