@@ -430,14 +430,18 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
   const int key0 = kb * kBlockRows + wave * kWaveRows;
   const uint16_t* Kh = K + kvh * k_stride_h;
 
-  bf16x8 kf[2][8];
+  // The wave's 64 keys come through its eighth of the ring as whole rows, 32 at a time (as fragments from
+  // memory they were 32 bytes of a row per load, lines evicted between loads): the first half while the
+  // row indices are on their way, the second while the normalisers are.
+  auto stage_keys = [&](int b) {
+    const RowWindow w = row_window(Kh, key0 + b * 32, Nk);
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int key = min(key0 + b * 32 + l32, Nk - 1);
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-      kf[b][s] = *reinterpret_cast<const bf16x8*>(Kh + static_cast<int64_t>(key) * kD + s * 16 + g * 8);
-  }
+    for (int i = 0; i < 8; ++i) {
+      const int row = i * 4 + (lane >> 4);
+      dma_16B_at(w.base, row_offset(w, row, k_chunk_pos(row, lane & 15)), lds0 + (wave * 8 + i) * 1024);
+    }
+  };
+  stage_keys(0);
 
   const int n_rows = rep * by_qs.d, n_vt = (n_rows + kTileRows - 1) / kTileRows;
   const int t_end = min((qsplit + 1) * per, n_vt);
@@ -474,22 +478,41 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
   f32x16 initA, initB;  // kUnitC: start values of the next sA / sB products, fetched one phase ahead
   auto startA = [&](int) -> const f32x16& { return initA; };
   auto startB = [&](int) -> const f32x16& { return initB; };
+  constexpr int kBatch = 4;
+  int head[kBatch], row[kBatch];   // where the rows lie that this thread prepares
+  auto find_rows = [&](int first) {
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int rho = min(first + i * kThreads, n_rows - 1), in_group = by_qs.of(rho);
+      head[i] = kvh * rep + in_group;
+      row[i] = rho - in_group * by_qs.d;
+      if (q_rows) row[i] = q_rows[row[i]];
+    }
+  };
+  bf16x8 kf[2][8];
+  auto take_keys = [&](int b) {   // all that is in flight has landed
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[b][s] = lds_frag(smem + wave * 8 * 1024 + a_off[s]);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+  bool first_rows = true;
+  find_rows(qsplit * per * kTileRows + threadIdx.x);
+#pragma unroll
+  for (int i = 0; i < kBatch; ++i) asm volatile("" : "+v"(row[i]));
+  take_keys(0);
+  stage_keys(1);
   for (int t0 = qsplit * per; t0 < t_end; t0 += kPrepTiles) {   // one turn but for thousands of scoring rows
     const int n = min(kPrepTiles, t_end - t0);
     // Sources and normalisers of the turn's rows, and of the kStages tiles after it that are fetched or
     // looked up but never used.  In the loop no load but the direct ones is then in flight: the
     // compiler waits for its own loads in order, which would drain the ring with them.
     // (16/4 heads x 512 rows x 193,792 keys: 377 -> 364 us.)
-    constexpr int kBatch = 4;
     for (int r0 = threadIdx.x; r0 < (n + kStages) * kTileRows; r0 += kBatch * kThreads) {
-      int head[kBatch], row[kBatch];
-#pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int rho = min(t0 * kTileRows + r0 + i * kThreads, n_rows - 1), in_group = by_qs.of(rho);
-        head[i] = kvh * rep + in_group;
-        row[i] = rho - in_group * by_qs.d;
-        if (q_rows) row[i] = q_rows[row[i]];
-      }
+      if (!first_rows) find_rows(t0 * kTileRows + r0);
+      first_rows = false;
       float v[kBatch];
       row_norms(norm, kvh, t0 * kTileRows + r0, kThreads, v);
 #pragma unroll
@@ -499,10 +522,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_colpass_bf16(
           s_norm[r0 + i * kThreads] = v[i];
         }
     }
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[b][s]));
+    if (t0 == qsplit * per) take_keys(1);
     __syncthreads();
     stage(0, src_of(0));
     stage(1, src_of(1));
