@@ -42,7 +42,7 @@ constexpr int kTileRows = 64;        // streamed rows per LDS slot
 constexpr int kRowBytes = kD * 2;
 constexpr int kTileBytes = kTileRows * kRowBytes;
 constexpr int kStages = 4;
-constexpr size_t kRowSmem = kStages * kTileBytes;
+constexpr size_t kRowSmem = kStages * kTileBytes + 8 * 32 * kRowBytes;   // the ring, 32 stationary rows per wave
 constexpr int kPrepTiles = 64;       // tiles whose rows pass 2 prepares in LDS at a time
 constexpr int kPrepRows = (kPrepTiles + kStages) * kTileRows;
 constexpr size_t kColSmem = kStages * kTileBytes + kPrepRows * 12;
@@ -106,28 +106,6 @@ __device__ __forceinline__ void stream_phase(const lds_u8* half, const lds_u8* n
 struct RowState {
   float m[2], l[2];
 };
-// Rows rho and rho + 32 of the scoring rows of a group (numbered head after head; clamped).  The row
-// index is waited for here: behind direct loads the wait would take those with it.
-struct RowPtrs {
-  const uint16_t* p[2];
-};
-__device__ __forceinline__ RowPtrs row_ptrs(const uint16_t* Qs, const int32_t* q_rows, int rho, int n_rows,
-                                            const Divisor& by_qs, int head0, int64_t q_stride_h) {
-  int head[2], row[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int r = min(rho + b * 32, n_rows - 1), in_group = by_qs.of(r);
-    head[b] = head0 + in_group;
-    row[b] = r - in_group * by_qs.d;
-    if (q_rows) row[b] = q_rows[row[b]];
-  }
-#pragma unroll
-  for (int b = 0; b < 2; ++b) asm volatile("" : "+v"(row[b]));
-  RowPtrs r;
-#pragma unroll
-  for (int b = 0; b < 2; ++b) r.p[b] = Qs + head[b] * q_stride_h + static_cast<int64_t>(row[b]) * kD;
-  return r;
-}
 struct NoInit {
   __device__ const f32x16& operator()(int) const { __builtin_unreachable(); }
 };
@@ -238,22 +216,46 @@ __global__ __launch_bounds__(kThreads, 1) void score_rowpass_bf16(
   f32x16 sA[2], sB[2];
 
   float psum[2] = {0.f, 0.f};
-  const RowPtrs qrow = row_ptrs(Qs, q_rows, row0 + l32, n_rows, by_qs, kvh * rep, q_stride_h);
-  stage(0);
-  stage(1);
-  stage(2);
-  bf16x8 qf[2][8];   // behind the first fetches: one memory latency covers both
+  // The wave's 64 rows come through LDS of its own as whole rows, 32 at a time, between the first fetches (as
+  // fragments from memory they were 32 bytes of a row per load, lines evicted between loads).  Lane l finds
+  // row l.
+  bf16x8 qf[2][8];
+  {
+    int64_t at;
+    {
+      const int r = min(row0 + lane, n_rows - 1), in_group = by_qs.of(r);
+      int row = r - in_group * by_qs.d;
+      if (q_rows) row = q_rows[row];
+      asm volatile("" : "+v"(row));
+      at = (kvh * rep + in_group) * q_stride_h + static_cast<int64_t>(row) * kD;
+    }
+    const uint32_t mine = kStages * kTileBytes + wave * 32 * kRowBytes;
+    auto fetch = [&](int b) {
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
+      for (int i = 0; i < 8; ++i) {
+        const int row = i * 4 + (lane >> 4);
+        dma_16B(Qs + __shfl(at, b * 32 + row) + k_chunk_pos(row, lane & 15) * 8,
+                __builtin_amdgcn_readfirstlane(lds0 + mine + i * 1024));
+      }
+    };
+    auto take = [&](int b) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[b][s] = *reinterpret_cast<const bf16x8*>(qrow.p[b] + g * 8 + s * 16);
+      for (int s = 0; s < 8; ++s) qf[b][s] = lds_frag(smem + mine + a_off[s]);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    fetch(0);
+    stage(0);
+    asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    take(0);
+    fetch(1);
+    stage(1);
+    stage(2);
+    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    take(1);
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[b][s]));
-  asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  __syncthreads();
+  __syncthreads();   // the first tile has landed: it was fetched before the second half of the rows
   bf16x8 ring[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) ring[r] = lds_frag(slot(0) + a_off[r]);
