@@ -1208,9 +1208,10 @@ struct RowPlan {
   bool small;
   int n_splits;
 };
-// Forming the normalisers in the column pass's work-groups: a few loads per thread, once per compute unit,
-// are 1-2 us less than a launch in between; with 16 shares of 1,024 rows they are 2-6 us more.
-bool merges_in_pass_2(int rows_here, int n_splits) { return ceil_div(rows_here, kThreads) * n_splits <= 16; }
+// Forming the normalisers in the column pass's work-groups, while their keys are on their way: some loads per
+// thread, once per compute unit, against a launch in between.  24/8 heads x 512 x 12,608 keys (20 loads) 75.4
+// us with the launch, 70.7 without; 16/4 x 100 x 20,000 (18) 34.8 / 32.9; with 32 they were 2-6 us more.
+bool merges_in_pass_2(int rows_here, int n_splits) { return ceil_div(rows_here, kThreads) * n_splits <= 24; }
 RowPlan plan_rows(int Hkv, int rows, int Nk, bool unit_c) {
   RowPlan best = {false, 1};
   double best_cost = 1e30;
@@ -1246,7 +1247,9 @@ ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
     const double c = PassCost{7.36, 1.12, 0.36, 4.46}.of(base * s, per) + reduce;
     if (c < best_cost) {
       best_cost = c;
-      best = {false, base * s <= 256 && merges_in_pass_2((per + kStages) * kTileRows, n_splits), s};
+      // several rounds of work-groups would each merge again; a log-sum-exp is just read (24/8 heads x 512 x
+      // 9,000 keys, two rounds: 37.5 us behind a launch, 36.4 without; from five rounds on no difference)
+      best = {false, base * s <= (n_splits == 1 ? 1024 : 256) && merges_in_pass_2((per + kStages) * kTileRows, n_splits), s};
     }
   }
   if (rows <= (n_splits > 1 ? kSmallMergeRows : kSmallMaxRows)) {
