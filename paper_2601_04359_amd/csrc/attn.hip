@@ -1019,12 +1019,12 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
       continue;
     }
     const int row = wave * kF32Rows + t * 16 + r;
-    float* mine = s_o + row * D + kg * 16;
+    // 16-byte piece c of row i at place c ^ (i % 16): the 16 rows of a wave's store use every bank
 #pragma unroll
     for (int b = 0; b < kB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<f32x4*>(mine + b * 64 + i * 4) =
+        *reinterpret_cast<f32x4*>(s_o + row * D + ((b * 16 + kg * 4 + i) ^ r) * 4) =
             f32x4{o[t][b][0][i], o[t][b][1][i], o[t][b][2][i], o[t][b][3][i]};
     if (kg == 0) {
       s_m[row] = m[t];
@@ -1049,7 +1049,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     for (int w = 0; w < kWaves; ++w) {
       const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);
       lt += wt * s_l[w * kF32Rows + row];
-      acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + col);
+      acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + (col / 4 ^ (row & 15)) * 4);
     }
     const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
     if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
