@@ -694,6 +694,23 @@ def test_score_bf16_short_512_row_passes(hq, hkv, n_qs, nk, step, fold):
         assert ((got - want).abs() <= 2e-7 + rel * want).all(), ((got - want).abs() / (want + 1e-30)).max().item()
 
 
+# one score for all heads of a call whose query rows are cut: heads in one and in two rounds of eight, the
+# parts' and the heads' sums in their order
+@pytest.mark.parametrize("hq,hkv,n,nk,begin", [(16, 1, 512, 700, 0), (16, 4, 512, 4600, 3), (8, 8, 2100, 513, 0), (12, 12, 2100, 700, 65)])
+def test_score_shared_heads_are_the_heads_added_in_order(hq, hkv, n, nk, begin):
+    assert pk.pc_score_cut(hq, hkv, n, nk, LN2, True, nk - begin)[3] > 1
+    rng = np.random.default_rng(hq * nk)
+    q, k = (dev(synth.to_bf16(rng.standard_normal(s).astype(np.float32)), "bf16") for s in ((hq, n, 128), (hkv, nk, 128)))
+    lse = torch.full((hq, n), 20.0, dtype=torch.float32, device=DEV)
+    per_head = host(pk.pc_score(q, k, nk, LN2, lse=lse, key_range=(begin, nk)))[:, begin:]
+    got = host(pk.pc_score(q, k, nk, LN2, lse=lse, share_heads=True, key_range=(begin, nk)))[0, begin:]
+    want = np.zeros(nk - begin, np.float32)
+    for h in range(hkv):
+        want = want + per_head[h]
+    assert np.isfinite(want).all() and (want > 0).all()
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("fold", [False, True])
 def test_score_with_supplied_lse_matches_internal_pass(fold):
     w = synth.midsize()
