@@ -149,12 +149,12 @@ __device__ void select_wave(const float* __restrict__ sc, int len, int k, int32_
 template <int kItems>
 __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ score,
                                                     int64_t score_stride_h, int32_t* __restrict__ idx,
-                                                    int64_t idx_stride_h, SegTable tab, Divisor by_hsel,
+                                                    int64_t idx_stride_h, SegTable tab, int hsel,
                                                     int64_t score_stride_l, int64_t idx_stride_l) {
-  const int s = blockIdx.x, layer = by_hsel.of(blockIdx.y), head = blockIdx.y - layer * by_hsel.d;
-  const int64_t sc_off = layer * score_stride_l + head * score_stride_h;
+  const int s = blockIdx.x, h = blockIdx.y;  // h runs over layers x selection heads
+  const int64_t sc_off = (h / hsel) * score_stride_l + (h % hsel) * score_stride_h;
   const int start = tab.start[s], len = tab.len[s], keep = tab.keep[s];
-  int32_t* out = idx + layer * idx_stride_l + head * idx_stride_h + tab.dst[s];
+  int32_t* out = idx + (h / hsel) * idx_stride_l + (h % hsel) * idx_stride_h + tab.dst[s];
   if (keep <= 0) return;
   if (!tab.prune[s]) {  // anchors, current frame, or a frame within budget: keep every row
     for (int e = threadIdx.x; e < len; e += 64) out[e] = start + e;
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
                                                            int64_t score_stride_h,
                                                            int32_t* __restrict__ idx, int64_t idx_stride_h,
                                                            SegTable tab, int32_t* __restrict__ clear,
-                                                           int n_clear, Divisor by_hsel, int64_t score_stride_l,
+                                                           int n_clear, int hsel, int64_t score_stride_l,
                                                            int64_t idx_stride_l) {
   constexpr int kBits = 11, kBins = 1 << kBits, kOwn = kBins / kThr, kWaves = kThr / 64;  // bins per thread
   static_assert(kOwn == 8 || kOwn == 2, "a thread reads its bins with two 16-byte loads or one of 8 bytes");
@@ -201,14 +201,13 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
     for (int i = b * kThr + threadIdx.x; i < n_clear; i += nb * kThr) clear[i] = 0;
   }
   const int start = tab.start[s], len = tab.len[s], k = tab.keep[s];
-  const int layer = by_hsel.of(h), head = h - layer * by_hsel.d;
-  int32_t* out = idx + layer * idx_stride_l + head * idx_stride_h + tab.dst[s];
+  int32_t* out = idx + (h / hsel) * idx_stride_l + (h % hsel) * idx_stride_h + tab.dst[s];
   if (k <= 0) return;  // block-uniform
   if (!tab.prune[s]) {
     for (int e = threadIdx.x; e < len; e += kThr) out[e] = start + e;
     return;
   }
-  const float* sc = score + layer * score_stride_l + head * score_stride_h + start;
+  const float* sc = score + (h / hsel) * score_stride_l + (h % hsel) * score_stride_h + start;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int e0 = t * kItems;
   uint32_t key[kItems];
@@ -586,15 +585,14 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
 
 __global__ __launch_bounds__(64) void select_rows_kernel(
     const float* __restrict__ score, int64_t score_stride_h, int32_t* __restrict__ idx, int64_t idx_stride_h,
-    SegTable tab, int32_t* __restrict__ clear, int n_clear, Divisor by_hsel, int64_t score_stride_l,
-    int64_t idx_stride_l) {
+    SegTable tab, int32_t* __restrict__ clear, int n_clear, int hsel, int64_t score_stride_l, int64_t idx_stride_l) {
   constexpr int kRows = PC_MAX_SELECT_LEN / 64;                     // 64 full rows at most
   constexpr int kBits = 11;
   __shared__ __align__(16) int hist[1 << kBits];
   const int lane = threadIdx.x;
   const int s = blockIdx.x, h = blockIdx.y;  // wave-uniform, like everything read from the table
   for (int i = (h * gridDim.x + s) * 64 + lane; i < n_clear; i += gridDim.x * gridDim.y * 64) clear[i] = 0;
-  const int layer = by_hsel.of(h), head = h - layer * by_hsel.d;
+  const int layer = __builtin_amdgcn_readfirstlane(h / hsel), head = __builtin_amdgcn_readfirstlane(h % hsel);
   const int start = tab.start[s], len = tab.len[s], k = tab.keep[s];
   int32_t* out = idx + layer * idx_stride_l + head * idx_stride_h + tab.dst[s];
   if (k <= 0) return;
@@ -625,19 +623,19 @@ template <int cpr /* 16-byte chunks per row */, int kRows /* packed rows per wor
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     const u32x4* __restrict__ K, const u32x4* __restrict__ V, const int32_t* __restrict__ pos,
     u32x4* __restrict__ Ko, u32x4* __restrict__ Vo, int32_t* __restrict__ pos_o,
-    const int32_t* __restrict__ idx, int64_t idx_stride_h, int share_heads, int Nk_in, int Nk_out,
+    const int32_t* __restrict__ idx, int64_t idx_stride_h, int share_heads, int Hkv, int Nk_in, int Nk_out,
     int64_t in_stride_c, int64_t out_stride_c,
     int64_t pos_stride_h, int64_t pos_out_stride_h, GatherSync* sync, int32_t* flags,
-    int chunks_per_head, SegTable tab, Divisor by_layer, Divisor by_heads, int64_t in_stride_lc, int64_t out_stride_lc,
+    int chunks_per_head, SegTable tab, int n_layers, int64_t in_stride_lc, int64_t out_stride_lc,
     int64_t pos_stride_l, int64_t pos_out_stride_l, int64_t idx_stride_l) {
   __shared__ int s_ticket;
   // launch order: layer by layer, the KV heads of a layer side by side (a few long sequential
   // streams at a time suit the memory better than one stream per (layer, head) all at once)
-  const int Hkv = by_heads.d;
-  const int l = by_layer.of(blockIdx.x), in_layer = blockIdx.x - l * by_layer.d;
-  int cc = by_heads.of(in_layer);
-  const int h = in_layer - cc * Hkv;
+  const int per_layer = gridDim.x / n_layers;
+  const int l = blockIdx.x / per_layer, in_layer = blockIdx.x % per_layer;
+  const int h = in_layer % Hkv;
   const int vh = l * Hkv + h;            // (layer, KV head) pair
+  int cc = in_layer / Hkv;
   if constexpr (kInPlace) {  // chunks of a head are taken in ticket order, not in launch order
     if (threadIdx.x == 0) s_ticket = atomicAdd(&sync->ticket[vh][0], 1);
     __syncthreads();
@@ -645,7 +643,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     // A ticket outside the launch's chunks means the counters were not cleared by the SELECT half
     // of this call (GATHER alone, or on another workspace): flag it and move nothing rather than
     // index the flags with it.  Block-uniform, and before any other barrier.
-    if (cc < 0 || static_cast<int64_t>(cc) * Hkv >= by_layer.d) {
+    if (cc < 0 || cc >= per_layer / Hkv) {
       if (threadIdx.x == 0) __hip_atomic_store(&sync->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
@@ -1145,7 +1143,6 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
   }
 
   const dim3 sgrid(n_seg, hsel * n_layers);
-  const Divisor by_hsel(hsel);
   // the select kernel also clears the in-place gather's counters and flags (contiguous in ws)
   int32_t* clear = in_place ? reinterpret_cast<int32_t*>(sync) : nullptr;
   const int n_clear = in_place ? static_cast<int>(lay.clear_bytes / sizeof(int32_t)) : 0;
@@ -1153,7 +1150,7 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
     // indices and cleared counters come from an earlier SELECT call with the same arguments
   } else if (max_prune_len > kRowsSelectMinLen && max_prune_len <= PC_MAX_SELECT_LEN &&
              n_seg * hsel * n_layers >= kRowsSelectMinUnits)
-    select_rows_kernel<<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, by_hsel,
+    select_rows_kernel<<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel,
                                              score_stride_l, idx_stride_layer);
   else if (max_prune_len <= PC_MAX_SELECT_LEN) {
     // Long segments, and at most one per compute unit: 1,024 threads each, a quarter of the serial work
@@ -1165,12 +1162,12 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
                         : wide                  ? select_block_kernel<4, 1024>
                                                 : select_block_kernel<16, 256>;
     const int threads = wide ? 1024 : 256;
-    kernel<<<sgrid, threads, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, by_hsel,
-                                      score_stride_l, idx_stride_layer);
+    kernel<<<sgrid, threads, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, clear, n_clear, hsel, score_stride_l,
+                                      idx_stride_layer);
   }
   else
   {
-    select_kernel<0><<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, by_hsel, score_stride_l,
+    select_kernel<0><<<sgrid, 64, 0, st>>>(score, score_stride_h, idx, idx_stride, tab, hsel, score_stride_l,
                                            idx_stride_layer);
     if (in_place) {
       PC_CHECK_LAUNCH("pc_compact select");
@@ -1184,15 +1181,14 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
   const int chunks_per_head = ceil_div(nk_out, kGatherRows);
   const int64_t in_stride_c = kv_stride_h * elt / 16, out_stride_c = kv_out_stride_h * elt / 16;
   const dim3 ggrid(chunks_per_head * Hkv * n_layers);
-  const Divisor by_layer(chunks_per_head * Hkv), by_heads(Hkv);
   PC_REQUIRE(!in_place || Hkv * n_layers <= kMaxTicketHeads, PC_ERR_UNSUPPORTED,
              "pc_compact: in place supports at most %d (layer, KV head) pairs", kMaxTicketHeads);
   const int64_t in_stride_lc = kv_stride_l * elt / 16, out_stride_lc = kv_out_stride_l * elt / 16;
 #define PC_LAUNCH_GATHER(CPR, ROWS, INPLACE)                                                             \
   gather_kernel<CPR, ROWS, INPLACE><<<ggrid, kGatherThreads, 0, st>>>(                                   \
       static_cast<const u32x4*>(K), static_cast<const u32x4*>(V), pos, static_cast<u32x4*>(K_out),       \
-      static_cast<u32x4*>(V_out), pos_out, idx, idx_stride, share_heads, nk_in, nk_out, in_stride_c,     \
-      out_stride_c, pos_stride_h, pos_out_stride_h, sync, flags, lay.chunks_per_head, tab, by_layer, by_heads, \
+      static_cast<u32x4*>(V_out), pos_out, idx, idx_stride, share_heads, Hkv, nk_in, nk_out, in_stride_c, \
+      out_stride_c, pos_stride_h, pos_out_stride_h, sync, flags, lay.chunks_per_head, tab, n_layers,      \
       in_stride_lc, out_stride_lc, pos_stride_l, pos_out_stride_l, idx_stride_layer)
   if (cpr == 16) {
     if (in_place) PC_LAUNCH_GATHER(16, kGatherRows, true); else PC_LAUNCH_GATHER(16, kGatherRows, false);
