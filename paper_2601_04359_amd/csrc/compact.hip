@@ -1103,7 +1103,10 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
     for (int s = n_seg - 1; s >= 0; --s)
       if (plan[s].len < seg_in[s].len) row0 = plan[s].start;
   }
-  if (phases == (PC_COMPACT_SELECT | PC_COMPACT_GATHER) && max_prune_len <= kFusedMaxLen && nk_in <= 0xFFFF &&
+  // One buffer passed as both K and V: two work-groups of the one-launch form would move the same bytes, in no
+  // order; in the gather a thread moves a K row's chunk and the same chunk of its V row.
+  const bool kv_apart = !in_place || K != V;
+  if (phases == (PC_COMPACT_SELECT | PC_COMPACT_GATHER) && kv_apart && max_prune_len <= kFusedMaxLen && nk_in <= 0xFFFF &&
       nk_out <= kFusedMaxRows && fused_pays(n_seg, max_prune_len, nk_out - row0, n_layers * Hkv, in_place)) {
     FusedArgs a;
     a.K = static_cast<const u32x4*>(K), a.V = static_cast<const u32x4*>(V), a.pos = pos;

@@ -901,6 +901,21 @@ def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv,
     assert np.array_equal(host(po[:, :nk]), pw)
 
 
+@pytest.mark.parametrize("Hkv,n,n_frames,dtype", [(1, 64, 4, "f32"), (2, 252, 6, "bf16"), (8, 120, 3, "bf16"), (4, 1100, 3, "bf16")])
+def test_in_place_compaction_of_one_buffer_passed_as_keys_and_values(Hkv, n, n_frames, dtype):
+    # small caches (which take one launch where K and V are two buffers) and a large one
+    rng = np.random.default_rng(Hkv * n)
+    segs = [(0, 16, pk.PC_SEG_TEXT, -1)] + [(16 + n * f, n, pk.PC_SEG_FRAME, f + 1) for f in range(n_frames)]
+    nk, budgets = 16 + n * n_frames, [16] + [n * (f + 1) // (n_frames + 1) for f in range(n_frames)]
+    K, sc = (rng.standard_normal(s).astype(np.float32) for s in ((Hkv, nk, 128), (Hkv, nk)))
+    K = orc.round_to_bf16(K).astype(np.float32)
+    pos = rng.integers(0, 10000, (Hkv, nk, 3)).astype(np.int32)
+    Kw, _, pw, _, sw = orc.compact(K, K, pos, sc, segs, budgets)
+    Kd, pd = dev(K, dtype), dev(pos, None)
+    sg, nko = pk.pc_compact(Kd, Kd, pd, dev(sc, None), segs, budgets)
+    assert sg == sw and np.array_equal(host(Kd[:, :nko]), Kw) and np.array_equal(host(pd[:, :nko]), pw)
+
+
 def test_in_place_compaction_repeated_random_budgets():
     # the in-place ordering protocol against the out-of-place result, many budget patterns
     w = synth.midsize(n_past=9, gh=16, gw=21, n_text=24)
