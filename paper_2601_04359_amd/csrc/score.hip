@@ -1201,18 +1201,20 @@ WsLayout ws_layout(int Hq, int Hkv, int n_qs, int Nk, int /*share_heads*/) {
 }
 
 // How the two passes of a bf16 call are cut: their form (512 stationary rows per work-group, or 64) and
-// the shares of the streamed axis.  The estimates are microseconds, fitted to 63 shapes (100 to 512
-// scoring rows a head, 8 to 24 heads, 600 to 20,000 keys) in both forms with every number of shares that
-// makes 64 to 768 work-groups: `start` is what a work-group costs beside its steps, a step gets slower as
-// the compute units fill up, a further round costs a new start, and pass 2 merges the row pass's
-// shares, itself or behind a launch of 2-5 us that does.  The row pass it picks is 0.9 % off the best on
-// average.  Where the lines lie, both sides measured (16/4 heads unless stated): row pass, both passes of
-// the call with 64 rows against 512: 100 rows a head x 4,500 keys 19.4 / 25.3 us, 330 x 2,600 24.5 / 27.4,
-// 330 x 12,000 49.7 / 51.5, 512 x 12,000 65.7 / 65.6, 512 x 20,000 98.4 / 96.6; column pass, fed with
-// log-sum-exps: 100 x 7,200 10.7 / 12.9, 100 x 12,000 16.1 / 15.4, 330 x 2,600 11.5 / 15.4, 330 x 7,200
-// 20.0 / 18.5, 512 x 2,600 14.4 / 15.8, 512 x 4,500 25.6 / 18.7.  With shares to merge in every
-// work-group the column pass keeps to three steps of 64 keys' form: there it gains 2-4 us (8/2 heads, 170
-// x 1,804 14.3 / 18.2), with 2,048 rows 0.5 or nothing (8/2, 512 x 4,500 27.2 / 26.5).
+// the shares of the streamed axis.  The estimates are microseconds: `start` is what a work-group costs
+// beside its steps, a step gets slower as the compute units fill up, a further round costs a new start, and
+// pass 2 merges the row pass's shares, itself or behind a launch of 2-5 us that does.
+// Row pass: fitted to 63 shapes (100 to 512 scoring rows a head, 8 to 24 heads, 600 to 20,000 keys) in both
+// forms with every number of shares that makes 64 to 768 work-groups; 0.9 % off the best on average.  Where the
+// line lies (16/4 heads, both passes of the call with 64 rows against 512): 100 rows a head x 4,500 keys 19.4 /
+// 25.3 us, 330 x 2,600 24.5 / 27.4, 330 x 12,000 49.7 / 51.5, 512 x 12,000 65.7 / 65.6, 512 x 20,000 98.4 / 96.6.
+// Column pass: both forms timed on 191 calls fed with log-sum-exps and 181 without (2 to 24 heads, 64 to 1,000
+// rows, 40 to 16,000 keys): 0.13 % and 0.44 % off the better form on average.  Where the line lies (16/4 heads,
+// log-sum-exps given, 64 keys against 512): 100 rows a head x 2,500 keys 5.4 / 7.7 us, x 6,000 9.5 / 9.0, 170 x
+// 12,300 23.4 / 15.0, 330 x 420 10.0 / 10.1, 330 x 7,300 19.0 / 15.0, 512 x 40 12.5 / 11.5, 512 x 1,300 13.1 /
+// 11.8, 512 x 6,500 25.6 / 18.7.  With shares to merge in every work-group the column pass keeps to three
+// steps of 64 keys' form: there it gains 2-4 us (8/2 heads, 170 x 1,804 14.3 / 18.2), with 2,048 rows 0.5 or
+// nothing (8/2, 512 x 4,500 27.2 / 26.5).
 struct PassCost {
   double start, step, step_filled, round;
   double of(int blocks, int steps) const {
@@ -1259,8 +1261,8 @@ ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
   for (int s = 1; s <= std::min(kMaxQSplits, n_vt); ++s) {
     const int per = ceil_div(n_vt, s);
     if (ceil_div(n_vt, per) != s) continue;
-    const double reduce = s == 1 ? 0.0 : 1.9 + 3.9e-6 * s * Hkv * nkr;
-    const double c = PassCost{7.36, 1.12, 0.36, 4.46}.of(base * s, per) + reduce;
+    const double reduce = s == 1 ? 0.0 : 2.1 + 4.6e-6 * s * Hkv * nkr;
+    const double c = PassCost{3.8, 1.27, 0.24, 4.15}.of(base * s, per) + reduce;
     if (c < best_cost) {
       best_cost = c;
       // several rounds of work-groups would each merge again; a log-sum-exp is just read (24/8 heads x 512 x
@@ -1269,8 +1271,8 @@ ColPlan plan_cols(int Hkv, int rows, int nkr, int n_splits) {
     }
   }
   if (rows <= (n_splits > 1 ? kSmallMergeRows : kSmallMaxRows)) {
-    const double c = PassCost{3.7, 1.2, 0.0, 2.0}.of(Hkv * ceil_div(nkr, kWaveRows), ceil_div(rows, 8 * kSmallStep)) +
-                     2.9e-4 * rows;   // the normalisers of all rows, in every work-group
+    const double c = PassCost{2.6, 0.91, 0.32, 1.8}.of(Hkv * ceil_div(nkr, kWaveRows), ceil_div(rows, 8 * kSmallStep)) +
+                     1.2e-3 * rows;   // the normalisers of all rows, in every work-group
     if (c < best_cost) best = {true, merges_in_pass_2(rows, n_splits), 1};
   }
   return best;

@@ -385,6 +385,14 @@ def test_parity_shapes_take_the_forms_they_are_meant_for(L):
             assert score(s, scale)[2:4] == (512, 1) and score(s, scale, True)[:4] == (0, 0, 512, 1)
 
 
+def test_column_pass_takes_the_form_that_was_faster():
+    # keys per work-group of the column pass where the two forms were timed 5 % or more apart, log-sum-exps given
+    for shape, keys in (((16, 4, 512, 40), 512), ((16, 4, 512, 178), 512), ((16, 4, 512, 1305), 512), ((8, 2, 512, 2551), 512),
+                        ((2, 1, 1000, 2948), 512), ((8, 2, 170, 11032), 512), ((16, 4, 100, 6000), 512), ((16, 4, 512, 13810), 512),
+                        ((16, 4, 64, 2392), 64), ((16, 4, 100, 2516), 64), ((8, 2, 170, 578), 64), ((8, 2, 330, 108), 64)):
+        assert pk.pc_score_cut(*shape, 0.088, True)[2] == keys, shape
+
+
 def test_cut_queries_refuse_what_the_calls_refuse(L):
     for bad in ((pk.PC_BF16, 3, 2, 10, 10, 128), (pk.PC_BF16, 2, 1, 0, 10, 128), (pk.PC_BF16, 2, 1, 10, 10, 64), (5, 2, 1, 10, 10, 128)):
         with pytest.raises(pk.PackCacheError):
