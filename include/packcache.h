@@ -291,6 +291,11 @@ int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V, int32_t* 
                            int64_t idx_stride_h, int64_t idx_stride_l, pc_segment* seg_out,
                            int32_t* Nk_out, void* ws, size_t ws_bytes, void* stream);
 
+/* Host only: how a whole call (both phases, K and V two buffers) is cut.  cut[0]: launches that select and
+ * move, 1 or 2 (0: nothing is kept); cut[1]: slices of a row that the one-launch form moves apart, else 0. */
+int pc_compact_cut(int n_layers, int Hkv, int dtype, int D, const pc_segment* seg_in, int n_seg,
+                   const int32_t* budget, int share_heads, int in_place, int32_t cut[2]);
+
 /* ---------------------------------------------------------------------------------------
  * pc_compact_status -- did the last in-place compaction that used workspace `ws` run to the
  * end?  Waits for `stream` (the stream that compaction was enqueued on), reads one word of

@@ -21,7 +21,7 @@ __all__ = [
     "PackCacheError", "lib", "lib_path", "pc_version", "pc_strerror", "pc_budget", "pc_rope3d", "pc_rebase",
     "pc_score", "pc_score_workspace_bytes", "pc_compact_plan", "pc_compact", "pc_compact_batch", "pc_compact_batch_workspace_bytes", "PC_COMPACT_SELECT", "PC_COMPACT_GATHER", "PC_SCALE_FOLDED", "folded_q_scale", "pc_masked_budgets", "pc_mask_scores", "pc_compact_status",
     "pc_compact_workspace_bytes", "pc_compact_prepared", "pc_compact_static", "pc_compact_static_capacity", "pc_frame_attn", "pc_frame_attn_workspace_bytes",
-    "pc_frame_attn_workspace_bytes_for", "pc_frame_attn_cut", "pc_score_cut",
+    "pc_frame_attn_workspace_bytes_for", "pc_frame_attn_cut", "pc_score_cut", "pc_compact_cut",
     "segment_budgets",
 ]
 
@@ -105,6 +105,7 @@ def lib() -> C.CDLL:
         L.pc_frame_attn_workspace_bytes_for.argtypes = [C.c_int] * 6
         L.pc_frame_attn_cut.argtypes = [C.c_int] * 6 + [sz, i32p]
         L.pc_score_cut.argtypes = [C.c_int] * 5 + [C.c_float, C.c_int, i32p]
+        L.pc_compact_cut.argtypes = [C.c_int] * 4 + [segp, C.c_int, i32p, C.c_int, C.c_int, i32p]
         L.pc_frame_attn.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i64,
                                     i64, i64, C.c_float, vp, vp, vp, sz, vp]
         L.pc_last_error_detail()    # touches the library's thread-local storage (see build.build_marshal)
@@ -410,6 +411,16 @@ def pc_compact(K, V, pos, score, segments, budgets, share_heads: bool = False, o
                             _ptr(idx), 0 if idx is None else idx.stride(0), seg_out, C.byref(nk),
                             ws.data_ptr(), ws.numel(), _stream()))
     return _seg_tuples(seg_out, n), nk.value
+
+
+def pc_compact_cut(n_layers: int, Hkv: int, dtype: int, D: int, segments, budgets, share_heads: bool = False,
+                   in_place: bool = False) -> tuple[int, ...]:
+    """How a call is cut: (launches that select and move, slices per row of the one-launch form or 0)."""
+    cut = (C.c_int32 * 2)()
+    n = len(segments)
+    _check(lib().pc_compact_cut(n_layers, Hkv, dtype, D, _seg_array(segments), n, _budget_array(budgets, n), int(share_heads),
+                                int(in_place), cut))
+    return tuple(cut)
 
 
 def pc_compact_static_capacity() -> int:

@@ -788,21 +788,62 @@ struct FusedArgs {
   int Hkv, hsel, log_chunks, log_slices;  // a slice is 2^log_chunks chunks, a row 2^log_slices slices
 };
 
-// Microseconds of the launch, fitted to 90 shapes (64 to 1,000 tokens per frame, 2 to 47 frames, within
-// 13 %): every round of 16 segments is a chain of a load and a histogram's steps, and a compute unit moves
-// one piece of a row per 3 clocks whatever its width.  Two launches take 8.3 to 11.5 in place and 7.1 to
-// 8.5 out of place where this one takes 4.8 to 9 (252-token frames, 6 of them, 4 heads: 10.3 -> 7.0 and
-// 7.6 -> 6.7; the same for 28 layers: 31 -> 22.6), and the launch saved is 3 on the host.  Out of place
-// many layers are better off with whole rows (28 layers x 8 heads, 600 x 3: 83 against 101).
-inline bool fused_pays(int n_seg, int max_len, int n_moved, int heads, bool in_place) {
-  const float us = 2.2f + 2.4f * ceil_div(n_seg, kFusedWaves) + 1.5f / 1024 * max_len + 2.4f / 1024 * n_moved;
-  return in_place ? us <= 10.f && heads <= kMaxTicketHeads : us <= 9.f && heads <= 112;
+// A slice is 128 bytes of a row, or 64 where that still pays: half of every cache line that a 64-byte slice
+// touches is its neighbour's.  Work-groups, those of the positions among them, stay within one per compute
+// unit: 56 heads of 256-byte rows in halves are 280 of them, and a quarter slower than 168 with whole rows; with
+// 32 heads halves gain 14 to 29 % once 300 rows move.  Out of place 64-byte slices gain 10 to 20 % up to 8
+// heads; in place they are within 3 % up to 4, and with 8 heads 6 % behind and up to 1.5 times when 2,000
+// rows move (1,925 rows, 13 segments: 13.6 us).
+inline bool slices_pay(int chunks, int work_groups, int pos_work_groups, bool in_place) {
+  return chunks >= 8 ? work_groups + pos_work_groups <= 256 : chunks == 4 && work_groups <= (in_place ? 32 : 64);
 }
-// Slices of 64 bytes waste half of every cache line they touch and pay only while few work-groups run (8
-// heads 6.2 against 6.5 us, 24 heads 8.2 against 6.8 for 128-byte slices); those pay up to one
-// work-group per compute unit (48 heads: 8.1 against 9.1 for whole rows).
-inline bool fused_slices_pay(int chunks, int work_groups) {
-  return chunks >= 8 ? work_groups <= 256 : chunks == 4 && work_groups <= 64;
+
+// Which form a call takes: one launch, and its slices per row as a power of two, or two launches.
+struct CompactCut {
+  bool one_launch;
+  int log_slices;
+};
+// Measured: 3,400 calls in both forms (1 to 60 segments of 16 to 1,024 rows, 1 to 224 heads, both row widths),
+// medians of graph replays.  The range bounds a work-group's serial part, rounds of sixteen segments (a chain
+// of a load and a histogram's steps each) and the rows it moves; beyond it, and out of place from 113 heads on,
+// either form may be the faster one (28 x 8 heads, three frames of 600, out of place: 83 us against 101 in one
+// launch), and the two launches stay.
+// In place the two launches take 9 us and more and lose inside the range (6 segments, 4 heads, 252 rows each:
+// 10.3 against 7.0; 28 layers of it 31 against 22.6; 16 x 8 heads, 15 segments, 755 rows kept 24.8 against
+// 19.9), but for hundreds of heads that keep one chunk of the gather each (28 x 8 heads, 91 rows kept: 9.0
+// against 11.2; 289 rows: 11.5 against 10.3; 16 x 8 heads, 48 rows: 8.1 against 7.5).
+// Out of place they start at 6.4 and win from the second round of pruned segments (2 heads x 28 segments
+// of 17 rows: 6.8 against 7.8; 24 segments, 6 of them pruned: 6.9 against 5.1): both forms' microseconds, fitted to 400
+// calls inside the range; the form they pick is over 2 % slower on 5 of them.
+CompactCut plan_compact(int layers, int Hkv, int row_bytes, const pc_segment* seg_in, const pc_segment* plan, int n_seg,
+                        bool share_heads, bool in_place) {
+  const CompactCut two_launches = {false, 0};
+  int nk_in = 0, nk_out = 0, n_pruned = 0, max_len = 0, row0 = -1;
+  for (int s = 0; s < n_seg; ++s) {
+    if (plan[s].len < seg_in[s].len) {
+      ++n_pruned;
+      max_len = std::max(max_len, seg_in[s].len);
+      if (row0 < 0) row0 = plan[s].start;   // in place, packed rows below it stay where they are
+    }
+    nk_in = seg_in[s].start + seg_in[s].len;
+    nk_out = plan[s].start + plan[s].len;
+  }
+  if (max_len > kFusedMaxLen || nk_in > 0xFFFF || nk_out > kFusedMaxRows) return two_launches;
+  if (static_cast<int64_t>(layers) * Hkv > (in_place ? kMaxTicketHeads : 112)) return two_launches;
+  const int heads = layers * Hkv, pos_groups = share_heads ? layers : heads, row_chunks = row_bytes / 16;
+  const int moved = !in_place ? nk_out : row0 < 0 ? 0 : nk_out - row0, rounds = ceil_div(n_seg, kFusedWaves);
+  if (2.4 * rounds + 1.5 / 1024 * max_len + 2.4 / 1024 * moved > (in_place ? 7.8 : 6.8)) return two_launches;
+  int log_slices = 0;
+  while (slices_pay(row_chunks >> (log_slices + 1), (heads * 2) << (log_slices + 1), pos_groups, in_place)) ++log_slices;
+  const CompactCut one_launch = {true, log_slices};
+  if (in_place) return heads > 128 && nk_out <= kGatherRows ? two_launches : one_launch;
+  const double spill = std::max(0.0, (((heads * 2) << log_slices) + pos_groups) / 256.0 - 1.0);   // work-groups
+  const double slice = static_cast<double>(moved) * (row_chunks >> log_slices) / 16384;           // of one of them
+  const double mbytes = 4e-6 * heads * moved * row_bytes, units = 1e-3 * n_seg * pos_groups;
+  const double one = 2.1 + 0.9 * ceil_div(n_pruned, kFusedWaves) + 1.2 * rounds + 0.7 / 1024 * max_len + 4.55 * slice +
+                     0.08 * mbytes + 10.0 * spill;
+  const double two = 6.4 + (row_bytes == 512 ? 1.43 : 0.0) + (max_len > 256 ? 0.57 : 0.0) + 0.17 * mbytes + 0.61 * units;
+  return one <= two ? one_launch : two_launches;
 }
 
 template <int cpr /* 16-byte chunks per row */, int kCap>
@@ -1096,18 +1137,19 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
   GatherSync* sync = reinterpret_cast<GatherSync*>(wsb + lay.sync_off);
   int32_t* flags = reinterpret_cast<int32_t*>(wsb + lay.flags_off);
 
-  const int row_chunks = row_bytes / 16;
-  int row0 = 0;  // in place, packed rows below it stay where they are
-  if (in_place) {
-    row0 = nk_out;
-    for (int s = n_seg - 1; s >= 0; --s)
-      if (plan[s].len < seg_in[s].len) row0 = plan[s].start;
-  }
   // One buffer passed as both K and V: two work-groups of the one-launch form would move the same bytes, in no
   // order; in the gather a thread moves a K row's chunk and the same chunk of its V row.
   const bool kv_apart = !in_place || K != V;
-  if (phases == (PC_COMPACT_SELECT | PC_COMPACT_GATHER) && kv_apart && max_prune_len <= kFusedMaxLen && nk_in <= 0xFFFF &&
-      nk_out <= kFusedMaxRows && fused_pays(n_seg, max_prune_len, nk_out - row0, n_layers * Hkv, in_place)) {
+  const CompactCut cut = phases == (PC_COMPACT_SELECT | PC_COMPACT_GATHER) && kv_apart
+                             ? plan_compact(n_layers, Hkv, row_bytes, seg_in, plan, n_seg, share_heads, in_place)
+                             : CompactCut{false, 0};
+  if (cut.one_launch) {
+    int row0 = 0;  // in place, packed rows below it stay where they are
+    if (in_place) {
+      row0 = nk_out;
+      for (int s = n_seg - 1; s >= 0; --s)
+        if (plan[s].len < seg_in[s].len) row0 = plan[s].start;
+    }
     FusedArgs a;
     a.K = static_cast<const u32x4*>(K), a.V = static_cast<const u32x4*>(V), a.pos = pos;
     a.Ko = static_cast<u32x4*>(K_out), a.Vo = static_cast<u32x4*>(V_out), a.pos_o = pos_out;
@@ -1120,10 +1162,8 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
     a.idx_stride_h = idx_stride_h, a.idx_stride_l = idx_stride_l;
     a.n_seg = n_seg, a.n_out = nk_out, a.Hkv = Hkv, a.hsel = hsel;
     a.row0 = row0;
-    a.log_slices = 0;
-    while (a.log_slices < 5 && fused_slices_pay(row_chunks >> (a.log_slices + 1), (n_layers * Hkv * 2) << (a.log_slices + 1)))
-      ++a.log_slices;
-    a.log_chunks = (row_chunks == 16 ? 4 : 5) - a.log_slices;
+    a.log_slices = cut.log_slices;
+    a.log_chunks = (row_bytes == 256 ? 4 : 5) - cut.log_slices;
     const dim3 grid(((Hkv * 2) << a.log_slices) + hsel, n_layers);
     auto fill = [&](auto& ft) {
       for (int s = 0; s < n_seg; ++s)
@@ -1202,6 +1242,25 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
   }
 #undef PC_LAUNCH_GATHER
   PC_CHECK_LAUNCH("pc_compact gather");
+  return PC_OK;
+}
+
+extern "C" int pc_compact_cut(int n_layers, int Hkv, int dtype, int D, const pc_segment* seg_in, int n_seg,
+                              const int32_t* budget, int share_heads, int in_place, int32_t* cut) {
+  PC_REQUIRE(cut, PC_ERR_NULL, "pc_compact_cut: cut is NULL");
+  PC_REQUIRE(dtype == PC_F32 || dtype == PC_BF16, PC_ERR_DTYPE, "pc_compact_cut: dtype %d", dtype);
+  PC_REQUIRE(Hkv > 0 && n_layers >= 1 && n_seg >= 0 && n_seg <= PC_MAX_SEGMENTS, PC_ERR_SHAPE,
+             "pc_compact_cut: layers=%d Hkv=%d n_seg=%d", n_layers, Hkv, n_seg);
+  const int row_bytes = D * (dtype == PC_BF16 ? 2 : 4);
+  PC_REQUIRE(row_bytes == 256 || row_bytes == 512, PC_ERR_UNSUPPORTED, "pc_compact_cut: rows of %d bytes", row_bytes);
+  PC_REQUIRE(!in_place || static_cast<int64_t>(n_layers) * Hkv <= kMaxTicketHeads, PC_ERR_UNSUPPORTED,
+             "pc_compact_cut: in place supports at most %d (layer, KV head) pairs", kMaxTicketHeads);
+  pc_segment plan[PC_MAX_SEGMENTS];
+  int32_t nk_out = 0;
+  if (int rc = pc_compact_plan(seg_in, n_seg, budget, plan, &nk_out)) return rc;
+  const CompactCut c = plan_compact(n_layers, Hkv, row_bytes, seg_in, plan, n_seg, share_heads, in_place);
+  cut[0] = nk_out == 0 ? 0 : c.one_launch ? 1 : 2;
+  cut[1] = nk_out != 0 && c.one_launch ? 1 << c.log_slices : 0;
   return PC_OK;
 }
 

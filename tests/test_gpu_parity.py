@@ -791,13 +791,27 @@ def _compact_run(w, sc, budgets, in_place, share=False, hsel=None):
         segs, nk = pk.pc_compact(K, V, pos, scd, w.segments, budgets, share_heads=share, out=(Ko, Vo, po), idx=idx)
         assert torch.equal(K, dev(w.K, dt))           # out of place leaves the cache alone
     assert segs == plan and nk == nk_out
+    # the two halves one by one, on a workspace that holds anything: the two-launch form, which small whole calls leave
+    Kt, Vt, pt = (t.clone()[None] for t in (dev(w.K, dt), dev(w.V, dt), dev(np.broadcast_to(w.pos_k[None], (hsel, w.Nk, 3)).copy(), None)))
+    out = None if in_place else tuple(torch.empty_like(t)[None] for t in (Ko, Vo, po))
+    ws = torch.full((pk.pc_compact_workspace_bytes(w.Hkv, w.Nk, share),), 0xA5, dtype=torch.uint8, device=DEV)
+    idx_t = torch.full_like(idx, -1)[None]
+    for phase in (pk.PC_COMPACT_SELECT, pk.PC_COMPACT_GATHER):
+        assert pk.pc_compact_batch(Kt, Vt, pt, scd[None], w.segments, budgets, share_heads=share, out=out, idx=idx_t,
+                                   ws=ws, phases=phase) == (segs, nk)
+    if in_place:
+        pk.pc_compact_status(ws)
+    for t, x in zip((Ko, Vo, po, idx), (*(out or (Kt, Vt, pt)), idx_t)):
+        assert torch.equal(x[0, :, :nk], t)
     return host(Ko), host(Vo), host(po), host(idx), segs
 
 
-def test_compact_status_reports_the_abort_word():
+@pytest.mark.parametrize("grid,launches", [((12, 21), 1), ((32, 33), 2)])
+def test_compact_status_reports_the_abort_word(grid, launches):
     """pc_compact_status is PC_OK after an ordinary in-place call; the abort word (set here from the
     host, never by making a kernel wait in vain) turns into PC_ERR_ABORTED; the next call resets it."""
-    w = synth.midsize()
+    w = synth.midsize(gh=grid[0], gw=grid[1])
+    assert pk.pc_compact_cut(1, w.Hkv, pk.PC_BF16, w.D, w.segments, budgets_for(w), False, True)[0] == launches
     sc = dev(np.random.default_rng(5).random((w.Hkv, w.Nk)).astype(np.float32), None)
     budgets = budgets_for(w)
     ws = torch.empty(pk.pc_compact_workspace_bytes(w.Hkv, w.Nk), dtype=torch.uint8, device=DEV)
@@ -868,25 +882,47 @@ def test_compact_long_segment_generic_select_and_negative_zero():
     assert np.array_equal(host(Kd[:, :nko]), Kw) and np.array_equal(host(pd[:, :nko]), pw)
 
 
-@pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("lens,D,dtype,Hkv,share", [
-    ([5, 1, 2, 3], 128, "bf16", 1, False),                       # frames shorter than a wave
-    ([16, 64, 63, 64, 65, 64], 64, "f32", 2, False),             # around one row of 64 keys
-    ([0, 1023, 1024, 7], 128, "bf16", 2, True),                  # the longest segments the one-launch form takes
-    ([0, 1023, 1025, 7], 128, "bf16", 2, False),                 # one key more: two launches
-    ([3] + [70] * 23, 128, "f32", 1, False),                     # 24 segments: the short table, two rounds of waves
-    ([3] + [70] * 24, 128, "bf16", 24, False),                   # 25: the long table; many heads, wide slices
-    ([0] + [130] * 16 + [0, 200], 128, "bf16", 2, False),        # empty segments between others
-])
-def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv, share, in_place):
-    rng = np.random.default_rng(sum(lens) + Hkv)
+# segment lengths (the first is an anchor), D, dtype, KV heads, share_heads, launches out of place and in place
+COMPACT_SMALL = [
+    ([5, 1, 2, 3], 128, "bf16", 1, False, (1, 1)),                       # frames shorter than a wave
+    ([16, 64, 63, 64, 65, 64], 64, "f32", 2, False, (1, 1)),             # around one row of 64 keys
+    ([0, 1023, 1024, 7], 128, "bf16", 2, True, (1, 1)),                  # the longest segments the one-launch form takes
+    ([0, 1023, 1025, 7], 128, "bf16", 2, False, (2, 2)),                 # one key more: two launches
+    ([3] + [70] * 23, 128, "f32", 1, False, (1, 1)),                     # 24 segments: the short table, two rounds of waves
+    ([3] + [70] * 24, 128, "bf16", 24, False, (1, 1)),                   # 25: the long table; many heads, wide slices
+    ([0] + [130] * 16 + [0, 200], 128, "bf16", 2, False, (2, 1)),        # empty segments between others
+    ([0] + [60] * 15 + [0, 70], 128, "bf16", 2, False, (1, 1)),          # the same out of place
+    ([3] + [16] * 26, 128, "bf16", 2, False, (2, 1)),                    # a second round of pruned segments
+    ([7700] + [1024] * 31, 64, "f32", 1, False, (2, 1)),                 # 8,192 kept rows, sources above 32,767
+    ([7701] + [1024] * 31, 64, "f32", 1, False, (2, 2)),                 # one kept row more
+    ([7], 128, "bf16", 2, False, (1, 1)),                                # nothing pruned: in place nothing moves
+    ([90, 300, 400], 128, "bf16", 8, False, (1, 1)),                     # 8 heads: 64-byte slices out of place only
+    ([30, 60, 70], 128, "bf16", 56, False, (1, 1)),                      # whole rows: halves would be 280 work-groups
+    ([10, 20, 20], 128, "bf16", 150, False, (2, 2)),                     # many heads, one chunk of the gather each
+    ([10, 200, 200], 128, "bf16", 150, True, (2, 1)),                    # and several
+]
+
+
+def small_table(lens):
+    """Segments and budgets of a table of COMPACT_SMALL: every kind of budget by turns, few rows of the 31 long ones."""
     segs, at = [], 0
     for i, n in enumerate(lens):
         segs.append((at, n, pk.PC_SEG_TEXT if i == 0 else pk.PC_SEG_FRAME, i))
         at += n
+    if len(lens) == 32:
+        return segs, at, [lens[0]] + [0] * 3 + [113] * 4 + [40] + [0] * 23
+    return segs, at, [n if i == 0 else (0, n, n // 3, max(1, n - 1), 1)[(i + 2) % 5] for i, n in enumerate(lens)]
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("lens,D,dtype,Hkv,share,launches", COMPACT_SMALL)
+def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv, share, launches, in_place):
+    rng = np.random.default_rng(sum(lens) + Hkv)
+    segs, at, budgets = small_table(lens)
+    code = pk.PC_BF16 if dtype == "bf16" else pk.PC_F32
+    assert pk.pc_compact_cut(1, Hkv, code, D, segs, budgets, share, in_place)[0] == launches[in_place]
     hsel = 1 if share else Hkv
     sc = np.round(np.exp(rng.standard_normal((hsel, at))) * 64).astype(np.float32) / 64     # with ties
-    budgets = [n if i == 0 else (0, n, n // 3, max(1, n - 1), 1)[(i + 2) % 5] for i, n in enumerate(lens)]
     K, V = (orc.round_to_bf16(rng.standard_normal((Hkv, at, D))).astype(np.float32) for _ in range(2))
     pos = rng.integers(0, 10000, (hsel, at, 3)).astype(np.int32)
     Kw, Vw, pw, iw, sw = orc.compact(K, V, pos, sc, segs, budgets, share_heads=share)
@@ -917,7 +953,8 @@ def test_in_place_compaction_of_one_buffer_passed_as_keys_and_values(Hkv, n, n_f
 
 
 def test_in_place_compaction_repeated_random_budgets():
-    # the in-place ordering protocol against the out-of-place result, many budget patterns
+    # the in-place ordering protocol against the out-of-place result, many budget patterns (_compact_run takes
+    # the two launches of the protocol as well as the one of such a small cache)
     w = synth.midsize(n_past=9, gh=16, gw=21, n_text=24)
     rng = np.random.default_rng(100)
     for trial in range(12):
@@ -1298,6 +1335,7 @@ def test_step_captured_in_a_hip_graph_replays_to_the_eager_result():
     rows = dev(w.score_rows.astype(np.int32), None)
     budgets = budgets_for(w)
     nk_out = pk.pc_compact_plan(w.segments, budgets)[1]
+    assert pk.pc_compact_cut(1, w.Hkv, pk.PC_BF16, w.D, w.segments, budgets, False, True)[0] == 2   # the bookkeeping's form
     sc = torch.empty((w.Hkv, w.Nk), dtype=torch.float32, device=DEV)
     O, lse = torch.empty_like(Q), torch.empty((w.Hq, w.Nq), dtype=torch.float32, device=DEV)
     ws_s = torch.empty(pk.pc_score_workspace_bytes(w.Hq, w.Hkv, rows.numel(), w.Nk), dtype=torch.uint8, device=DEV)

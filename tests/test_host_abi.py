@@ -385,6 +385,35 @@ def test_parity_shapes_take_the_forms_they_are_meant_for(L):
             assert score(s, scale)[2:4] == (512, 1) and score(s, scale, True)[:4] == (0, 0, 512, 1)
 
 
+def test_small_compactions_take_the_form_that_was_faster():
+    import test_gpu_parity as g
+    for lens, D, dtype, Hkv, share, launches in g.COMPACT_SMALL:
+        segs, _, budgets = g.small_table(lens)
+        for in_place in (False, True):
+            cut = pk.pc_compact_cut(1, Hkv, pk.PC_BF16 if dtype == "bf16" else pk.PC_F32, D, segs, budgets, share, in_place)
+            assert cut[0] == launches[in_place], (lens, Hkv, in_place)
+
+    def cut(layers, Hkv, lens, keep, in_place, wide=False, share=False):
+        segs = [(sum(lens[:i]), n, pk.PC_SEG_FRAME, i) for i, n in enumerate(lens)]
+        return pk.pc_compact_cut(layers, Hkv, pk.PC_F32 if wide else pk.PC_BF16, 128, segs, keep, share, in_place)
+
+    # timed in both forms, and with every number of slices: the faster of them is taken
+    assert cut(1, 8, [600] + [221] * 12, [237] + [140] * 12, True) == (1, 2)        # 64-byte slices: 13.6 us, two launches 9.6
+    assert cut(1, 8, [300] * 3, [150] * 3, False) == (1, 4) and cut(1, 4, [300] * 3, [150] * 3, True) == (1, 4)
+    assert cut(4, 8, [300] * 3, [150] * 3, True) == (1, 2) and cut(7, 8, [300] * 3, [150] * 3, True) == (1, 1)
+    assert cut(1, 2, [17] * 28, [10] * 28, False)[0] == 2 and cut(1, 2, [17] * 28, [10] * 28, True)[0] == 1
+    assert cut(1, 2, [17] * 28, [17] * 20 + [10] * 8, False)[0] == 1
+    assert cut(28, 8, [60, 40], [60, 31], True)[0] == 2 and cut(28, 8, [280, 17], [280, 9], True)[0] == 1
+    # no launch, what is refused, and what the call itself refuses
+    assert cut(1, 2, [40, 50], [0, 0], True) == (0, 0) and cut(1, 2, [], [], True) == (0, 0)
+    for bad in (lambda: cut(0, 2, [40], [4], True), lambda: cut(1, 0, [40], [4], True), lambda: cut(257, 1, [40], [4], True),
+                lambda: cut(1, 2, [40], [-1], True), lambda: pk.pc_compact_cut(1, 2, 7, 128, [(0, 4, 2, 0)], [2]),
+                lambda: pk.pc_compact_cut(1, 2, pk.PC_BF16, 96, [(0, 4, 2, 0)], [2])):
+        with pytest.raises(pk.PackCacheError):
+            bad()
+    assert cut(1 << 20, 1 << 15, [40], [4], False) == (2, 0)
+
+
 def test_column_pass_takes_the_form_that_was_faster():
     # keys per work-group of the column pass where the two forms were timed 5 % or more apart, log-sum-exps given
     for shape, keys in (((16, 4, 512, 40), 512), ((16, 4, 512, 178), 512), ((16, 4, 512, 1305), 512), ((8, 2, 512, 2551), 512),

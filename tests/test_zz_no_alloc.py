@@ -38,8 +38,8 @@ def _raw_call(name, K, V, pos, score, segments, budgets, idx, ws=None):
     return [(s.start, s.len, s.kind, s.frame) for s in seg_out], nk.value
 
 
-def _case(seed, n_past):
-    w = synth.midsize(seed=seed, n_past=n_past)
+def _case(seed, n_past, grid=(12, 21)):
+    w = synth.midsize(seed=seed, n_past=n_past, gh=grid[0], gw=grid[1])
     sc = orc.score(w.Q[:, w.score_rows], w.K, w.scale).astype(np.float32)
     budgets = pk.segment_budgets(w.segments, pk.pc_budget(pk.PC_BUDGET_POW, w.n_frame, w.n_past, w.gamma, w.b_min))
     bf = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(torch.bfloat16).to(DEV)
@@ -49,10 +49,13 @@ def _case(seed, n_past):
     return w, budgets, mk
 
 
-def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row():
+# small frames are selected and moved in one launch, which needs none of the array's bookkeeping; larger ones in two
+@pytest.mark.parametrize("grid,launches", [((12, 21), 1), ((32, 33), 2)])
+def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row(grid, launches):
     assert pk.pc_compact_static_capacity() == 4 << 20
     for seed, n_past in ((41, 9), (42, 4)):          # the second call is the smaller one
-        w, budgets, mk = _case(seed, n_past)
+        w, budgets, mk = _case(seed, n_past, grid)
+        assert pk.pc_compact_cut(1, w.Hkv, pk.PC_BF16, w.D, w.segments, budgets, False, True)[0] == launches
         nk_out = pk.pc_compact_plan(w.segments, budgets)[1]
         Ka, Va, pa, sa = mk()
         Kb, Vb, pb, sb = mk()
@@ -83,11 +86,13 @@ def test_static_scratch_entry_rejects_what_does_not_fit():
     assert e.value.status == -6 and "scratch" in str(e.value)
 
 
-def test_static_scratch_entry_replays_from_a_hip_graph():
+@pytest.mark.parametrize("grid,launches", [((12, 21), 1), ((32, 33), 2)])
+def test_static_scratch_entry_replays_from_a_hip_graph(grid, launches):
     """What the entry point is for: a caller under graph capture.  After one eager call (which
     looks the array's address up) the call is recorded and re-played; every replay must give the
     eager result (the bookkeeping in the array is cleared by a kernel of the call itself)."""
-    w, budgets, mk = _case(43, 7)
+    w, budgets, mk = _case(43, 7, grid)
+    assert pk.pc_compact_cut(1, w.Hkv, pk.PC_BF16, w.D, w.segments, budgets, False, True)[0] == launches
     nk_out = pk.pc_compact_plan(w.segments, budgets)[1]
     K0, V0, p0, sc = mk()
     K, V, p = K0.clone(), V0.clone(), p0.clone()
