@@ -35,12 +35,14 @@ struct Library {
 PyObject* current_device = nullptr;   // torch's raw queries of the current device and of its stream
 PyObject* raw_stream = nullptr;
 
+// The lock comes back on every way out: an exception's way leads to a Python error.
 template <class F>
 auto unlocked(F&& call) {
-  PyThreadState* state = PyEval_SaveThread();
-  const auto r = call();
-  PyEval_RestoreThread(state);
-  return r;
+  struct Lock {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Lock() { PyEval_RestoreThread(state); }
+  } lock;
+  return call();
 }
 
 // ---- plain arguments -------------------------------------------------------------------------

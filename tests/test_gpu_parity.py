@@ -1447,3 +1447,23 @@ def test_plain_calls_are_marshalled_alike_by_both_halves_of_the_binding(monkeypa
         want = outcome(call)
         assert len(got) == len(want) and all(same(a, b) for a, b in zip(got, want)), (name, got, want)
         assert name is not None or isinstance(want[0], int)
+
+
+def test_an_exception_inside_the_library_comes_back_as_a_python_error(monkeypatch):
+    """No entry point of the library throws; a C++ function that does stands in for one (host code: nothing is
+    launched).  The interpreter's lock is back when the error is made, in every call that gives it up."""
+    import ctypes
+    from paper_2601_04359_amd import binding
+    calls, _ = _marshalled_calls()
+    L = pk.lib()
+    throws = ctypes.cast(ctypes.CDLL("libstdc++.so.6")._ZSt17__throw_bad_allocv, ctypes.c_void_p).value
+    size = ctypes.cast(L.pc_frame_attn_workspace_bytes_for, ctypes.c_void_p).value
+    try:
+        binding._NATIVE.bind(*[throws] * 5, size, throws, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        for name, call in calls.items():
+            with pytest.raises(RuntimeError, match="bad_alloc"):
+                call()
+    finally:
+        binding._bind_native(L)
+    for call in calls.values():
+        call()
