@@ -61,6 +61,7 @@ typedef struct pc_segment {
   int32_t frame; /* frame id (caller's bookkeeping; copied through) */
 } pc_segment;
 
+#define PC_VERSION 105          /* goes up with every change of an entry point's arguments, and with new ones */
 #define PC_MAX_SEGMENTS 120
 #define PC_MAX_SELECT_LEN 4096 /* longest FRAME segment the register-resident select handles
                                   (one work-group per segment); longer segments take a slower
@@ -68,7 +69,7 @@ typedef struct pc_segment {
 
 const char* pc_strerror(int status);
 const char* pc_last_error_detail(void);
-int pc_version(void);
+int pc_version(void);            /* the PC_VERSION that the library was built with */
 
 /* ---------------------------------------------------------------------------------------
  * pc_budget -- per-frame token budgets from the temporal decay kernel (Sec. 3.4, Eq. 4-8).

@@ -11,6 +11,7 @@ import ctypes as C
 import os
 import struct
 import sys
+import warnings
 from functools import lru_cache
 from itertools import chain
 from typing import Iterable, Sequence
@@ -116,18 +117,22 @@ def lib() -> C.CDLL:
 
 
 def _bind_native(L) -> None:
-    """Hands the loaded entry points to the compiled half.  Where it was not built, or torch lacks the raw
-    stream query, every call takes the path through ctypes."""
+    """Hands the loaded entry points to the compiled half.  Where it was not built, was built for another torch or
+    library, or torch lacks the raw stream query, every call takes the path through ctypes."""
     global _NATIVE
     try:
         import torch
         from . import _marshal
+        built_for, loaded = (_marshal.torch_version, _marshal.pc_version), (torch.__version__, L.pc_version())
+        if built_for != loaded:
+            raise ImportError(f"built for torch and library {built_for}, loaded are {loaded}")
         entries = [C.cast(f, C.c_void_p).value for f in (L.pc_rope3d, L.pc_score, L.pc_compact, L.pc_compact_batch,
                                                          L.pc_frame_attn, L.pc_frame_attn_workspace_bytes_for, L.pc_budget)]
         _marshal.bind(*entries, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
         _NATIVE = _marshal
-    except (ImportError, AttributeError):
+    except (ImportError, AttributeError) as e:
         _NATIVE = False
+        warnings.warn(f"the binding's compiled half is not used, calls take 5 to 10 us more on the host: {e}")
 
 
 def _check(status: int) -> None:

@@ -411,4 +411,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// What this file was built against, for the loader to compare: it reads torch's tensors through inlined accessors
+// and calls the library through the header's signatures, and neither is checked anywhere else.
+PyMODINIT_FUNC PyInit__marshal() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && (PyModule_AddStringConstant(m, "torch_version", PC_TORCH_VERSION) < 0 ||
+            PyModule_AddIntConstant(m, "pc_version", PC_VERSION) < 0))
+    Py_CLEAR(m);
+  return m;
+}

@@ -166,6 +166,41 @@ def test_binding_raises_without_library(monkeypatch, tmp_path):
         binding.pc_version()
 
 
+@pytest.mark.parametrize("other", [dict(torch_version="0.0"), dict(pc_version=-1)])
+def test_compiled_half_of_another_build_is_not_bound(L, monkeypatch, other):
+    import torch  # noqa: F401
+    from paper_2601_04359_amd import _marshal
+    monkeypatch.setattr(binding, "_NATIVE", None)
+    for name, value in other.items():
+        monkeypatch.setattr(_marshal, name, value)
+    with pytest.warns(UserWarning, match="built for"):
+        binding._bind_native(L)
+    assert binding._NATIVE is False
+    monkeypatch.undo()
+    binding._bind_native(L)
+    assert binding._NATIVE is _marshal
+
+
+def test_library_builds_where_the_compiled_half_cannot(monkeypatch, tmp_path):
+    from paper_2601_04359_amd import build
+    commands = []
+
+    def run(cmd):
+        commands.append(cmd[0])
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        return ""
+
+    for name in ("PKG", "LIB_DIR"):
+        monkeypatch.setattr(build, name, str(tmp_path))
+    monkeypatch.setattr(build, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    (tmp_path / "_marshal.so").write_bytes(b"an older build's")
+    monkeypatch.setattr(build, "_run", run)
+    with pytest.warns(UserWarning, match="not built"):
+        assert build.build_library() == build.LIB_PATH
+    assert len(commands) == len(build.SOURCES) + 2 and not (tmp_path / "_marshal.so").exists()
+
+
 def test_masked_budgets_match_the_oracle():
     w = synth.midsize()
     rng = np.random.default_rng(0)
