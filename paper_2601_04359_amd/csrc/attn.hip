@@ -433,6 +433,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
         for (int e = 0; e < 4; ++e) v[e] = o[db][a * 4 + e];
         *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(mine + l32 * 512 + ((db * 8 + a * 2 + g) ^ l32) * 16) = v;
       }
+    wave_lds_sync();   // rows come back from other lanes of the wave
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = i * 2 + g;
@@ -452,6 +453,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
       out[1] = pack_bf16x2(o[db][a * 4 + 2] * inv, o[db][a * 4 + 3] * inv);
       *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(mine + l32 * kRowBytes + k_chunk_pos(l32, db * 4 + a) * 16 + g * 8) = out;
     }
+  wave_lds_sync();
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int row = i * 4 + (lane >> 4), chunk = k_chunk_pos(row, lane & 15);

@@ -84,6 +84,13 @@ __device__ __forceinline__ int xcd_contiguous_index(int b, int n) {
   return x * q + (x < rem ? x : rem) + r;
 }
 
+// LDS written by other lanes of this wave becomes visible; nothing moves across
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Division by a number that the host knows, for 0 <= n < 2^31: n / d = n m >> sh with sh = 31 + ceil(log2 d)
 // and m = floor(2^sh / d) + 1 (m d exceeds 2^sh by at most 2^(sh - 31), which n times is below 2^sh).
 struct Divisor {

@@ -430,11 +430,6 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
   constexpr int kBins = 1 << kBits, kOwn = kBins / 64;  // bins per lane
   const int lane = threadIdx.x & 63;
   uint32_t* cand = reinterpret_cast<uint32_t*>(hist);  // the candidates reuse the histogram's first words
-  auto wave_sync = [] {  // LDS written by other lanes of this wave becomes visible; nothing moves across
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
   const int n_full = len >> 6, tail = len & 63;
   const bool in_tail = lane < tail;  // this lane has a key in the ragged row
   uint32_t key[kRows], key_r;
@@ -472,7 +467,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
     int4* h4 = reinterpret_cast<int4*>(hist);
 #pragma unroll
     for (int j = 0; j < kOwn / 4; ++j) h4[j * 64 + lane] = make_int4(0, 0, 0, 0);
-    wave_sync();
+    wave_lds_sync();
     // byte offset of a key's bin: the digit times four, as one shift and one mask
     const uint32_t byte_mask = ((1u << width) - 1u) << 2;
     const uint32_t rot = static_cast<uint32_t>(shift - 2) & 31u;  // rotate right: bit `shift` lands on bit 2
@@ -491,7 +486,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
       });
     }
     first = false;
-    wave_sync();
+    wave_lds_sync();
     // lane l owns bins 32 l .. 32 l + 31; the eight 16-byte reads are rotated by the lane so that
     // neighbouring lanes use different LDS banks
     int mine = 0;
@@ -520,7 +515,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
       // the candidates (keys that match the prefix so far), one per lane
       const uint32_t lo_mask = 0xFFFFFFFFu << hi;
       int n_cand = 0;
-      wave_sync();  // the histogram has been read
+      wave_lds_sync();  // the histogram has been read
       auto collect = [&](uint32_t kv, bool m) {
         const uint64_t bm = __ballot(m);
         if (bm != 0) {  // wave-uniform
@@ -531,7 +526,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
       };
       collect(key_r, in_tail && (key_r & lo_mask) == prefix);
       rows_down_from<kRows>(n_full, [&](int i) { collect(key[i], (key[i] & lo_mask) == prefix); });
-      wave_sync();
+      wave_lds_sync();
       n_cand = min(n_cand, 64);
       const bool has = lane < n_cand;
       const uint32_t my = has ? cand[lane] : 0u;
