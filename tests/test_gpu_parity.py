@@ -1411,11 +1411,39 @@ def _marshalled_calls():
         r = pk.pc_frame_attn(Q, K, V, 85, 0.1, O=O, lse=lse, **kw)
         return r is O, O, lse
 
-    calls = dict(rope3d=rope, score=score, compact=compact, compact_batch=batch, frame_attn=attn)
+    # out of place: a destination of another capacity, and (batch) one whose layers lie apart and heads close together
+    def compact_out(K=K, room=60):
+        out = tuple(torch.full((2, room, n), 7, dtype=t.dtype, device=DEV) for t, n in ((K, 128), (V, 128), (pos, 3)))
+        i = torch.zeros((2, 64), dtype=torch.int32, device=DEV)[:, :60]
+        r = pk.pc_compact(K, V, pos, sc, segs, budgets, out=out, idx=i, ws=empty(pk.pc_compact_workspace_bytes(2, 85)))
+        return r, *out, i
+
+    def batch_out(share=False, long=1):
+        Kb, Vb, pb, sb = (torch.cat([torch.stack([t, t.flip(0)])] * long, dim=2) for t in (K, V, pos, sc))
+        sel = 1 if share else 2
+        pb, sb = pb[:, :sel], sb[:, :sel]
+        out = tuple(torch.full((2, 3, 70 * long, n), 7, dtype=t.dtype, device=DEV)[:, :h] for t, n, h in ((K, 128, 2), (V, 128, 2), (pos, 3, sel)))
+        table = [(85 * j + a, n, kind, f) for j in range(long) for a, n, kind, f in segs]
+        assert pk.pc_compact_cut(2, 2, pk.PC_BF16, 128, table, budgets * long, share)[0] == (1 if long == 1 else 2)
+        r = pk.pc_compact_batch(Kb, Vb, pb, sb, table, budgets * long, share_heads=share, out=out,
+                                ws=empty(pk.pc_compact_batch_workspace_bytes(2, 2, 85 * long, share)))
+        return r, *out
+
+    def batch_short(lead):
+        Kb, Vb, pb, sb = (torch.stack([t, t.flip(0)]) for t in (K, V, pos, sc))
+        Ko, Vo, po = Kb.clone(), Vb.clone(), pb.clone()
+        return pk.pc_compact_batch(Kb, Vb, pb, sb, segs, budgets, out=lead(Ko, Vo, po),
+                                   ws=empty(pk.pc_compact_batch_workspace_bytes(2, 2, 85)))
+
+    calls = {"rope3d": rope, "score": score, "compact": compact, "compact_batch": batch, "frame_attn": attn,
+             "compact out": compact_out, "compact_batch out": batch_out, "compact_batch out, one selection": lambda: batch_out(share=True),
+             "compact_batch out, two launches": lambda: batch_out(long=30)}
     refused = [lambda: rope(sections=(32, 48, 40)), lambda: rope(x=Q.transpose(0, 1)), lambda: score(K=K[..., :64]),
                lambda: compact(K=K.to(torch.float16)), lambda: compact(budgets=[10, -1, 25]),
                lambda: compact(out=(K.clone(), V.clone()[:, :80], pos.clone())), lambda: batch(share_heads=True),
-               lambda: attn(V=torch.cat([V, V], dim=1))]
+               lambda: attn(V=torch.cat([V, V], dim=1)), lambda: compact_out(room=30),
+               lambda: batch_short(lambda a, b, c: (a, b[:, :, :80], c)), lambda: batch_short(lambda a, b, c: (a, b.transpose(0, 1), c)),
+               lambda: batch_short(lambda a, b, c: (a, b, c[:, :1])), lambda: batch_short(lambda a, b, c: (a[..., :64], b[..., :64], c))]
     return calls, refused
 
 
@@ -1438,11 +1466,12 @@ def test_plain_calls_are_marshalled_alike_by_both_halves_of_the_binding(monkeypa
             return e.status, str(e)
 
     same = lambda a, b: torch.equal(a, b) if torch.is_tensor(a) else a == b
+    assert len(calls) == 9
     for name, call in [*calls.items(), *((None, r) for r in refused)]:
         seen.clear()
         monkeypatch.setattr(binding, "_NATIVE", Spy())
         got = outcome(call)
-        assert name is None or any(n == name and r is not None for n, r in seen)   # no fallback for a plain call
+        assert name is None or any(n == name.split()[0] and r is not None for n, r in seen)   # no fallback for a plain call
         monkeypatch.setattr(binding, "_NATIVE", False)
         want = outcome(call)
         assert len(got) == len(want) and all(same(a, b) for a, b in zip(got, want)), (name, got, want)
@@ -1467,3 +1496,19 @@ def test_an_exception_inside_the_library_comes_back_as_a_python_error(monkeypatc
         binding._bind_native(L)
     for call in calls.values():
         call()
+
+
+def test_cache_views_are_the_same_from_both_halves_of_the_binding(monkeypatch):
+    from paper_2601_04359_amd import binding
+    pk.pc_budget(pk.PC_BUDGET_POW, 10, 1, 0.5, 0)
+    native = binding._NATIVE
+    layer = tuple(torch.zeros((2, 50, n), dtype=t, device=DEV) for n, t in ((128, torch.bfloat16), (128, torch.bfloat16), (3, torch.int32)))
+    stack = tuple(torch.zeros((3, 2, 50, n), device=DEV) for n in (128, 128, 3))
+    shape = lambda views: [(v.data_ptr(), tuple(v.shape), v.stride()) for v in views]
+    for caches, dim in ((layer, 1), (stack, 2)):
+        for start, n in ((0, 50), (0, 1), (17, 9), (49, 1), (17, 33), (50, 0), (3, 0), (17, 34), (50, 4), (60, 2)):   # to the end and past it
+            monkeypatch.setattr(binding, "_NATIVE", native)
+            views = binding._rows(*caches, dim, start, n)
+            assert (native.rows(*caches, dim, start, n) is None) == (start + n > 50)
+            monkeypatch.setattr(binding, "_NATIVE", False)
+            assert shape(views) == shape(binding._rows(*caches, dim, start, n)), (dim, start, n)

@@ -166,6 +166,46 @@ def test_binding_raises_without_library(monkeypatch, tmp_path):
         binding.pc_version()
 
 
+def test_table_helpers_agree_with_their_fallbacks(L, monkeypatch):
+    """What RollingLayer and RollingStack score and move, from the compiled half and without it."""
+    import torch  # noqa: F401
+    if binding._NATIVE is None:
+        binding._bind_native(L)
+    native, rng = binding._NATIVE, np.random.default_rng(12)
+    assert native
+    T, C0, F, S = pk.PC_SEG_TEXT, pk.PC_SEG_COND, pk.PC_SEG_FRAME, pk.PC_SEG_SELF
+
+    def both(f, *args):
+        got = []
+        for half in (native, False):
+            monkeypatch.setattr(binding, "_NATIVE", half)
+            try:
+                got.append(f(*args))
+            except (IndexError, TypeError) as e:
+                got.append(type(e))
+        assert got[0] == got[1], (f.__name__, args, got)
+        return got[0]
+
+    for trial in range(300):
+        kinds = [int(k) for k in rng.choice([T, C0, F, F, F, S], int(rng.integers(0, 9)))]     # anchors behind frames too
+        lens = [int(rng.choice([0, 1, 5, 40])) for _ in kinds]                                 # zero-length frames
+        segs = [(sum(lens[:i]), n, k, i) for i, (n, k) in enumerate(zip(lens, kinds))]
+        n_frames = both(binding._past_frames, segs)
+        assert n_frames == kinds.count(F)
+        by = [int(b) for b in rng.integers(0, 41, n_frames)]
+        budgets = both(pk.segment_budgets, segs, by)
+        both(pk.segment_budgets, [list(s) for s in segs], tuple(by) + (3,))
+        if n_frames:
+            assert both(pk.segment_budgets, segs, by[:-1]) is IndexError
+        over = [i for i, s in enumerate(segs) if s[2] == F and budgets[i] < s[1]]
+        want = (segs[over[0]][0], segs[over[-1]][0] + segs[over[-1]][1]) if over else None
+        assert both(binding._prunable_span, segs, budgets) == want
+        assert both(binding._prunable_span, segs, [s[1] for s in segs]) is None        # none is over its budget
+        both(binding._prunable_span, segs, budgets[:-1])
+    both(pk.segment_budgets, [(0, np.int64(4), np.int32(F), 0)], [np.int32(2)])          # not built-in: converted
+    both(pk.segment_budgets, [(0, 4, F, 0)], [True])
+
+
 @pytest.mark.parametrize("other", [dict(torch_version="0.0"), dict(pc_version=-1)])
 def test_compiled_half_of_another_build_is_not_bound(L, monkeypatch, other):
     import torch  # noqa: F401
