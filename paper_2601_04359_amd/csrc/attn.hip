@@ -477,8 +477,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 // attn_bf16_kernel makes of the same rows, each an eighth as long; K and V come through L2 once per
 // 32 rows instead of once per 256, which is why large calls do not take this form (a step of 8 x 32
 // keys takes 1.4 us with every compute unit at it: 0.78 PFLOP/s at most).  8/2 heads x 252 rows x
-// 1,179 keys: 34 us in 8 work-groups of 256 rows, 10.2 us un-split in 64 of these (11.3 before the query rows
-// came through LDS; 2/1 x 184 x 900 8.9 -> 7.8).  The loop runs at what a compute unit draws from L2 (128 KB a
+// 1,179 keys: 29.7 us in 8 work-groups of 256 rows, 9.9 us un-split in 64 of these (11.3 before the query rows
+// came through LDS; 2/1 x 184 x 900 8.9 -> 7.7).  The loop runs at what a compute unit draws from L2 (128 KB a
 // step in 1.17 us).  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
 // ------------------------------------------------------------------------------------------
 constexpr int kSmallRows = 32;
@@ -770,11 +770,13 @@ constexpr int kMaxKeySplits = 16;
 // 29,500 keys) in both forms with 1 to 16 shares: `start` is what a work-group costs beside its
 // steps, a step is 64 keys here and 8 x 32 keys there and gets slower as the compute units fill up,
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
-// (512 bytes written and read per row and share).  On 144 further shapes (2/1 to 24/8 heads, 64 to 1,000
-// rows, 300 to 8,000 keys) the cut it picks is 0.75 % off the best on average.  Where the line lies, both
-// sides measured: 8/2 heads x 252 rows x 1,179 keys, 10.2 us with 32 rows against 18.8 with 256 (and 34
-// un-split); 16/4 x 400 x 3,000, 21.6 against 27.2; 24/8 x 568 x 2,200, 33.9 against 32.1; 16/4 x 1,008 x
-// 7,455, 92.9 against 67.4.
+// (512 bytes written and read per row and share).  The 32-row form's start was fitted again, to 144 shapes (2/1
+// to 24/8 heads, 64 to 1,000 rows, 300 to 8,000 keys), when its query rows came to go through LDS: 6.0 -> 4.9, the
+// cut 0.75 % off the best on average (1.7 before).  On 160 further shapes (up to 1,500 rows and 12,000 keys) the
+// form it picks is 0.5 % off the other one, at most 13 % (24/8 heads x 883 x 1,379).  Where the line lies, both
+// sides measured: 8/2 heads x 252 rows x 1,179 keys, 9.9 us with 32 rows against 16.8 with 256 (and 29.7
+// un-split); 16/4 x 400 x 3,000, 19.9 against 29.4; 24/8 x 568 x 2,200, 29.5 against 30.6; 16/4 x 1,008 x
+// 7,455, 90 against 69.
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
 // rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
 // third of the partial rows and a round less: 363 us, 381 with all of them cut).
@@ -839,9 +841,13 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
 //     64 db + 4 r + e, so a lane's accumulators are whole 16-byte pieces of its output row.
 //   * Softmax in base 2: a score is s (c + c_lo) with one rounding, c + c_lo = scale * log2(e).
 // Measured: 8/2 heads, 252 rows, 1,804 keys, D = 128 (1.86 GFLOP, 12 us at the rate a large fp32
-// product reaches) 30 us a call with kR = 2 and four key shares, 37 with kR = 1 and two, 3,945 with
-// one thread per row and plain FMA; 24/8 heads, 1,000 rows, 8,000 keys 874 us against 1,220
-// (112 TFLOP/s); 8/2 heads, 60 rows, 300 keys 13 us against 10.
+// product reaches) 29 us a call with kR = 2 and four key shares, 35 with kR = 1 and two, 3,945 with
+// one thread per row and plain FMA; 24/8 heads, 1,000 rows, 8,000 keys 872 us against 1,197
+// (113 TFLOP/s); 8/2 heads, 60 rows, 300 keys 11 us against 9.
+// Where those 29 us go (clock stamps): every wave fetches all the query rows itself, 64 bytes of a row per
+// load, and the second wave of a SIMD gets its first loads issued 6.5 us behind the first, whose products start
+// at 4.2 us; with both running a step of each takes 4.1 us, at the matrix rate (2 x 128 products of 32 cycles
+// are 3.7); they end at 24.6, the merge through LDS takes 1.1 and the merge launch the rest.
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 8;
 template <int D, int kR>

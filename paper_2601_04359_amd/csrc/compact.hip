@@ -422,7 +422,7 @@ __device__ __forceinline__ int lanes_below(uint64_t mask, int base) {  // base +
 }
 
 // The k best of the len scores at sc, by one wave: store(at, source row) for the at-th of them in
-// ascending row order.  kRows x 64 keys at most (plus the ragged row); hist: 2^kBits words of LDS of the
+// ascending row order.  kRows x 64 keys at most; hist: 2^kBits words of LDS of the
 // wave's own.
 template <int kRows, int kBits, class Store>
 __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int len, int k, int start, int* hist,
@@ -487,8 +487,8 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
     }
     first = false;
     wave_lds_sync();
-    // lane l owns bins 32 l .. 32 l + 31; the eight 16-byte reads are rotated by the lane so that
-    // neighbouring lanes use different LDS banks
+    // lane l owns the kOwn bins from kOwn l on; its 16-byte reads are rotated by the lane so that neighbouring
+    // lanes use different LDS banks
     int mine = 0;
 #pragma unroll
     for (int j = 0; j < kOwn / 4; ++j) {
@@ -500,7 +500,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ sc, int le
     const uint64_t owner_mask = __ballot(above < remaining && remaining <= above + mine);  // exactly one lane
     const int owner = owner_mask ? __builtin_ctzll(owner_mask) : 0;
     const int above_owner = __builtin_amdgcn_readlane(above, owner);
-    // the owner's 32 bins, one per lane of the lower half wave; suffix sums again
+    // the owner's bins, one per lane; suffix sums again
     const int c_bin = lane < kOwn ? hist[owner * kOwn + lane] : 0;
     const int upto_b = wave_prefix_sum(c_bin);
     const int above_b = above_owner + __builtin_amdgcn_readlane(upto_b, kOwn - 1) - upto_b;  // matching keys with a larger digit
@@ -756,8 +756,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
 // needs no order between work-groups: each one selects for itself (a wave per segment, kept rows in
 // LDS), then walks the packed rows upwards, loads of a pass before its stores.
 constexpr int kFusedThreads = 1024, kFusedWaves = kFusedThreads / 64;
-constexpr int kFusedBits = 8;         // bins of a wave's histogram: 1 KB of LDS each
-constexpr int kFusedSelRows = 16;     // segments of up to 1,024 scores (and a ragged row)
+constexpr int kFusedBits = 8;         // digit of a wave's histogram: 256 bins, 1 KB of LDS
+constexpr int kFusedSelRows = 16;     // segments of up to 1,024 scores
 constexpr int kFusedMaxLen = kFusedSelRows * 64;
 constexpr int kFusedMaxRows = 8192;   // kept rows in LDS
 constexpr int kFusedPasses = 4;       // pieces a thread has in flight
