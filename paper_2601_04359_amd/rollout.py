@@ -276,7 +276,7 @@ class RollingStack:
 
     def repack(self) -> None:
         """End of the frame step: every layer keeps, per past frame, its top-budget keys; one
-        select launch and one gather launch for the whole stack, in place."""
+        select launch and one gather launch (small caches: one for both) for the whole stack, in place."""
         budgets = self.budgets()
         if pk._prunable_span(self.segments, budgets) is None:
             return
