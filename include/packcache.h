@@ -253,8 +253,8 @@ int pc_compact_static(void* K, void* V, int32_t* pos, int dtype, int Hkv, int D,
 /* ---------------------------------------------------------------------------------------
  * pc_compact_batch -- pc_compact for n_layers layers at once (the caches of a layer stack are
  * re-packed together at a frame-step boundary): one select launch and one gather launch
- * (for small caches one launch in all, see pc_compact_cut) cover every layer, so the small per-layer launches neither queue behind each other nor
- * leave the chip part empty.  Layer l of every tensor starts *_stride_l elements after
+ * (for small caches one launch in all, see pc_compact_cut) cover every layer, so the small
+ * per-layer launches neither queue behind each other nor leave the chip part empty.  Layer l of every tensor starts *_stride_l elements after
  * layer l-1 (K, V: elements of dtype; pos, idx: int32; score: fp32); everything else is as
  * in pc_compact and is the same for all layers: one segment table, one budget per segment
  * (budgets depend on the temporal distance only), one dtype, Hkv and D.  n_layers = 1 with
