@@ -828,32 +828,56 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
 // cycles, twice the rate of scalar FMAs).  Bound: matrix rate and the loads of K and V when the chip
 // is full, latency at the few-hundred-token sizes this tier is used at, so the work is cut fine: a
 // work-group owns 16 kR query rows (numbered through the heads of the KV head, as above), its 8 waves
-// take the keys in steps of 32 / kR by turns (no LDS, no barrier in the loop) and merge their
+// take the keys in steps of 16 by turns (LDS of their own, no barrier in the loop) and merge their
 // (O, m, l) through LDS once; when that leaves compute units idle the host cuts the keys into shares
-// as well (plan_f32).  kR = 2 loads K and V half as often per product, kR = 1 starts and ends sooner.
+// as well (plan_f32).  kR = 2 reads K and V half as often per product, kR = 1 starts and ends sooner.
 //   * S^T = K Q^T: lane (r = l % 16, kg = l / 16) holds key row r, dims 16 s + 4 kg .. + 3 as one
 //     16-byte load; the four MFMAs of step s contract over (kg, element e), the same permutation
 //     of the head dimension on both operands.
 //   * The result leaves lane (q = l % 16, kg) with keys 4 kg .. 4 kg + 3 of its query column:
 //     max and sum need two cross-lane steps, and P^T is already the B operand of O^T += V^T P^T
 //     (product e contracts over keys 4 kg + e).
-//   * V is the A operand through 16-byte loads too: row r of output block (db, e) stands for dim
+//   * V is the A operand through 16-byte reads too: row r of output block (db, e) stands for dim
 //     64 db + 4 r + e, so a lane's accumulators are whole 16-byte pieces of its output row.
 //   * Softmax in base 2: a score is s (c + c_lo) with one rounding, c + c_lo = scale * log2(e).
+//   * Rows travel whole (1 KB per load) to registers and from there to LDS; as fragments straight from memory they
+//     were 64 bytes of each of 16 rows per load, and lines were fetched twice.  One instruction stream
+//     forms the scores of a step and the probabilities of the step before, and moves a piece of K or V between
+//     products: a wave that issues all its loads at once waits for the seven others' in front of its products.
 // Measured: 8/2 heads, 252 rows, 1,804 keys, D = 128 (1.86 GFLOP, 12 us at the rate a large fp32
-// product reaches) 29 us a call with kR = 2 and four key shares, 35 with kR = 1 and two, 3,945 with
-// one thread per row and plain FMA; 24/8 heads, 1,000 rows, 8,000 keys 872 us against 1,197
-// (113 TFLOP/s); 8/2 heads, 60 rows, 300 keys 11 us against 9.
-// Where those 29 us go (clock stamps): every wave fetches all the query rows itself, 64 bytes of a row per
-// load, and the second wave of a SIMD gets its first loads issued 6.5 us behind the first, whose products start
-// at 4.2 us; with both running a step of each takes 4.1 us, at the matrix rate (2 x 128 products of 32 cycles
-// are 3.7); they end at 24.6, the merge through LDS takes 1.1 and the merge launch the rest.
+// product reaches) 29.1 -> 26.1 us; 260 calls of the sizes this tier is used at 1.11 times as fast at the median, none
+// slower (24/8 heads x 155 x 1,379 37.1 -> 32.1, 8/2 x 63 x 261 9.5 -> 8.6; D = 64, 8/2 x 169 x 345 8.3 -> 7.1).
+// A large call, 24/8 x 1,000 x 8,000: 872 -> 821 us (120 TFLOP/s).
+// Where the 26 us go (clock stamps; the chip runs at 2.04 GHz): queries in LDS at 1.1 us, the first scores at
+// 3.9, then 4.7 us for a step of both waves of a SIMD, of which the matrix pipe works 4.0 (2 x 128 products of
+// 32 cycles); eight such steps on the SIMD with the most, the merge through LDS from 22.3 on and the merge launch.
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 8;
-template <int D, int kR>
-constexpr size_t f32_smem_bytes() {
-  return sizeof(float) * kF32Waves * 16 * kR * (D + 2);
+constexpr int kF32Keys = 16;   // keys of a wave's step
+constexpr float kF32Trigger = 256.f;
+template <int D, int kR, int kWaves>
+constexpr size_t f32_smem_bytes() {   // a step's K and V rows of every wave, the query rows, the waves' (m, l)
+  return sizeof(float) * (kWaves * (kWaves <= 2 ? 1 : 2) * kF32Keys * D + 16 * kR * D + kWaves * 16 * kR * 2);
 }
+
+// Sixteen rows as D / 16 pieces of 1 KB, 16 bytes per lane, through a buffer descriptor: rows past the end are zeros,
+// and a piece costs no address arithmetic.
+template <int D>
+struct F32Rows {
+  __amdgpu_buffer_rsrc_t rows;
+  __device__ __forceinline__ F32Rows(const float* __restrict__ base, int k0, int n_rows) {
+    const int first = min(k0, n_rows);
+    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + static_cast<int64_t>(first) * D), 0,
+                                             min(n_rows - first, kF32Keys) * D * 4, 0x00020000);
+  }
+  __device__ __forceinline__ f32x4 piece(int j, int lane_bytes) const {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, lane_bytes, j * 1024, 0));
+  }
+};
+// Rows in LDS: 16-byte chunk c of row i lies at place c ^ (i % 16), so that writing whole rows and reading either
+// operand's fragments use every bank.  Offsets are a lane's own number and an exclusive or with what is known.
+template <int D>
+__device__ __forceinline__ int f32_place(int row, int chunk) { return (row * (D / 4) + (chunk ^ (row & 15))) * 16; }
 
 template <int D, int kR, int kWaves>
 __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
@@ -861,14 +885,21 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     float* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
     int64_t kv_stride_h, int64_t o_stride_h, float scale, int keys_per_split, Divisor by_tiles_q, int n_tiles,
     float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
-  static_assert(kR == 1 || kR == 2, "a step is two 16 x 16 products");
-  constexpr int kS = D / 16, kB = D / 64, kF32Rows = 16 * kR, kT = 2 / kR, kF32Keys = 16 * kT;  // kT: key blocks
+  constexpr int kS = D / 16, kB = D / 64, kF32Rows = 16 * kR;
+  using Rows = F32Rows<D>;
   extern __shared__ __align__(16) uint8_t smem_raw[];
-  float* s_o = reinterpret_cast<float*>(smem_raw);        // [wave][row][D]
-  float* s_m = s_o + kWaves * kF32Rows * D;               // [wave][row]
-  float* s_l = s_m + kWaves * kF32Rows;
+  lds_u8* smem = (lds_u8*)smem_raw;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
+  constexpr int kTile = kF32Keys * D * 4;      // bytes of a step's keys
+  constexpr bool kOneStep = kWaves <= 2;       // the host gives no wave of these a second step
+  constexpr int kValues = kOneStep ? 0 : kTile, kMine = kValues + kTile;   // LDS of a wave: its keys, its values (where
+                                               // the keys were if there is one step); its rows in the merge
+  constexpr int kQAt = kWaves * kMine;         // the query rows
+  float* s_m = reinterpret_cast<float*>(smem_raw + kQAt + kF32Rows * D * 4);   // the merge: [wave][row]
+  float* s_l = s_m + kWaves * kF32Rows;
+  static_assert(kF32Rows * D * 4 <= kMine, "a wave's rows on their way to the merge lie where its keys were");
+  auto at4 = [&](int bytes) { return reinterpret_cast<__attribute__((address_space(3))) f32x4*>(smem + bytes); };
   // logical order: key split slowest, then KV head, then row tile: the work-groups of one XCD (one L2)
   // read the same keys
   int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);
@@ -877,15 +908,41 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
   const float* Kh = K + kvh * kv_stride_h;
   const float* Vh = V + kvh * kv_stride_h;
   const int k_begin = split * keys_per_split, k_end = min(k_begin + keys_per_split, Nk);
+  constexpr int kStride = kWaves * kF32Keys;
+  const int k_first = k_begin + wave * kF32Keys;
+  const int n = k_first >= k_end ? 0 : kOneStep ? 1 : (k_end - k_first + kStride - 1) / kStride;   // steps of this wave
 
-  f32x4 q[kR][kS];
+  // The query rows come through LDS once and stay there.
+  constexpr int kQPieces = kF32Rows * (D / 4), kQPasses = (kQPieces + 64 * kWaves - 1) / (64 * kWaves);
+  f32x4 raw_q[kQPasses], raw[kS], raw_k[kS], raw_v[kS];
 #pragma unroll
-  for (int t = 0; t < kR; ++t) {
-    const RowAt at = row_at(min(row0 + t * 16 + r, n_rows - 1), kvh, rep, by_nq);
-    const float* qrow = Q + at.head * q_stride_h + static_cast<int64_t>(at.row) * D + kg * 4;
-#pragma unroll
-    for (int s = 0; s < kS; ++s) q[t][s] = load_f32x4(qrow + s * 16);
+  for (int i = 0; i < kQPasses; ++i) {
+    const int e = min(static_cast<int>(threadIdx.x) + i * 64 * kWaves, kQPieces - 1);
+    const RowAt at = row_at(min(row0 + e / (D / 4), n_rows - 1), kvh, rep, by_nq);
+    raw_q[i] = load_f32x4(Q + at.head * q_stride_h + static_cast<int64_t>(at.row) * D + e % (D / 4) * 4);
   }
+  const int lane_bytes = lane * 16;
+  {
+    const Rows k(Kh, k_first, Nk);
+#pragma unroll
+    for (int j = 0; j < kS; ++j) raw[j] = k.piece(j, lane_bytes);
+  }
+  const Rows k_second(Kh, k_first + kStride, Nk), v_first(Vh, k_first, Nk);
+  if constexpr (kOneStep) {
+#pragma unroll
+    for (int j = 0; j < kS; ++j) raw_v[j] = v_first.piece(j, lane_bytes);
+  }
+#pragma unroll
+  for (int i = 0; i < kQPasses; ++i) {
+    const int e = min(static_cast<int>(threadIdx.x) + i * 64 * kWaves, kQPieces - 1);
+    *at4(kQAt + f32_place<D>(e / (D / 4), e % (D / 4))) = raw_q[i];
+  }
+  // What a lane adds to or exclusive-ors with: piece j it writes, key and query fragment s, value fragment (e, b).
+  constexpr int kRowsPer = 256 / D;   // rows of a piece
+  int put_at = wave * kMine + f32_place<D>(lane / (D / 4), lane % (D / 4));
+  int key_at = wave * kMine + f32_place<D>(r, kg), q_at = kQAt + f32_place<D>(r, kg);
+  int val_at = wave * kMine + kValues + f32_place<D>(kg * 4, r);
+  auto put = [&](int tile, int j, f32x4 v) { *at4((put_at ^ (kRowsPer * j * 16)) + tile + j * 1024) = v; };
   f32x4 o[kR][kB][4];
 #pragma unroll
   for (int t = 0; t < kR; ++t)
@@ -904,107 +961,147 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
   auto rest = [&] { return fmaf(scale, 1.92596299e-8f, fmaf(scale, 1.4426950216293335f, -c)); };
   if (rest() < 0.f) c = __uint_as_float(__float_as_uint(c) - 1);
   const float c_lo = fmaxf(rest(), 1.17549435e-38f);
+  auto scaled = [&](float x) { return fmaf(x, c, x * c_lo); };
 
-  // Software pipeline: the V loads of a step fly during its score products, the K loads of the
-  // next step (into the registers those products just freed) during its softmax and value products.
-  // Rows of a step lie at 32-bit offsets from its first one (a scalar); past the end: the last row.
-  f32x4 kf[kT][kS], v[kT][4][kB];
-  auto load_k = [&](int k0) {
-    const int first = min(k0, Nk - 1), last = Nk - 1 - first;
-    const float* base = Kh + static_cast<int64_t>(first) * D;
+  __syncthreads();   // the query rows
+  // Scores of the keys in LDS; behind the products of contraction step s runs epi(s).
+  auto score_products = [&](f32x4 (&out)[kR], auto&& epi) {
+    f32x4 kf[2], qf[2][kR];
+    auto fetch = [&](int s) {
+      kf[s & 1] = *at4(key_at ^ (s * 64));
 #pragma unroll
-    for (int u = 0; u < kT; ++u) {
-      const uint32_t at = min(u * 16 + r, last) * D + kg * 4;
+      for (int t = 0; t < kR; ++t) qf[s & 1][t] = *at4((q_at ^ (s * 64)) + t * kTile);
+    };
 #pragma unroll
-      for (int s = 0; s < kS; ++s) kf[u][s] = load_f32x4(base + at + s * 16);
+    for (int t = 0; t < kR; ++t) out[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+#pragma unroll
+    for (int s = 0; s < kS; ++s) {
+      if (s + 1 < kS) fetch(s + 1);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < kR; ++t) out[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s & 1][e], qf[s & 1][t][e], out[t], 0, 0, 0);
+      epi(s);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  load_k(k_begin + wave * kF32Keys);
-  for (int k0 = k_begin + wave * kF32Keys; k0 < k_end; k0 += kWaves * kF32Keys) {
-    const int last = Nk - 1 - k0;
-    const float* v_base = Vh + static_cast<int64_t>(k0) * D;
+  // Exact maximum of a step's (scaled) scores becomes the reference; O and l follow it.
+  auto new_reference = [&](const f32x4 (&sc)[kR]) {
 #pragma unroll
-    for (int u = 0; u < kT; ++u)
+    for (int t = 0; t < kR; ++t) {
+      float mx = scaled(sc[t][0]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t at = min(u * 16 + kg * 4 + e, last) * D + r * 4;
+      for (int e = 1; e < 4; ++e) mx = fmaxf(mx, scaled(sc[t][e]));
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = wave_half_max(mx);
+      const float m_new = fmaxf(m[t], mx), alpha = __builtin_amdgcn_exp2f(m[t] - m_new);
+      l[t] *= alpha;
 #pragma unroll
-        for (int b = 0; b < kB; ++b) v[u][e][b] = load_f32x4(v_base + at + b * 64);
-      }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 sc[kR][kT];   // two independent products, interleaved
+      for (int b = 0; b < kB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[t][b][e] *= alpha;
+      m[t] = m_new;
+    }
+  };
+  auto mask = [&](f32x4 (&sc)[kR], int k0) {
+    if (k0 + kF32Keys <= k_end) return;
 #pragma unroll
     for (int t = 0; t < kR; ++t)
 #pragma unroll
-      for (int u = 0; u < kT; ++u) sc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < kS; ++s)
-#pragma unroll
       for (int e = 0; e < 4; ++e)
+        if (k0 + kg * 4 + e >= k_end) sc[t][e] = -INFINITY;
+  };
+
+  // Software pipeline: while the scores of a step are formed, the probabilities of the step before are, against
+  // the reference as it stands (no maximum is taken unless a sum of them comes out above kF32Trigger);
+  // then that step's values are added up.  Piece by piece between the products, the values of a step go to LDS
+  // while its successor's scores are formed and the keys after those are fetched into the registers that become
+  // free, and the other way round: a wave never waits for the loads of eight to be taken.
+  f32x4 sc[kR], nxt[kR], p[kR];
+  if (n > 0) {
 #pragma unroll
-        for (int t = 0; t < kR; ++t)
-#pragma unroll
-          for (int u = 0; u < kT; ++u)
-            sc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][s][e], q[t][s][e], sc[t][u], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_k(k0 + kWaves * kF32Keys);  // past the end: clamped rows, never used
-    __builtin_amdgcn_sched_barrier(0);
-    float mx[kR];
-    bool lags = false;   // a reference may lag by 2^8
-#pragma unroll
-    for (int t = 0; t < kR; ++t) {
-      mx[t] = -INFINITY;
-#pragma unroll
-      for (int u = 0; u < kT; ++u) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sc[t][u][e] = fmaf(sc[t][u][e], c, sc[t][u][e] * c_lo);
-        if (k0 + kF32Keys > k_end) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (k0 + u * 16 + kg * 4 + e >= k_end) sc[t][u][e] = -INFINITY;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mx[t] = fmaxf(mx[t], sc[t][u][e]);
+    for (int j = 0; j < kS; ++j) put(0, j, raw[j]);
+    wave_lds_sync();
+    score_products(sc, [&](int s) {
+      if constexpr (!kOneStep) {
+        raw_k[s] = k_second.piece(s, lane_bytes);
+        raw_v[s] = v_first.piece(s, lane_bytes);
       }
-      mx[t] = fmaxf(mx[t], __shfl_xor(mx[t], 16));
-      mx[t] = wave_half_max(mx[t]);
-      lags = lags || !(mx[t] <= m[t] + 8.f);
+    });
+    mask(sc, k_first);
+    new_reference(sc);
+    wave_lds_sync();   // the first keys' fragments have been read
+#pragma unroll
+    for (int j = 0; j < kS; ++j) {
+      if constexpr (!kOneStep) put(0, j, raw_k[j]);
+      raw[j] = raw_v[j];
     }
-    if (__any(lags)) {
+  }
+  for (int i = 0; i < n; ++i) {
+    const int k0 = k_first + i * kStride;
+    const Rows k_next(Kh, k0 + 2 * kStride, Nk), v_next(Vh, k0 + kStride, Nk);   // past the end: never used
+    // (opaque: else every offset formed from them becomes a register that is kept across the loop)
+    asm volatile("" : "+v"(put_at), "+v"(key_at), "+v"(q_at), "+v"(val_at));
+    wave_lds_sync();
+    float sum[kR];
 #pragma unroll
-      for (int t = 0; t < kR; ++t) {
-        const float m_new = fmaxf(m[t], mx[t]), alpha = __builtin_amdgcn_exp2f(m[t] - m_new);
-        l[t] *= alpha;
+    for (int t = 0; t < kR; ++t) sum[t] = 0.f;
+    auto probability = [&](int j) {
+      const int t = j / 4, e = j % 4;
+      p[t][e] = __builtin_amdgcn_exp2f(scaled(sc[t][e]) - m[t]);
+      sum[t] += p[t][e];
+    };
+    if (!kOneStep && i + 1 < n) {   // wave-uniform
+      score_products(nxt, [&](int s) {
+        put(kValues, s, raw[s]);
+        raw[s] = k_next.piece(s, lane_bytes);
 #pragma unroll
-        for (int b = 0; b < kB; ++b)
+        for (int j = s * kR * 4 / kS; j < (s + 1) * kR * 4 / kS; ++j) probability(j);
+      });
+      mask(nxt, k0 + kStride);
+    } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[t][b][e] *= alpha;
-        m[t] = m_new;
-      }
+      for (int s = 0; s < kS; ++s) put(kValues, s, raw[s]);
+#pragma unroll
+      for (int j = 0; j < kR * 4; ++j) probability(j);
+    }
+    bool away = false;
+#pragma unroll
+    for (int t = 0; t < kR; ++t) away = away || !(sum[t] <= kF32Trigger);   // inf and NaN too
+    if (__any(away)) {
+      new_reference(sc);
+#pragma unroll
+      for (int t = 0; t < kR; ++t) sum[t] = 0.f;
+#pragma unroll
+      for (int j = 0; j < kR * 4; ++j) probability(j);
     }
 #pragma unroll
-    for (int t = 0; t < kR; ++t) {
-      float sum = 0.f;
+    for (int t = 0; t < kR; ++t) l[t] += sum[t];
+    wave_lds_sync();
+    auto add_values = [&](auto more) {
+      f32x4 v[2];
+      auto fetch = [&](int j) { v[j & 1] = *at4((val_at ^ (j / kB * 16)) + j / kB * D * 4 + j % kB * 256); };
+      fetch(0);
 #pragma unroll
-      for (int u = 0; u < kT; ++u)
+      for (int j = 0; j < 4 * kB; ++j) {
+        const int e = j / kB, b = j % kB;
+        if (j + 1 < 4 * kB) fetch(j + 1);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          sc[t][u][e] = __builtin_amdgcn_exp2f(sc[t][u][e] - m[t]);
-          sum += sc[t][u][e];
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int t = 0; t < kR; ++t)
+            o[t][b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j & 1][x], p[t][e], o[t][b][x], 0, 0, 0);
+        if constexpr (decltype(more)::value) {
+          put(0, j, raw[j]);
+          raw[j] = v_next.piece(j, lane_bytes);
         }
-      l[t] += sum;
-    }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (!kOneStep && i + 1 < n) add_values(std::true_type{}); else add_values(std::false_type{});
 #pragma unroll
-    for (int u = 0; u < kT; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int b = 0; b < kB; ++b)
-#pragma unroll
-          for (int x = 0; x < 4; ++x)
-#pragma unroll
-            for (int t = 0; t < kR; ++t)
-              o[t][b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][e][b][x], sc[t][u][e], o[t][b][x], 0, 0, 0);
+    for (int t = 0; t < kR; ++t) sc[t] = nxt[t];
   }
 
   // accumulator element (b, x, i) of lane (q = r, kg) is dim 64 b + 16 kg + 4 i + x of its query row
@@ -1027,12 +1124,11 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
       continue;
     }
     const int row = wave * kF32Rows + t * 16 + r;
-    // 16-byte piece c of row i at place c ^ (i % 16): the 16 rows of a wave's store use every bank
 #pragma unroll
     for (int b = 0; b < kB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<f32x4*>(s_o + row * D + ((b * 16 + kg * 4 + i) ^ r) * 4) =
+        *at4(wave * kMine + f32_place<D>(t * 16 + r, b * 16 + kg * 4 + i)) =
             f32x4{o[t][b][0][i], o[t][b][1][i], o[t][b][2][i], o[t][b][3][i]};
     if (kg == 0) {
       s_m[row] = m[t];
@@ -1057,7 +1153,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     for (int w = 0; w < kWaves; ++w) {
       const float wt = __builtin_amdgcn_exp2f(s_m[w * kF32Rows + row] - M);
       lt += wt * s_l[w * kF32Rows + row];
-      acc += wt * *reinterpret_cast<const f32x4*>(s_o + (w * kF32Rows + row) * D + (col / 4 ^ (row & 15)) * 4);
+      acc += wt * *at4(w * kMine + f32_place<D>(row, col / 4));
     }
     const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;   // row number over all heads
     if (part_o != nullptr) {  // one of several key shares: merged by attn_merge_kernel
@@ -1072,18 +1168,18 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
   }
 }
 
-// How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 13 shapes (2 to 24 heads, 40
-// to 1,000 rows, 100 to 8,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it
-// picks is the best of them on 12 and 4 % off on the last.  A step's waves contend for the matrix
-// pipes and the loads, so a part-filled step costs its part.  Shares that need more than 16 MB of workspace
-// have to save more than those 4 % (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
-// The keys of one step need one wave and no merge (16/4 heads, 4,032 rows, 32 keys, D = 64: 33.3 us with
-// eight waves, 15.1 with one; 3 keys, D = 128: 49.5 and 26.1).
+// How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 400 calls (2 to 24 heads, 33 to 700
+// rows, 70 to 4,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it picks is 0.4 %
+// off the best of them on average, 2.5 % on one call in twenty.  A SIMD has two of the eight waves, so a share
+// lasts as long as a quarter of its steps.  Shares that need more than 16 MB of workspace have to save more than
+// those 4 % (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
+// The keys of one or two steps need as many waves, whose values take the place of their keys in LDS (16/4 heads,
+// 4,032 rows, 32 keys, D = 64: 33.3 us with eight waves, 12.9 with two; 3 keys, D = 128: 49.5, and 19.3 with one).
 struct F32Plan {
   int kr, n_splits, waves;
 };
 F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
-  if (Nk <= 32) return {1, 1, 1};
+  if (Nk <= 2 * kF32Keys) return {1, 1, Nk <= kF32Keys ? 1 : 2};
   F32Plan best = {1, 1, kF32Waves};
   double best_cost = 1e30;
   F32Plan uncut = best;
@@ -1095,9 +1191,10 @@ F32Plan plan_f32(int Hkv, int rows, int Nk, int D, size_t ws_bytes) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
       if (attn_partial_bytes(static_cast<int64_t>(Hkv) * rows, D, s) > ws_bytes) break;
-      const double merge = s == 1 ? 0.0 : 2.2 + 8.6e-4 * s * Hkv * rows * f;
-      const double cost = (kr == 1 ? 2.1 : 3.5) + 3.4 * f +
-                          ceil_div(blocks * s, 256) * (kr == 1 ? 7.0 : 5.15) * f * per / kF32Waves + merge;
+      const double merge = s == 1 ? 0.0 : 2.65 + 4.5e-4 * s * Hkv * rows * f;
+      const int steps = ceil_div(ceil_div(per * (32 / kr), kF32Keys), 4);   // of a SIMD
+      const double cost = (kr == 1 ? 2.25 + 1.0 * f : 3.4 + 0.3 * f) +
+                          ceil_div(blocks * s, 256) * (kr == 1 ? 1.31 : 2.16) * f * steps + merge;
       if (cost < best_cost) {
         best_cost = cost;
         best = {kr, s, kF32Waves};
@@ -1118,11 +1215,15 @@ int attn_f32(const float* Q, const float* K, const float* V, int Hq, int rep, in
              hipStream_t s) {
   const F32Plan plan = plan_f32(Hq / rep, rep * Nq, Nk, D, usable_bytes(ws, ws_bytes));
   const auto kernel = plan.waves == 1 ? attn_f32_kernel<D, 1, 1>
+                      : plan.waves == 2 ? attn_f32_kernel<D, 1, 2>
                       : plan.kr == 2  ? attn_f32_kernel<D, 2, kF32Waves>
                                       : attn_f32_kernel<D, 1, kF32Waves>;
-  const size_t smem = plan.waves == 1 ? 0 : plan.kr == 2 ? f32_smem_bytes<D, 2>() : f32_smem_bytes<D, 1>();
+  const size_t smem = plan.waves == 1 ? f32_smem_bytes<D, 1, 1>()
+                      : plan.waves == 2 ? f32_smem_bytes<D, 1, 2>()
+                      : plan.kr == 2  ? f32_smem_bytes<D, 2, kF32Waves>()
+                                      : f32_smem_bytes<D, 1, kF32Waves>();
   static std::atomic<uint64_t> lds_ok[2];
-  if (smem != 0)
+  if (plan.waves == kF32Waves)
     if (int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), smem, lds_ok[plan.kr - 1], "pc_frame_attn"))
       return rc;
   const int n_tiles_q = ceil_div(rep * Nq, 16 * plan.kr), n_splits = plan.n_splits, unit = 32 / plan.kr;
