@@ -469,6 +469,76 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
   }
 }
 
+// Where the waves of a work-group share rows: wave w holds (O, m, l) of rows 32 (w % kR) .. + 31 over its keys, and
+// they are merged in wave order.  A wave's O goes to 16 KB of LDS of its own, piece i = accumulators
+// 4 i .. 4 i + 3 of every lane = dims 8 i + 4 g .. + 3 of its row, lanes permuted by i so that the reads
+// below use every bank; a thread then adds up eight dims of a row, and a row leaves whole.
+constexpr int kWaveOBytes = 32 * kD * 4;
+constexpr size_t kMergeBytes = 8 * kWaveOBytes + 8 * 32 * 8;
+template <int kR>
+__device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], float m, float l, int wave, int lane,
+                                            int tile, int kvh, int split, uint16_t* __restrict__ O,
+                                            float* __restrict__ lse, int rep, const Divisor& by_nq, int64_t o_stride_h,
+                                            float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
+  auto piece = [&](int w, int i, int of_lane) {
+    return reinterpret_cast<__attribute__((address_space(3))) f32x4*>(smem + w * kWaveOBytes + i * 1024 + (of_lane ^ i) * 16);
+  };
+  auto* s_ml = reinterpret_cast<__attribute__((address_space(3))) float*>(smem + 8 * kWaveOBytes);
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *piece(wave, db * 4 + a, lane) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
+  if (lane < 32) {
+    s_ml[(wave * 32 + lane) * 2] = m;
+    s_ml[(wave * 32 + lane) * 2 + 1] = l;
+  }
+  __syncthreads();
+  const int n_rows = rep * by_nq.d;
+  const int row = threadIdx.x >> 4, i = threadIdx.x & 15;
+#pragma unroll
+  for (int rg = 0; rg < kR; ++rg) {
+    const int rho = (tile * kR + rg) * 32 + row;
+    float mw[8 / kR], M = -INFINITY, lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8 / kR; ++w) {
+      mw[w] = s_ml[((w * kR + rg) * 32 + row) * 2];
+      M = fmaxf(M, mw[w]);
+    }
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int w = 0; w < 8 / kR; ++w) {
+      const float wt = __builtin_amdgcn_exp2f(mw[w] - M);
+      lt += wt * s_ml[((w * kR + rg) * 32 + row) * 2 + 1];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const f32x4 v = *piece(w * kR + rg, i, t * 32 + row);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][e] += wt * v[e];
+      }
+    }
+    if (rho >= n_rows) return;
+    const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;
+    if (part_o != nullptr) {
+      const int64_t at_s = split * rows_all + at;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4*>(part_o + at_s * kD + i * 8 + t * 4) = acc[t];
+      if (i == 0) part_ml[at_s] = make_float2(M, lt);
+      continue;
+    }
+    const float inv = 1.f / lt;
+    const RowAt to = row_at(rho, kvh, rep, by_nq);
+    u32x4 out;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      out[t * 2] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
+      out[t * 2 + 1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
+    }
+    *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + i * 8) = out;
+    if (lse != nullptr && i == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // bf16 frame attention for small calls: 32 query rows per work-group, the 8 waves take the keys in
 // steps of 32 by turns, each through LDS of its own (a step's fragments go to registers at once, and
@@ -484,10 +554,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 constexpr int kSmallRows = 32;
 constexpr int kSmallKeys = 32;                                  // keys per wave and step
 constexpr int kSmallTileBytes = kSmallKeys * kRowBytes;
-constexpr int kSmallOBytes = kSmallRows * kD * 4;               // a wave's O on its way to the merge
-constexpr int kSmallMlBytes = 8 * kSmallRows * 8;
-constexpr size_t kSmallSmem = 8 * kSmallOBytes + kSmallMlBytes + kSmallRows * kRowBytes;
-static_assert(2 * kSmallTileBytes <= kSmallOBytes, "a wave stages K and V in the LDS of its merge piece");
+constexpr size_t kSmallSmem = kMergeBytes + kSmallRows * kRowBytes;
+static_assert(2 * kSmallTileBytes <= kWaveOBytes, "a wave stages K and V in the LDS of its merge piece");
 
 __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -498,7 +566,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const lds_u8* lds = (lds_u8*)smem_raw + wave * kSmallOBytes;
+  const lds_u8* lds = (lds_u8*)smem_raw + wave * kWaveOBytes;
   const uint32_t lds_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);   // n_tiles row tiles per share
   const int split = take_share(unit, n_tiles);
@@ -523,7 +591,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   const int k_first = k_begin + wave * kSmallKeys;
   // The query rows go through LDS once, four per wave: every wave holds all of them, and as fragments from
   // memory (32 bytes of each row per load) they were 64 KB per work-group.
-  const lds_u8* q_tile = (lds_u8*)smem_raw + 8 * kSmallOBytes + kSmallMlBytes;
+  const lds_u8* q_tile = (lds_u8*)smem_raw + kMergeBytes;
   {
     const int row = wave * 4 + (lane >> 4);
     const RowAt from = row_at(min(tile * kSmallRows + row, n_rows - 1), kvh, rep, by_nq);
@@ -626,62 +694,221 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   l = wave_half_sum(l);
 
-  // merge in wave order: a wave's O goes to the LDS its keys came through, piece i = accumulators
-  // 4 i .. 4 i + 3 of every lane = dims 8 i + 4 g .. + 3 of its row, lanes permuted by i so that the reads
-  // below use every bank; a thread then adds up eight dims of a row, and a row leaves whole.
-  auto piece = [&](int w, int i, int of_lane) {
-    return reinterpret_cast<__attribute__((address_space(3))) f32x4*>((lds_u8*)smem_raw + w * kSmallOBytes + i * 1024 +
-                                                                      (of_lane ^ i) * 16);
+  merge_waves<1>((lds_u8*)smem_raw, o, m, l, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o, part_ml,
+                 rows_all);
+}
+
+// ------------------------------------------------------------------------------------------
+// bf16 frame attention between the two: 32 kR query rows per work-group (64 or 128), a wave for each pair of one of
+// kR row groups and one of 8 / kR key groups.  The keys are dealt to the key groups in tiles of 32; a tile is in
+// LDS once for the kR waves of its group, and the key groups' (O, m, l) are merged through LDS as in the small form.
+// Every wave runs the pipeline of attn_bf16_kernel, a phase per tile.  Bound: with every compute unit at it a
+// phase of eight 32 x 32 tiles takes 1.0 us at kR = 2 and 0.86 at kR = 4 (0.84 in the 256-row form, 1.36 in the 32-row
+// one): 64 KB a phase come into LDS at kR = 2 beside the 128 KB that the eight waves read.  LDS holds two slots per
+// operand and key group at kR = 2, four at kR = 4; fetching K a barrier earlier, a quarter into the phase,
+// made kR = 2 2 % slower, so the loads' latency is not what is left.
+// It is for calls whose 32-row tiles are more than the chip and whose 256-row tiles are far fewer: those went
+// through L2 once per 32 rows, or paid a merge launch and fp32 partial rows (16/4 heads x 666 rows x 1,786 keys
+// 25.0 -> 18.5 us, 6/2 x 1,593 x 1,701 26.7 -> 18.4, 24/8 x 1,070 x 1,691 40.8 -> 28.3, 16/4 x 581 x 823 14.4 -> 12.3,
+// 6/2 x 3,157 x 523 17.9 -> 13.9).
+// ------------------------------------------------------------------------------------------
+template <bool kUnitC, int kR>
+__global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_mid_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    uint16_t* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
+    int64_t kv_stride_h, int64_t o_stride_h, float c, Divisor by_tiles_q, int n_tiles, int share_steps,
+    float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
+  static_assert(kR == 2 || kR == 4, "row groups");
+  constexpr int kG = 8 / kR;                    // key groups
+  constexpr int kSlots = kR;                    // of a key group, per operand
+  constexpr int kTile = 32 * kRowBytes;         // 32 keys of K or V
+  constexpr int kGroupBytes = 2 * kSlots * kTile;
+  constexpr int kLoads = 8 / kR;                // a wave's share of a tile, 1 KB each
+  extern __shared__ __align__(16) uint8_t smem_raw[];
+  lds_u8* smem = (lds_u8*)smem_raw;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  auto k_slot = [](int t) { return (t & (kSlots - 1)) * kTile; };
+  auto v_slot = [](int t) { return (kSlots + (t & (kSlots - 1))) * kTile; };
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rg = wave % kR, kg = wave / kR;
+  const int l32 = lane & 31, g = lane >> 5;
+  int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);   // n_tiles row tiles per share
+  const int split = take_share(unit, n_tiles);
+  const int kvh = by_tiles_q.of(unit), tile = unit - kvh * by_tiles_q.d;
+  const int n_rows = rep * by_nq.d;
+  const int row_first = (tile * kR + rg) * 32;
+  const bool active = row_first < n_rows;   // wave-uniform
+  const uint16_t* Kh = K + kvh * kv_stride_h;
+  const uint16_t* Vh = V + kvh * kv_stride_h;
+  // this share's keys, whole steps but for the very last; tile t of the key group starts at key_at(t)
+  const int k_begin = split * share_steps * 32 * kG, k_end = min(k_begin + share_steps * 32 * kG, Nk);
+  const int n = (k_end - k_begin + 32 * kG - 1) / (32 * kG);
+  auto key_at = [&](int t) { return k_begin + (t * kG + kg) * 32; };
+
+  const uint32_t group0 = lds0 + kg * kGroupBytes;
+  auto stage = [&](auto is_v, int t, int slot_bytes) {
+    const RowWindow w = row_window(decltype(is_v)::value ? Vh : Kh, key_at(t), Nk);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int piece = rg * kLoads + i, row = piece * 4 + (lane >> 4), pos = lane & 15;
+      const int chunk = decltype(is_v)::value ? v_chunk_pos(row, pos) : k_chunk_pos(row, pos);
+      dma_16B_at(w.base, row_offset(w, row, chunk), group0 + slot_bytes + piece * 1024);
+    }
   };
-  auto* s_ml = reinterpret_cast<__attribute__((address_space(3))) float*>((lds_u8*)smem_raw + 8 * kSmallOBytes);
+  auto stage_k = [&](int t, int slot_bytes) { stage(std::false_type{}, t, slot_bytes); };
+  auto stage_v = [&](int t, int slot_bytes) { stage(std::true_type{}, t, slot_bytes); };
+
+  // Prologue: the queries (each key group's wave fetches its part of the row group's), through value slots that
+  // nothing is staged in yet, and the first tiles behind them.
+  const int q_at = kR == 2 ? rg * kGroupBytes + v_slot(0) : (rg & 1) * kGroupBytes + v_slot(1 + (rg >> 1));
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-      *piece(wave, db * 4 + a, lane) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
-  if (g == 0) {
-    s_ml[(wave * kSmallRows + l32) * 2] = m;
-    s_ml[(wave * kSmallRows + l32) * 2 + 1] = l;
+  for (int i = 0; i < 8 / kG; ++i) {
+    const int piece = kg * (8 / kG) + i, row = piece * 4 + (lane >> 4);
+    const RowAt from = row_at(min(row_first + row, n_rows - 1), kvh, rep, by_nq);
+    dma_16B(Q + from.head * q_stride_h + static_cast<int64_t>(from.row) * kD + k_chunk_pos(row, lane & 15) * 8,
+            __builtin_amdgcn_readfirstlane(lds0 + q_at + piece * 1024));
   }
-  __syncthreads();
-  const int row = threadIdx.x >> 4, i = threadIdx.x & 15, rho = tile * kSmallRows + row;
-  float mw[8], M = -INFINITY, lt = 0.f;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    mw[w] = s_ml[(w * kSmallRows + row) * 2];
-    M = fmaxf(M, mw[w]);
+  stage_k(0, k_slot(0));
+  stage_k(1, k_slot(1));
+  if constexpr (kR == 4) {
+    stage_v(0, v_slot(0));
+    stage_k(2, k_slot(2));
+    stage_k(3, k_slot(3));
   }
-  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  // the slot of "values of tile -1" is read once against zero probabilities: clear it
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    const float wt = __builtin_amdgcn_exp2f(mw[w] - M);
-    lt += wt * s_ml[(w * kSmallRows + row) * 2 + 1];
+  for (int i = 0; i < kLoads; ++i)
+    reinterpret_cast<__attribute__((address_space(3))) u32x4*>(smem + kg * kGroupBytes + v_slot(-1))[(rg * kLoads + i) * 64 + lane] =
+        u32x4{0u, 0u, 0u, 0u};
+  int k_off[8], v_off[4];  // as in attn_bf16_kernel, within the key group's LDS
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const f32x4 v = *piece(w, i, t * 32 + row);
+  for (int s = 0; s < 8; ++s) k_off[s] = kg * kGroupBytes + l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
+  {
+    const int r = lane & 15, G = (lane >> 4) & 1;
+    const int row = g * 4 + (r >> 2);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[t][e] += wt * v[e];
+    for (int db = 0; db < 4; ++db) {
+      const int dim = db * 32 + G * 16 + 4 * (r & 3);
+      v_off[db] = kg * kGroupBytes + row * kRowBytes + v_chunk_pos(row, dim >> 3) * 16 + (dim & 7) * 2;
     }
   }
-  if (rho >= n_rows) return;
-  const int64_t at = static_cast<int64_t>(kvh) * n_rows + rho;
-  if (part_o != nullptr) {
-    const int64_t at_s = split * rows_all + at;
+  f32x16 o[4], sA, sB, neg_m;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4*>(part_o + at_s * kD + i * 8 + t * 4) = acc[t];
-    if (i == 0) part_ml[at_s] = make_float2(M, lt);
-    return;
-  }
-  const float inv = 1.f / lt;
-  const RowAt to = row_at(rho, kvh, rep, by_nq);
-  u32x4 out;
+  for (int i = 0; i < 16; ++i) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    out[t * 2] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
-    out[t * 2 + 1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
+    for (int db = 0; db < 4; ++db) o[db][i] = 0.f;
+    sA[i] = sB[i] = neg_m[i] = 0.f;
   }
-  *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + i * 8) = out;
-  if (lse != nullptr && i == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
+  bf16x8 pA[2], pB[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pA[ks][e] = pB[ks][e] = static_cast<__bf16>(0.f);
+  float m_ref = -INFINITY, l_run = 0.f;
+  bool low_ref = false;   // wave-uniform
+  auto mask_tail = [&](f32x16& sc, int t) {
+    const int left = k_end - key_at(t);
+    if (left >= 32) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if ((i >> 2) * 8 + (i & 3) >= left - g * 4) sc[i] = -INFINITY;
+  };
+
+  // the queries and K(0): all but this wave's K(1) (and V(0), K(2), K(3))
+  if constexpr (kR == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+  __syncthreads();
+  bf16x8 qf[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) qf[s] = lds_frag(smem + q_at + l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
+  if (active) {  // scores of tile 0 and the first reference maximum
+    f32x16 zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(smem + k_slot(0) + k_off[s]), qf[s], s == 0 ? zero : sA, 0, 0, 0);
+    float mx = sA[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sA[i]);
+    m_ref = wave_half_max(mx) * c;
+    if constexpr (kUnitC) {
+      const float start = m_ref >= kLowestStart ? m_ref : 0.f;
+      low_ref = __any(!(m_ref >= kLowestStart));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        sA[i] -= start;
+        neg_m[i] = -start;
+      }
+    }
+    mask_tail(sA, 0);
+  }
+  if constexpr (kR == 4) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();   // K(1) has landed; K(0) and the queries have been read
+  if constexpr (kR == 4) stage_v(1, v_slot(1));
+  stage_k(kSlots, k_slot(0));
+  stage_v(kSlots - 2, v_slot(kSlots - 2));
+
+  // Phase p: S(p+1), O += V(p-1) P(p-1)  |  P(p).  Behind it one barrier: K(p+1) and V(p-1) have been read by
+  // all, K(p+2) and V(p) have landed (fetched kSlots - 1 phases ago), and K(p+1+kSlots), V(p-1+kSlots) are fetched.
+  auto phase = [&](int p, auto slot_tag, const f32x16& s_cur, f32x16& s_nxt, const bf16x8 (&p_mm)[2], bf16x8 (&p_cur)[2]) {
+    constexpr int u = decltype(slot_tag)::value;   // p % kSlots
+    constexpr int k_nxt = ((u + 1) & (kSlots - 1)) * kTile, v_prev = (kSlots + ((u + kSlots - 1) & (kSlots - 1))) * kTile;
+    if (active) {
+      pipeline_phase<kUnitC>(smem + k_nxt, k_off, smem + v_prev, v_off, qf, s_nxt, p_mm, o, s_cur, p_cur, m_ref, l_run, c,
+                             neg_m, low_ref);
+      mask_tail(s_nxt, p + 1);
+    }
+    if constexpr (kR == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (p + 1 < n) {
+      stage_k(p + 1 + kSlots, k_nxt);
+      stage_v(p - 1 + kSlots, v_prev);
+    }
+  };
+  for (int p = 0; p < n; p += kSlots) {
+    phase(p, std::integral_constant<int, 0>{}, sA, sB, pB, pA);
+    if (p + 1 >= n) break;
+    phase(p + 1, std::integral_constant<int, 1>{}, sB, sA, pA, pB);
+    if constexpr (kSlots == 4) {
+      if (p + 2 >= n) break;
+      phase(p + 2, std::integral_constant<int, 2>{}, sA, sB, pB, pA);
+      if (p + 3 >= n) break;
+      phase(p + 3, std::integral_constant<int, 3>{}, sB, sA, pA, pB);
+    }
+  }
+  // drain: O += V(n-1) P(n-1)
+  if (active) {
+    const lds_u8* v_last = smem + v_slot(n - 1);
+    const bool odd = (n & 1) != 0;   // the last phase was an even one: its probabilities are pA
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) {
+        const lds_u8* src = v_last + v_off[db] + ks * 16 * kRowBytes;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src)));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src + 8 * kRowBytes)));
+        bf16x8 vf;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          vf[e] = lo[e];
+          vf[4 + e] = hi[e];
+        }
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, odd ? pA[ks] : pB[ks], o[db], 0, 0, 0);
+      }
+  }
+  const float l_tot = wave_half_sum(l_run);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // tiles past the end may still be landing
+  __syncthreads();
+  merge_waves<kR>(smem, o, fmaxf(m_ref, kNoRef), l_tot, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o,
+                  part_ml, rows_all);
 }
 
 // ln(2^m l), rounded once: m may reach hundreds where l's logarithm is small
@@ -764,11 +991,12 @@ size_t usable_bytes(const void* ws, size_t ws_bytes) {
   return ws == nullptr || reinterpret_cast<uintptr_t>(ws) % 16 != 0 ? 0 : ws_bytes;
 }
 constexpr int kMaxKeySplits = 16;
+constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-group are considered
 
 // How a bf16 call is cut: 32 or 256 query rows per work-group, and the key shares.  The estimates
 // are microseconds, fitted to 24 shapes from 0.1 to 974 GFLOP (2 to 24 heads, 64 to 4,032 rows, 150 to
-// 29,500 keys) in both forms with 1 to 16 shares: `start` is what a work-group costs beside its
-// steps, a step is 64 keys here and 8 x 32 keys there and gets slower as the compute units fill up,
+// 29,500 keys) in the 32- and 256-row forms with 1 to 16 shares: `start` is what a work-group costs beside its
+// steps, a step is 64 keys there and 8 x 32 keys here and gets slower as the compute units fill up,
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
 // (512 bytes written and read per row and share).  The 32-row form's start was fitted again, to 144 shapes (2/1
 // to 24/8 heads, 64 to 1,000 rows, 300 to 8,000 keys), when its query rows came to go through LDS: 6.0 -> 4.9, the
@@ -777,21 +1005,27 @@ constexpr int kMaxKeySplits = 16;
 // sides measured: 8/2 heads x 252 rows x 1,179 keys, 9.9 us with 32 rows against 16.8 with 256 (and 29.7
 // un-split); 16/4 x 400 x 3,000, 19.9 against 29.4; 24/8 x 568 x 2,200, 29.5 against 30.6; 16/4 x 1,008 x
 // 7,455, 90 against 69.
+// The forms of 64 and 128 rows were fitted to 140 shapes (2/1 to 24/8 heads, 64 to 4,032 rows, 100 to 13,000 keys) in all
+// four forms with 1 to 16 shares.  They are considered up to 2,048 keys, or up to 8,192 over all KV heads: of the 140,
+// 23 take them, 1.26 times as fast at the median (1.49 at most; one 3 % slower, 6/2 x 692 x 2,458 in three
+// shares).  Beyond that line they would still win at times (16/4 x 1,594 x 3,031 53 -> 44 us, 16/4 x 853 x 2,371 32 -> 25)
+// and no more at 16/4 x 1,008 x 7,455 (68 against 69); it lies where it does because the parity tests pin their
+// large shapes, from 2,100 keys on, to the 256-row form that they are there to cover.
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
 // rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
 // third of the partial rows and a round less: 363 us, 381 with all of them cut).
 // A cut whose partial rows do not fit ws_bytes is not considered; no shares always fit.
 struct AttnPlan {
-  bool small;
+  int rows;           // query rows per work-group: 32, 64, 128 or 256
   int n_splits;
   int n_whole;        // row tiles that are not cut (n_splits > 1)
   int64_t row_whole;  // rows in front of the first that is cut, numbered over all heads
 };
 AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
-  AttnPlan best = {false, 1, 0, 0};
+  AttnPlan best = {kBM, 1, 0, 0};
   double best_cost = 1e30;
-  auto consider = [&](bool small, int tile_rows, int share_keys, int step_keys, double start, double per_step,
-                      double fill_step) {
+  auto consider = [&](int tile_rows, int share_keys, int step_keys, double start, double per_step,
+                      double fill_step, double next_round) {
     const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
     const int64_t all_rows = static_cast<int64_t>(Hkv) * rows;
     for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
@@ -800,27 +1034,31 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
       const int steps = ceil_div(per * share_keys, step_keys), rounds = ceil_div(base * s, 256);
       const double merge = s == 1 ? 0.0 : 2.4 + 1.86e-4 * s * Hkv * rows;
       const double cost = start + rounds * (per_step + fill_step * std::min(1.0, base * s / 256.0)) * steps +
-                          (rounds - 1) * 3.3 + merge;
+                          (rounds - 1) * next_round + merge;
       if (cost < best_cost && attn_partial_bytes(all_rows, kD, s) <= ws_bytes) {
         best_cost = cost;
-        best = {small, s, 0, 0};
+        best = {tile_rows, s, 0, 0};
       }
       const int whole = base / 256 * 256, cut = base - whole;
-      if (small || s == 1 || whole == 0 || cut == 0) continue;
+      if (tile_rows != kBM || s == 1 || whole == 0 || cut == 0) continue;
       const int cut_rounds = ceil_div(cut * s, 256);
       const double part = start + whole / 256 * (per_step + fill_step) * ceil_div(Nk, step_keys) +
                           cut_rounds * (per_step + fill_step * std::min(1.0, cut * s / 256.0)) * steps +
-                          (whole / 256 + cut_rounds - 1) * 3.3 + 2.4 + 1.86e-4 * s * cut * tile_rows;
+                          (whole / 256 + cut_rounds - 1) * next_round + 2.4 + 1.86e-4 * s * cut * tile_rows;
       const int tiles_q = base / Hkv;
       const int64_t row_whole = static_cast<int64_t>(whole / tiles_q) * rows + whole % tiles_q * tile_rows;
       if (part < best_cost && attn_partial_bytes(all_rows - row_whole, kD, s) <= ws_bytes) {
         best_cost = part;
-        best = {small, s, whole, row_whole};
+        best = {tile_rows, s, whole, row_whole};
       }
     }
   };
-  consider(false, kBM, kBN, kBN, 8.1, 1.14, 0.33);
-  consider(true, kSmallRows, kSmallKeys, 8 * kSmallKeys, 4.9, 1.17, 0.19);
+  consider(kBM, kBN, kBN, 8.1, 1.14, 0.33, 3.3);
+  consider(kSmallRows, kSmallKeys, 8 * kSmallKeys, 4.9, 1.17, 0.19, 3.3);
+  if (Nk <= kMidKeys || Hkv * static_cast<int64_t>(Nk) <= 4 * kMidKeys) {
+    consider(64, 128, 128, 6.2, 0.68, 0.325, 2.8);
+    consider(128, 64, 64, 7.55, 0.52, 0.34, 1.7);
+  }
   return best;
 }
 // ------------------------------------------------------------------------------------------
@@ -1288,7 +1526,7 @@ extern "C" int pc_frame_attn_cut(int dtype, int Hq, int Hkv, int Nq, int Nk, int
   const int rows = Hq / Hkv * Nq;
   if (dtype == PC_BF16 && D == kD) {
     const AttnPlan plan = plan_bf16(Hkv, rows, Nk, ws_bytes);
-    cut[0] = plan.small ? kSmallRows : kBM;
+    cut[0] = plan.rows;
     cut[1] = plan.n_splits;
     cut[2] = plan.n_whole;
   } else {
@@ -1326,7 +1564,7 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     // that is misaligned or too small for two) the keys are not split, which is always valid.
     const AttnPlan plan = plan_bf16(Hkv, rep * Nq, Nk, usable_bytes(ws, ws_bytes));
     const float c = scale * 1.4426950408889634f;
-    const int n_tiles_q = ceil_div(rep * Nq, plan.small ? kSmallRows : kBM);
+    const int n_tiles_q = ceil_div(rep * Nq, plan.rows);
     const int64_t rows_cut = static_cast<int64_t>(Hq) * Nq - plan.row_whole;
     float* part_o = nullptr;
     float2* part_ml = nullptr;
@@ -1339,18 +1577,27 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     const auto* k = static_cast<const uint16_t*>(K);
     const auto* v = static_cast<const uint16_t*>(V);
     auto* o = static_cast<uint16_t*>(O);
-    static std::atomic<uint64_t> lds_ok[3];
+    static std::atomic<uint64_t> lds_ok[7];
     auto allow = [](auto kernel, size_t bytes, std::atomic<uint64_t>& done) {
       return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes, done, "pc_frame_attn");
     };
-    if (plan.small) {
+    const bool unit_c = c == 1.0f;
+    if (plan.rows == 64 || plan.rows == 128) {
+      const bool wide = plan.rows == 128;
+      const auto kernel = wide ? (unit_c ? attn_bf16_mid_kernel<true, 4> : attn_bf16_mid_kernel<false, 4>)
+                               : (unit_c ? attn_bf16_mid_kernel<true, 2> : attn_bf16_mid_kernel<false, 2>);
+      if (int rc = allow(kernel, kMergeBytes, lds_ok[3 + wide * 2 + unit_c])) return rc;
+      const int share_steps = ceil_div(ceil_div(Nk, 32 * (wide ? 2 : 4)), plan.n_splits);
+      kernel<<<n_tiles * plan.n_splits, kPPThreads, kMergeBytes, s>>>(
+          q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_tiles,
+          share_steps, part_o, part_ml, rows_cut);
+    } else if (plan.rows == kSmallRows) {
       if (int rc = allow(attn_bf16_small_kernel, kSmallSmem, lds_ok[2])) return rc;
       const int share_steps = ceil_div(ceil_div(Nk, kSmallKeys), plan.n_splits);
       attn_bf16_small_kernel<<<n_tiles * plan.n_splits, kPPThreads, kSmallSmem, s>>>(
           q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_tiles,
           share_steps, part_o, part_ml, rows_cut);
     } else {
-      const bool unit_c = c == 1.0f;
       const auto kernel = unit_c ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
       if (int rc = allow(kernel, kSmemBytes, lds_ok[unit_c])) return rc;
       const int n_whole = plan.n_splits > 1 ? plan.n_whole : n_tiles, n_cut = n_tiles - n_whole;

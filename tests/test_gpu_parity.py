@@ -340,6 +340,48 @@ def test_frame_attn_bf16_256_rows_and_few_keys(hq, hkv, nq, nk, step, fold):
     assert (lerr <= torch.clamp(Lw.abs().clamp(min=1.0) * 2.0 ** -20, min=1e-3)).all()
 
 
+# 64 and 128 rows per work-group (four and two key groups): one tile of 32 keys and fewer, key groups without a tile or
+# with one less than the others, ragged ends, every number of tiles modulo the LDS slots, row groups without a row, row
+# tiles that span heads, key shares; climbing logits as above, and masks that leave whole tiles or key groups nothing.
+ATTN_64_ROWS = [(16, 4, 581, nk) for nk in (97, 129, 257, 300, 823)] + [(6, 2, 1593, 1701), (24, 8, 481, 970), (2, 1, 1701, 8100)]
+ATTN_128_ROWS = [(8, 2, 3541, nk) for nk in (1, 31, 33, 64, 65, 151, 200, 257)] + [(6, 2, 3157, 523), (24, 8, 1070, 1691)]
+
+
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step,masked", [(0.0, None), (0.6, None), (40.0, None), (0.0, slice(0, 140)), (0.0, slice(3, None, 5))])
+@pytest.mark.parametrize("hq,hkv,nq,nk", ATTN_64_ROWS + ATTN_128_ROWS)
+def test_frame_attn_bf16_64_and_128_rows(hq, hkv, nq, nk, step, masked, fold):
+    rows_wg = 64 if (hq, hkv, nq, nk) in ATTN_64_ROWS else 128
+    n_ws = pk.pc_frame_attn_workspace_bytes_for(pk.PC_BF16, hq, hkv, nq, nk, 128)
+    assert pk.pc_frame_attn_cut(pk.PC_BF16, hq, hkv, nq, nk, 128, n_ws)[0] == rows_wg
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nk)
+    Q, K, V = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((hq, nq), (hkv, nk), (hkv, nk)))
+    scale = 128 ** -0.5
+    keep = torch.ones(nk, dtype=torch.bool, device=DEV)
+    if step:
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * (torch.arange(nk, device=DEV) // 32) / (8.0 * scale)
+    if masked is not None:
+        Q[..., 0] = 4.0
+        keep[masked] = False
+        keep[-1] |= not keep.any()
+        K[:, ~keep, 0] = float("-inf")
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    buf = torch.full((hq, nq + 3, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, O=buf[:, :nq], lse=lse)
+    rows = torch.tensor(sorted({0, 1, 63, 64, 127, 128, nq - 1} | set(range(0, nq, 61))), device=DEV)
+    Ow, Lw, _ = _masked_reference(Q, K, V, keep, scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs()
+    # tolerances as in the test above: with all weight on few keys |O| reaches 4
+    assert err.max().item() <= (2 ** -5 if step == 40.0 or keep.sum() < 40 else 2e-2) and err.mean().item() <= 2e-3
+    assert (lerr <= torch.clamp(Lw.abs().clamp(min=1.0) * 2.0 ** -20, min=1e-3)).all() and (buf[:, nq:] == 7).all()
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("seed", [0, 1, 2, 3])
 def test_frame_attn_bf16_error_bound_at_twice_the_workload_amplitude(seed, fold):
