@@ -76,10 +76,6 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x) {  // OR over the wave, 
   const int r = wave_scan(static_cast<int>(x), 0, [](int a, int b) { return a | b; });
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(r, 63));
 }
-__device__ __forceinline__ uint32_t wave_and(uint32_t x) {
-  const int r = wave_scan(static_cast<int>(x), -1, [](int a, int b) { return a & b; });
-  return static_cast<uint32_t>(__builtin_amdgcn_readlane(r, 63));
-}
 
 // One wave selects the top `k` of `len` scores.  Keys are register resident when
 // kItems > 0 (len <= 64 * kItems); kItems == 0 re-reads the scores on every pass.
@@ -163,22 +159,41 @@ __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ sc
   select_wave<kItems>(score + sc_off + start, len, keep, out, start);
 }
 
+// Sum of the first n of kWaves words in LDS, n wave-uniform: a lane takes one each and a scan of the row does the rest
+// (one read after another, up to fifteen of them stood in front of a wave).
+template <int kWaves>
+__device__ __forceinline__ int sum_of_first(const int* words, int n) {
+  static_assert(kWaves == 4 || kWaves == 16, "one row of lanes holds the words");
+  int x = words[threadIdx.x & (kWaves - 1)];
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  if constexpr (kWaves == 16) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  }
+  return n > 0 ? __builtin_amdgcn_readlane(x, n - 1) : 0;
+}
+
 // One work-group of kThr threads per segment; thread t keeps the kItems CONSECUTIVE keys
 // [t kItems, (t+1) kItems) of the segment in registers as order-preserving integers.
-//   * The bits all keys share (sign, most of the exponent) are found with one AND / OR reduction
+//   * The bits all keys share (sign, most of the exponent) are found with one OR reduction
 //     and skipped.
 //   * The k-th largest key is then found eleven bits at a time: keys that still match the prefix
 //     vote into a 2,048-bin LDS histogram; a thread owns 2,048 / kThr neighbouring bins, the threads
 //     take a suffix sum over their totals (wave scan + one exchange) and the thread whose bins
 //     contain the k-th key walks them.  With 4,032 keys over 2,048 bins the chosen bin
 //     nearly always holds a handful of keys: up to 64 are put into LDS and ranked against each
-//     other by every wave (no second pass over the histogram); more than 64 take another pass.
+//     other by all waves together (no second pass over the histogram); more than 64 take another pass.
 //   * Output in ascending index order: with consecutive keys per thread a kept key's position is
 //     (kept keys of lower threads) + (kept keys earlier in this thread), so one more scan over
 //     the threads (keys above the threshold and keys equal to it, packed in one word) places
 //     everything; equal keys are taken lowest index first.
 // The kernel is bound by its instruction count once a stack of layers fills the chip with these
 // work-groups, hence few, wide passes and no per-key cross-lane work.
+// Alone it is a chain of barriers (clock stamps, 196 segments of 4,032 keys: 1.8 us to the scores, then six
+// steps of 0.3 to 0.8 us).  What stood in it one after another is done side by side: sums over the waves in front (up to
+// fifteen LDS reads, twice), the candidates' ranks (every wave went through all of them), AND and OR over
+// sixteen waves.  One layer at frame 48, select and gather: 36.7 -> 34.9 us.
 // Blocks also clear the in-place gather's ticket counters and flags (n_clear words).
 template <int kItems, int kThr>
 __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restrict__ score,
@@ -190,10 +205,11 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
   constexpr int kBits = 11, kBins = 1 << kBits, kOwn = kBins / kThr, kWaves = kThr / 64;  // bins per thread
   static_assert(kOwn == 8 || kOwn == 2, "a thread reads its bins with two 16-byte loads or one of 8 bytes");
   __shared__ __align__(16) int s_hist[kBins];
-  __shared__ int s_wave_sum[kWaves];
+  __shared__ int s_wave_sum[kWaves], s_kept[kWaves];
   __shared__ int s_pick[3];  // chosen digit, keys above it, keys in it
-  __shared__ uint32_t s_and[kWaves], s_or[kWaves];
-  __shared__ uint32_t s_cand[64];  // the keys of the chosen bin when they are few
+  __shared__ int s_differ[kWaves];
+  __shared__ __align__(16) uint32_t s_cand[64];  // the keys of the chosen bin when they are few
+  __shared__ int s_rank[64];                     // of each: how many are above it, and not below it (upper half)
   __shared__ int s_n_cand;
   const int s = blockIdx.x, h = blockIdx.y;
   {
@@ -208,8 +224,9 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
     return;
   }
   const float* sc = score + (h / hsel) * score_stride_l + (h % hsel) * score_stride_h + start;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int e0 = t * kItems;
+  const float first = sc[0];   // the same load in every thread
   uint32_t key[kItems];
   if constexpr (kItems % 4 == 0) {
     const bool aligned = (reinterpret_cast<uintptr_t>(sc) & 15) == 0;  // block-uniform
@@ -233,22 +250,15 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
 #pragma unroll
     for (int i = 0; i < kItems; ++i) key[i] = e0 + i < len ? order_key(sc[e0 + i]) : 0u;
   }
-  // Bits shared by every key of the segment are settled at once: only the bits from the highest
-  // differing one down go through the histogram.
-  uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
+  const uint32_t key0 = __builtin_amdgcn_readfirstlane(order_key(first));
+  // Bits shared by every key of the segment are settled at once (every key against the first one): only the bits
+  // from the highest differing one down go through the histogram.
+  uint32_t mine_differ = 0u;
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    if (e0 + i < len) {
-      k_and &= key[i];
-      k_or |= key[i];
-    }
-  }
-  k_and = wave_and(k_and);
-  k_or = wave_or(k_or);
-  if (lane == 0) {
-    s_and[wave] = k_and;
-    s_or[wave] = k_or;
-  }
+  for (int i = 0; i < kItems; ++i)
+    if (e0 + i < len) mine_differ |= key[i] ^ key0;
+  mine_differ = wave_or(mine_differ);
+  if (lane == 0) s_differ[wave] = static_cast<int>(mine_differ);
   auto clear_bins = [&] {  // this thread's own bins
     if constexpr (kOwn == 8) {
       reinterpret_cast<int4*>(s_hist)[2 * t] = make_int4(0, 0, 0, 0);
@@ -259,17 +269,11 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
   };
   clear_bins();  // for the first pass
   if (t == 0) s_n_cand = 0;
+  if (t < 64) s_rank[t] = 0;
   __syncthreads();
-  k_and = s_and[0];
-  k_or = s_or[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) {
-    k_and &= s_and[w];
-    k_or |= s_or[w];
-  }
-  const uint32_t differ = k_and ^ k_or;
+  const uint32_t differ = wave_or(static_cast<uint32_t>(s_differ[lane & (kWaves - 1)]));
   int hi = differ ? 32 - __clz(differ) : 0;  // number of undecided low bits
-  uint32_t prefix = hi >= 32 ? 0u : (k_or >> hi) << hi;
+  uint32_t prefix = hi >= 32 ? 0u : (key0 >> hi) << hi;
   int remaining = k;
   bool cleared = true;
   while (hi > 0) {
@@ -299,11 +303,10 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
     for (int j = 0; j < kOwn; ++j) mine += c[j];
     // suffix sums over the threads: above = matching keys with a digit beyond this thread's bins
     const int upto = wave_prefix_sum(mine);
-    const int incl = __builtin_amdgcn_readlane(upto, 63) - upto + mine;  // this lane and the lanes above it
-    if (lane == 0) s_wave_sum[wave] = incl;
+    const int of_wave = __builtin_amdgcn_readlane(upto, 63);
+    if (lane == 0) s_wave_sum[kWaves - 1 - wave] = of_wave;   // the last wave first
     __syncthreads();
-    int above = incl - mine;
-    for (int w = wave + 1; w < kWaves; ++w) above += s_wave_sum[w];
+    const int above = of_wave - upto + sum_of_first<kWaves>(s_wave_sum, kWaves - 1 - wave);
     if (above < remaining && remaining <= above + mine) {  // exactly one thread: walk its bins downwards
       int ab = above, digit = 0, cnt = 0;
       bool found = false;
@@ -326,8 +329,8 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
     hi = shift;
     if (hi > 0 && s_pick[2] <= 64) {
       // block-uniform: the chosen bin holds few keys (with 4,032 keys over 2,048 bins nearly always).
-      // They go to LDS, and every wave ranks them for itself: lane j counts the candidates above and
-      // not below its own; the lane whose counts bracket the remaining rank holds the threshold.
+      // They go to LDS; lane i of every wave holds candidate i and counts those above and not below it among
+      // the four that its wave compares with.  The lane whose counts bracket the remaining rank holds the threshold.
       const uint32_t lo_mask = 0xFFFFFFFFu << hi;
 #pragma unroll
       for (int i = 0; i < kItems; ++i)
@@ -339,12 +342,16 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
       const int n_cand = min(s_n_cand, 64);
       const bool has = lane < n_cand;
       const uint32_t my = has ? s_cand[lane] : 0u;
-      int gt = 0, ge = 0;
-      for (int j = 0; j < n_cand; ++j) {
-        const uint32_t x = __builtin_amdgcn_readlane(my, j);
-        gt += x > my ? 1 : 0;
-        ge += x >= my ? 1 : 0;
+      for (int j0 = wave * 4; j0 < n_cand; j0 += kWaves * 4) {
+        const u32x4 other = *reinterpret_cast<const u32x4*>(s_cand + j0);
+        int counts = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          counts += j0 + j < n_cand ? (other[j] > my ? 1 : 0) + (other[j] >= my ? 1 << 16 : 0) : 0;
+        if (has) atomicAdd(&s_rank[lane], counts);
       }
+      __syncthreads();
+      const int gt = s_rank[lane] & 0xFFFF, ge = s_rank[lane] >> 16;
       const uint64_t thr_mask = __ballot(has && gt < remaining && remaining <= ge);
       const int thr_lane = thr_mask ? __builtin_ctzll(thr_mask) : 0;
       prefix = __builtin_amdgcn_readlane(my, thr_lane);
@@ -360,11 +367,9 @@ __global__ __launch_bounds__(kThr) void select_block_kernel(const float* __restr
     mine += (valid && key[i] > prefix ? 1 : 0) + (valid && key[i] == prefix ? 1 << 16 : 0);
   }
   const int incl = wave_prefix_sum(mine);  // this lane and the lanes below it
-  __syncthreads();  // s_wave_sum is free again
-  if (lane == 63) s_wave_sum[wave] = incl;
+  if (lane == 63) s_kept[wave] = incl;
   __syncthreads();
-  int before = incl - mine;
-  for (int w = 0; w < wave; ++w) before += s_wave_sum[w];
+  const int before = incl - mine + sum_of_first<kWaves>(s_kept, wave);
   const int gt_before = before & 0xFFFF;
   int eq_run = before >> 16;                       // threshold keys at lower indices
   int at = gt_before + min(eq_run, remaining);     // kept keys at lower indices
