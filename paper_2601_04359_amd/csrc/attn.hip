@@ -475,8 +475,9 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_kernel(
 // below use every bank; a thread then adds up eight dims of a row, and a row leaves whole.
 constexpr int kWaveOBytes = 32 * kD * 4;
 constexpr size_t kMergeBytes = 8 * kWaveOBytes + 8 * 32 * 8;
-template <int kR>
-__device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], float m, float l, int wave, int lane,
+// kBlocks: blocks of 32 dims that the work-group holds, from dim0 on.
+template <int kR, int kBlocks>
+__device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[kBlocks], int dim0, float m, float l, int wave, int lane,
                                             int tile, int kvh, int split, uint16_t* __restrict__ O,
                                             float* __restrict__ lse, int rep, const Divisor& by_nq, int64_t o_stride_h,
                                             float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t rows_all) {
@@ -485,7 +486,7 @@ __device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], 
   };
   auto* s_ml = reinterpret_cast<__attribute__((address_space(3))) float*>(smem + 8 * kWaveOBytes);
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
     for (int a = 0; a < 4; ++a)
       *piece(wave, db * 4 + a, lane) = f32x4{o[db][a * 4], o[db][a * 4 + 1], o[db][a * 4 + 2], o[db][a * 4 + 3]};
@@ -496,6 +497,7 @@ __device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], 
   __syncthreads();
   const int n_rows = rep * by_nq.d;
   const int row = threadIdx.x >> 4, i = threadIdx.x & 15;
+  if (i >= 4 * kBlocks) return;
 #pragma unroll
   for (int rg = 0; rg < kR; ++rg) {
     const int rho = (tile * kR + rg) * 32 + row;
@@ -522,8 +524,8 @@ __device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], 
     if (part_o != nullptr) {
       const int64_t at_s = split * rows_all + at;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4*>(part_o + at_s * kD + i * 8 + t * 4) = acc[t];
-      if (i == 0) part_ml[at_s] = make_float2(M, lt);
+      for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4*>(part_o + at_s * kD + dim0 + i * 8 + t * 4) = acc[t];
+      if (dim0 + i == 0) part_ml[at_s] = make_float2(M, lt);
       continue;
     }
     const float inv = 1.f / lt;
@@ -534,8 +536,8 @@ __device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], 
       out[t * 2] = pack_bf16x2(acc[t][0] * inv, acc[t][1] * inv);
       out[t * 2 + 1] = pack_bf16x2(acc[t][2] * inv, acc[t][3] * inv);
     }
-    *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + i * 8) = out;
-    if (lse != nullptr && i == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
+    *reinterpret_cast<u32x4*>(O + to.head * o_stride_h + static_cast<int64_t>(to.row) * kD + dim0 + i * 8) = out;
+    if (lse != nullptr && dim0 + i == 0) lse[at] = (M + log2f(lt)) * 0.6931471805599453f;
   }
 }
 
@@ -550,6 +552,11 @@ __device__ __forceinline__ void merge_waves(lds_u8* smem, const f32x16 (&o)[4], 
 // 1,179 keys: 29.7 us in 8 work-groups of 256 rows, 9.9 us un-split in 64 of these (11.3 before the query rows
 // came through LDS; 2/1 x 184 x 900 8.9 -> 7.7).  The loop runs at what a compute unit draws from L2 (128 KB a
 // step in 1.17 us).  K straight into registers (32 rows x 32 bytes per load) took 2.2 us a step.
+// So where half of the compute units would idle, two or four work-groups take the same rows and keys and divide the
+// output's dims (kBlocks of 32 each): each forms all scores, but fetches and adds up only its part of V (96 or
+// 80 KB a step, not 128) and merges only its part of O; there is nothing to put together behind them and the
+// bits are the same.  8/2 x 252 x 1,179 (64 work-groups of 32 rows) 10.2 us undivided, 8.8 in two, 8.7 in four; 2/1
+// x 1,718 x 1,000 (108) 9.4 and 8.2 in two.
 // ------------------------------------------------------------------------------------------
 constexpr int kSmallRows = 32;
 constexpr int kSmallKeys = 32;                                  // keys per wave and step
@@ -557,6 +564,7 @@ constexpr int kSmallTileBytes = kSmallKeys * kRowBytes;
 constexpr size_t kSmallSmem = kMergeBytes + kSmallRows * kRowBytes;
 static_assert(2 * kSmallTileBytes <= kWaveOBytes, "a wave stages K and V in the LDS of its merge piece");
 
+template <int kBlocks>
 __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ lse, int rep, Divisor by_nq, int Nk, int64_t q_stride_h,
@@ -568,7 +576,15 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
   const int l32 = lane & 31, g = lane >> 5;
   const lds_u8* lds = (lds_u8*)smem_raw + wave * kWaveOBytes;
   const uint32_t lds_w = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  constexpr int kParts = 4 / kBlocks;           // work-groups that share rows and keys
+  constexpr int kVRow = kBlocks * 64, kVChunks = kVRow / 16, kVLoads = 2 * kBlocks;   // a V row in LDS, loads of a step's
+  // chunk c of V row r lies where the four rows of a quarter wave's read use different banks
+  auto v_pos = [](int row, int chunk) {
+    return kBlocks == 4 ? v_chunk_pos(row, chunk) : kBlocks == 2 ? chunk ^ ((row & 2) << 1) : chunk;
+  };
   int unit = xcd_contiguous_index(blockIdx.x, gridDim.x);   // n_tiles row tiles per share
+  const int dim0 = unit % kParts * kBlocks * 32;
+  unit /= kParts;
   const int split = take_share(unit, n_tiles);
   const int kvh = by_tiles_q.of(unit), tile = unit - kvh * by_tiles_q.d;
   const int n_rows = rep * by_nq.d;
@@ -585,7 +601,10 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     for (int i = 0; i < 8; ++i) {
       const int row = i * 4 + (lane >> 4);
       dma_16B_at(wk.base, row_offset(wk, row, k_chunk_pos(row, lane & 15)), lds_w + i * 1024);
-      dma_16B_at(wv.base, row_offset(wv, row, v_chunk_pos(row, lane & 15)), lds_w + kSmallTileBytes + i * 1024);
+      if (i < kVLoads) {
+        const int v_row = i * (1024 / kVRow) + lane / kVChunks;
+        dma_16B_at(wv.base, row_offset(wv, v_row, dim0 / 8 + v_pos(v_row, lane % kVChunks)), lds_w + kSmallTileBytes + i * 1024);
+      }
     }
   };
   const int k_first = k_begin + wave * kSmallKeys;
@@ -599,10 +618,13 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
             static_cast<uint32_t>(reinterpret_cast<uintptr_t>(q_tile)) + wave * 1024);
   }
   stage(k_first);
-  int k_off[8], v_off[4];  // as in attn_bf16_kernel
+  int k_off[8], v_off[kBlocks];  // as in attn_bf16_kernel
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_off[s] = l32 * kRowBytes + k_chunk_pos(l32, 2 * s + g) * 16;
-  asm volatile("s_waitcnt vmcnt(16)" ::: "memory");   // this wave's queries: the 16 loads behind them are its first keys
+  // this wave's queries: the loads behind them are its first keys
+  if constexpr (kBlocks == 4) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  else if constexpr (kBlocks == 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
   __syncthreads();
   bf16x8 qf[8];
 #pragma unroll
@@ -611,14 +633,14 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     const int r = lane & 15, G = (lane >> 4) & 1;
     const int row = g * 4 + (r >> 2);
 #pragma unroll
-    for (int db = 0; db < 4; ++db) {
+    for (int db = 0; db < kBlocks; ++db) {
       const int dim = db * 32 + G * 16 + 4 * (r & 3);
-      v_off[db] = kSmallTileBytes + row * kRowBytes + v_chunk_pos(row, dim >> 3) * 16 + (dim & 7) * 2;
+      v_off[db] = kSmallTileBytes + row * kVRow + v_pos(row, dim >> 3) * 16 + (dim & 7) * 2;
     }
   }
-  f32x16 o[4];
+  f32x16 o[kBlocks];
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
   float m = kNoRef, l = 0.f;
@@ -627,18 +649,18 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
     // This step's rows have landed (they are all that is in flight): take every fragment into
     // registers, so that the next step's rows can be fetched into the same LDS at once.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    bf16x8 kf[8], vf[2][4];
+    bf16x8 kf[8], vf[2][kBlocks];
 #pragma unroll
     for (int s = 0; s < 8; ++s) kf[s] = lds_frag(lds + k_off[s]);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int db = 0; db < 4; ++db) {
-        const lds_u8* src = lds + v_off[db] + ks * 16 * kRowBytes;
+      for (int db = 0; db < kBlocks; ++db) {
+        const lds_u8* src = lds + v_off[db] + ks * 16 * kVRow;
         const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
             reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src)));
         const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src + 8 * kRowBytes)));
+            reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(const_cast<lds_u8*>(src + 8 * kVRow)));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           vf[ks][db][e] = lo[e];
@@ -650,7 +672,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(vf[ks][db]));
+      for (int db = 0; db < kBlocks; ++db) asm volatile("" : "+v"(vf[ks][db]));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (k0 + 8 * kSmallKeys < k_end) stage(k0 + 8 * kSmallKeys);  // wave-uniform
     f32x16 sc;
@@ -671,7 +693,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
       const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
       m = m_new;
@@ -688,13 +710,13 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_small_kernel(
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int db = 0; db < 4; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], p[ks], o[db], 0, 0, 0);
+      for (int db = 0; db < kBlocks; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], p[ks], o[db], 0, 0, 0);
   }
   // a wave without keys still has its first fetch in flight
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   l = wave_half_sum(l);
 
-  merge_waves<1>((lds_u8*)smem_raw, o, m, l, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o, part_ml,
+  merge_waves<1, kBlocks>((lds_u8*)smem_raw, o, dim0, m, l, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o, part_ml,
                  rows_all);
 }
 
@@ -907,7 +929,7 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_bf16_mid_kernel(
   const float l_tot = wave_half_sum(l_run);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // tiles past the end may still be landing
   __syncthreads();
-  merge_waves<kR>(smem, o, fmaxf(m_ref, kNoRef), l_tot, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o,
+  merge_waves<kR, 4>(smem, o, 0, fmaxf(m_ref, kNoRef), l_tot, wave, lane, tile, kvh, split, O, lse, rep, by_nq, o_stride_h, part_o,
                   part_ml, rows_all);
 }
 
@@ -1011,6 +1033,10 @@ constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-gr
 // shares).  Beyond that line they would still win at times (16/4 x 1,594 x 3,031 53 -> 44 us, 16/4 x 853 x 2,371 32 -> 25)
 // and no more at 16/4 x 1,008 x 7,455 (68 against 69); it lies where it does because the parity tests pin their
 // large shapes, from 2,100 keys on, to the 256-row form that they are there to cover.
+// The small form's work-groups divide the output's dims while all of them still have a compute unit (small_blocks): of
+// 27 shapes with 4 to 252 work-groups, the division that fits was the fastest on 26 (by 8 to 21 %; 1 % off on the
+// last), one that does not fit took 1.1 to 2.2 times as long (16/4 x 141 x 474, 72 of them: 6.7 us whole, 5.9 in
+// two, 9.2 in four; 2/1 x 690 x 868, 176: 9.0 and 11.3).
 // Where there are more row tiles than compute units, the whole rounds of them walk all keys and only the
 // rest is cut (24/8 heads x 4,032 x 8,320: 128 of 384 tiles in two shares instead of all of them, a
 // third of the partial rows and a round less: 363 us, 381 with all of them cut).
@@ -1021,6 +1047,8 @@ struct AttnPlan {
   int n_whole;        // row tiles that are not cut (n_splits > 1)
   int64_t row_whole;  // rows in front of the first that is cut, numbered over all heads
 };
+// Blocks of 32 dims of a work-group of the small form.
+int small_blocks(int work_groups) { return work_groups <= 64 ? 1 : work_groups <= 128 ? 2 : 4; }
 AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
   AttnPlan best = {kBM, 1, 0, 0};
   double best_cost = 1e30;
@@ -1577,7 +1605,7 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
     const auto* k = static_cast<const uint16_t*>(K);
     const auto* v = static_cast<const uint16_t*>(V);
     auto* o = static_cast<uint16_t*>(O);
-    static std::atomic<uint64_t> lds_ok[7];
+    static std::atomic<uint64_t> lds_ok[9];
     auto allow = [](auto kernel, size_t bytes, std::atomic<uint64_t>& done) {
       return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes, done, "pc_frame_attn");
     };
@@ -1592,9 +1620,11 @@ extern "C" int pc_frame_attn(const void* Q, const void* K, const void* V, int dt
           q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_tiles,
           share_steps, part_o, part_ml, rows_cut);
     } else if (plan.rows == kSmallRows) {
-      if (int rc = allow(attn_bf16_small_kernel, kSmallSmem, lds_ok[2])) return rc;
+      const int blocks = small_blocks(n_tiles * plan.n_splits);
+      const auto kernel = blocks == 1 ? attn_bf16_small_kernel<1> : blocks == 2 ? attn_bf16_small_kernel<2> : attn_bf16_small_kernel<4>;
+      if (int rc = allow(kernel, kSmallSmem, lds_ok[blocks == 4 ? 2 : 6 + blocks])) return rc;
       const int share_steps = ceil_div(ceil_div(Nk, kSmallKeys), plan.n_splits);
-      attn_bf16_small_kernel<<<n_tiles * plan.n_splits, kPPThreads, kSmallSmem, s>>>(
+      kernel<<<n_tiles * plan.n_splits * (4 / blocks), kPPThreads, kSmallSmem, s>>>(
           q, k, v, o, lse, rep, Divisor(Nq), Nk, q_stride_h, kv_stride_h, o_stride_h, c, Divisor(n_tiles_q), n_tiles,
           share_steps, part_o, part_ml, rows_cut);
     } else {

@@ -382,6 +382,33 @@ def test_frame_attn_bf16_64_and_128_rows(hq, hkv, nq, nk, step, masked, fold):
     assert (lerr <= torch.clamp(Lw.abs().clamp(min=1.0) * 2.0 ** -20, min=1e-3)).all() and (buf[:, nq:] == 7).all()
 
 
+# 32 rows per work-group whose output's dims are divided by four, by two and not at all: the last row tile before and
+# the first behind each line, key shares of both, waves without a key, ragged ends; NaN behind the last V row.
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("nq,nk,work_groups", [(1024, 1, 64), (1025, 33, 65), (2048, 257, 128), (2049, 300, 129),
+                                               (1000, 255, 63), (93, 2000, 48), (184, 5000, 120)])
+def test_frame_attn_bf16_output_dims_divided(nq, nk, work_groups, fold):
+    cut = pk.pc_frame_attn_cut(pk.PC_BF16, 2, 1, nq, nk, 128, 1 << 40)
+    assert cut[0] == 32 and -(-2 * nq // 32) * cut[1] == work_groups
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nq)
+    Q, K, V = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((2, nq), (1, nk + 40), (1, nk + 40)))
+    scale = 128 ** -0.5
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    V[:, nk:] = float("nan")
+    lse = torch.empty((2, nq), dtype=torch.float32, device=DEV)
+    buf = torch.full((2, nq + 3, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, O=buf[:, :nq], lse=lse)
+    rows = torch.tensor(sorted({0, 1, 31, 32, nq - 1} | set(range(0, nq, 61))), device=DEV)
+    Ow, Lw, _ = _masked_reference(Q, K[:, :nk], V[:, :nk], torch.ones(nk, dtype=torch.bool, device=DEV), scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs()
+    # outputs and probabilities rounded once each; with few keys |O| reaches 4, where bf16 values lie 2^-6 apart
+    assert err.max().item() <= (2 ** -5 if nk < 40 else 2e-2) and err.mean().item() <= 2e-3
+    assert lerr.max().item() <= 1e-3 and (buf[:, nq:] == 7).all()
+
+
 @pytest.mark.parametrize("fold", [False, True])
 @pytest.mark.parametrize("seed", [0, 1, 2, 3])
 def test_frame_attn_bf16_error_bound_at_twice_the_workload_amplitude(seed, fold):
