@@ -1020,13 +1020,13 @@ constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-gr
 // 29,500 keys) in the 32- and 256-row forms with 1 to 16 shares: `start` is what a work-group costs beside its
 // steps, a step is 64 keys there and 8 x 32 keys here and gets slower as the compute units fill up,
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
-// (512 bytes written and read per row and share).  The 32-row form's start was fitted again, to 144 shapes (2/1
-// to 24/8 heads, 64 to 1,000 rows, 300 to 8,000 keys), when its query rows came to go through LDS: 6.0 -> 4.9, the
-// cut 0.75 % off the best on average (1.7 before).  On 160 further shapes (up to 1,500 rows and 12,000 keys) the
-// form it picks is 0.5 % off the other one, at most 13 % (24/8 heads x 883 x 1,379).  Where the line lies, both
-// sides measured: 8/2 heads x 252 rows x 1,179 keys, 9.9 us with 32 rows against 16.8 with 256 (and 29.7
-// un-split); 16/4 x 400 x 3,000, 19.9 against 29.4; 24/8 x 568 x 2,200, 29.5 against 30.6; 16/4 x 1,008 x
-// 7,455, 90 against 69.
+// (512 bytes written and read per row and share).  The 32-row form was fitted again, to
+// 210 shapes (2/1 to 24/8 heads, 33 to 4,032 rows, 64 to 13,000 keys), for each division of its output's dims: a
+// work-group with a quarter or half of them costs less, so fewer calls are worth a merge launch (2/1 heads x 690
+// rows x 868 keys: four shares 9.0 us, none 6.1; 16/4 x 115 x 1,234 three 10.4, none 8.5).  The cut is 0.5 % off
+// the best of all forms on average.  Where the line to 256 rows lies, both sides measured: 8/2 x 252 x 1,179, 8.7
+// us with 32 rows against 15.8 with 256 (and 29.7 un-split); 16/4 x 400 x 3,000, 19.9 against 29.4; 24/8 x 568 x
+// 2,200, 29.5 against 30.6; 16/4 x 1,008 x 7,455, 85 against 68.
 // The forms of 64 and 128 rows were fitted to 140 shapes (2/1 to 24/8 heads, 64 to 4,032 rows, 100 to 13,000 keys) in all
 // four forms with 1 to 16 shares.  They are considered up to 2,048 keys, or up to 8,192 over all KV heads: of the 140,
 // 23 take them, 1.26 times as fast at the median (1.49 at most; one 3 % slower, 6/2 x 692 x 2,458 in three
@@ -1052,13 +1052,16 @@ int small_blocks(int work_groups) { return work_groups <= 64 ? 1 : work_groups <
 AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
   AttnPlan best = {kBM, 1, 0, 0};
   double best_cost = 1e30;
-  auto consider = [&](int tile_rows, int share_keys, int step_keys, double start, double per_step,
-                      double fill_step, double next_round) {
+  struct Cost {
+    double start, per_step, fill_step, next_round;
+  };
+  auto consider = [&](int tile_rows, int share_keys, int step_keys, auto&& cost_of /* that many work-groups */) {
     const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
     const int64_t all_rows = static_cast<int64_t>(Hkv) * rows;
     for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      const auto [start, per_step, fill_step, next_round] = cost_of(base * s);
       const int steps = ceil_div(per * share_keys, step_keys), rounds = ceil_div(base * s, 256);
       const double merge = s == 1 ? 0.0 : 2.4 + 1.86e-4 * s * Hkv * rows;
       const double cost = start + rounds * (per_step + fill_step * std::min(1.0, base * s / 256.0)) * steps +
@@ -1081,11 +1084,14 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
       }
     }
   };
-  consider(kBM, kBN, kBN, 8.1, 1.14, 0.33, 3.3);
-  consider(kSmallRows, kSmallKeys, 8 * kSmallKeys, 4.9, 1.17, 0.19, 3.3);
+  consider(kBM, kBN, kBN, [](int) { return Cost{8.1, 1.14, 0.33, 3.3}; });
+  consider(kSmallRows, kSmallKeys, 8 * kSmallKeys, [](int work_groups) {
+    const int blocks = small_blocks(work_groups);
+    return blocks == 1 ? Cost{3.4, 0.62, 1.5, 3.3} : blocks == 2 ? Cost{3.9, 0.8, 0.5, 3.3} : Cost{4.9, 1.03, 0.32, 3.3};
+  });
   if (Nk <= kMidKeys || Hkv * static_cast<int64_t>(Nk) <= 4 * kMidKeys) {
-    consider(64, 128, 128, 6.2, 0.68, 0.325, 2.8);
-    consider(128, 64, 64, 7.55, 0.52, 0.34, 1.7);
+    consider(64, 128, 128, [](int) { return Cost{6.2, 0.68, 0.325, 2.8}; });
+    consider(128, 64, 64, [](int) { return Cost{7.55, 0.52, 0.34, 1.7}; });
   }
   return best;
 }
