@@ -983,6 +983,27 @@ def small_table(lens):
     return segs, at, [n if i == 0 else (0, n, n // 3, max(1, n - 1), 1)[(i + 2) % 5] for i, n in enumerate(lens)]
 
 
+# In place, frames that are dropped whole are not what a one-launch compaction is bounded by: most of 42 segments and
+# all but the newest of 60 keep nothing; with two dropped of 42 the call takes two launches.
+@pytest.mark.parametrize("n_seg,dropped,launches", [(42, 32, 1), (60, 58, 1), (42, 2, 2)])
+def test_compact_in_place_with_frames_dropped_whole(n_seg, dropped, launches):
+    lens = [9] + [120] * (n_seg - 1)
+    segs = [(sum(lens[:i]), n, pk.PC_SEG_TEXT if i == 0 else pk.PC_SEG_FRAME, i) for i, n in enumerate(lens)]
+    budgets = [9] + [0] * dropped + [17 + i % 3 for i in range(n_seg - 1 - dropped)]
+    assert pk.pc_compact_cut(1, 2, pk.PC_BF16, 128, segs, budgets, False, True)[0] == launches
+    rng = np.random.default_rng(n_seg)
+    at = sum(lens)
+    sc = np.round(np.exp(rng.standard_normal((2, at))) * 64).astype(np.float32) / 64     # with ties
+    K, V = (orc.round_to_bf16(rng.standard_normal((2, at, 128))).astype(np.float32) for _ in range(2))
+    pos = rng.integers(0, 10000, (2, at, 3)).astype(np.int32)
+    Kw, Vw, pw, _, sw = orc.compact(K, V, pos, sc, segs, budgets)
+    Kd, Vd, pd = dev(K, "bf16"), dev(V, "bf16"), dev(pos, None)
+    table, nk = pk.pc_compact(Kd, Vd, pd, dev(sc, None), segs, budgets)
+    assert table == sw and nk == sw[-1][0] + sw[-1][1]
+    for got, want in ((Kd, Kw), (Vd, Vw), (pd, pw)):
+        assert np.array_equal(host(got)[:, :nk], want)
+
+
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("lens,D,dtype,Hkv,share,launches", COMPACT_SMALL)
 def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv, share, launches, in_place):
