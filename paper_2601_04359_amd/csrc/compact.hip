@@ -806,8 +806,9 @@ struct CompactCut {
 // Measured: 3,400 calls in both forms (1 to 60 segments of 16 to 1,024 rows, 1 to 224 heads, both row widths),
 // medians of graph replays.  The range bounds a work-group's serial part, rounds of sixteen segments (a chain
 // of a load and a histogram's steps each) and the rows it moves.  In place a segment that keeps nothing or lies in
-// front of all that moves costs nothing and is not counted (8 heads, 43 segments, 3 of which keep rows, 8.0 us in two
-// launches, 4.0 in one; 72 heads, 46 and 10, 15.1 and 9.1).  Beyond the range, and out of place from 113 heads on,
+// front of all that moves costs nothing, and a table with up to sixteen others is one round (8 heads, 43 segments, 3 of
+// which keep rows, 8.0 us in two launches, 4.0 in one; 72 heads, 46 and 10, 15.1 and 9.1; with more of them either
+// form may win: 2 heads, 42 and 31, 10.0 and 10.8, 24 heads, 34 and 34, 11.0 and 9.4).  Beyond the range, and out of place from 113 heads on,
 // either form may be the faster one (28 x 8 heads, three frames of 600, out of place: 83 us against 101 in one
 // launch), and the two launches stay.
 // In place the two launches take 9 us and more and lose inside the range (6 segments, 4 heads, 252 rows each:
@@ -821,22 +822,24 @@ CompactCut plan_compact(int layers, int Hkv, int row_bytes, const pc_segment* se
                         bool share_heads, bool in_place) {
   const CompactCut two_launches = {false, 0};
   int nk_in = 0, nk_out = 0, n_pruned = 0, max_len = 0, row0 = -1;
-  int rounds = 0, of_wave[kFusedWaves] = {};   // of segments; in place those kept in front of all that moves, or dropped, do not count
+  int n_active = 0;   // segments that keep rows, from the first on that loses any
   for (int s = 0; s < n_seg; ++s) {
     if (plan[s].len < seg_in[s].len) {
       ++n_pruned;
       max_len = std::max(max_len, seg_in[s].len);
       if (row0 < 0) row0 = plan[s].start;   // in place, packed rows below it stay where they are
     }
-    if (!in_place || (plan[s].len > 0 && row0 >= 0)) rounds = std::max(rounds, ++of_wave[s % kFusedWaves]);
+    if (plan[s].len > 0 && row0 >= 0) ++n_active;
     nk_in = seg_in[s].start + seg_in[s].len;
     nk_out = plan[s].start + plan[s].len;
   }
   if (max_len > kFusedMaxLen || nk_in > 0xFFFF || nk_out > kFusedMaxRows) return two_launches;
   if (static_cast<int64_t>(layers) * Hkv > (in_place ? kMaxTicketHeads : 112)) return two_launches;
   const int heads = layers * Hkv, pos_groups = share_heads ? layers : heads, row_chunks = row_bytes / 16;
-  const int moved = !in_place ? nk_out : row0 < 0 ? 0 : nk_out - row0;
-  if (2.4 * rounds + 1.5 / 1024 * max_len + 2.4 / 1024 * moved > (in_place ? 7.8 : 6.8)) return two_launches;
+  const int moved = !in_place ? nk_out : row0 < 0 ? 0 : nk_out - row0, rounds = ceil_div(n_seg, kFusedWaves);
+  const double moving = 2.4 / 1024 * moved, select = 1.5 / 1024 * max_len;
+  const bool one_round = in_place && n_active <= kFusedWaves && 2.4 + select + moving <= 7.8;
+  if (!one_round && 2.4 * rounds + select + moving > (in_place ? 7.8 : 6.8)) return two_launches;
   int log_slices = 0;
   while (slices_pay(row_chunks >> (log_slices + 1), (heads * 2) << (log_slices + 1), pos_groups, in_place)) ++log_slices;
   const CompactCut one_launch = {true, log_slices};
