@@ -1132,8 +1132,9 @@ constexpr size_t f32_smem_bytes() {   // a step's K and V rows of every wave, th
   return sizeof(float) * (kWaves * (kWaves <= 2 ? 1 : 2) * kF32Keys * D + 16 * kR * D + kWaves * 16 * kR * 2);
 }
 
-// Sixteen rows as D / 16 pieces of 1 KB, 16 bytes per lane, through a buffer descriptor: rows past the end are zeros,
-// and a piece costs no address arithmetic.
+// Sixteen rows as D / 16 pieces of 1 KB, 16 bytes per lane, through a buffer descriptor: rows past the end are zeros.
+// What a piece adds stands in the lane's offset, where the range check is defined to see it (of the scalar offset
+// it is not); pieces below 4 KB are immediates of their loads, those above them cost one more register.
 template <int D>
 struct F32Rows {
   __amdgpu_buffer_rsrc_t rows;
@@ -1143,7 +1144,7 @@ struct F32Rows {
                                              min(n_rows - first, kF32Keys) * D * 4, 0x00020000);
   }
   __device__ __forceinline__ f32x4 piece(int j, int lane_bytes) const {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, lane_bytes, j * 1024, 0));
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, lane_bytes + j * 1024, 0, 0));
   }
 };
 // Rows in LDS: 16-byte chunk c of row i lies at place c ^ (i % 16), so that writing whole rows and reading either
@@ -1193,7 +1194,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     const RowAt at = row_at(min(row0 + e / (D / 4), n_rows - 1), kvh, rep, by_nq);
     raw_q[i] = load_f32x4(Q + at.head * q_stride_h + static_cast<int64_t>(at.row) * D + e % (D / 4) * 4);
   }
-  const int lane_bytes = lane * 16;
+  int lane_bytes = lane * 16;
   {
     const Rows k(Kh, k_first, Nk);
 #pragma unroll
@@ -1314,7 +1315,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     const int k0 = k_first + i * kStride;
     const Rows k_next(Kh, k0 + 2 * kStride, Nk), v_next(Vh, k0 + kStride, Nk);   // past the end: never used
     // (opaque: else every offset formed from them becomes a register that is kept across the loop)
-    asm volatile("" : "+v"(put_at), "+v"(key_at), "+v"(q_at), "+v"(val_at));
+    asm volatile("" : "+v"(put_at), "+v"(key_at), "+v"(q_at), "+v"(val_at), "+v"(lane_bytes));
     wave_lds_sync();
     float sum[kR];
 #pragma unroll

@@ -603,6 +603,21 @@ def test_frame_attn_capacity_larger_than_rows():
     assert err.max() <= 2e-2 and err.mean() <= 2e-3
 
 
+# fp32: whatever lies in the spare rows behind the last key stays out of it, in a step's rows and in steps wholly
+# behind the end: one and two waves' keys, rests of a step of every kind, waves that run out before the others (16
+# and 32 rows per work-group), key shares
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,hkv,nq,nk", [(4, 2, 37, n) for n in (1, 3, 15, 17, 31, 33, 129, 255)] + [(2, 1, 64, 336), (8, 2, 252, 1804), (3, 1, 301, 2501)])
+def test_frame_attn_f32_capacity_larger_than_rows(d, hq, hkv, nq, nk):
+    Q, K, V = _attn_case("f32", hq, hkv, nq, nk, d, nk)
+    buf = torch.full((2, hkv, nk + 300, d), float("nan"), dtype=torch.float32, device=DEV)
+    buf[0, :, :nk], buf[1, :, :nk] = dev(K, None), dev(V, None)
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(dev(Q, None), buf[0], buf[1], nk, d ** -0.5, lse=lse)
+    Ow, Lw = orc.frame_attn(Q, K, V, d ** -0.5)
+    assert np.abs(host(O) - Ow).max() <= 1e-5 and np.abs(host(lse) - Lw).max() <= 1e-5
+
+
 # ------------------------------------------------------------------------------- score
 def _score_check(w, Qs, K, share=False, lse=None, fold=False):
     dt = w.dtype
