@@ -784,7 +784,7 @@ struct FusedArgs {
   int64_t in_stride_c, out_stride_c, in_stride_lc, out_stride_lc;       // 16-byte chunks
   int64_t pos_stride_h, pos_out_stride_h, pos_stride_l, pos_out_stride_l;
   int64_t score_stride_h, score_stride_l, idx_stride_h, idx_stride_l;
-  int n_seg, n_out, row0;  // packed rows below row0 stay where they are (0 out of place)
+  int n_seg, n_out, row0;  // segments that keep rows; packed rows below row0 stay where they are (0 out of place)
   int Hkv, hsel, log_chunks, log_slices;  // a slice is 2^log_chunks chunks, a row 2^log_slices slices
 };
 
@@ -806,11 +806,12 @@ struct CompactCut {
 // Measured: 3,400 calls in both forms (1 to 60 segments of 16 to 1,024 rows, 1 to 224 heads, both row widths),
 // medians of graph replays.  The range bounds a work-group's serial part, rounds of sixteen segments (a chain
 // of a load and a histogram's steps each) and the rows it moves.  In place a segment that keeps nothing or lies in
-// front of all that moves costs nothing, and a table with up to sixteen others is one round (8 heads, 43 segments, 3 of
+// front of all that moves costs nothing, and a table with up to sixteen others is one round wherever they stand: the
+// launch is handed the segments that keep rows, and its waves take those by turns (8 heads, 43 segments, 3 of
 // which keep rows, 8.0 us in two launches, 4.0 in one; 72 heads, 46 and 10, 15.1 and 9.1; with more of them either
-// form may win: 2 heads, 42 and 31, 10.0 and 10.8, 24 heads, 34 and 34, 11.0 and 9.4).  Beyond the range, and out of place from 113 heads on,
-// either form may be the faster one (28 x 8 heads, three frames of 600, out of place: 83 us against 101 in one
-// launch), and the two launches stay.
+// form may win: 2 heads, 42 and 31, 10.0 and 10.8, 24 heads, 34 and 34, 11.0 and 9.4).  Beyond the range, and out of place
+// from 113 heads on, either form may be the faster one (28 x 8 heads, three frames of 600, out of place: 83 us against
+// 101 in one launch), and the two launches stay.
 // In place the two launches take 9 us and more and lose inside the range (6 segments, 4 heads, 252 rows each:
 // 10.3 against 7.0; 28 layers of it 31 against 22.6; 16 x 8 heads, 15 segments, 755 rows kept 24.8 against
 // 19.9), but for hundreds of heads that keep one chunk of the gather each (28 x 8 heads, 91 rows kept: 9.0
@@ -869,7 +870,7 @@ __global__ __launch_bounds__(kFusedThreads) void compact_fused_kernel(FusedArgs 
   for (int s = wave; s < a.n_seg; s += kFusedWaves) {
     const uint2 g = tab.seg[s];
     const int start = g.x & 0xFFFF, len = g.x >> 16, keep = g.y & 0xFFFF, dst = g.y >> 16;
-    if (keep == 0 || dst + keep <= row0) continue;  // wave-uniform
+    if (dst + keep <= row0) continue;  // wave-uniform
     if (keep == len)
       for (int e = lane; e < len; e += 64) s_idx[dst + e] = start + e;
     else
@@ -1167,17 +1168,22 @@ extern "C" int pc_compact_batch_phase(int phases, int n_layers, void* K, void* V
     a.pos_stride_l = pos_stride_l, a.pos_out_stride_l = pos_out_stride_l;
     a.score_stride_h = score_stride_h, a.score_stride_l = score_stride_l;
     a.idx_stride_h = idx_stride_h, a.idx_stride_l = idx_stride_l;
-    a.n_seg = n_seg, a.n_out = nk_out, a.Hkv = Hkv, a.hsel = hsel;
+    a.n_seg = 0, a.n_out = nk_out, a.Hkv = Hkv, a.hsel = hsel;
+    for (int s = 0; s < n_seg; ++s) a.n_seg += plan[s].len > 0 ? 1 : 0;
     a.row0 = row0;
     a.log_slices = cut.log_slices;
     a.log_chunks = (row_bytes == 256 ? 4 : 5) - cut.log_slices;
     const dim3 grid(((Hkv * 2) << a.log_slices) + hsel, n_layers);
+    // Segments that keep nothing are left out: the waves take the segments by turns, and kept frames sixteen apart in
+    // the table would all be one wave's (113 segments of 64 rows, 2 heads, seven of them kept: 17.2 us, 5.1 with the
+    // others left out, 9.2 in two launches).
     auto fill = [&](auto& ft) {
-      for (int s = 0; s < n_seg; ++s)
-        ft.seg[s] = make_uint2(static_cast<uint32_t>(seg_in[s].start) | static_cast<uint32_t>(seg_in[s].len) << 16,
-                               static_cast<uint32_t>(plan[s].len) | static_cast<uint32_t>(plan[s].start) << 16);
+      for (int s = 0, at = 0; s < n_seg; ++s)
+        if (plan[s].len > 0)
+          ft.seg[at++] = make_uint2(static_cast<uint32_t>(seg_in[s].start) | static_cast<uint32_t>(seg_in[s].len) << 16,
+                                    static_cast<uint32_t>(plan[s].len) | static_cast<uint32_t>(plan[s].start) << 16);
     };
-    if (n_seg <= 24) {
+    if (a.n_seg <= 24) {
       FusedTable<24> ft;
       fill(ft);
       if (row_bytes == 256) compact_fused_kernel<16, 24><<<grid, kFusedThreads, 0, st>>>(a, ft);

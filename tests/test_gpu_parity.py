@@ -1019,6 +1019,50 @@ def test_compact_in_place_with_frames_dropped_whole(n_seg, dropped, launches):
         assert np.array_equal(host(got)[:, :nk], want)
 
 
+# Up to sixteen kept frames are one round of the one launch's waves wherever they stand among dropped ones: sixteen
+# apart they take as long as side by side (in one wave's turn they took three times as long).
+@pytest.mark.parametrize("front", [1, 40])
+def test_compact_in_place_with_kept_frames_far_apart(front):
+    n_seg, Hkv = 113, 2
+    lens = [9] + [64] * (n_seg - 1)
+    segs = [(sum(lens[:i]), n, pk.PC_SEG_TEXT if i == 0 else pk.PC_SEG_FRAME, i) for i, n in enumerate(lens)]
+    at = sum(lens)
+    rng = np.random.default_rng(front)
+    sc = np.round(np.exp(rng.standard_normal((Hkv, at))) * 64).astype(np.float32) / 64     # with ties
+    K, V = (orc.round_to_bf16(rng.standard_normal((Hkv, at, 128))).astype(np.float32) for _ in range(2))
+    pos = rng.integers(0, 10000, (Hkv, at, 3)).astype(np.int32)
+
+    def budgets(kept):   # `front` segments are kept whole, then those of `kept`
+        return [n if i < front else 20 if i in kept else 0 for i, n in enumerate(lens)]
+    apart, together = budgets(range(front, n_seg, 16)), budgets(range(front, front + len(range(front, n_seg, 16))))
+    micros = []
+    for b in (apart, together):
+        assert pk.pc_compact_cut(1, Hkv, pk.PC_BF16, 128, segs, b, False, True)[0] == 1
+        Kw, Vw, pw, iw, sw = orc.compact(K, V, pos, sc, segs, b)
+        nk = sw[-1][0] + sw[-1][1]
+        for idx in (None, torch.full((Hkv, nk), -1, dtype=torch.int32, device=DEV)):
+            Kd, Vd, pd, sd = dev(K, "bf16"), dev(V, "bf16"), dev(pos, None), dev(sc, None)
+            assert pk.pc_compact(Kd, Vd, pd, sd, segs, b, idx=idx) == (sw, nk)
+            for got, want in ((Kd, Kw), (Vd, Vw), (pd, pw)):
+                assert np.array_equal(host(got)[:, :nk], want)
+            assert idx is None or np.array_equal(host(idx), iw)
+        ws = torch.empty(pk.pc_compact_workspace_bytes(Hkv, at), dtype=torch.uint8, device=DEV)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                pk.pc_compact(Kd, Vd, pd, sd, segs, b, ws=ws)
+        times = []
+        for _ in range(10):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            graph.replay()
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end) * 50)
+        micros.append(min(times))
+    assert micros[0] <= 1.5 * micros[1], micros
+
+
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("lens,D,dtype,Hkv,share,launches", COMPACT_SMALL)
 def test_compact_small_caches_select_and_move_in_one_launch(lens, D, dtype, Hkv, share, launches, in_place):
