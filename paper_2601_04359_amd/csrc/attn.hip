@@ -1032,7 +1032,10 @@ constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-gr
 // 23 take them, 1.26 times as fast at the median (1.49 at most; one 3 % slower, 6/2 x 692 x 2,458 in three
 // shares).  Beyond that line they would still win at times (16/4 x 1,594 x 3,031 53 -> 44 us, 16/4 x 853 x 2,371 32 -> 25)
 // and no more at 16/4 x 1,008 x 7,455 (68 against 69); it lies where it does because the parity tests pin their
-// large shapes, from 2,100 keys on, to the 256-row form that they are there to cover.
+// large shapes, from 2,100 keys on, to the 256-row form that they are there to cover.  They take one round of work-groups
+// at most: of 426 shapes (1/1 to 28/4 heads, up to 260,000 rows in all, 1 to 2,048 keys) 107 take them, none of them
+// slower than the other two forms (0.92 times as long at the median); of the 136 that are several rounds in either, 133
+// are slower (1.39 times as long at the median, 1 % faster at best: 16/4 x 5,311 x 4 24.2 us, 18.8 with 256 rows).
 // The small form's work-groups divide the output's dims while all of them still have a compute unit (small_blocks): of
 // 27 shapes with 4 to 252 work-groups, the division that fits was the fastest on 26 (by 8 to 21 %; 1 % off on the
 // last), one that does not fit took 1.1 to 2.2 times as long (16/4 x 141 x 474, 72 of them: 6.7 us whole, 5.9 in
@@ -1057,10 +1060,12 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
   };
   auto consider = [&](int tile_rows, int share_keys, int step_keys, auto&& cost_of /* that many work-groups */) {
     const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
+    const bool one_round = tile_rows == 64 || tile_rows == 128;
     const int64_t all_rows = static_cast<int64_t>(Hkv) * rows;
     for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
+      if (one_round && base * s > 256) break;
       const auto [start, per_step, fill_step, next_round] = cost_of(base * s);
       const int steps = ceil_div(per * share_keys, step_keys), rounds = ceil_div(base * s, 256);
       const double merge = s == 1 ? 0.0 : 2.4 + 1.86e-4 * s * Hkv * rows;
@@ -1090,8 +1095,8 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
     return blocks == 1 ? Cost{3.4, 0.62, 1.5, 3.3} : blocks == 2 ? Cost{3.9, 0.8, 0.5, 3.3} : Cost{4.9, 1.03, 0.32, 3.3};
   });
   if (Nk <= kMidKeys || Hkv * static_cast<int64_t>(Nk) <= 4 * kMidKeys) {
-    consider(64, 128, 128, [](int) { return Cost{6.2, 0.68, 0.325, 2.8}; });
-    consider(128, 64, 64, [](int) { return Cost{7.55, 0.52, 0.34, 1.7}; });
+    consider(64, 128, 128, [](int) { return Cost{6.2, 0.68, 0.325, 0.0}; });
+    consider(128, 64, 64, [](int) { return Cost{7.55, 0.52, 0.34, 0.0}; });
   }
   return best;
 }

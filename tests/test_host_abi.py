@@ -460,6 +460,16 @@ def test_parity_shapes_take_the_forms_they_are_meant_for(L):
             assert score(s, scale)[2:4] == (512, 1) and score(s, scale, True)[:4] == (0, 0, 512, 1)
 
 
+def test_many_rows_over_few_keys_take_256_rows():
+    # more than one round of 128-row tiles: 256 rows per work-group were timed 1.03 to 1.4 times as fast
+    for shape in ((16, 4, 5311, 4), (28, 4, 7066, 10), (16, 16, 13805, 25), (2, 1, 35636, 42), (16, 4, 9892, 63),
+                  (3, 1, 23314, 130), (28, 4, 5607, 153), (16, 4, 5936, 347), (4, 2, 21761, 465), (3, 1, 28705, 776)):
+        assert pk.pc_frame_attn_cut(pk.PC_BF16, *shape, 128, 1 << 40)[0] == 256, shape
+    # the last tile that is one round, and one more
+    assert pk.pc_frame_attn_cut(pk.PC_BF16, 16, 4, 64 * 32, 700, 128, 0)[0] == 128
+    assert pk.pc_frame_attn_cut(pk.PC_BF16, 16, 4, 64 * 32 + 1, 700, 128, 0)[0] != 128
+
+
 def test_small_compactions_take_the_form_that_was_faster():
     import test_gpu_parity as g
     for lens, D, dtype, Hkv, share, launches in g.COMPACT_SMALL:
