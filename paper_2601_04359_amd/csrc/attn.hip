@@ -1036,6 +1036,9 @@ constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-gr
 // at most: of 426 shapes (1/1 to 28/4 heads, up to 260,000 rows in all, 1 to 2,048 keys) 107 take them, none of them
 // slower than the other two forms (0.92 times as long at the median); of the 136 that are several rounds in either, 133
 // are slower (1.39 times as long at the median, 1 % faster at best: 16/4 x 5,311 x 4 24.2 us, 18.8 with 256 rows).
+// Their estimate was raised by 6 % and key shares of 128 rows are not considered: on 163 shapes of up to 8,192 keys
+// over all KV heads they had been picked in shares where 32 rows in fewer are up to 1.19 times as fast (2/1 x 2,527 x 2,601
+// 20.8 us, 17.5; 2/1 x 696 x 6,694 19.0, 16.8); now 49 take them, 0.91 times as long at the median and 3 % longer at worst.
 // The small form's work-groups divide the output's dims while all of them still have a compute unit (small_blocks): of
 // 27 shapes with 4 to 252 work-groups, the division that fits was the fastest on 26 (by 8 to 21 %; 1 % off on the
 // last), one that does not fit took 1.1 to 2.2 times as long (16/4 x 141 x 474, 72 of them: 6.7 us whole, 5.9 in
@@ -1062,7 +1065,7 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
     const int base = Hkv * ceil_div(rows, tile_rows), units = ceil_div(Nk, share_keys);
     const bool one_round = tile_rows == 64 || tile_rows == 128;
     const int64_t all_rows = static_cast<int64_t>(Hkv) * rows;
-    for (int s = 1; s <= std::min(kMaxKeySplits, units); ++s) {
+    for (int s = 1; s <= std::min(tile_rows == 128 ? 1 : kMaxKeySplits, units); ++s) {
       const int per = ceil_div(units, s);
       if (ceil_div(units, per) != s) continue;   // would leave a share empty
       if (one_round && base * s > 256) break;
@@ -1095,8 +1098,8 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
     return blocks == 1 ? Cost{3.4, 0.62, 1.5, 3.3} : blocks == 2 ? Cost{3.9, 0.8, 0.5, 3.3} : Cost{4.9, 1.03, 0.32, 3.3};
   });
   if (Nk <= kMidKeys || Hkv * static_cast<int64_t>(Nk) <= 4 * kMidKeys) {
-    consider(64, 128, 128, [](int) { return Cost{6.2, 0.68, 0.325, 0.0}; });
-    consider(128, 64, 64, [](int) { return Cost{7.55, 0.52, 0.34, 0.0}; });
+    consider(64, 128, 128, [](int) { return Cost{6.57, 0.72, 0.345, 0.0}; });
+    consider(128, 64, 64, [](int) { return Cost{8.0, 0.55, 0.36, 0.0}; });
   }
   return best;
 }
