@@ -282,8 +282,9 @@ ATTN_256_ROWS_UNCUT = [(16, 4, 3990, nk) for nk in (1, 31, 33, 64, 65, 128, 129,
 
 # Row tiles that span query heads (nq is no multiple of the tile), steps and tiles of the keys that are
 # empty, single or ragged, and both forms of the kernel: the first five shapes take 32 rows per
-# work-group (four un-split, one in key shares), the others 256 rows (in key shares twice; a whole round of
-# row tiles un-split and the rest in key shares).  test_host_abi.py pins these forms.
+# work-group (four un-split, one in key shares; all with divided output dims, ATTN_32_ROWS_WHOLE has the others), the
+# others 256 rows (in key shares twice; a whole round of row tiles un-split and the rest in key shares).
+# test_host_abi.py pins these forms.
 # step: logits climb along the key axis, as above.  Every row is computed; the oracle checks the rows
 # at the tile edges and a stride of the others.
 @pytest.mark.parametrize("fold", [False, True])
@@ -407,6 +408,74 @@ def test_frame_attn_bf16_output_dims_divided(nq, nk, work_groups, fold):
     # outputs and probabilities rounded once each; with few keys |O| reaches 4, where bf16 values lie 2^-6 apart
     assert err.max().item() <= (2 ** -5 if nk < 40 else 2e-2) and err.mean().item() <= 2e-3
     assert lerr.max().item() <= 1e-3 and (buf[:, nq:] == 7).all()
+
+
+# 32 rows per work-group whose output's dims are not divided (more than 128 work-groups): less than a step of keys, a
+# step and a ragged one, many steps, key shares, two rounds of work-groups; climbing logits and masks as above, which
+# leave steps and waves nothing or move every reference
+ATTN_32_ROWS_WHOLE = [(6, 2, 691, 33, 1), (6, 2, 700, 257, 1), (16, 4, 300, 1804, 1), (6, 2, 300, 3000, 4), (28, 4, 573, 2243, 1)]
+
+
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("step,masked", [(0.05, None), (0.6, None), (40.0, None), (0.0, slice(0, 140)), (0.0, slice(40, 300)),
+                                         (0.0, slice(3, None, 5)), (0.0, slice(0, -3)), (0.0, slice(5, None))])
+@pytest.mark.parametrize("hq,hkv,nq,nk,shares", ATTN_32_ROWS_WHOLE)
+def test_frame_attn_bf16_output_dims_not_divided(hq, hkv, nq, nk, shares, step, masked, fold):
+    n_ws = pk.pc_frame_attn_workspace_bytes_for(pk.PC_BF16, hq, hkv, nq, nk, 128)
+    assert pk.pc_frame_attn_cut(pk.PC_BF16, hq, hkv, nq, nk, 128, n_ws)[:2] == (32, shares)
+    assert hkv * -(-(hq // hkv * nq) // 32) * shares > 128
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nq + nk)
+    Q, K, V = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((hq, nq), (hkv, nk), (hkv, nk)))
+    scale = 128 ** -0.5
+    keep = torch.ones(nk, dtype=torch.bool, device=DEV)
+    if step:
+        Q[..., 0] = 8.0
+        K *= 0.1
+        K[..., 0] = step * (torch.arange(nk, device=DEV) // 32) / (8.0 * scale)
+    if masked is not None:
+        Q[..., 0] = 4.0
+        keep[masked] = False
+        keep[-1] |= not keep.any()
+        K[:, ~keep, 0] = float("-inf")
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, lse=lse)
+    rows = torch.tensor(sorted({0, 1, 31, 32, nq - 1} | set(range(0, nq, 37))), device=DEV)
+    Ow, Lw, _ = _masked_reference(Q, K, V, keep, scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs()
+    # tolerances as in the tests above: with all weight on few keys |O| reaches 4
+    assert err.max().item() <= (2 ** -5 if step == 40.0 or keep.sum() < 40 else 2e-2) and err.mean().item() <= 2e-3
+    assert (lerr <= torch.clamp(Lw.abs().clamp(min=1.0) * 2.0 ** -20, min=1e-3)).all()
+
+
+# What lies in the spare rows behind the last key stays out of it in every form: 32, 64, 128 and 256 rows per work-group,
+# a ragged last tile, key groups and shares without a whole one
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("rows_wg,hq,hkv,nq,nk", [(32, 6, 2, 691, 33), (32, 6, 2, 300, 3000), (32, 4, 2, 70, 900)] +
+                         [(64, 16, 4, 581, n) for n in (97, 129, 257)] + [(64, 2, 1, 1701, 8100)] +
+                         [(128, 8, 2, 3541, n) for n in (1, 33, 65, 151)] + [(128, 24, 8, 1070, 1691), (256, 16, 4, 1008, 7455)])
+def test_frame_attn_bf16_spare_rows_stay_out(rows_wg, hq, hkv, nq, nk, fold):
+    n_ws = pk.pc_frame_attn_workspace_bytes_for(pk.PC_BF16, hq, hkv, nq, nk, 128)
+    assert pk.pc_frame_attn_cut(pk.PC_BF16, hq, hkv, nq, nk, 128, n_ws)[0] == rows_wg
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nk)
+    Q, K, V = (torch.randn((h, n, 128), generator=gen, device=DEV) for h, n in ((hq, nq), (hkv, nk + 600), (hkv, nk + 600)))
+    scale = 128 ** -0.5
+    if fold:
+        Q, scale = Q * q_fold(scale), LN2
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    K[:, nk:], V[:, nk:] = float("nan"), float("nan")
+    lse = torch.empty((hq, nq), dtype=torch.float32, device=DEV)
+    O = pk.pc_frame_attn(Q, K, V, nk, scale, lse=lse)
+    rows = torch.tensor(sorted({0, 1, nq - 1} | set(range(0, nq, 61))), device=DEV)
+    Ow, Lw, _ = _masked_reference(Q, K[:, :nk], V[:, :nk], torch.ones(nk, dtype=torch.bool, device=DEV), scale, rows)
+    err, lerr = (O[:, rows].double() - Ow).abs(), (lse[:, rows].double() - Lw).abs()
+    assert not O.isnan().any() and not lse.isnan().any()
+    # outputs and probabilities rounded once each; with few keys |O| reaches 4, where bf16 values lie 2^-6 apart
+    assert err.max().item() <= (2 ** -5 if nk < 40 else 2e-2) and err.mean().item() <= 2e-3 and lerr.max().item() <= 1e-3
 
 
 @pytest.mark.parametrize("fold", [False, True])
@@ -557,7 +626,8 @@ def test_frame_attn_f32_takes_buffers_that_are_not_16_byte_aligned():
 # A caller that masks keys through a coordinate of its own (the queries carry a constant there): their
 # logits are -inf, the type's lowest value times a constant, or far below the rest.  Steps, waves, half
 # tiles and key shares that hold nothing else, first and last ones among them: 32 rows per work-group
-# un-split and in shares, 256 un-split and in four shares of 1,920 keys; fp32 with 16 and 32.
+# in two and in ten shares (un-split: ATTN_32_ROWS_WHOLE), 256 un-split and in four shares of 1,920 keys; fp32 with 16
+# and 32.
 @pytest.mark.parametrize("value", [float("-inf"), "lowest", -3e5])
 @pytest.mark.parametrize("masked", [slice(3, None, 5), slice(40, 300), slice(0, 140), slice(1900, 2040), slice(0, -3), slice(5, None)])
 @pytest.mark.parametrize("dtype,d,fold,hq,hkv,nq,nk", [

@@ -441,7 +441,12 @@ def test_parity_shapes_take_the_forms_they_are_meant_for(L):
     assert cuts[:4] == [(32, 1, 0)] * 4 and cuts[4][0] == 32 and cuts[4][1] > 1
     assert all(c[0] == 256 and c[1] > 1 for c in cuts[5:]) and [c[2] for c in cuts[5:]] == [0, 0, 256]
     assert all(attn(s, 0) == (256, 1, 0) for s in g.ATTN_256_ROWS_UNCUT)
-    # masked keys: 32 rows in shares, 256 rows un-split and in four shares of 1,920 keys, fp32 with 16 and 32
+    # 32 rows with divided output dims (128 work-groups at most) and undivided ones
+    assert all(s[1] * -(-(s[0] // s[1] * s[2]) // 32) * c[1] <= 128 for s, c in zip(g.ATTN_ACROSS_HEADS[:5], cuts))
+    for *shape, shares in g.ATTN_32_ROWS_WHOLE:
+        assert attn(shape) == (32, shares, 0) and shape[1] * -(-(shape[0] // shape[1] * shape[2]) // 32) * shares > 128
+    # masked keys: 32 rows in two and ten shares, 256 un-split and in four shares of 1,920 keys, fp32 with 16 and 32
+    assert attn((8, 2, 252, 1804)) == (32, 2, 0)
     assert attn((2, 1, 184, 5000))[:2] == (32, 10) and attn((16, 4, 4032, 2048)) == (256, 1, 0)
     assert attn((16, 4, 1008, 7455)) == (256, 4, 0)
     f32 = lambda shape, d: pk.pc_frame_attn_cut(pk.PC_F32, *shape, d, ample)
