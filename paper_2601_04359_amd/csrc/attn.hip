@@ -1015,10 +1015,10 @@ size_t usable_bytes(const void* ws, size_t ws_bytes) {
 constexpr int kMaxKeySplits = 16;
 constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-group are considered
 
-// How a bf16 call is cut: 32 or 256 query rows per work-group, and the key shares.  The estimates
+// How a bf16 call is cut: 32, 64, 128 or 256 query rows per work-group, and the key shares.  The estimates
 // are microseconds, fitted to 24 shapes from 0.1 to 974 GFLOP (2 to 24 heads, 64 to 4,032 rows, 150 to
 // 29,500 keys) in the 32- and 256-row forms with 1 to 16 shares: `start` is what a work-group costs beside its
-// steps, a step is 64 keys there and 8 x 32 keys here and gets slower as the compute units fill up,
+// steps, a step is 8 x 32 keys with 32 rows and 64 keys with 256 and gets slower as the compute units fill up,
 // a further round costs a new start, and key shares cost the merge launch and the fp32 partial rows
 // (512 bytes written and read per row and share).  The 32-row form was fitted again, to
 // 210 shapes (2/1 to 24/8 heads, 33 to 4,032 rows, 64 to 13,000 keys), for each division of its output's dims: a
@@ -1028,9 +1028,9 @@ constexpr int kMidKeys = 2048;   // keys up to which 64 and 128 rows per work-gr
 // us with 32 rows against 15.8 with 256 (and 29.7 un-split); 16/4 x 400 x 3,000, 19.9 against 29.4; 24/8 x 568 x
 // 2,200, 29.5 against 30.6; 16/4 x 1,008 x 7,455, 85 against 68.
 // The forms of 64 and 128 rows were fitted to 140 shapes (2/1 to 24/8 heads, 64 to 4,032 rows, 100 to 13,000 keys) in all
-// four forms with 1 to 16 shares.  They are considered up to 2,048 keys, or up to 8,192 over all KV heads: of the 140,
-// 23 take them, 1.26 times as fast at the median (1.49 at most; one 3 % slower, 6/2 x 692 x 2,458 in three
-// shares).  Beyond that line they would still win at times (16/4 x 1,594 x 3,031 53 -> 44 us, 16/4 x 853 x 2,371 32 -> 25)
+// four forms with 1 to 16 shares (a step is 128 keys with 64 rows and 64 with 128).  They are considered up to 2,048 keys,
+// or up to 8,192 over all KV heads: of the 140, 23 took them, 1.26 times as fast at the median and 1.49 at most (one of
+// them, 6/2 x 692 x 2,458, 3 % slower; it is not among those that take them now).  Beyond that line they would still win at times (16/4 x 1,594 x 3,031 53 -> 44 us, 16/4 x 853 x 2,371 32 -> 25)
 // and no more at 16/4 x 1,008 x 7,455 (68 against 69); it lies where it does because the parity tests pin their
 // large shapes, from 2,100 keys on, to the 256-row form that they are there to cover.  They take one round of work-groups
 // at most: of 426 shapes (1/1 to 28/4 heads, up to 260,000 rows in all, 1 to 2,048 keys) 107 take them, none of them
@@ -1125,8 +1125,10 @@ AttnPlan plan_bf16(int Hkv, int rows, int Nk, size_t ws_bytes) {
 //     forms the scores of a step and the probabilities of the step before, and moves a piece of K or V between
 //     products: a wave that issues all its loads at once waits for the seven others' in front of its products.
 // Measured: 8/2 heads, 252 rows, 1,804 keys, D = 128 (1.86 GFLOP, 12 us at the rate a large fp32
-// product reaches) 29.1 -> 26.1 us; 260 calls of the sizes this tier is used at 1.11 times as fast at the median, none
-// slower (24/8 heads x 155 x 1,379 37.1 -> 32.1, 8/2 x 63 x 261 9.5 -> 8.6; D = 64, 8/2 x 169 x 345 8.3 -> 7.1).
+// product reaches) 29.1 -> 26.1 us; of 700 calls (1 to 28 heads, 1 to 2,500 rows, 1 to 12,000 keys) those with D = 128 take
+// 0.88 times as long at the median and those with 64 0.93 (24/8 heads x 155 x 1,379 37.1 -> 32.1, 8/2 x 63 x 261 9.5 -> 8.6;
+// D = 64, 8/2 x 169 x 345 8.3 -> 7.1); five are 3 to 4 % slower (16/16 x 3 x 65, D = 64, 4.7 -> 4.9; 8/2 x 2,468 x 42
+// 22.4 -> 23.1).
 // A large call, 24/8 x 1,000 x 8,000: 872 -> 821 us (120 TFLOP/s).
 // Where the 26 us go (clock stamps; the chip runs at 2.04 GHz): queries in LDS at 1.1 us, the first scores at
 // 3.9, then 4.7 us for a step of both waves of a SIMD, of which the matrix pipe works 4.0 (2 x 128 products of
@@ -1452,8 +1454,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
 // How an fp32 call is cut: kR and the key shares.  Microseconds, fitted to 400 calls (2 to 24 heads, 33 to 700
 // rows, 70 to 4,000 keys, both head dimensions) in both forms with 1 to 16 shares; the cut it picks is 0.4 %
 // off the best of them on average, 2.5 % on one call in twenty.  A SIMD has two of the eight waves, so a share
-// lasts as long as a quarter of its steps.  Shares that need more than 16 MB of workspace have to save more than
-// those 4 % (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
+// lasts as long as a quarter of its steps.  Shares that need more than 16 MB of workspace have to save more than 4 %:
+// less is within what the estimate errs by (16/4 heads x 4,032 rows x 97,024 keys: eight of them, 256 MB, for 1.6 %).
 // The keys of one or two steps need as many waves, whose values take the place of their keys in LDS (16/4 heads,
 // 4,032 rows, 32 keys, D = 64: 33.3 us with eight waves, 12.9 with two; 3 keys, D = 128: 49.5, and 19.3 with one).
 struct F32Plan {
